@@ -98,6 +98,100 @@ dmr_status_t hip_status(hipError_t e) { return e == hipSuccess ? DMR_OK : DMR_ER
 
 }  // namespace
 
+namespace {
+
+// The forwards with an optional bf16 residual added where the result is stored.
+dmr_status_t forward_quant(const dmr_qlinear_t *layer, const uint16_t *d_x, int64_t M, void *d_y, dmr_out_t out,
+                           const uint16_t *res, void *d_ws, size_t ws_bytes, hipStream_t s) {
+    if (!layer) return DMR_ERR_NULL;
+    if (M < 0 || M > (int64_t(1) << 22)) return DMR_ERR_SHAPE;
+    if (out != DMR_OUT_BF16 && out != DMR_OUT_FP32) return DMR_ERR_UNSUPPORTED;
+    if (M == 0) return DMR_OK;
+    if (!d_x || !d_y) return DMR_ERR_NULL;
+    if (!aligned16(d_x) || !aligned16(d_y) || (d_ws && !aligned16(d_ws))) return DMR_ERR_ALIGN;
+    const bool f32 = out == DMR_OUT_FP32;
+    if (layer->bits == 3) {
+        const dmr::LayerView3 L3{layer->K, layer->N, layer->wt3, layer->sz};
+        const size_t need3 = dmr_qlinear_w3_workspace_bytes(M, layer->K, layer->N);
+        if (need3 > 0 && (!d_ws || ws_bytes < need3)) return DMR_ERR_WORKSPACE;
+        switch (w3_path(M, layer->K, layer->N)) {
+            case W3Path::Gemv: return hip_status(dmr::launch_w3_gemv(L3, d_x, d_y, f32, res, s));
+            case W3Path::Stream: return hip_status(dmr::launch_w3_stream(L3, d_x, M, d_y, f32, res, s));
+            case W3Path::Panel: return hip_status(dmr::launch_w3_panel(L3, d_x, M, d_y, f32, res, d_ws, s));
+            case W3Path::Wide: return hip_status(dmr::launch_w3_wide(L3, d_x, M, d_y, f32, res, s));
+            case W3Path::Mid: return hip_status(dmr::launch_w3_mid(L3, d_x, M, d_y, f32, res, d_ws, s));
+            case W3Path::Gemm: return hip_status(dmr::launch_w3_gemm(L3, d_x, M, d_y, f32, res, s));
+            case W3Path::GemmRescale: return hip_status(dmr::launch_w3_gemm_rescale(L3, d_x, M, d_y, f32, res, d_ws, s));
+        }
+        return DMR_ERR_UNSUPPORTED;
+    }
+    const size_t need = dmr_qlinear_workspace_bytes(M, layer->K, layer->N);
+    if (need > 0 && (!d_ws || ws_bytes < need)) return DMR_ERR_WORKSPACE;
+    const dmr::LayerView L{layer->K, layer->N, layer->wt, layer->sz, layer->szs};
+    const W4Path path = w4_path(M, layer->K, layer->N);
+    dmr::Fusion f;
+    f.res = res;
+    if (path == W4Path::Gemv) {
+        const hipError_t e = dmr::launch_w4_gemv_fused(L, d_x, d_y, f32, f, s);
+        if (e != hipErrorInvalidValue) return hip_status(e);   // else: shape outside its range
+    }
+    if (path == W4Path::Stream) {
+        const hipError_t e = dmr::launch_w4_stream_fused(L, d_x, M, d_y, f32, f, s);
+        if (e != hipErrorInvalidValue) return hip_status(e);   // else: activations do not fit LDS
+    }
+    if (path == W4Path::Panel) return hip_status(dmr::launch_w4_panel(L, d_x, M, d_y, f32, res, d_ws, s));
+    if (path == W4Path::Wide) return hip_status(dmr::launch_w4_wide(L, d_x, M, d_y, f32, res, s));
+    if (path == W4Path::Mid) return hip_status(dmr::launch_w4_mid(L, d_x, M, d_y, f32, res, d_ws, s));
+    if (path == W4Path::Skinny2) return hip_status(dmr::launch_w4_skinny2(L, d_x, M, d_y, f32, d_ws, s));
+    if (M <= kSkinnyMaxM) return hip_status(dmr::launch_w4_skinny(L, d_x, M, d_y, f32, s));
+    if (path == W4Path::GemmRescale) return hip_status(dmr::launch_w4_gemm_rescale(L, d_x, M, d_y, f32, res, d_ws, s));
+    // Not reached with the present crossovers (the rescaling kernel takes every tiled shape and calls this kernel
+    // itself for the column blocks it declines): 128 x 128 tiles on the exact integer codes q - z, the group's scale
+    // applied to the group's partial sums in fp32.  (No tiled kernel rounds the weights to bf16 on their way into
+    // LDS, what dmr_qlinear_dequantize returns: that leaves an error of about 1.7e-3 rms(y) standard deviation per
+    // output, so that the largest of 10^7 .. 10^8 outputs lands at 0.8 .. 1.1 times the 1e-2 rms bound.)
+    return hip_status(dmr::launch_w4_gemm(L, d_x, M, d_y, f32, res, s));
+}
+
+dmr_status_t forward_bf16(const uint16_t *d_w, const uint16_t *d_x, int64_t M, int64_t K, int64_t N, void *d_y,
+                          dmr_out_t out, const uint16_t *res, void *d_ws, size_t ws_bytes, hipStream_t s) {
+    const dmr_status_t shape = check_shape(K, N, dmr::kGroup);
+    if (shape != DMR_OK) return shape;
+    if (M < 0 || M > (int64_t(1) << 22)) return DMR_ERR_SHAPE;
+    if (out != DMR_OUT_BF16 && out != DMR_OUT_FP32) return DMR_ERR_UNSUPPORTED;
+    if (M == 0) return DMR_OK;
+    if (!d_w || !d_x || !d_y) return DMR_ERR_NULL;
+    if (!aligned16(d_w) || !aligned16(d_x) || !aligned16(d_y) || (d_ws && !aligned16(d_ws)))
+        return DMR_ERR_ALIGN;
+    const size_t need = dmr_qlinear_bf16_workspace_bytes(M, K, N);
+    if (need > 0 && (!d_ws || ws_bytes < need)) return DMR_ERR_WORKSPACE;
+    const bool f32 = out == DMR_OUT_FP32;
+    const Bf16Path path = bf16_path(M, K, N);
+    if (path == Bf16Path::Gemv) {
+        dmr::Fusion fusion;
+        fusion.res = res;
+        const hipError_t e = dmr::launch_bf16_gemv_fused(d_w, d_x, K, N, d_y, f32, fusion, s);
+        if (e != hipErrorInvalidValue) return hip_status(e);   // else: K outside its range
+        return hip_status(dmr::launch_bf16_skinny(d_w, d_x, M, K, N, d_y, f32, res, s));
+    }
+    switch (path) {
+        case Bf16Path::Stream: return hip_status(dmr::launch_bf16_stream(d_w, d_x, M, K, N, d_y, f32, res, s));
+        case Bf16Path::Skinny: return hip_status(dmr::launch_bf16_skinny(d_w, d_x, M, K, N, d_y, f32, res, s));
+        case Bf16Path::Mid: return hip_status(dmr::launch_bf16_mid(d_w, d_x, M, K, N, d_y, f32, res, d_ws, s));
+        case Bf16Path::GemmBig: return hip_status(dmr::launch_bf16_gemm_w8(d_w, d_x, M, K, N, d_y, f32, res, s));
+        default: {
+            // 128 x 128 tiles: the direct-to-LDS kernel while its pipeline has room to pay (K >= 1024) and the
+            // grid is at most ~3 workgroups per CU (measured: 25-30 % ahead at 256 workgroups, level at 512,
+            // 8 % ahead at 768, 6 % behind at 1056)
+            const int64_t wgs = ((M + 127) / 128) * ((N + 127) / 128);
+            if (K >= 1024 && wgs <= 800) return hip_status(dmr::launch_bf16_gemm_dma128(d_w, d_x, M, K, N, d_y, f32, res, s));
+            return hip_status(dmr::launch_bf16_gemm(d_w, d_x, M, K, N, d_y, f32, res, s));
+        }
+    }
+}
+
+}  // namespace
+
 extern "C" {
 
 size_t dmr_qlinear_storage_bytes(int64_t K, int64_t N, int32_t g) {
@@ -268,90 +362,13 @@ dmr_status_t dmr_qlinear_dequantize(const dmr_qlinear_t *layer, uint16_t *d_w_bf
 
 dmr_status_t dmr_qlinear_forward(const dmr_qlinear_t *layer, const uint16_t *d_x, int64_t M, void *d_y,
                                  dmr_out_t out, void *d_ws, size_t ws_bytes, void *stream) {
-    if (!layer) return DMR_ERR_NULL;
-    if (M < 0 || M > (int64_t(1) << 22)) return DMR_ERR_SHAPE;
-    if (out != DMR_OUT_BF16 && out != DMR_OUT_FP32) return DMR_ERR_UNSUPPORTED;
-    if (M == 0) return DMR_OK;
-    if (!d_x || !d_y) return DMR_ERR_NULL;
-    if (!aligned16(d_x) || !aligned16(d_y) || (d_ws && !aligned16(d_ws))) return DMR_ERR_ALIGN;
-    hipStream_t s = static_cast<hipStream_t>(stream);
-    const bool f32 = out == DMR_OUT_FP32;
-    if (layer->bits == 3) {
-        const dmr::LayerView3 L3{layer->K, layer->N, layer->wt3, layer->sz};
-        const size_t need3 = dmr_qlinear_w3_workspace_bytes(M, layer->K, layer->N);
-        if (need3 > 0 && (!d_ws || ws_bytes < need3)) return DMR_ERR_WORKSPACE;
-        switch (w3_path(M, layer->K, layer->N)) {
-            case W3Path::Gemv: return hip_status(dmr::launch_w3_gemv(L3, d_x, d_y, f32, s));
-            case W3Path::Stream: return hip_status(dmr::launch_w3_stream(L3, d_x, M, d_y, f32, s));
-            case W3Path::Panel: return hip_status(dmr::launch_w3_panel(L3, d_x, M, d_y, f32, d_ws, s));
-            case W3Path::Wide: return hip_status(dmr::launch_w3_wide(L3, d_x, M, d_y, f32, s));
-            case W3Path::Mid: return hip_status(dmr::launch_w3_mid(L3, d_x, M, d_y, f32, d_ws, s));
-            case W3Path::Gemm: return hip_status(dmr::launch_w3_gemm(L3, d_x, M, d_y, f32, s));
-            case W3Path::GemmRescale: return hip_status(dmr::launch_w3_gemm_rescale(L3, d_x, M, d_y, f32, d_ws, s));
-        }
-        return DMR_ERR_UNSUPPORTED;
-    }
-    const size_t need = dmr_qlinear_workspace_bytes(M, layer->K, layer->N);
-    if (need > 0 && (!d_ws || ws_bytes < need)) return DMR_ERR_WORKSPACE;
-    const dmr::LayerView L{layer->K, layer->N, layer->wt, layer->sz, layer->szs};
-    const W4Path path = w4_path(M, layer->K, layer->N);
-    if (path == W4Path::Gemv) {
-        const hipError_t e = dmr::launch_w4_gemv(L, d_x, d_y, f32, s);
-        if (e != hipErrorInvalidValue) return hip_status(e);   // else: shape outside its range
-    }
-    if (path == W4Path::Stream) {
-        const hipError_t e = dmr::launch_w4_stream(L, d_x, M, d_y, f32, s);
-        if (e != hipErrorInvalidValue) return hip_status(e);   // else: activations do not fit LDS
-    }
-    if (path == W4Path::Panel) return hip_status(dmr::launch_w4_panel(L, d_x, M, d_y, f32, d_ws, s));
-    if (path == W4Path::Wide) return hip_status(dmr::launch_w4_wide(L, d_x, M, d_y, f32, s));
-    if (path == W4Path::Mid) return hip_status(dmr::launch_w4_mid(L, d_x, M, d_y, f32, d_ws, s));
-    if (path == W4Path::Skinny2) return hip_status(dmr::launch_w4_skinny2(L, d_x, M, d_y, f32, d_ws, s));
-    if (M <= kSkinnyMaxM) return hip_status(dmr::launch_w4_skinny(L, d_x, M, d_y, f32, s));
-    if (path == W4Path::GemmRescale) return hip_status(dmr::launch_w4_gemm_rescale(L, d_x, M, d_y, f32, d_ws, s));
-    // Not reached with the present crossovers (the rescaling kernel takes every tiled shape and calls this kernel
-    // itself for the column blocks it declines): 128 x 128 tiles on the exact integer codes q - z, the group's scale
-    // applied to the group's partial sums in fp32.  (No tiled kernel rounds the weights to bf16 on their way into
-    // LDS, what dmr_qlinear_dequantize returns: that leaves an error of about 1.7e-3 rms(y) standard deviation per
-    // output, so that the largest of 10^7 .. 10^8 outputs lands at 0.8 .. 1.1 times the 1e-2 rms bound.)
-    return hip_status(dmr::launch_w4_gemm(L, d_x, M, d_y, f32, s));
+    return forward_quant(layer, d_x, M, d_y, out, nullptr, d_ws, ws_bytes, static_cast<hipStream_t>(stream));
 }
 
 dmr_status_t dmr_qlinear_bf16_forward(const uint16_t *d_w, const uint16_t *d_x, int64_t M, int64_t K,
                                       int64_t N, void *d_y, dmr_out_t out, void *d_ws, size_t ws_bytes,
                                       void *stream) {
-    const dmr_status_t shape = check_shape(K, N, dmr::kGroup);
-    if (shape != DMR_OK) return shape;
-    if (M < 0 || M > (int64_t(1) << 22)) return DMR_ERR_SHAPE;
-    if (out != DMR_OUT_BF16 && out != DMR_OUT_FP32) return DMR_ERR_UNSUPPORTED;
-    if (M == 0) return DMR_OK;
-    if (!d_w || !d_x || !d_y) return DMR_ERR_NULL;
-    if (!aligned16(d_w) || !aligned16(d_x) || !aligned16(d_y) || (d_ws && !aligned16(d_ws)))
-        return DMR_ERR_ALIGN;
-    const size_t need = dmr_qlinear_bf16_workspace_bytes(M, K, N);
-    if (need > 0 && (!d_ws || ws_bytes < need)) return DMR_ERR_WORKSPACE;
-    hipStream_t s = static_cast<hipStream_t>(stream);
-    const bool f32 = out == DMR_OUT_FP32;
-    const Bf16Path path = bf16_path(M, K, N);
-    if (path == Bf16Path::Gemv) {
-        const hipError_t e = dmr::launch_bf16_gemv(d_w, d_x, K, N, d_y, f32, s);
-        if (e != hipErrorInvalidValue) return hip_status(e);   // else: K outside its range
-        return hip_status(dmr::launch_bf16_skinny(d_w, d_x, M, K, N, d_y, f32, s));
-    }
-    switch (path) {
-        case Bf16Path::Stream: return hip_status(dmr::launch_bf16_stream(d_w, d_x, M, K, N, d_y, f32, nullptr, s));
-        case Bf16Path::Skinny: return hip_status(dmr::launch_bf16_skinny(d_w, d_x, M, K, N, d_y, f32, s));
-        case Bf16Path::Mid: return hip_status(dmr::launch_bf16_mid(d_w, d_x, M, K, N, d_y, f32, d_ws, s));
-        case Bf16Path::GemmBig: return hip_status(dmr::launch_bf16_gemm_w8(d_w, d_x, M, K, N, d_y, f32, s));
-        default: {
-            // 128 x 128 tiles: the direct-to-LDS kernel while its pipeline has room to pay (K >= 1024) and the
-            // grid is at most ~3 workgroups per CU (measured: 25-30 % ahead at 256 workgroups, level at 512,
-            // 8 % ahead at 768, 6 % behind at 1056)
-            const int64_t wgs = ((M + 127) / 128) * ((N + 127) / 128);
-            if (K >= 1024 && wgs <= 800) return hip_status(dmr::launch_bf16_gemm_dma128(d_w, d_x, M, K, N, d_y, f32, s));
-            return hip_status(dmr::launch_bf16_gemm(d_w, d_x, M, K, N, d_y, f32, s));
-        }
-    }
+    return forward_bf16(d_w, d_x, M, K, N, d_y, out, nullptr, d_ws, ws_bytes, static_cast<hipStream_t>(stream));
 }
 
 dmr_status_t dmr_glue_rmsnorm(const uint16_t *d_x, const uint16_t *d_gamma, float eps, int64_t M, int64_t K,
@@ -405,12 +422,29 @@ dmr_status_t check_fused(dmr_prologue_t pro, const uint16_t *d_in, const uint16_
     return DMR_OK;
 }
 
-// The unfused composition: glue kernel into the workspace, plain forward (fp32 if a residual
-// follows), residual add.  `forward` runs the plain forward on (x, y, out type, inner workspace).
+// Whether the kernel that serves M rows of this layer adds a residual where it stores the result (the two direct-from-L2
+// kernels do not).
+bool quant_adds_residual(const dmr_qlinear_t *layer, int64_t M) {
+    if (layer->bits == 3) return true;
+    const W4Path path = w4_path(M, layer->K, layer->N);
+    return path != W4Path::Skinny2 && !(path == W4Path::Gemv && !dmr::w4_gemv_fits(layer->K, layer->N, true));
+}
+
+bool overlap(const void *a, size_t na, const void *b, size_t nb) {
+    const uintptr_t pa = reinterpret_cast<uintptr_t>(a), pb = reinterpret_cast<uintptr_t>(b);
+    return pa < pb + nb && pb < pa + na;
+}
+
+// The composition for more rows than the kernels that fuse the prologue take: glue kernel into the workspace, then the
+// forward, which adds the residual where it stores the result.  (That replaced an fp32 result [M][N] in the workspace and a
+// launch that added the residual to it: same sums, one launch and two passes over M x N less; rollout of eight rows
+// 214 -> 209 us for four decoder layers, prefill chunk of 1000 rows 972 -> 950 us for two.)  The fp32 detour is left for
+// the kernels without a residual and for an output over the activations that the forward still reads.  `forward` runs the
+// plain forward on (x, y, out type, residual, inner workspace).
 template <typename Forward>
 dmr_status_t run_unfused(dmr_prologue_t pro, const uint16_t *d_in, const uint16_t *d_gamma, float eps,
-                         const uint16_t *d_residual, int64_t M, int64_t K, int64_t N, void *d_y, dmr_out_t out,
-                         void *d_ws, size_t ws_bytes, hipStream_t s, Forward forward) {
+                         const uint16_t *d_residual, bool adds_residual, int64_t M, int64_t K, int64_t N, void *d_y,
+                         dmr_out_t out, void *d_ws, size_t ws_bytes, hipStream_t s, Forward forward) {
     uint8_t *ws = static_cast<uint8_t *>(d_ws);
     size_t used = 0;
     const uint16_t *x = d_in;
@@ -422,10 +456,13 @@ dmr_status_t run_unfused(dmr_prologue_t pro, const uint16_t *d_in, const uint16_
         if (e != hipSuccess) return DMR_ERR_HIP;
         x = xg;
     }
-    if (!d_residual) return forward(x, d_y, out, ws + used, ws_bytes - used);
+    const size_t y_bytes = (size_t)M * (size_t)N * (out == DMR_OUT_FP32 ? 4 : 2);
+    if (!d_residual || (adds_residual && !overlap(d_y, y_bytes, x, (size_t)M * (size_t)K * 2) &&
+                        (d_y == d_residual ? out == DMR_OUT_BF16 : !overlap(d_y, y_bytes, d_residual, (size_t)M * (size_t)N * 2))))
+        return forward(x, d_y, out, d_residual, ws + used, ws_bytes - used);
     float *acc = reinterpret_cast<float *>(ws + used);
     used += align256((size_t)M * (size_t)N * 4);
-    const dmr_status_t st = forward(x, acc, DMR_OUT_FP32, ws + used, ws_bytes - used);
+    const dmr_status_t st = forward(x, acc, DMR_OUT_FP32, nullptr, ws + used, ws_bytes - used);
     if (st != DMR_OK) return st;
     return hip_status(dmr::launch_add_residual(acc, d_residual, M * N, d_y, out == DMR_OUT_FP32, s));
 }
@@ -453,31 +490,10 @@ dmr_status_t dmr_qlinear_forward_fused(const dmr_qlinear_t *layer, dmr_prologue_
         const hipError_t e = dmr::launch_w4_gemv_fused(L, d_in, d_y, out == DMR_OUT_FP32, f, s);
         if (e != hipErrorInvalidValue) return hip_status(e);   // else: shape outside the GEMV's range
     }
-    if (M >= 2 && M <= 16 && layer->bits == 4 && dmr::w4_stream_fits(M, layer->K, layer->N)) {
-        const dmr::LayerView L{layer->K, layer->N, layer->wt, layer->sz, layer->szs};
-        dmr::Fusion f;
-        f.pro = (int)pro;
-        f.aux = d_gamma;
-        f.eps = eps;
-        f.res = d_residual;
-        const uint16_t *x = d_in;
-        // In this kernel every workgroup would recompute the prologue for all M rows, which measured
-        // slower than one launch of the stand-alone kernel: the prologue runs on its own, the residual
-        // stays fused.
-        if (pro != DMR_PRO_NONE) {
-            uint16_t *xg = static_cast<uint16_t *>(d_ws);
-            const hipError_t eg = pro == DMR_PRO_RMSNORM ? dmr::launch_rmsnorm(d_in, d_gamma, eps, M, layer->K, xg, s)
-                                                          : dmr::launch_swiglu(d_in, M, layer->K, xg, s);
-            if (eg != hipSuccess) return DMR_ERR_HIP;
-            x = xg;
-            f.pro = dmr::kProNone;
-        }
-        const hipError_t e = dmr::launch_w4_stream_fused(L, x, M, d_y, out == DMR_OUT_FP32, f, s);
-        if (e != hipErrorInvalidValue) return hip_status(e);
-    }
-    return run_unfused(pro, d_in, d_gamma, eps, d_residual, M, layer->K, layer->N, d_y, out, d_ws, ws_bytes, s,
-                       [&](const uint16_t *x, void *y, dmr_out_t o, void *ws, size_t wsb) {
-                           return dmr_qlinear_forward(layer, x, M, y, o, ws, wsb, stream);
+    return run_unfused(pro, d_in, d_gamma, eps, d_residual, quant_adds_residual(layer, M), M, layer->K, layer->N, d_y, out,
+                       d_ws, ws_bytes, s,
+                       [&](const uint16_t *x, void *y, dmr_out_t o, const uint16_t *res, void *ws, size_t wsb) {
+                           return forward_quant(layer, x, M, y, o, res, ws, wsb, s);
                        });
 }
 
@@ -503,22 +519,9 @@ dmr_status_t dmr_qlinear_bf16_forward_fused(const uint16_t *d_w, dmr_prologue_t 
         const hipError_t e = dmr::launch_bf16_gemv_fused(d_w, d_in, K, N, d_y, out == DMR_OUT_FP32, f, s);
         if (e != hipErrorInvalidValue) return hip_status(e);   // else: K outside its range, or RMSNorm over slices
     }
-    if (bf16_path(M, K, N) == Bf16Path::Stream) {
-        // as in the INT4 kernel of this size class: stand-alone prologue, residual fused at the store
-        const uint16_t *x = d_in;
-        if (pro != DMR_PRO_NONE) {
-            uint16_t *xg = static_cast<uint16_t *>(d_ws);
-            const hipError_t eg = pro == DMR_PRO_RMSNORM ? dmr::launch_rmsnorm(d_in, d_gamma, eps, M, K, xg, s)
-                                                          : dmr::launch_swiglu(d_in, M, K, xg, s);
-            if (eg != hipSuccess) return DMR_ERR_HIP;
-            x = xg;
-        }
-        const hipError_t e = dmr::launch_bf16_stream(d_w, x, M, K, N, d_y, out == DMR_OUT_FP32, d_residual, s);
-        if (e != hipErrorInvalidValue) return hip_status(e);
-    }
-    return run_unfused(pro, d_in, d_gamma, eps, d_residual, M, K, N, d_y, out, d_ws, ws_bytes, s,
-                       [&](const uint16_t *x, void *y, dmr_out_t o, void *ws, size_t wsb) {
-                           return dmr_qlinear_bf16_forward(d_w, x, M, K, N, y, o, ws, wsb, stream);
+    return run_unfused(pro, d_in, d_gamma, eps, d_residual, true, M, K, N, d_y, out, d_ws, ws_bytes, s,
+                       [&](const uint16_t *x, void *y, dmr_out_t o, const uint16_t *res, void *ws, size_t wsb) {
+                           return forward_bf16(d_w, x, M, K, N, y, o, res, ws, wsb, s);
                        });
 }
 

@@ -135,11 +135,6 @@ bool bf16_gemv_fits(int64_t K) {
     return (chunks + kWaves - 1) / kWaves <= 8;
 }
 
-hipError_t launch_bf16_gemv(const uint16_t *w, const uint16_t *x, int64_t K, int64_t N, void *y,
-                            bool out_f32, hipStream_t stream) {
-    return launch_bf16_gemv_fused(w, x, K, N, y, out_f32, Fusion{}, stream);
-}
-
 hipError_t launch_bf16_gemv_fused(const uint16_t *w, const uint16_t *x, int64_t K, int64_t N, void *y, bool out_f32,
                                   const Fusion &f, hipStream_t stream) {
     // slices per row: keep at most 8 chunks of 512 values of x in registers

@@ -25,7 +25,8 @@ __global__ __launch_bounds__(64 * WM * NW, 2) void bf16_mid_kernel(const uint16_
                                                                    const uint16_t *__restrict__ x,
                                                                    void *__restrict__ y, int M, int64_t K,
                                                                    int64_t N, int groups, int tiles, int gps,
-                                                                   int out_mode) {
+                                                                   int out_mode,
+                                                                   const uint16_t *__restrict__ res) {
     constexpr int THREADS = 64 * WM * NW;
     constexpr int BM = 16 * MTW * WM;
     constexpr int ROWS_PER_PASS = THREADS / 16;
@@ -130,6 +131,17 @@ __global__ __launch_bounds__(64 * WM * NW, 2) void bf16_mid_kernel(const uint16_
         }
     }
 
+    if (res && out_mode != 2) {      // clamped, unconditional loads: all of them in flight at once
+#pragma unroll
+        for (int rt = 0; rt < R; ++rt)
+#pragma unroll
+            for (int mt = 0; mt < MTW; ++mt)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int m = min(m0 + (wm * MTW + mt) * 16 + c * 4 + q, M - 1);
+                    acc[rt][mt][q] += bf16_bits_to_f32(res[(int64_t)m * N + (int64_t)min(tile0 + rt, tiles - 1) * kTileRows + j]);
+                }
+    }
     const int64_t part = out_mode == 2 ? (int64_t)blockIdx.z * M * N : 0;
 #pragma unroll
     for (int rt = 0; rt < R; ++rt) {
@@ -152,7 +164,7 @@ __global__ __launch_bounds__(64 * WM * NW, 2) void bf16_mid_kernel(const uint16_
 
 template <int MTW, int WM, int NW, int R>
 hipError_t launch_cfg(const uint16_t *w, const uint16_t *x, int M, int64_t K, int64_t N, void *dst, int out_mode,
-                      const MidPlan &p, hipStream_t stream) {
+                      const uint16_t *res, const MidPlan &p, hipStream_t stream) {
     constexpr int BM = 16 * MTW * WM;
     constexpr size_t lds = 2ull * BM * ROW_BYTES;
     // once per process and kernel instantiation (thread-safe static initialisation)
@@ -162,15 +174,15 @@ hipError_t launch_cfg(const uint16_t *w, const uint16_t *x, int M, int64_t K, in
     const int groups = (int)(K / kGroup), tiles = (int)(N / kTileRows);
     const dim3 grid((unsigned)((tiles + NW * R - 1) / (NW * R)), (unsigned)((M + BM - 1) / BM), (unsigned)p.SK);
     hipLaunchKernelGGL((bf16_mid_kernel<MTW, WM, NW, R>), grid, dim3(64 * WM * NW), lds, stream, w, x, dst, M, K, N,
-                       groups, tiles, p.gps, out_mode);
+                       groups, tiles, p.gps, out_mode, res);
     return hipGetLastError();
 }
 
 template <int MTW, int WM, int NW>
 hipError_t launch_r(const uint16_t *w, const uint16_t *x, int M, int64_t K, int64_t N, void *dst, int out_mode,
-                    const MidPlan &p, hipStream_t stream) {
-    return p.R == 2 ? launch_cfg<MTW, WM, NW, 2>(w, x, M, K, N, dst, out_mode, p, stream)
-                    : launch_cfg<MTW, WM, NW, 1>(w, x, M, K, N, dst, out_mode, p, stream);
+                    const uint16_t *res, const MidPlan &p, hipStream_t stream) {
+    return p.R == 2 ? launch_cfg<MTW, WM, NW, 2>(w, x, M, K, N, dst, out_mode, res, p, stream)
+                    : launch_cfg<MTW, WM, NW, 1>(w, x, M, K, N, dst, out_mode, res, p, stream);
 }
 
 }  // namespace
@@ -181,7 +193,7 @@ size_t bf16_mid_workspace_bytes(int64_t M, int64_t K, int64_t N) {
 }
 
 hipError_t launch_bf16_mid(const uint16_t *w, const uint16_t *x, int64_t M, int64_t K, int64_t N, void *y,
-                           bool out_f32, void *ws, hipStream_t stream) {
+                           bool out_f32, const uint16_t *res, void *ws, hipStream_t stream) {
     const MidPlan p = plan_mid(M, K, N);
     const bool split = p.SK > 1;
     void *dst = split ? ws : y;
@@ -190,17 +202,17 @@ hipError_t launch_bf16_mid(const uint16_t *w, const uint16_t *x, int64_t M, int6
     hipError_t e;
     if (p.WM == 1) {
         switch (p.MTW) {
-            case 1: e = launch_r<1, 1, 4>(w, x, iM, K, N, dst, out_mode, p, stream); break;
-            case 2: e = launch_r<2, 1, 4>(w, x, iM, K, N, dst, out_mode, p, stream); break;
-            case 3: e = launch_r<3, 1, 4>(w, x, iM, K, N, dst, out_mode, p, stream); break;
-            default: e = launch_r<4, 1, 4>(w, x, iM, K, N, dst, out_mode, p, stream); break;
+            case 1: e = launch_r<1, 1, 4>(w, x, iM, K, N, dst, out_mode, res, p, stream); break;
+            case 2: e = launch_r<2, 1, 4>(w, x, iM, K, N, dst, out_mode, res, p, stream); break;
+            case 3: e = launch_r<3, 1, 4>(w, x, iM, K, N, dst, out_mode, res, p, stream); break;
+            default: e = launch_r<4, 1, 4>(w, x, iM, K, N, dst, out_mode, res, p, stream); break;
         }
     } else {
-        e = p.MTW == 3 ? launch_r<3, 2, 2>(w, x, iM, K, N, dst, out_mode, p, stream)
-                       : launch_r<4, 2, 2>(w, x, iM, K, N, dst, out_mode, p, stream);
+        e = p.MTW == 3 ? launch_r<3, 2, 2>(w, x, iM, K, N, dst, out_mode, res, p, stream)
+                       : launch_r<4, 2, 2>(w, x, iM, K, N, dst, out_mode, res, p, stream);
     }
     if (e != hipSuccess || !split) return e;
-    return launch_splitk_reduce(static_cast<const float *>(ws), y, M * N, p.SK, out_f32, stream);
+    return launch_splitk_reduce(static_cast<const float *>(ws), y, M * N, p.SK, out_f32, res, stream);
 }
 
 }  // namespace dmr

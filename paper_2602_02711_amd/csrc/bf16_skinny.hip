@@ -42,7 +42,7 @@ __device__ __forceinline__ void load_step(StepRegs<MT> &r, const uint16_t *__res
 template <int MT, bool OUT_F32>
 __global__ __launch_bounds__(bf16_max_waves<MT>() * 64) void bf16_skinny_kernel(
     const uint16_t *__restrict__ w, const uint16_t *__restrict__ x, void *__restrict__ y, int64_t M,
-    int64_t K, int64_t N) {
+    int64_t K, int64_t N, const uint16_t *__restrict__ res) {
     extern __shared__ float red[];   // [S][MT * 4][64]
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
@@ -96,6 +96,7 @@ __global__ __launch_bounds__(bf16_max_waves<MT>() * 64) void bf16_skinny_kernel(
         const int64_t m = mt * 16 + (l >> 4) * 4 + q;
         const int64_t n = T * kTileRows + (l & 15);
         if (m < M) {
+            sum = plus_residual(sum, res, m * N + n);
             if (OUT_F32)
                 reinterpret_cast<float *>(y)[m * N + n] = sum;
             else
@@ -112,27 +113,27 @@ int pick_waves(int64_t tiles, int steps, int max_waves) {
 
 template <int MT>
 hipError_t launch_mt(const uint16_t *w, const uint16_t *x, int64_t M, int64_t K, int64_t N, void *y,
-                     bool out_f32, hipStream_t stream) {
+                     bool out_f32, const uint16_t *res, hipStream_t stream) {
     const int64_t tiles = N / kTileRows;
     const int S = pick_waves(tiles, (int)(K / 128), bf16_max_waves<MT>());
     const size_t lds = (size_t)S * MT * 4 * 64 * sizeof(float);
     if (out_f32)
         hipLaunchKernelGGL((bf16_skinny_kernel<MT, true>), dim3((unsigned)tiles), dim3(S * 64), lds,
-                           stream, w, x, y, M, K, N);
+                           stream, w, x, y, M, K, N, res);
     else
         hipLaunchKernelGGL((bf16_skinny_kernel<MT, false>), dim3((unsigned)tiles), dim3(S * 64), lds,
-                           stream, w, x, y, M, K, N);
+                           stream, w, x, y, M, K, N, res);
     return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_bf16_skinny(const uint16_t *w, const uint16_t *x, int64_t M, int64_t K, int64_t N,
-                              void *y, bool out_f32, hipStream_t stream) {
-    if (M <= 16) return launch_mt<1>(w, x, M, K, N, y, out_f32, stream);
-    if (M <= 32) return launch_mt<2>(w, x, M, K, N, y, out_f32, stream);
-    if (M <= 48) return launch_mt<3>(w, x, M, K, N, y, out_f32, stream);
-    return launch_mt<4>(w, x, M, K, N, y, out_f32, stream);
+                              void *y, bool out_f32, const uint16_t *res, hipStream_t stream) {
+    if (M <= 16) return launch_mt<1>(w, x, M, K, N, y, out_f32, res, stream);
+    if (M <= 32) return launch_mt<2>(w, x, M, K, N, y, out_f32, res, stream);
+    if (M <= 48) return launch_mt<3>(w, x, M, K, N, y, out_f32, res, stream);
+    return launch_mt<4>(w, x, M, K, N, y, out_f32, res, stream);
 }
 
 }  // namespace dmr

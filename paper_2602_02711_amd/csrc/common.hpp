@@ -55,6 +55,12 @@ __device__ __forceinline__ uint16_t f32_to_bf16(float f) {
     return (uint16_t)(pack_bf16x2(f, 0.0f) & 0xFFFFu);
 }
 
+// v plus element o of an optional bf16 residual (res == nullptr: v itself), the sum formed in fp32 before the output is
+// rounded, as the stand-alone residual kernel forms it.
+__device__ __forceinline__ float plus_residual(float v, const uint16_t *__restrict__ res, int64_t o) {
+    return res ? v + bf16_bits_to_f32(res[o]) : v;
+}
+
 // Streaming (read-once) loads: keep weight traffic from displacing the activations in the caches.
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ uint4 load_stream(const uint4 *p) {
@@ -139,25 +145,21 @@ inline size_t weight_region_bytes(int64_t K, int64_t N) { return (size_t)N * (si
 inline size_t sz_region_bytes(int64_t K, int64_t N) { return (size_t)N * (size_t)(K / kGroup) * 4; }
 inline size_t sz_region_bytes_per_channel(int64_t N) { return (size_t)N * 4; }
 
-// Kernel launchers (each returns hipGetLastError() after its launch).
+// Kernel launchers (each returns hipGetLastError() after its launch).  `res`, where a forward has it: a bf16 residual
+// [M][N] that the store of the result adds in fp32 before rounding, or nullptr.  An element of it is read by the thread that
+// stores the same element of y, before it stores it, so y may be the residual's own buffer.
 hipError_t launch_retile(int64_t K, int64_t N, const uint32_t *qweight, const uint16_t *scales,
                          const uint16_t *zeros, uint4 *wt, uint32_t *sz, bool per_channel,
                          hipStream_t stream);
 hipError_t launch_dequantize(const LayerView &L, uint16_t *w_bf16, hipStream_t stream);
 hipError_t launch_quantize(int64_t K, int64_t N, const float *w, uint32_t *qweight,
                            uint16_t *scales, uint16_t *zeros, hipStream_t stream);
-// M == 1 decode kernel; returns hipErrorInvalidValue (nothing launched) for shapes it does not take.
+// M == 1 decode kernel (launch_w4_gemv_fused): the shapes it takes.
 bool w4_gemv_fits(int64_t K, int64_t N, bool with_residual);
-hipError_t launch_w4_gemv(const LayerView &L, const uint16_t *x, void *y, bool out_f32,
-                          hipStream_t stream);
-// M == 1 bf16 kernel; hipErrorInvalidValue (nothing launched) for K beyond its range.
+// M == 1 bf16 kernel (launch_bf16_gemv_fused): the K it takes.
 bool bf16_gemv_fits(int64_t K);
-hipError_t launch_bf16_gemv(const uint16_t *w, const uint16_t *x, int64_t K, int64_t N, void *y,
-                            bool out_f32, hipStream_t stream);
-// 2 <= M <= 16 streaming kernel; hipErrorInvalidValue (nothing launched) when the activations do not fit LDS.
+// 2 <= M <= 16 streaming kernel (launch_w4_stream_fused): whether the activations fit LDS.
 bool w4_stream_fits(int64_t M, int64_t K, int64_t N);
-hipError_t launch_w4_stream(const LayerView &L, const uint16_t *x, int64_t M, void *y, bool out_f32,
-                            hipStream_t stream);
 // bf16 twin of the streaming kernel (optional residual added at the store).
 bool bf16_stream_fits(int64_t M, int64_t K, int64_t N);
 hipError_t launch_bf16_stream(const uint16_t *w, const uint16_t *x, int64_t M, int64_t K, int64_t N, void *y,
@@ -169,15 +171,15 @@ hipError_t launch_w4_skinny2(const LayerView &L, const uint16_t *x, int64_t M, v
 // 16 < M up to a few hundred rows: weights straight into registers, activations through LDS, optional
 // split of K whose fp32 partials go to `ws` (w4_mid_workspace_bytes) and are added by a second kernel.
 size_t w4_mid_workspace_bytes(int64_t M, int64_t K, int64_t N);
-hipError_t launch_w4_mid(const LayerView &L, const uint16_t *x, int64_t M, void *y, bool out_f32, void *ws,
-                         hipStream_t stream);
+hipError_t launch_w4_mid(const LayerView &L, const uint16_t *x, int64_t M, void *y, bool out_f32, const uint16_t *res,
+                         void *ws, hipStream_t stream);
 // The same kernel on a 3-bit layer (same plan and workspace as launch_w4_mid).
-hipError_t launch_w3_mid(const LayerView3 &L, const uint16_t *x, int64_t M, void *y, bool out_f32, void *ws,
-                         hipStream_t stream);
+hipError_t launch_w3_mid(const LayerView3 &L, const uint16_t *x, int64_t M, void *y, bool out_f32, const uint16_t *res,
+                         void *ws, hipStream_t stream);
 // bf16 twin of launch_w4_mid.
 size_t bf16_mid_workspace_bytes(int64_t M, int64_t K, int64_t N);
 hipError_t launch_bf16_mid(const uint16_t *w, const uint16_t *x, int64_t M, int64_t K, int64_t N, void *y,
-                           bool out_f32, void *ws, hipStream_t stream);
+                           bool out_f32, const uint16_t *res, void *ws, hipStream_t stream);
 hipError_t launch_retile3(int64_t K, int64_t N, const uint32_t *qweight, const uint16_t *scales,
                           const uint16_t *zeros, uint32_t *wt, uint32_t *sz, hipStream_t stream);
 hipError_t launch_dequantize3(const LayerView3 &L, uint16_t *w_bf16, hipStream_t stream);
@@ -185,22 +187,23 @@ hipError_t launch_quantize3(int64_t K, int64_t N, const float *w, uint32_t *qwei
                             uint16_t *zeros, hipStream_t stream);
 // 2 <= M <= 16 on a 3-bit layer; hipErrorInvalidValue (nothing launched) when the activations do not fit LDS.
 hipError_t launch_w3_stream(const LayerView3 &L, const uint16_t *x, int64_t M, void *y, bool out_f32,
-                            hipStream_t stream);
+                            const uint16_t *res, hipStream_t stream);
 bool w3_gemv_fits(int64_t K, int64_t N);
-hipError_t launch_w3_gemv(const LayerView3 &L, const uint16_t *x, void *y, bool out_f32, hipStream_t stream);
+hipError_t launch_w3_gemv(const LayerView3 &L, const uint16_t *x, void *y, bool out_f32, const uint16_t *res, hipStream_t stream);
 hipError_t launch_hbm_read_probe(const void *buf, size_t bytes, uint32_t *sink, int blocks,
                                  hipStream_t stream);
 hipError_t launch_empty_probe(int blocks, int threads, size_t lds_bytes, hipStream_t stream);
 hipError_t launch_w4_skinny(const LayerView &L, const uint16_t *x, int64_t M, void *y, bool out_f32,
                             hipStream_t stream);
 hipError_t launch_bf16_skinny(const uint16_t *w, const uint16_t *x, int64_t M, int64_t K, int64_t N,
-                              void *y, bool out_f32, hipStream_t stream);
+                              void *y, bool out_f32, const uint16_t *res, hipStream_t stream);
 // 128 x 128 tiles on the exact integer codes q - z; the scale is applied per group in fp32.
-hipError_t launch_w4_gemm(const LayerView &L, const uint16_t *x, int64_t M, void *y, bool out_f32, hipStream_t stream);
+hipError_t launch_w4_gemm(const LayerView &L, const uint16_t *x, int64_t M, void *y, bool out_f32, const uint16_t *res,
+                          hipStream_t stream);
 // The exact kernel restricted to the column blocks of 128 rows with a nonzero word in `only` (device memory, one word
 // per 32 rows; `pairs`: to the aligned pairs of blocks with one).
 hipError_t launch_w4_gemm_flagged(const LayerView &L, const uint16_t *x, int64_t M, void *y, bool out_f32,
-                                  const uint32_t *only, bool pairs, hipStream_t stream);
+                                  const uint16_t *res, const uint32_t *only, bool pairs, hipStream_t stream);
 // 256 x 256 or 256 x 128 tiles on the exact codes 16 + q with one accumulator tile kept in units of the current group's scale;
 // a pre-pass writes the zero-point operands, the rescale factors and per-column-block flags into `ws`
 // (w4_gemm_rescale_workspace_bytes), and the 128 x 128 exact kernel takes the column blocks it flags.
@@ -208,22 +211,23 @@ bool w4_gemm_rescale_applies(int64_t M, int64_t N);
 int w4_gemm_rescale_tile_rows(int64_t M, int64_t N);      // 128: 128 x 128 tiles (then the next function does not apply); 256
 int w4_gemm_rescale_wave_columns(int64_t M, int64_t N);   // 4: 256 x 256 tiles; 2: 256 x 128
 size_t w4_gemm_rescale_workspace_bytes(int64_t M, int64_t K, int64_t N);
-hipError_t launch_w4_gemm_rescale(const LayerView &L, const uint16_t *x, int64_t M, void *y, bool out_f32, void *ws,
-                                  hipStream_t stream);
+hipError_t launch_w4_gemm_rescale(const LayerView &L, const uint16_t *x, int64_t M, void *y, bool out_f32, const uint16_t *res,
+                                  void *ws, hipStream_t stream);
 // The exact-code 128 x 128 kernel on a 3-bit layer; the 256-row kernel and its fallback for flagged column blocks.
-hipError_t launch_w3_gemm(const LayerView3 &L, const uint16_t *x, int64_t M, void *y, bool out_f32, hipStream_t stream);
+hipError_t launch_w3_gemm(const LayerView3 &L, const uint16_t *x, int64_t M, void *y, bool out_f32, const uint16_t *res,
+                          hipStream_t stream);
 hipError_t launch_w3_gemm_flagged(const LayerView3 &L, const uint16_t *x, int64_t M, void *y, bool out_f32,
-                                  const uint32_t *only, bool pairs, hipStream_t stream);
-hipError_t launch_w3_gemm_rescale(const LayerView3 &L, const uint16_t *x, int64_t M, void *y, bool out_f32, void *ws,
-                                  hipStream_t stream);
+                                  const uint16_t *res, const uint32_t *only, bool pairs, hipStream_t stream);
+hipError_t launch_w3_gemm_rescale(const LayerView3 &L, const uint16_t *x, int64_t M, void *y, bool out_f32, const uint16_t *res,
+                                  void *ws, hipStream_t stream);
 hipError_t launch_bf16_gemm(const uint16_t *w, const uint16_t *x, int64_t M, int64_t K, int64_t N,
-                            void *y, bool out_f32, hipStream_t stream);
+                            void *y, bool out_f32, const uint16_t *res, hipStream_t stream);
 // 256 x 256 tiles on eight wavefronts (direct-to-LDS operand loads, four-stage pipeline, two waves per SIMD) for
 // problems large enough to fill the chip with them.
 bool gemm_big_applies(int64_t M, int64_t N);
 hipError_t launch_bf16_gemm_w8(const uint16_t *w, const uint16_t *x, int64_t M, int64_t K, int64_t N, void *y, bool out_f32,
-                               hipStream_t stream);
+                               const uint16_t *res, hipStream_t stream);
 hipError_t launch_bf16_gemm_dma128(const uint16_t *w, const uint16_t *x, int64_t M, int64_t K, int64_t N,
-                                   void *y, bool out_f32, hipStream_t stream);
+                                   void *y, bool out_f32, const uint16_t *res, hipStream_t stream);
 
 }  // namespace dmr

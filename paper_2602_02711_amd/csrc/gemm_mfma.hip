@@ -121,13 +121,13 @@ __device__ __forceinline__ void store_lds(const Prefetch<SRC> &p, uint16_t *As, 
     }
 }
 
-template <int SRC, bool OUT_F32>
+template <int SRC, bool OUT_F32, bool RES>
 __global__ __launch_bounds__(256, 2) void gemm_kernel(const void *__restrict__ wsrc,
                                                    const uint32_t *__restrict__ sz,
                                                    const uint16_t *__restrict__ x,
                                                    void *__restrict__ y, int64_t M, int64_t K,
                                                    int64_t N, int szs, const uint32_t *__restrict__ only,
-                                                   int only_pairs) {
+                                                   int only_pairs, const uint16_t *__restrict__ res) {
     // `only` (optional): one word per 32 columns; the block is computed here only when one of the words of its 128
     // columns is nonzero (with only_pairs: of the 256 columns of its aligned pair of blocks)
     if (only) {
@@ -225,14 +225,24 @@ __global__ __launch_bounds__(256, 2) void gemm_kernel(const void *__restrict__ w
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
                 const int64_t n = n0 + wn * 64 + j * 32 + (lane & 31);
+                float rv[16];
+                if constexpr (RES) {      // unconditional loads, a tile's all in flight (with the branch at run time, no template
+                    // flag, the calls without a residual ran 5-7 % slower)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        const int64_t m = min(m0 + wm * 64 + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3), M - 1);
+                        rv[r] = bf16_bits_to_f32(res[m * N + min(n, N - 1)]);
+                    }
+                }
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
                     const int64_t m = m0 + wm * 64 + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
                     if (m < M && n < N) {
+                        const float v = RES ? acc[i][j][r] + rv[r] : acc[i][j][r];
                         if (OUT_F32)
-                            reinterpret_cast<float *>(y)[m * N + n] = acc[i][j][r];
+                            reinterpret_cast<float *>(y)[m * N + n] = v;
                         else
-                            reinterpret_cast<uint16_t *>(y)[m * N + n] = f32_to_bf16(acc[i][j][r]);
+                            reinterpret_cast<uint16_t *>(y)[m * N + n] = f32_to_bf16(v);
                     }
                 }
             }
@@ -241,45 +251,43 @@ __global__ __launch_bounds__(256, 2) void gemm_kernel(const void *__restrict__ w
 
 template <int SRC>
 hipError_t launch(const void *wsrc, const uint32_t *sz, int szs, const uint16_t *x, int64_t M, int64_t K,
-                  int64_t N, void *y, bool out_f32, hipStream_t stream, const uint32_t *only = nullptr,
+                  int64_t N, void *y, bool out_f32, const uint16_t *res, hipStream_t stream, const uint32_t *only = nullptr,
                   bool only_pairs = false) {
     const unsigned row_blocks = (unsigned)((M + BM - 1) / BM);
     const dim3 grid((unsigned)((N + BN - 1) / BN), only ? (row_blocks < 4 ? row_blocks : 4) : row_blocks);
-    if (out_f32)
-        hipLaunchKernelGGL((gemm_kernel<SRC, true>), grid, dim3(256), 0, stream, wsrc, sz, x, y, M, K, N, szs, only,
-                           (int)only_pairs);
-    else
-        hipLaunchKernelGGL((gemm_kernel<SRC, false>), grid, dim3(256), 0, stream, wsrc, sz, x, y, M, K, N, szs, only,
-                           (int)only_pairs);
+    auto kernel = out_f32 ? (res ? &gemm_kernel<SRC, true, true> : &gemm_kernel<SRC, true, false>)
+                          : (res ? &gemm_kernel<SRC, false, true> : &gemm_kernel<SRC, false, false>);
+    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, wsrc, sz, x, y, M, K, N, szs, only, (int)only_pairs, res);
     return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_w4_gemm(const LayerView &L, const uint16_t *x, int64_t M, void *y, bool out_f32, hipStream_t stream) {
-    return launch<kSrcW4Exact>(L.wt, L.sz, L.szs, x, M, L.K, L.N, y, out_f32, stream);
+hipError_t launch_w4_gemm(const LayerView &L, const uint16_t *x, int64_t M, void *y, bool out_f32, const uint16_t *res,
+                          hipStream_t stream) {
+    return launch<kSrcW4Exact>(L.wt, L.sz, L.szs, x, M, L.K, L.N, y, out_f32, res, stream);
 }
 
 // The exact kernel on the column blocks of 128 rows that have a nonzero word in `only` (device memory, one word per
 // 32 rows); with `pairs`, on both blocks of an aligned pair (256 columns) when either has one.
 hipError_t launch_w4_gemm_flagged(const LayerView &L, const uint16_t *x, int64_t M, void *y, bool out_f32,
-                                  const uint32_t *only, bool pairs, hipStream_t stream) {
-    return launch<kSrcW4Exact>(L.wt, L.sz, L.szs, x, M, L.K, L.N, y, out_f32, stream, only, pairs);
+                                  const uint16_t *res, const uint32_t *only, bool pairs, hipStream_t stream) {
+    return launch<kSrcW4Exact>(L.wt, L.sz, L.szs, x, M, L.K, L.N, y, out_f32, res, stream, only, pairs);
 }
 
-hipError_t launch_w3_gemm(const LayerView3 &L, const uint16_t *x, int64_t M, void *y, bool out_f32,
+hipError_t launch_w3_gemm(const LayerView3 &L, const uint16_t *x, int64_t M, void *y, bool out_f32, const uint16_t *res,
                           hipStream_t stream) {
-    return launch<kSrcW3Exact>(L.wt, L.sz, 1, x, M, L.K, L.N, y, out_f32, stream);
+    return launch<kSrcW3Exact>(L.wt, L.sz, 1, x, M, L.K, L.N, y, out_f32, res, stream);
 }
 
 hipError_t launch_w3_gemm_flagged(const LayerView3 &L, const uint16_t *x, int64_t M, void *y, bool out_f32,
-                                  const uint32_t *only, bool pairs, hipStream_t stream) {
-    return launch<kSrcW3Exact>(L.wt, L.sz, 1, x, M, L.K, L.N, y, out_f32, stream, only, pairs);
+                                  const uint16_t *res, const uint32_t *only, bool pairs, hipStream_t stream) {
+    return launch<kSrcW3Exact>(L.wt, L.sz, 1, x, M, L.K, L.N, y, out_f32, res, stream, only, pairs);
 }
 
 hipError_t launch_bf16_gemm(const uint16_t *w, const uint16_t *x, int64_t M, int64_t K, int64_t N,
-                            void *y, bool out_f32, hipStream_t stream) {
-    return launch<kSrcBf16>(w, nullptr, 1, x, M, K, N, y, out_f32, stream);
+                            void *y, bool out_f32, const uint16_t *res, hipStream_t stream) {
+    return launch<kSrcBf16>(w, nullptr, 1, x, M, K, N, y, out_f32, res, stream);
 }
 
 }  // namespace dmr

@@ -88,9 +88,10 @@ __device__ __forceinline__ void mfma_16(const Frag (&a)[T], const Frag (&b)[T], 
             acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i].v, b[j].v, acc[i][j], 0, 0, 0);
 }
 
-template <bool OUT_F32, int T>
+template <bool OUT_F32, bool RES, int T>
 __global__ __launch_bounds__(256) void gemm_dma_kernel(const uint16_t *__restrict__ w, const uint16_t *__restrict__ x,
-                                                       void *__restrict__ y, int64_t M, int64_t K, int64_t N, int nbn) {
+                                                       void *__restrict__ y, int64_t M, int64_t K, int64_t N, int nbn,
+                                                       const uint16_t *__restrict__ res) {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];   // NS stages of {A, B}
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -189,38 +190,51 @@ __global__ __launch_bounds__(256) void gemm_dma_kernel(const uint16_t *__restric
 #pragma unroll
         for (int j = 0; j < T; ++j) {
             const int64_t n = n0 + wn * 32 * T + j * 32 + (lane & 31);
+            float rv[16];
+            if constexpr (RES) {      // unconditional loads, a tile's all in flight (with the branch at run time, no template
+                // flag, the calls without a residual ran 5-7 % slower)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int64_t m = min(m0 + wm * 32 * T + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3), M - 1);
+                    rv[r] = bf16_bits_to_f32(res[m * N + min(n, N - 1)]);
+                }
+            }
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const int64_t m = m0 + wm * 32 * T + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
                 if (m < M && n < N) {
+                    const float v = RES ? acc[i][j][r] + rv[r] : acc[i][j][r];
                     if (OUT_F32)
-                        reinterpret_cast<float *>(y)[m * N + n] = acc[i][j][r];
+                        reinterpret_cast<float *>(y)[m * N + n] = v;
                     else
-                        reinterpret_cast<uint16_t *>(y)[m * N + n] = f32_to_bf16(acc[i][j][r]);
+                        reinterpret_cast<uint16_t *>(y)[m * N + n] = f32_to_bf16(v);
                 }
             }
         }
 }
 
-template <bool OUT_F32, int T>
-hipError_t launch_one(const uint16_t *w, const uint16_t *x, int64_t M, int64_t K, int64_t N, void *y, hipStream_t stream) {
+template <bool OUT_F32, bool RES, int T>
+hipError_t launch_one(const uint16_t *w, const uint16_t *x, int64_t M, int64_t K, int64_t N, void *y, const uint16_t *res,
+                      hipStream_t stream) {
     using G = Geo<T>;
     constexpr int BT = G::BT;
     if (K / BK < 4) return hipErrorInvalidValue;
-    static const hipError_t attr_status = hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_dma_kernel<OUT_F32, T>),
+    static const hipError_t attr_status = hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_dma_kernel<OUT_F32, RES, T>),
                                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)G::LDS_BYTES);
     if (attr_status != hipSuccess) return attr_status;
     const int nbm = (int)((M + BT - 1) / BT), nbn = (int)((N + BT - 1) / BT);
-    hipLaunchKernelGGL((gemm_dma_kernel<OUT_F32, T>), dim3((unsigned)(nbm * nbn)), dim3(256), G::LDS_BYTES, stream, w, x, y, M, K, N,
-                       nbn);
+    hipLaunchKernelGGL((gemm_dma_kernel<OUT_F32, RES, T>), dim3((unsigned)(nbm * nbn)), dim3(256), G::LDS_BYTES, stream, w, x, y, M, K, N,
+                       nbn, res);
     return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_bf16_gemm_dma128(const uint16_t *w, const uint16_t *x, int64_t M, int64_t K, int64_t N, void *y,
-                                   bool out_f32, hipStream_t stream) {
-    return out_f32 ? launch_one<true, 2>(w, x, M, K, N, y, stream) : launch_one<false, 2>(w, x, M, K, N, y, stream);
+                                   bool out_f32, const uint16_t *res, hipStream_t stream) {
+    if (res)
+        return out_f32 ? launch_one<true, true, 2>(w, x, M, K, N, y, res, stream) : launch_one<false, true, 2>(w, x, M, K, N, y, res, stream);
+    return out_f32 ? launch_one<true, false, 2>(w, x, M, K, N, y, res, stream) : launch_one<false, false, 2>(w, x, M, K, N, y, res, stream);
 }
 
 }  // namespace dmr

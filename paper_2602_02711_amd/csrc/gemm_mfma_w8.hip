@@ -71,9 +71,10 @@ __device__ __forceinline__ void mfma_all(const Frag (&a)[TM], const Frag (&b)[TN
 // already in registers, nothing to wait for) while waves 4..7 fetch their fragments of step kt from LDS and issue their
 // loads; then the roles swap.  Two barriers per k step, the same number on both paths.  A wave's fragments of a whole k
 // step (both sub-steps, 48 registers) live in registers from its fetch phase to its multiply phase.
-template <bool OUT_F32>
+template <bool OUT_F32, bool RES>
 __global__ __launch_bounds__(512) void gemm_w8_kernel(const uint16_t *__restrict__ w, const uint16_t *__restrict__ x,
-                                                         void *__restrict__ y, int64_t M, int64_t K, int64_t N, int nbn, int lg_xm) {
+                                                         void *__restrict__ y, int64_t M, int64_t K, int64_t N, int nbn, int lg_xm,
+                                                         const uint16_t *__restrict__ res) {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -198,23 +199,34 @@ __global__ __launch_bounds__(512) void gemm_w8_kernel(const uint16_t *__restrict
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
             const int64_t n = n0 + wn * 32 * TN + j * 32 + (lane & 31);
+            float rv[16];
+            if constexpr (RES) {      // unconditional loads, a tile's all in flight (with the branch at run time, no template
+                // flag, the calls without a residual ran 5-7 % slower)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int64_t m = min(m0 + wm * 32 * TM + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3), M - 1);
+                    rv[r] = bf16_bits_to_f32(res[m * N + min(n, N - 1)]);
+                }
+            }
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const int64_t m = m0 + wm * 32 * TM + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
                 if (m < M && n < N) {
+                    const float v = RES ? acc[i][j][r] + rv[r] : acc[i][j][r];
                     if (OUT_F32)
-                        reinterpret_cast<float *>(y)[m * N + n] = acc[i][j][r];
+                        reinterpret_cast<float *>(y)[m * N + n] = v;
                     else
-                        reinterpret_cast<uint16_t *>(y)[m * N + n] = f32_to_bf16(acc[i][j][r]);
+                        reinterpret_cast<uint16_t *>(y)[m * N + n] = f32_to_bf16(v);
                 }
             }
         }
 }
 
-template <bool OUT_F32>
-hipError_t launch_one(const uint16_t *w, const uint16_t *x, int64_t M, int64_t K, int64_t N, void *y, hipStream_t stream) {
+template <bool OUT_F32, bool RES>
+hipError_t launch_one(const uint16_t *w, const uint16_t *x, int64_t M, int64_t K, int64_t N, void *y, const uint16_t *res,
+                      hipStream_t stream) {
     if (K / BK < 4) return hipErrorInvalidValue;
-    static const hipError_t attr_status = hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_w8_kernel<OUT_F32>),
+    static const hipError_t attr_status = hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_w8_kernel<OUT_F32, RES>),
                                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_BYTES);
     if (attr_status != hipSuccess) return attr_status;
     // Workgroups go to the 8 XCDs round-robin by linear index and each XCD has its own L2.  When the
@@ -226,8 +238,8 @@ hipError_t launch_one(const uint16_t *w, const uint16_t *x, int64_t M, int64_t K
     const int nbm = (int)((M + BM - 1) / BM), nbn = (int)((N + BN - 1) / BN);
     int lg_xm = 2;
     while (lg_xm >= 0 && (nbm % (4 << lg_xm) != 0 || nbn % (8 * (8 >> lg_xm)) != 0)) --lg_xm;
-    hipLaunchKernelGGL((gemm_w8_kernel<OUT_F32>), dim3((unsigned)(nbm * nbn)), dim3(512), LDS_BYTES, stream, w, x, y, M, K, N, nbn,
-                       lg_xm);
+    hipLaunchKernelGGL((gemm_w8_kernel<OUT_F32, RES>), dim3((unsigned)(nbm * nbn)), dim3(512), LDS_BYTES, stream, w, x, y, M, K, N, nbn,
+                       lg_xm, res);
     return hipGetLastError();
 }
 
@@ -241,8 +253,10 @@ bool gemm_big_applies(int64_t M, int64_t N) {
 }
 
 hipError_t launch_bf16_gemm_w8(const uint16_t *w, const uint16_t *x, int64_t M, int64_t K, int64_t N, void *y, bool out_f32,
-                               hipStream_t stream) {
-    return out_f32 ? launch_one<true>(w, x, M, K, N, y, stream) : launch_one<false>(w, x, M, K, N, y, stream);
+                               const uint16_t *res, hipStream_t stream) {
+    if (res)
+        return out_f32 ? launch_one<true, true>(w, x, M, K, N, y, res, stream) : launch_one<false, true>(w, x, M, K, N, y, res, stream);
+    return out_f32 ? launch_one<true, false>(w, x, M, K, N, y, res, stream) : launch_one<false, false>(w, x, M, K, N, y, res, stream);
 }
 
 }  // namespace dmr

@@ -46,6 +46,8 @@
 // first reads of the next stage between them.  The rescale factors of a wave's 64 columns come direct-to-LDS into a
 // slot of the wave's own, one instruction per group.  The zero-point loop runs on four stages of 32 k with both
 // operands direct-to-LDS (rows of 64 bytes, chunks swizzled with bits 2..3 of the row number).
+#include <type_traits>
+
 #include "common.hpp"
 
 namespace dmr {
@@ -218,11 +220,11 @@ __device__ __forceinline__ void read_wave_factors(const uint8_t *__restrict__ p,
 // s[G - 1] / s[G] for G >= 1, the LAST scale for G = 0 (the accumulator is zero when group 0 starts, so that slot is
 // free), 1 in the slot behind the last group.  a2 / b2: bf16 [M][KP] / [N][KP].  flags: one word per 32 columns,
 // nonzero = those columns do not qualify; a tile with a flagged part is left to the other kernel as a whole.
-template <int WM, int WN, int TM, int TN, int BITS, bool OUT_F32, bool PC>
+template <int WM, int WN, int TM, int TN, int BITS, bool OUT_F32, bool PC, bool RES>
 __global__ __launch_bounds__(64 * WM * WN, TM * TN <= 2 ? 2 : 1) void gemm_w4_rescale_kernel(
     const void *__restrict__ wt, const float *__restrict__ rfac, const uint16_t *__restrict__ x, const uint16_t *__restrict__ a2,
     const uint16_t *__restrict__ b2, const uint32_t *__restrict__ flags, void *__restrict__ y, int64_t M, int64_t K, int64_t N,
-    int KP, int nbn, int lg_xm) {
+    int KP, int nbn, int lg_xm, const uint16_t *__restrict__ res) {
     using G = Geo<WM, WN, TM, TN, BITS>;
     constexpr int BM = G::BM, BN = G::BN, STAGE_BYTES = G::STAGE_BYTES, A_BYTES = G::A_BYTES, A2S_BYTES = G::A2S_BYTES;
     constexpr int LA = G::LA, LB = G::LB, L2 = G::L2;
@@ -606,14 +608,24 @@ __global__ __launch_bounds__(64 * WM * WN, TM * TN <= 2 ? 2 : 1) void gemm_w4_re
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
             const int64_t n = n0 + wn * 32 * TN + j * 32 + (lane & 31);
+            float rv[16];
+            if constexpr (RES) {      // unconditional loads, a tile's all in flight (with the branch at run time, no template
+                // flag, the calls without a residual ran 5-7 % slower)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int64_t m = min(m0 + wm * 32 * TM + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3), M - 1);
+                    rv[r] = bf16_bits_to_f32(res[m * N + min(n, N - 1)]);
+                }
+            }
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const int64_t m = m0 + wm * 32 * TM + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
                 if (m < M && n < N) {
+                    const float v = RES ? acc[i][j][r] + rv[r] : acc[i][j][r];
                     if (OUT_F32)
-                        reinterpret_cast<float *>(y)[m * N + n] = acc[i][j][r];
+                        reinterpret_cast<float *>(y)[m * N + n] = v;
                     else
-                        reinterpret_cast<uint16_t *>(y)[m * N + n] = f32_to_bf16(acc[i][j][r]);
+                        reinterpret_cast<uint16_t *>(y)[m * N + n] = f32_to_bf16(v);
                 }
             }
         }
@@ -788,7 +800,7 @@ struct Operands {       // what the pre-pass leaves in the workspace
 
 template <int WM, int WN, int TM, int TN, int BITS>
 hipError_t launch_tile(const void *wt, bool pc, const uint16_t *x, int64_t M, int64_t K, int64_t N, void *y, bool out_f32,
-                       const RescalePlan &p, const Operands &o, hipStream_t stream) {
+                       const uint16_t *res, const RescalePlan &p, const Operands &o, hipStream_t stream) {
     using G = Geo<WM, WN, TM, TN, BITS>;
     const int nbm = (int)((M + G::BM - 1) / G::BM), nbn = (int)((N + G::BN - 1) / G::BN);
     // XCD-aware tile order when the grid of tiles divides into regions of 8 patches of 4 x 8 tiles (see the kernel)
@@ -799,23 +811,25 @@ hipError_t launch_tile(const void *wt, bool pc, const uint16_t *x, int64_t M, in
                                             (int)G::LDS_BYTES);
         if (st != hipSuccess) return st;
         hipLaunchKernelGGL(kernel, dim3((unsigned)(nbm * nbn)), dim3(G::THREADS), G::LDS_BYTES, stream, wt, o.rfac, x, o.a2, o.b2,
-                           o.flags, y, M, K, N, p.KP, nbn, lg_xm);
+                           o.flags, y, M, K, N, p.KP, nbn, lg_xm, res);
         return hipGetLastError();
     };
+    auto pick = [&](auto per_channel, auto with_res) {
+        constexpr bool PC = decltype(per_channel)::value, RES = decltype(with_res)::value;
+        return out_f32 ? go(&gemm_w4_rescale_kernel<WM, WN, TM, TN, BITS, true, PC, RES>)
+                       : go(&gemm_w4_rescale_kernel<WM, WN, TM, TN, BITS, false, PC, RES>);
+    };
     if constexpr (BITS == 4) {
-        if (pc)
-            return out_f32 ? go(&gemm_w4_rescale_kernel<WM, WN, TM, TN, 4, true, true>)
-                           : go(&gemm_w4_rescale_kernel<WM, WN, TM, TN, 4, false, true>);
+        if (pc) return res ? pick(std::true_type{}, std::true_type{}) : pick(std::true_type{}, std::false_type{});
     }
-    return out_f32 ? go(&gemm_w4_rescale_kernel<WM, WN, TM, TN, BITS, true, false>)
-                   : go(&gemm_w4_rescale_kernel<WM, WN, TM, TN, BITS, false, false>);
+    return res ? pick(std::false_type{}, std::true_type{}) : pick(std::false_type{}, std::false_type{});
 }
 
 // Pre-pass, then the rescaling kernel; the caller launches the 128 x 128 exact kernel behind them for the column blocks
 // the pre-pass flagged (normally none: its workgroups then return at once).
 template <int BITS>
 hipError_t launch_rescale(const void *wt, const uint32_t *sz, int szs, int64_t K, int64_t N, const uint16_t *x, int64_t M, void *y,
-                          bool out_f32, void *ws, const uint32_t **flags_out, bool *pairs_out, hipStream_t stream) {
+                          bool out_f32, const uint16_t *res, void *ws, const uint32_t **flags_out, bool *pairs_out, hipStream_t stream) {
     const RescalePlan p = plan_rescale(M, K, N);
     uint8_t *base = reinterpret_cast<uint8_t *>(ws);
     uint16_t *a2 = reinterpret_cast<uint16_t *>(base + p.off_a2);
@@ -831,10 +845,10 @@ hipError_t launch_rescale(const void *wt, const uint32_t *sz, int szs, int64_t K
     const Operands o{a2, b2, rfac, flags};
     *flags_out = flags;
     *pairs_out = wn == 4;
-    if (wn == 4) return launch_tile<2, 4, 4, 2, BITS>(wt, szs == 0, x, M, K, N, y, out_f32, p, o, stream);
-    if (w4_gemm_rescale_tile_rows(M, N) == 128) return launch_tile<2, 4, 2, 1, BITS>(wt, szs == 0, x, M, K, N, y, out_f32, p, o, stream);
+    if (wn == 4) return launch_tile<2, 4, 4, 2, BITS>(wt, szs == 0, x, M, K, N, y, out_f32, res, p, o, stream);
+    if (w4_gemm_rescale_tile_rows(M, N) == 128) return launch_tile<2, 4, 2, 1, BITS>(wt, szs == 0, x, M, K, N, y, out_f32, res, p, o, stream);
     // 256 x 128 tiles: eight waves of 128 x 32 (measured 0-8 % ahead of four waves of 128 x 64 and of eight of 64 x 64)
-    return launch_tile<2, 4, 4, 1, BITS>(wt, szs == 0, x, M, K, N, y, out_f32, p, o, stream);
+    return launch_tile<2, 4, 4, 1, BITS>(wt, szs == 0, x, M, K, N, y, out_f32, res, p, o, stream);
 }
 
 }  // namespace
@@ -872,22 +886,22 @@ int w4_gemm_rescale_tile_rows(int64_t M, int64_t N) {
 
 size_t w4_gemm_rescale_workspace_bytes(int64_t M, int64_t K, int64_t N) { return plan_rescale(M, K, N).total; }
 
-hipError_t launch_w4_gemm_rescale(const LayerView &Lv, const uint16_t *x, int64_t M, void *y, bool out_f32, void *ws,
-                                  hipStream_t stream) {
+hipError_t launch_w4_gemm_rescale(const LayerView &Lv, const uint16_t *x, int64_t M, void *y, bool out_f32, const uint16_t *res,
+                                  void *ws, hipStream_t stream) {
     const uint32_t *flags = nullptr;
     bool pairs = false;
-    const hipError_t e = launch_rescale<4>(Lv.wt, Lv.sz, Lv.szs, Lv.K, Lv.N, x, M, y, out_f32, ws, &flags, &pairs, stream);
+    const hipError_t e = launch_rescale<4>(Lv.wt, Lv.sz, Lv.szs, Lv.K, Lv.N, x, M, y, out_f32, res, ws, &flags, &pairs, stream);
     if (e != hipSuccess) return e;
-    return launch_w4_gemm_flagged(Lv, x, M, y, out_f32, flags, pairs, stream);
+    return launch_w4_gemm_flagged(Lv, x, M, y, out_f32, res, flags, pairs, stream);
 }
 
-hipError_t launch_w3_gemm_rescale(const LayerView3 &Lv, const uint16_t *x, int64_t M, void *y, bool out_f32, void *ws,
-                                  hipStream_t stream) {
+hipError_t launch_w3_gemm_rescale(const LayerView3 &Lv, const uint16_t *x, int64_t M, void *y, bool out_f32, const uint16_t *res,
+                                  void *ws, hipStream_t stream) {
     const uint32_t *flags = nullptr;
     bool pairs = false;
-    const hipError_t e = launch_rescale<3>(Lv.wt, Lv.sz, 1, Lv.K, Lv.N, x, M, y, out_f32, ws, &flags, &pairs, stream);
+    const hipError_t e = launch_rescale<3>(Lv.wt, Lv.sz, 1, Lv.K, Lv.N, x, M, y, out_f32, res, ws, &flags, &pairs, stream);
     if (e != hipSuccess) return e;
-    return launch_w3_gemm_flagged(Lv, x, M, y, out_f32, flags, pairs, stream);
+    return launch_w3_gemm_flagged(Lv, x, M, y, out_f32, res, flags, pairs, stream);
 }
 
 }  // namespace dmr

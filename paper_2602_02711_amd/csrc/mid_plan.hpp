@@ -47,8 +47,8 @@ inline MidPlan plan_mid(int64_t M, int64_t K, int64_t N) {
     return p;
 }
 
-// y = sum over splits of part[split] (fp32 [splits][M][N]), splits in ascending order.
-hipError_t launch_splitk_reduce(const float *part, void *y, int64_t total, int splits, bool out_f32,
+// y = sum over splits of part[split] (fp32 [splits][M][N]), splits in ascending order, plus the residual if there is one.
+hipError_t launch_splitk_reduce(const float *part, void *y, int64_t total, int splits, bool out_f32, const uint16_t *res,
                                 hipStream_t stream);
 
 }  // namespace dmr

@@ -30,7 +30,8 @@ __global__ __launch_bounds__(1024) void w3_gemv_kernel(const uint32_t *__restric
                                                        const uint32_t *__restrict__ sz,
                                                        const uint16_t *__restrict__ x,
                                                        void *__restrict__ y, int groups, int tiles,
-                                                       int lgS, int lgTW, int nT_max, int out_f32) {
+                                                       int lgS, int lgTW, int nT_max, int out_f32,
+                                                       const uint16_t *__restrict__ res) {
     extern __shared__ uint4 smem[];          // x (16 uint4 per group), X[groups], red[nT_max][TW][S][16]
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform (SGPR)
@@ -126,6 +127,7 @@ __global__ __launch_bounds__(1024) void w3_gemv_kernel(const uint32_t *__restric
                     red[((((ct << lgTW) + tw) << lgS) + s) * 16 + lane] = acc;
                 } else {
                     const int64_t n = (int64_t)(t_first + ct * t_step) * kTileRows + lane;
+                    acc = plus_residual(acc, res, n);
                     if (out_f32)
                         reinterpret_cast<float *>(y)[n] = acc;
                     else
@@ -168,6 +170,7 @@ __global__ __launch_bounds__(1024) void w3_gemv_kernel(const uint32_t *__restric
         const int tile = ((int)blockIdx.x << lgTW) + (slot & (TW - 1)) + (slot >> lgTW) * t_step;
         if (q == 0 && tile < tiles) {
             const int64_t n = (int64_t)tile * kTileRows + col;
+            v = plus_residual(v, res, n);
             if (out_f32)
                 reinterpret_cast<float *>(y)[n] = v;
             else
@@ -212,7 +215,7 @@ bool w3_gemv_fits(int64_t K, int64_t N) {
 }
 
 hipError_t launch_w3_gemv(const LayerView3 &L, const uint16_t *x, void *y, bool out_f32,
-                          hipStream_t stream) {
+                          const uint16_t *res, hipStream_t stream) {
     const int groups = (int)(L.K / kGroup);
     const int tiles = (int)(L.N / kTileRows);
     const int cus = compute_units();
@@ -248,7 +251,7 @@ hipError_t launch_w3_gemv(const LayerView3 &L, const uint16_t *x, void *y, bool 
     const int of = out_f32 ? 1 : 0;
 #define DMR_GEMV3_LAUNCH(PP, XX)                                                                        \
     hipLaunchKernelGGL((w3_gemv_kernel<PP, XX>), g, b, lds, stream, L.wt, L.sz, x, y, groups, tiles, lgS, \
-                       lgTW, nT_max, of)
+                       lgTW, nT_max, of, res)
 #define DMR_GEMV3_CASE(PP)                                                                              \
     case PP:                                                                                           \
         if (xl_need <= 1) DMR_GEMV3_LAUNCH(PP, 1);                                                      \

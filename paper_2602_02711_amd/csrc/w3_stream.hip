@@ -46,7 +46,8 @@ __global__ __launch_bounds__(1024) void w3_stream_kernel(const uint32_t *__restr
                                                          const uint16_t *__restrict__ x,
                                                          void *__restrict__ y, int M, int64_t N,
                                                          int groups, int tiles, int lgS, int lgTW,
-                                                         int nT_max, int gw_max, int out_f32, uint32_t x16_magic) {
+                                                         int nT_max, int gw_max, int out_f32, uint32_t x16_magic,
+                                                         const uint16_t *__restrict__ res) {
     extern __shared__ uint4 smem[];   // x rows [M][groups * 16 + 1] uint4, then red[TW][S][64] float4
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -106,6 +107,7 @@ __global__ __launch_bounds__(1024) void w3_stream_kernel(const uint32_t *__restr
     if (total > B0 * T) stage_rows<8>(x, smem, total, x16_magic, B0 * T);
     __syncthreads();
     auto store_out = [&](int64_t o, float v) {
+        v = plus_residual(v, res, o);
         if (out_f32)
             reinterpret_cast<float *>(y)[o] = v;
         else
@@ -198,7 +200,7 @@ __global__ __launch_bounds__(1024) void w3_stream_kernel(const uint32_t *__restr
 }  // namespace
 
 hipError_t launch_w3_stream(const LayerView3 &L, const uint16_t *x, int64_t M, void *y, bool out_f32,
-                            hipStream_t stream) {
+                            const uint16_t *res, hipStream_t stream) {
     // same LDS footprint and launch shapes as the 4-bit kernel
     if (!w4_stream_fits(M, L.K, L.N)) return hipErrorInvalidValue;
     const int groups = (int)(L.K / kGroup);
@@ -242,7 +244,7 @@ hipError_t launch_w3_stream(const LayerView3 &L, const uint16_t *x, int64_t M, v
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024); \
         if (attr_status != hipSuccess) return attr_status; \
         hipLaunchKernelGGL((w3_stream_kernel<PP>), dim3(grid), dim3(nw * 64), lds, stream, L.wt, L.sz, x, y, iM, \
-                           L.N, groups, tiles, lgS, lgTW, nT_max, gw_max, of, x16_magic);                \
+                           L.N, groups, tiles, lgS, lgTW, nT_max, gw_max, of, x16_magic, res);           \
     } break;
     switch (P) {
         DMR_W3STREAM_CASE(1) DMR_W3STREAM_CASE(2) DMR_W3STREAM_CASE(3) DMR_W3STREAM_CASE(4)

@@ -267,11 +267,6 @@ bool w4_gemv_fits(int64_t K, int64_t N, bool with_residual) {
     return lds <= 64 * 1024;
 }
 
-hipError_t launch_w4_gemv(const LayerView &L, const uint16_t *x, void *y, bool out_f32,
-                          hipStream_t stream) {
-    return launch_w4_gemv_fused(L, x, y, out_f32, Fusion{}, stream);
-}
-
 hipError_t launch_w4_gemv_fused(const LayerView &L, const uint16_t *x, void *y, bool out_f32, const Fusion &f,
                                 hipStream_t stream) {
     const int groups = (int)(L.K / kGroup);

@@ -34,7 +34,8 @@ constexpr int ROW_BYTES = 272;   // one activation row of a group in LDS: 128 bf
 template <int MTW, int WM, int NW, int R, int BITS>
 __global__ __launch_bounds__(64 * WM * NW, (WM * NW == 4) ? 2 : 1) void w4_mid_kernel(
     const void *__restrict__ wt, const uint32_t *__restrict__ sz, const uint16_t *__restrict__ x,
-    void *__restrict__ y, int M, int64_t K, int64_t N, int groups, int tiles, int gps, int out_mode, int szs) {
+    void *__restrict__ y, int M, int64_t K, int64_t N, int groups, int tiles, int gps, int out_mode, int szs,
+    const uint16_t *__restrict__ res) {
     constexpr int THREADS = 64 * WM * NW;
     constexpr int BM = 16 * MTW * WM;
     constexpr int ROWS_PER_PASS = THREADS / 16;
@@ -188,6 +189,17 @@ __global__ __launch_bounds__(64 * WM * NW, (WM * NW == 4) ? 2 : 1) void w4_mid_k
         }
     }
 
+    if (res && out_mode != 2) {      // clamped, unconditional loads: all of them in flight at once
+#pragma unroll
+        for (int rt = 0; rt < R; ++rt)
+#pragma unroll
+            for (int mt = 0; mt < MTW; ++mt)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int m = min(m0 + (wm * MTW + mt) * 16 + c * 4 + q, M - 1);
+                    acc[rt][mt][q] += bf16_bits_to_f32(res[(int64_t)m * N + (int64_t)min(tile0 + rt, tiles - 1) * kTileRows + j]);
+                }
+    }
     const int64_t part = out_mode == 2 ? (int64_t)blockIdx.z * M * N : 0;
 #pragma unroll
     for (int rt = 0; rt < R; ++rt) {
@@ -208,9 +220,11 @@ __global__ __launch_bounds__(64 * WM * NW, (WM * NW == 4) ? 2 : 1) void w4_mid_k
     }
 }
 
-// y = sum over splits of part[split], four outputs per thread, splits in ascending order.
+// y = sum over splits of part[split], four outputs per thread, splits in ascending order; an optional residual is added
+// to the fp32 sum (a launch of its own for it cost 2-4 us and two more passes over M x N fp32).
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *__restrict__ part, void *__restrict__ y,
-                                                            int64_t total, int splits, int out_f32) {
+                                                            int64_t total, int splits, int out_f32,
+                                                            const uint16_t *__restrict__ res) {
     const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 4;
     if (i >= total) return;
     f32x4 v = *reinterpret_cast<const f32x4 *>(part + i);
@@ -218,6 +232,13 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *__restr
         const f32x4 u = *reinterpret_cast<const f32x4 *>(part + (int64_t)s * total + i);
 #pragma unroll
         for (int k = 0; k < 4; ++k) v[k] += u[k];
+    }
+    if (res) {
+        const uint2 r = *reinterpret_cast<const uint2 *>(res + i);
+        v[0] += __uint_as_float(r.x << 16);
+        v[1] += __uint_as_float(r.x & 0xFFFF0000u);
+        v[2] += __uint_as_float(r.y << 16);
+        v[3] += __uint_as_float(r.y & 0xFFFF0000u);
     }
     if (out_f32) {
         *reinterpret_cast<f32x4 *>(reinterpret_cast<float *>(y) + i) = v;
@@ -231,7 +252,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *__restr
 
 template <int MTW, int WM, int NW, int R, int BITS>
 hipError_t launch_cfg(const void *wt, const uint32_t *sz, int szs, int64_t K, int64_t N, const uint16_t *x, int M, void *dst,
-                      int out_mode, const MidPlan &p, hipStream_t stream) {
+                      int out_mode, const uint16_t *res, const MidPlan &p, hipStream_t stream) {
     constexpr int BM = 16 * MTW * WM;
     constexpr size_t lds = 2ull * BM * ROW_BYTES;
     // once per process and kernel instantiation (thread-safe static initialisation)
@@ -242,22 +263,22 @@ hipError_t launch_cfg(const void *wt, const uint32_t *sz, int szs, int64_t K, in
     const int groups = (int)(K / kGroup), tiles = (int)(N / kTileRows);
     const dim3 grid((unsigned)((tiles + NW * R - 1) / (NW * R)), (unsigned)((M + BM - 1) / BM), (unsigned)p.SK);
     hipLaunchKernelGGL((w4_mid_kernel<MTW, WM, NW, R, BITS>), grid, dim3(64 * WM * NW), lds, stream, wt, sz, x, dst, M,
-                       K, N, groups, tiles, p.gps, out_mode, szs);
+                       K, N, groups, tiles, p.gps, out_mode, szs, res);
     return hipGetLastError();
 }
 
 template <int MTW, int WM, int NW, int BITS>
 hipError_t launch_r(const void *wt, const uint32_t *sz, int szs, int64_t K, int64_t N, const uint16_t *x, int M, void *dst,
-                    int out_mode, const MidPlan &p, hipStream_t stream) {
+                    int out_mode, const uint16_t *res, const MidPlan &p, hipStream_t stream) {
     // R = 4 was measured too: never faster, and with 4 row tiles per wave it needs more than the 256
     // registers that two waves per SIMD leave
-    return p.R == 2 ? launch_cfg<MTW, WM, NW, 2, BITS>(wt, sz, szs, K, N, x, M, dst, out_mode, p, stream)
-                    : launch_cfg<MTW, WM, NW, 1, BITS>(wt, sz, szs, K, N, x, M, dst, out_mode, p, stream);
+    return p.R == 2 ? launch_cfg<MTW, WM, NW, 2, BITS>(wt, sz, szs, K, N, x, M, dst, out_mode, res, p, stream)
+                    : launch_cfg<MTW, WM, NW, 1, BITS>(wt, sz, szs, K, N, x, M, dst, out_mode, res, p, stream);
 }
 
 template <int BITS>
 hipError_t launch_mid(const void *wt, const uint32_t *sz, int szs, int64_t K, int64_t N, const uint16_t *x, int64_t M, void *y,
-                      bool out_f32, void *ws, hipStream_t stream) {
+                      bool out_f32, const uint16_t *res, void *ws, hipStream_t stream) {
     const MidPlan p = plan_mid(M, K, N);
     const bool split = p.SK > 1;
     if (split && !ws) return hipErrorInvalidValue;
@@ -267,25 +288,25 @@ hipError_t launch_mid(const void *wt, const uint32_t *sz, int szs, int64_t K, in
     hipError_t e;
     if (p.WM == 1) {
         switch (p.MTW) {
-            case 1: e = launch_r<1, 1, 4, BITS>(wt, sz, szs, K, N, x, iM, dst, out_mode, p, stream); break;
-            case 2: e = launch_r<2, 1, 4, BITS>(wt, sz, szs, K, N, x, iM, dst, out_mode, p, stream); break;
-            case 3: e = launch_r<3, 1, 4, BITS>(wt, sz, szs, K, N, x, iM, dst, out_mode, p, stream); break;
-            default: e = launch_r<4, 1, 4, BITS>(wt, sz, szs, K, N, x, iM, dst, out_mode, p, stream); break;
+            case 1: e = launch_r<1, 1, 4, BITS>(wt, sz, szs, K, N, x, iM, dst, out_mode, res, p, stream); break;
+            case 2: e = launch_r<2, 1, 4, BITS>(wt, sz, szs, K, N, x, iM, dst, out_mode, res, p, stream); break;
+            case 3: e = launch_r<3, 1, 4, BITS>(wt, sz, szs, K, N, x, iM, dst, out_mode, res, p, stream); break;
+            default: e = launch_r<4, 1, 4, BITS>(wt, sz, szs, K, N, x, iM, dst, out_mode, res, p, stream); break;
         }
     } else {
-        e = p.MTW == 3 ? launch_r<3, 2, 2, BITS>(wt, sz, szs, K, N, x, iM, dst, out_mode, p, stream)
-                       : launch_r<4, 2, 2, BITS>(wt, sz, szs, K, N, x, iM, dst, out_mode, p, stream);
+        e = p.MTW == 3 ? launch_r<3, 2, 2, BITS>(wt, sz, szs, K, N, x, iM, dst, out_mode, res, p, stream)
+                       : launch_r<4, 2, 2, BITS>(wt, sz, szs, K, N, x, iM, dst, out_mode, res, p, stream);
     }
     if (e != hipSuccess || !split) return e;
-    return launch_splitk_reduce(static_cast<const float *>(ws), y, M * N, p.SK, out_f32, stream);
+    return launch_splitk_reduce(static_cast<const float *>(ws), y, M * N, p.SK, out_f32, res, stream);
 }
 
 }  // namespace
 
-hipError_t launch_splitk_reduce(const float *part, void *y, int64_t total, int splits, bool out_f32,
+hipError_t launch_splitk_reduce(const float *part, void *y, int64_t total, int splits, bool out_f32, const uint16_t *res,
                                 hipStream_t stream) {
     hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)((total / 4 + 255) / 256)), dim3(256), 0, stream, part, y,
-                       total, splits, out_f32 ? 1 : 0);
+                       total, splits, out_f32 ? 1 : 0, res);
     return hipGetLastError();
 }
 
@@ -294,14 +315,14 @@ size_t w4_mid_workspace_bytes(int64_t M, int64_t K, int64_t N) {
     return p.SK > 1 ? (size_t)p.SK * (size_t)M * (size_t)N * sizeof(float) : 0;
 }
 
-hipError_t launch_w4_mid(const LayerView &L, const uint16_t *x, int64_t M, void *y, bool out_f32, void *ws,
-                         hipStream_t stream) {
-    return launch_mid<4>(L.wt, L.sz, L.szs, L.K, L.N, x, M, y, out_f32, ws, stream);
+hipError_t launch_w4_mid(const LayerView &L, const uint16_t *x, int64_t M, void *y, bool out_f32, const uint16_t *res,
+                         void *ws, hipStream_t stream) {
+    return launch_mid<4>(L.wt, L.sz, L.szs, L.K, L.N, x, M, y, out_f32, res, ws, stream);
 }
 
-hipError_t launch_w3_mid(const LayerView3 &L, const uint16_t *x, int64_t M, void *y, bool out_f32, void *ws,
-                         hipStream_t stream) {
-    return launch_mid<3>(L.wt, L.sz, 1, L.K, L.N, x, M, y, out_f32, ws, stream);
+hipError_t launch_w3_mid(const LayerView3 &L, const uint16_t *x, int64_t M, void *y, bool out_f32, const uint16_t *res,
+                         void *ws, hipStream_t stream) {
+    return launch_mid<3>(L.wt, L.sz, 1, L.K, L.N, x, M, y, out_f32, res, ws, stream);
 }
 
 }  // namespace dmr

@@ -241,11 +241,6 @@ bool w4_stream_fits(int64_t M, int64_t K, int64_t N) {
     return xbytes + (S > 1 ? (size_t)nw * 64 * sizeof(f32x4) : 0) <= 160 * 1024;
 }
 
-hipError_t launch_w4_stream(const LayerView &L, const uint16_t *x, int64_t M, void *y, bool out_f32,
-                            hipStream_t stream) {
-    return launch_w4_stream_fused(L, x, M, y, out_f32, Fusion{}, stream);
-}
-
 hipError_t launch_w4_stream_fused(const LayerView &L, const uint16_t *x, int64_t M, void *y, bool out_f32,
                                   const Fusion &f, hipStream_t stream) {
     if (M < 2 || M > 16 || f.pro != kProNone) return hipErrorInvalidValue;
