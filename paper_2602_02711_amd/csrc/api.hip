@@ -70,7 +70,7 @@ Bf16Path bf16_path(int64_t M, int64_t K, int64_t N) {
     // measured crossover: the tiled kernels win once they have more than ~128 workgroups
     const int64_t gemm_wgs = ((M + 127) / 128) * ((N + 127) / 128);
     if (M <= 64 || gemm_wgs <= 128) return Bf16Path::Mid;
-    return dmr::gemm_big_applies(M, N) ? Bf16Path::GemmBig : Bf16Path::Gemm;
+    return dmr::gemm_big_tile_rows(M, K, N) != 0 ? Bf16Path::GemmBig : Bf16Path::Gemm;
 }
 
 size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
@@ -180,11 +180,9 @@ dmr_status_t forward_bf16(const uint16_t *d_w, const uint16_t *d_x, int64_t M, i
         case Bf16Path::Mid: return hip_status(dmr::launch_bf16_mid(d_w, d_x, M, K, N, d_y, f32, res, d_ws, s));
         case Bf16Path::GemmBig: return hip_status(dmr::launch_bf16_gemm_w8(d_w, d_x, M, K, N, d_y, f32, res, s));
         default: {
-            // 128 x 128 tiles: the direct-to-LDS kernel while its pipeline has room to pay (K >= 1024) and the
-            // grid is at most ~3 workgroups per CU (measured: 25-30 % ahead at 256 workgroups, level at 512,
-            // 8 % ahead at 768, 6 % behind at 1056)
-            const int64_t wgs = ((M + 127) / 128) * ((N + 127) / 128);
-            if (K >= 1024 && wgs <= 800) return hip_status(dmr::launch_bf16_gemm_dma128(d_w, d_x, M, K, N, d_y, f32, res, s));
+            // 128 x 128 tiles: the direct-to-LDS kernel while its pipeline has room to pay (25-30 % ahead at 256
+            // workgroups; the grids of more than about 500, where that shrinks, have gone to the larger tiles by now)
+            if (K >= 1024) return hip_status(dmr::launch_bf16_gemm_dma128(d_w, d_x, M, K, N, d_y, f32, res, s));
             return hip_status(dmr::launch_bf16_gemm(d_w, d_x, M, K, N, d_y, f32, res, s));
         }
     }
@@ -552,11 +550,11 @@ const char *dmr_qlinear_kernel_path(dmr_format_t format, int64_t M, int64_t K, i
             case Bf16Path::Stream: return "bf16_stream";
             case Bf16Path::Skinny: return "bf16_skinny";
             case Bf16Path::Mid: return "bf16_mid";
-            case Bf16Path::GemmBig: return "bf16_gemm256";
-            default: {
-                const int64_t wgs = ((M + 127) / 128) * ((N + 127) / 128);
-                return (K >= 1024 && wgs <= 800) ? "bf16_gemm128_dma" : "bf16_gemm128";
+            case Bf16Path::GemmBig: {
+                const int rows = dmr::gemm_big_tile_rows(M, K, N);
+                return rows == 256 ? "bf16_gemm256" : rows == 192 ? "bf16_gemm192x256" : "bf16_gemm128x256";
             }
+            default: return K >= 1024 ? "bf16_gemm128_dma" : "bf16_gemm128";
         }
     };
     switch (format) {

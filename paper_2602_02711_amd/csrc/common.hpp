@@ -224,7 +224,7 @@ hipError_t launch_bf16_gemm(const uint16_t *w, const uint16_t *x, int64_t M, int
                             void *y, bool out_f32, const uint16_t *res, hipStream_t stream);
 // 256 x 256 tiles on eight wavefronts (direct-to-LDS operand loads, four-stage pipeline, two waves per SIMD) for
 // problems large enough to fill the chip with them.
-bool gemm_big_applies(int64_t M, int64_t N);
+int gemm_big_tile_rows(int64_t M, int64_t K, int64_t N);      // 256, 192, 128; 0: the 128 x 128 kernels
 hipError_t launch_bf16_gemm_w8(const uint16_t *w, const uint16_t *x, int64_t M, int64_t K, int64_t N, void *y, bool out_f32,
                                const uint16_t *res, hipStream_t stream);
 hipError_t launch_bf16_gemm_dma128(const uint16_t *w, const uint16_t *x, int64_t M, int64_t K, int64_t N,
