@@ -118,7 +118,7 @@ dmr_status_t forward_quant(const dmr_qlinear_t *layer, const uint16_t *d_x, int6
             case W3Path::Gemv: return hip_status(dmr::launch_w3_gemv(L3, d_x, d_y, f32, res, s));
             case W3Path::Stream: return hip_status(dmr::launch_w3_stream(L3, d_x, M, d_y, f32, res, s));
             case W3Path::Panel: return hip_status(dmr::launch_w3_panel(L3, d_x, M, d_y, f32, res, d_ws, s));
-            case W3Path::Wide: return hip_status(dmr::launch_w3_wide(L3, d_x, M, d_y, f32, res, s));
+            case W3Path::Wide: return hip_status(dmr::launch_w3_wide(L3, d_x, M, d_y, f32, res, d_ws, s));
             case W3Path::Mid: return hip_status(dmr::launch_w3_mid(L3, d_x, M, d_y, f32, res, d_ws, s));
             case W3Path::Gemm: return hip_status(dmr::launch_w3_gemm(L3, d_x, M, d_y, f32, res, s));
             case W3Path::GemmRescale: return hip_status(dmr::launch_w3_gemm_rescale(L3, d_x, M, d_y, f32, res, d_ws, s));
@@ -140,7 +140,7 @@ dmr_status_t forward_quant(const dmr_qlinear_t *layer, const uint16_t *d_x, int6
         if (e != hipErrorInvalidValue) return hip_status(e);   // else: activations do not fit LDS
     }
     if (path == W4Path::Panel) return hip_status(dmr::launch_w4_panel(L, d_x, M, d_y, f32, res, d_ws, s));
-    if (path == W4Path::Wide) return hip_status(dmr::launch_w4_wide(L, d_x, M, d_y, f32, res, s));
+    if (path == W4Path::Wide) return hip_status(dmr::launch_w4_wide(L, d_x, M, d_y, f32, res, d_ws, s));
     if (path == W4Path::Mid) return hip_status(dmr::launch_w4_mid(L, d_x, M, d_y, f32, res, d_ws, s));
     if (path == W4Path::Skinny2) return hip_status(dmr::launch_w4_skinny2(L, d_x, M, d_y, f32, d_ws, s));
     if (M <= kSkinnyMaxM) return hip_status(dmr::launch_w4_skinny(L, d_x, M, d_y, f32, s));
@@ -202,6 +202,7 @@ size_t dmr_qlinear_workspace_bytes(int64_t M, int64_t K, int64_t N) {
     switch (w4_path(M, K, N)) {
         case W4Path::Mid: return dmr::w4_mid_workspace_bytes(M, K, N);    // fp32 partials when K is split
         case W4Path::Panel: return dmr::w4_panel_workspace_bytes(M, K, N);    // likewise
+        case W4Path::Wide: return dmr::w4_wide_workspace_bytes(M, K, N);      // likewise
         case W4Path::Skinny2: return dmr::w4_skinny2_workspace_bytes(M, K);   // re-ordered activations
         case W4Path::GemmRescale: return dmr::w4_gemm_rescale_workspace_bytes(M, K, N);   // zero-point operands, factors
         default: return 0;
@@ -296,6 +297,7 @@ size_t dmr_qlinear_w3_workspace_bytes(int64_t M, int64_t K, int64_t N) {
     switch (w3_path(M, K, N)) {
         case W3Path::Panel: return dmr::w4_panel_workspace_bytes(M, K, N);   // fp32 partials of the k slices
         case W3Path::Mid: return dmr::w4_mid_workspace_bytes(M, K, N);       // fp32 partials when K is split
+        case W3Path::Wide: return dmr::w4_wide_workspace_bytes(M, K, N);     // likewise
         case W3Path::GemmRescale: return dmr::w4_gemm_rescale_workspace_bytes(M, K, N);   // zero-point operands, factors
         default: return 0;
     }

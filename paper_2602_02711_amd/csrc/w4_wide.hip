@@ -1,5 +1,5 @@
-// W4A16 kernel for 17 <= M <= 64 rows on wide layers (enough 16-row weight tiles that every CU gets a
-// workgroup without splitting K): one pass over the packed weights with the activations in LDS.
+// W4A16 kernel for 17 <= M <= 64 rows on wide layers, and on narrower ones whose K splits into pieces long enough that
+// every CU gets a workgroup: one pass over the packed weights with the activations in LDS.
 //
 // A workgroup of 8 wavefronts owns TW * R weight tiles (TW = 8 / S tile lanes, R tiles per wave) and
 // walks k in chunks of CG groups.  The chunk's x panel, MT * 16 rows x 128 CG columns, sits in one of
@@ -8,13 +8,16 @@
 // sums of x that the zero-point term needs are formed once per workgroup and chunk (MFMAs against
 // all-ones, table [group][row tile][row quad] of fp32x4 behind a second barrier), so the main loop
 // spends its MFMAs on weights only.  The weights never touch LDS: wave (s, tw) streams the R blocks
-// of groups s * CG / S .. of every chunk straight into registers, one chunk ahead (the
-// requests cross chunk boundaries freely).  An activation fragment read from LDS feeds R weight
+// of groups s * CG / S .. of every chunk straight into registers, two chunks ahead (one chunk ahead measured 4 %
+// slower at 20 and 33 rows, level at 64).  An activation fragment read from LDS feeds R weight
 // tiles.  The S partial tiles of a workgroup meet in LDS at the end (the panels' memory) and are added
-// in ascending order.  Splitting K over workgroups was measured and never paid on layers this wide
-// (the fp32 partials cost as much as the weights).  Rows of the last row tile beyond M are staged as copies of row M - 1 and never stored.
+// in ascending order.  Layers too narrow to give every CU a workgroup split K over blockIdx.y (fp32 partials
+// added by the shared reduction kernel).  What bounds it (64 rows, gate+up, 32 us): no single pipe; LDS reads 60 %, VALU
+// 33 %, MFMA 24 % of the cycles with two waves per SIMD that meet at two barriers per chunk.  Four weight tiles per wave
+// (half the LDS reads) measured no faster.  Rows of the last row tile beyond M are staged as copies of row M - 1 and never stored.
 // BITS = 3 runs the same kernel on the 3-bit streaming layout (768-byte blocks, three words per lane).
 #include "w3_unpack.hpp"
+#include "mid_plan.hpp"
 #include "wide_plan.hpp"
 
 namespace dmr {
@@ -31,12 +34,13 @@ struct WideItem {
 
 constexpr int ilog2(int v) { return v <= 1 ? 0 : 1 + ilog2(v / 2); }
 
+// out_mode: 0 = fp32 y, 1 = bf16 y, 2 = fp32 partial [split][M][N] (no residual)
 template <int MT, int R, int S, int CG, int BITS>
 __global__ __launch_bounds__(512) void w4_wide_kernel(const void *__restrict__ wt, const uint32_t *__restrict__ sz,
                                                       const uint16_t *__restrict__ x, void *__restrict__ y, int M,
-                                                      int64_t K, int64_t N, int groups, int tiles, int out_f32, int szs,
+                                                      int64_t K, int64_t N, int groups, int tiles, int cps, int out_mode, int szs,
                                                       const uint16_t *__restrict__ res) {
-    constexpr int WAVES = 8, THREADS = 512, TW = WAVES / S, GWc = CG / S, P = GWc;
+    constexpr int WAVES = 8, THREADS = 512, TW = WAVES / S, GWc = CG / S, P = 2 * GWc;
     constexpr int ROW = CG * 16 + 1;                  // uint4 per panel row
     constexpr int ROWS = MT * 16;
     constexpr int PANEL = ROWS * ROW;                 // uint4 per buffer
@@ -51,7 +55,9 @@ __global__ __launch_bounds__(512) void w4_wide_kernel(const void *__restrict__ w
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int s = wave % S, tw = wave / S;
     const int c = lane >> 4, j = lane & 15;
-    const int nch = groups / CG;                      // chunks (the group count is a multiple of CG)
+    // chunks of this split of K (the group count is a multiple of CG): [ch0, ch0 + nch), nch >= 1
+    const int ch0 = (int)blockIdx.y * cps;
+    const int nch = min(groups / CG - ch0, cps);
     const int items = nch * GWc;
     const int tile0 = ((int)blockIdx.x * TW + tw) * R;
 
@@ -59,7 +65,7 @@ __global__ __launch_bounds__(512) void w4_wide_kernel(const void *__restrict__ w
     WideItem<R> ring[P];
     auto issue = [&](WideItem<R> &dst, int n) {
         n = n < items ? n : items - 1;
-        const int g = (n / GWc) * CG + s * GWc + (n % GWc);
+        const int g = (ch0 + n / GWc) * CG + s * GWc + (n % GWc);
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             const int tile = min(tile0 + r, tiles - 1);
@@ -89,7 +95,7 @@ __global__ __launch_bounds__(512) void w4_wide_kernel(const void *__restrict__ w
     auto fetch_x = [&](int ch) {
 #pragma unroll
         for (int u = 0; u < XL; ++u)
-            xr[u] = *reinterpret_cast<const u32x4_t *>(x + xoff[u] + ch * (CG * kGroup));
+            xr[u] = *reinterpret_cast<const u32x4_t *>(x + xoff[u] + (ch0 + ch) * (CG * kGroup));
     };
     auto put_x = [&](int buf) {
 #pragma unroll
@@ -163,13 +169,12 @@ __global__ __launch_bounds__(512) void w4_wide_kernel(const void *__restrict__ w
     // One chunk: request the next panel, work through this wave's GWc items (the ring holds exactly one
     // chunk's items, so each slot is refilled with the same item of the next chunk), publish the next
     // panel and its sums.
-    auto chunk_step = [&](int ch, bool more) {
-        const int buf = ch & 1;
+    auto chunk_step = [&](int ch, int buf, bool more) {      // buf = ch & 1, a constant where this is expanded
         fetch_x(min(ch + 1, nch - 1));                 // unconditional (the last chunk re-reads itself)
 #pragma unroll
         for (int i = 0; i < GWc; ++i) {
-            const WideItem<R> cur = ring[i];
-            issue(ring[i], (ch + 1) * GWc + i);
+            const WideItem<R> cur = ring[buf * GWc + i];
+            issue(ring[buf * GWc + i], (ch + 2) * GWc + i);
             consume(cur, buf, s * GWc + i);
         }
         if (more) {                                    // uniform over the workgroup
@@ -187,8 +192,12 @@ __global__ __launch_bounds__(512) void w4_wide_kernel(const void *__restrict__ w
     __syncthreads();
     sums(0);
     __syncthreads();
-    for (int ch = 0; ch < nch; ++ch) chunk_step(ch, ch + 1 < nch);
+    for (int ch = 0; ch < nch; ch += 2) {
+        chunk_step(ch, 0, ch + 1 < nch);
+        if (ch + 1 < nch) chunk_step(ch + 1, 1, ch + 2 < nch);      // uniform
+    }
 
+    const int64_t part = out_mode == 2 ? (int64_t)blockIdx.y * M * N : 0;
     auto store_tile = [&](int tile, int mt, const f32x4 &v) {
         if (tile >= tiles) return;
 #pragma unroll
@@ -197,8 +206,8 @@ __global__ __launch_bounds__(512) void w4_wide_kernel(const void *__restrict__ w
             if (row < M) {
                 const int64_t o = (int64_t)row * N + (int64_t)tile * kTileRows + j;
                 const float r = plus_residual(v[q], res, o);
-                if (out_f32)
-                    reinterpret_cast<float *>(y)[o] = r;
+                if (out_mode != 1)
+                    reinterpret_cast<float *>(y)[part + o] = r;
                 else
                     reinterpret_cast<uint16_t *>(y)[o] = f32_to_bf16(r);
             }
@@ -236,7 +245,7 @@ __global__ __launch_bounds__(512) void w4_wide_kernel(const void *__restrict__ w
 
 template <int MT, int R, int S, int CG, int BITS>
 hipError_t launch_cfg(const void *wt, const uint32_t *sz, int szs, int64_t K, int64_t N, const uint16_t *x, int M, void *y,
-                      bool out_f32, const uint16_t *res, hipStream_t stream) {
+                      int out_mode, const uint16_t *res, const WidePlan &p, hipStream_t stream) {
     // once per process and kernel instantiation (thread-safe static initialisation)
     static const hipError_t attr_status = hipFuncSetAttribute(
         reinterpret_cast<const void *>(&w4_wide_kernel<MT, R, S, CG, BITS>), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -246,37 +255,49 @@ hipError_t launch_cfg(const void *wt, const uint32_t *sz, int szs, int64_t K, in
     constexpr int TW = 8 / S;
     static_assert(TW * R == kWideTilesPerWg && CG == kWideChunk, "the planner assumes this shape");
     const unsigned grid = (unsigned)((tiles + TW * R - 1) / (TW * R));
-    hipLaunchKernelGGL((w4_wide_kernel<MT, R, S, CG, BITS>), dim3(grid), dim3(512), wide_lds_bytes(MT, R, S, CG), stream,
-                       wt, sz, x, y, M, K, N, groups, tiles, out_f32 ? 1 : 0, szs, res);
+    hipLaunchKernelGGL((w4_wide_kernel<MT, R, S, CG, BITS>), dim3(grid, (unsigned)p.SK), dim3(512), wide_lds_bytes(MT, R, S, CG), stream,
+                       wt, sz, x, y, M, K, N, groups, tiles, p.cps, out_mode, szs, out_mode == 2 ? nullptr : res);
     return hipGetLastError();
 }
 
 template <int BITS>
 hipError_t launch_wide(const void *wt, const uint32_t *sz, int szs, int64_t K, int64_t N, const uint16_t *x, int64_t M, void *y,
-                       bool out_f32, const uint16_t *res, hipStream_t stream) {
+                       bool out_f32, const uint16_t *res, void *ws, hipStream_t stream) {
     const WidePlan p = plan_wide(M, K, N);
     if (!p.ok) return hipErrorInvalidValue;
+    const bool split = p.SK > 1;
+    if (split && !ws) return hipErrorInvalidValue;
+    void *dst = split ? ws : y;
+    const int out_mode = split ? 2 : (out_f32 ? 0 : 1);
     const int iM = (int)M;
+    hipError_t e;
     switch (p.MT) {
-        case 2: return launch_cfg<2, 2, 2, 4, BITS>(wt, sz, szs, K, N, x, iM, y, out_f32, res, stream);
-        case 3: return launch_cfg<3, 2, 2, 4, BITS>(wt, sz, szs, K, N, x, iM, y, out_f32, res, stream);
-        case 4: return launch_cfg<4, 2, 2, 4, BITS>(wt, sz, szs, K, N, x, iM, y, out_f32, res, stream);
+        case 2: e = launch_cfg<2, 2, 2, 4, BITS>(wt, sz, szs, K, N, x, iM, dst, out_mode, res, p, stream); break;
+        case 3: e = launch_cfg<3, 2, 2, 4, BITS>(wt, sz, szs, K, N, x, iM, dst, out_mode, res, p, stream); break;
+        case 4: e = launch_cfg<4, 2, 2, 4, BITS>(wt, sz, szs, K, N, x, iM, dst, out_mode, res, p, stream); break;
         default: return hipErrorInvalidValue;
     }
+    if (e != hipSuccess || !split) return e;
+    return launch_splitk_reduce(static_cast<const float *>(ws), y, M * N, p.SK, out_f32, res, stream);
 }
 
 }  // namespace
 
 bool w4_wide_applies(int64_t M, int64_t K, int64_t N) { return plan_wide(M, K, N).ok; }
 
+size_t w4_wide_workspace_bytes(int64_t M, int64_t K, int64_t N) {
+    const WidePlan p = plan_wide(M, K, N);
+    return p.ok && p.SK > 1 ? (size_t)p.SK * (size_t)M * (size_t)N * sizeof(float) : 0;
+}
+
 hipError_t launch_w4_wide(const LayerView &L, const uint16_t *x, int64_t M, void *y, bool out_f32,
-                          const uint16_t *res, hipStream_t stream) {
-    return launch_wide<4>(L.wt, L.sz, L.szs, L.K, L.N, x, M, y, out_f32, res, stream);
+                          const uint16_t *res, void *ws, hipStream_t stream) {
+    return launch_wide<4>(L.wt, L.sz, L.szs, L.K, L.N, x, M, y, out_f32, res, ws, stream);
 }
 
 hipError_t launch_w3_wide(const LayerView3 &L, const uint16_t *x, int64_t M, void *y, bool out_f32,
-                          const uint16_t *res, hipStream_t stream) {
-    return launch_wide<3>(L.wt, L.sz, 1, L.K, L.N, x, M, y, out_f32, res, stream);
+                          const uint16_t *res, void *ws, hipStream_t stream) {
+    return launch_wide<3>(L.wt, L.sz, 1, L.K, L.N, x, M, y, out_f32, res, ws, stream);
 }
 
 }  // namespace dmr
