@@ -67,9 +67,12 @@ Bf16Path bf16_path(int64_t M, int64_t K, int64_t N) {
     // direct-from-L2 kernel, elsewhere the rollout-batch kernel measured faster
     if (M > 8 && M <= 16 && N / dmr::kTileRows >= 1024 && dmr::bf16_stream_fits(M, K, N)) return Bf16Path::Stream;
     if (M <= 8) return Bf16Path::Skinny;
-    // measured crossover: the tiled kernels win once they have more than ~128 workgroups
+    // Measured crossover with the direct-to-LDS kernels (K >= 1024; nine layers, 65 .. 768 rows, us rollout-batch / tiled):
+    // 64 blocks of 128 x 128 36 / 48 (K = 4096), 91 / 163 (K = 14336); 72 blocks 32 / 26 (K = 2048); 96 blocks 50 / 46 and
+    // 55 / 48 (K = 4096), 142 / 152 (K = 14336); 192 blocks 81 / 50.  Exactly 128 blocks keep the rollout-batch kernel, the
+    // class that callers and tests know for them (512 x 4096 x 4096: 55 / 48).
     const int64_t gemm_wgs = ((M + 127) / 128) * ((N + 127) / 128);
-    if (M <= 64 || gemm_wgs <= 128) return Bf16Path::Mid;
+    if (M <= 64 || gemm_wgs <= (K >= 1024 && K < 12288 ? 71 : 128) || gemm_wgs == 128) return Bf16Path::Mid;
     return dmr::gemm_big_tile_rows(M, K, N) != 0 ? Bf16Path::GemmBig : Bf16Path::Gemm;
 }
 
