@@ -1,7 +1,7 @@
 // One-off, integer-mostly kernels around the streaming layout: re-tile at create time,
 // dequantize (the parity anchor of the layout), and the round-to-nearest quantiser that
 // produces canonical inputs on the device.
-#include "common.hpp"
+#include "convert.hpp"
 
 namespace dmr {
 
@@ -19,8 +19,7 @@ __global__ __launch_bounds__(256) void retile_kernel(int64_t K, int64_t N,
     const int64_t slots = N * K / 32;
     if (slot >= slots) return;
     const int l = (int)(slot & 63);
-    const int64_t block = slot >> 6;
-    const int64_t T = block / groups, G = block % groups;
+    const auto [T, G] = block_pos(slot >> 6, groups);
     const int c = l >> 4, j = l & 15;
     const int64_t n = T * kTileRows + j;
     const uint4 src = *reinterpret_cast<const uint4 *>(qweight + n * (K / 8) + G * 16 + c * 4);
@@ -59,32 +58,14 @@ __global__ __launch_bounds__(256) void dequantize_kernel(int64_t K, int64_t N,
                                                          const uint4 *__restrict__ wt,
                                                          const uint32_t *__restrict__ sz,
                                                          uint16_t *__restrict__ w_bf16, int szs) {
+    __shared__ __attribute__((aligned(16))) uint32_t turn[4][kTurnWords];
     const int64_t groups = K / kGroup;
     const int64_t slot = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (slot >= N * K / 32) return;
-    const int l = (int)(slot & 63);
-    const int64_t block = slot >> 6;
-    const int64_t T = block / groups, G = block % groups;
-    const int c = l >> 4, j = l & 15;
-    const int64_t n = T * kTileRows + j;
-    const uint4 src = wt[slot];
-    const uint32_t szw = sz[sz_index(T, G, groups, szs, j)];
-    const float s = bf16_bits_to_f32(szw & 0xFFFFu);
-    const float z = -bf16_bits_to_f32(szw >> 16) - 128.0f;
-    const uint32_t in[4] = {src.x, src.y, src.z, src.w};
-    uint4 *dst = reinterpret_cast<uint4 *>(w_bf16 + n * K + G * kGroup + c * 32);
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        uint32_t o[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            // (q - z) * s: a 5-bit integer times an 8-bit significand, exact in fp32
-            const float lo = ((float)((in[t] >> (4 * nibble_of_position(2 * i))) & 0xFu) - z) * s;
-            const float hi = ((float)((in[t] >> (4 * nibble_of_position(2 * i + 1))) & 0xFu) - z) * s;
-            o[i] = pack_bf16x2(lo, hi);
-        }
-        dst[t] = make_uint4(o[0], o[1], o[2], o[3]);
-    }
+    const bool live = slot < N * K / 32;         // whole wavefronts: a block is 64 slots
+    const auto [T, G] = block_pos(live ? slot >> 6 : 0, groups);
+    const uint4 src = live ? wt[slot] : make_uint4(0, 0, 0, 0);
+    const uint32_t szw = sz[sz_index(T, G, groups, szs, (int)(slot & 15))];
+    store_dequantized<true>(turn[threadIdx.x >> 6], src, szw, live, T, G, K, w_bf16);
 }
 
 hipError_t launch_dequantize(const LayerView &L, uint16_t *w_bf16, hipStream_t stream) {
@@ -96,8 +77,8 @@ hipError_t launch_dequantize(const LayerView &L, uint16_t *w_bf16, hipStream_t s
 }
 
 // ---- quantise: fp32 [N][K] -> canonical codes, scales, zero points (round to nearest) --------
-// 16 consecutive lanes share one group of 128 weights (8 each): range by a 16-lane butterfly,
-// then every lane derives the same scale and zero point in fp64 and packs its own word.
+// 16 consecutive lanes share one group of 128 weights (8 each): range over the 16 lanes, then every lane derives the
+// same scale and zero point and packs its own word.
 __global__ __launch_bounds__(256) void quantize_kernel(int64_t K, int64_t N,
                                                        const float *__restrict__ w,
                                                        uint32_t *__restrict__ qweight,
@@ -118,33 +99,18 @@ __global__ __launch_bounds__(256) void quantize_kernel(int64_t K, int64_t N,
             hi = fmaxf(hi, v[i]);
         }
     }
-#pragma unroll
-    for (int mask = 1; mask < 16; mask <<= 1) {
-        lo = fminf(lo, __shfl_xor(lo, mask, 16));
-        hi = fmaxf(hi, __shfl_xor(hi, mask, 16));
-    }
+    row16_range(lo, hi);
     if (!live) return;
     const float s32 = (float)(((double)hi - (double)lo) / 15.0);
     uint32_t s_bits = f32_to_bf16(s32);
-    double s = (double)bf16_bits_to_f32(s_bits);
-    if (s == 0.0) {
-        s = 1.0;
-        s_bits = 0x3F80u;
-    }
-    double z = rint(-(double)lo / s);
-    z = (z > 0.0) ? fmin(z, 15.0) : 0.0;   // code 0 is +0 also when -lo / s is -0
-    uint32_t packed = 0;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        double c = rint((double)v[i] / s) + z;
-        c = fmin(fmax(c, 0.0), 15.0);
-        packed |= (uint32_t)(int)c << (4 * i);
-    }
+    if ((s_bits & 0x7FFFu) == 0) s_bits = 0x3F80u;
+    float z;
+    const uint32_t packed = quantize_codes<15, 4>(v, bf16_bits_to_f32(s_bits), lo, z);
     qweight[word] = packed;
     if ((word & 15) == 0) {
         const int64_t group = word >> 4;     // (n, G) flattened: rows hold K/128 groups each
         scales[group] = (uint16_t)s_bits;
-        zeros[group] = f32_to_bf16((float)z);
+        zeros[group] = f32_to_bf16(z);
     }
 }
 

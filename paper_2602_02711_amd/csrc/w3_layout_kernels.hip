@@ -9,7 +9,7 @@
 // bytes (r % 2) and (r % 2) + 2.  The two spare bits of each byte carry the last eight codes:
 // registers 12, 13 (14, 15) have their low two bits in bits [6, 8) of the bytes of word 0 (word 1)
 // and their third bit in bit 6 (bit 7) of the same byte of word 2.
-#include "common.hpp"
+#include "convert.hpp"
 
 namespace dmr {
 
@@ -56,7 +56,7 @@ __global__ __launch_bounds__(256) void retile3_kernel(int64_t K, int64_t N,
     if (slot >= N * K / 32) return;
     const int l = (int)(slot & 63);
     const int64_t block = slot >> 6;
-    const int64_t T = block / groups, G = block % groups;
+    const auto [T, G] = block_pos(block, groups);
     const int c = l >> 4, j = l & 15;
     const int64_t n = T * kTileRows + j;
     // the lane's 32 codes are one canonical run of three words
@@ -87,30 +87,19 @@ __global__ __launch_bounds__(256) void dequantize3_kernel(int64_t K, int64_t N,
                                                           const uint32_t *__restrict__ wt,
                                                           const uint32_t *__restrict__ sz,
                                                           uint16_t *__restrict__ w_bf16) {
+    __shared__ __attribute__((aligned(16))) uint32_t turn[4][kTurnWords];
     const int64_t groups = K / kGroup;
     const int64_t slot = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (slot >= N * K / 32) return;
-    const int l = (int)(slot & 63);
-    const int64_t block = slot >> 6;
-    const int64_t T = block / groups, G = block % groups;
-    const int c = l >> 4, j = l & 15;
-    const int64_t n = T * kTileRows + j;
-    const uint32_t w[3] = {wt[slot * 3], wt[slot * 3 + 1], wt[slot * 3 + 2]};
-    const uint32_t szw = sz[block * kTileRows + j];
-    const float s = bf16_bits_to_f32(szw & 0xFFFFu);
-    const float z = -bf16_bits_to_f32(szw >> 16) - 128.0f;
-    uint4 *dst = reinterpret_cast<uint4 *>(w_bf16 + n * K + G * kGroup + c * 32);
+    const bool live = slot < N * K / 32;         // whole wavefronts: a block is 64 slots
+    const int64_t from = live ? slot : (slot & 63);
+    const auto [T, G] = block_pos(from >> 6, groups);
+    const uint32_t w[3] = {wt[from * 3], wt[from * 3 + 1], wt[from * 3 + 2]};
+    const uint32_t szw = sz[(from >> 6) * kTileRows + (from & 15)];
+    uint32_t words[4] = {0, 0, 0, 0};
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        uint32_t o[4];
-#pragma unroll
-        for (int p = 0; p < 4; ++p) {
-            const float lo = ((float)decode_lane(w, 8 * t + 2 * p) - z) * s;       // exact in fp32
-            const float hi = ((float)decode_lane(w, 8 * t + 2 * p + 1) - z) * s;
-            o[p] = pack_bf16x2(lo, hi);
-        }
-        dst[t] = make_uint4(o[0], o[1], o[2], o[3]);
-    }
+    for (int i = 0; i < 32; ++i) words[i / 8] |= decode_lane(w, i) << (4 * (i % 8));
+    store_dequantized<false>(turn[threadIdx.x >> 6], make_uint4(words[0], words[1], words[2], words[3]), szw, live, T, G, K,
+                             w_bf16);
 }
 
 // Quantiser: 16 lanes share a group (8 weights each), as in the 4-bit kernel; four lanes together
@@ -137,27 +126,12 @@ __global__ __launch_bounds__(256) void quantize3_kernel(int64_t K, int64_t N, co
 #pragma unroll
         for (int i = 0; i < 8; ++i) v[i] = 0.f;
     }
-#pragma unroll
-    for (int mask = 1; mask < 16; mask <<= 1) {
-        lo = fminf(lo, __shfl_xor(lo, mask, 16));
-        hi = fmaxf(hi, __shfl_xor(hi, mask, 16));
-    }
+    row16_range(lo, hi);
     const float s32 = (float)(((double)hi - (double)lo) / 7.0);
     uint32_t s_bits = f32_to_bf16(s32);
-    double s = (double)bf16_bits_to_f32(s_bits);
-    if (s == 0.0) {
-        s = 1.0;
-        s_bits = 0x3F80u;
-    }
-    double z = rint(-(double)lo / s);
-    z = (z > 0.0) ? fmin(z, 7.0) : 0.0;
-    uint32_t piece = 0;   // this lane's 24 bits
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        double c = rint((double)v[i] / s) + z;
-        c = fmin(fmax(c, 0.0), 7.0);
-        piece |= (uint32_t)(int)c << (3 * i);
-    }
+    if ((s_bits & 0x7FFFu) == 0) s_bits = 0x3F80u;
+    float z;
+    const uint32_t piece = quantize_codes<7, 3>(v, bf16_bits_to_f32(s_bits), lo, z);   // this lane's 24 bits
     // lanes 4q..4q+3 hold pieces p0..p3 of one run: word0 = p0 | p1 << 24, word1 = p1 >> 8 | p2 << 16,
     // word2 = p2 >> 16 | p3 << 8.  Lane 4q + i (i < 3) writes word i.
     const int lane = threadIdx.x & 63, i4 = lane & 3;
@@ -170,7 +144,7 @@ __global__ __launch_bounds__(256) void quantize3_kernel(int64_t K, int64_t N, co
     if (live && (oct & 15) == 0) {
         const int64_t group = oct >> 4;
         scales[group] = (uint16_t)s_bits;
-        zeros[group] = f32_to_bf16((float)z);
+        zeros[group] = f32_to_bf16(z);
     }
 }
 
