@@ -15,6 +15,15 @@ __device__ __forceinline__ BlockPos block_pos(int64_t block, int64_t groups) {
     return {(int64_t)t, (int64_t)(b - t * g)};
 }
 
+// Eight consecutive fp32 weights, read once: past the caches, which the codes that the re-tiling reads next can then keep
+// (28672 x 4096 and three narrower layers, 4 bits: quantise 54.4 -> 49.9, re-tile 13.1 -> 12.2 us on average).
+__device__ __forceinline__ void load_weights(const float *__restrict__ w, float (&v)[8]) {
+    const uint4 a = load_stream(reinterpret_cast<const uint4 *>(w)), b = load_stream(reinterpret_cast<const uint4 *>(w + 4));
+    const uint32_t bits[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = __uint_as_float(bits[i]);
+}
+
 // Minimum / maximum over each aligned group of 16 lanes, in every lane: four rotations on the VALU, no LDS round trip.
 __device__ __forceinline__ void row16_range(float &lo, float &hi) {
     lo = fminf(lo, dpp_move<0x128>(lo)); hi = fmaxf(hi, dpp_move<0x128>(hi));
@@ -74,7 +83,9 @@ __device__ __forceinline__ uint32_t quantize_codes(const float (&v)[8], float s,
 // Dequantised store of one block by one wavefront: lane 16 c + j brings its 32 codes as four words of eight nibbles
 // (position p of a word in nibble SHUFFLED ? nibble_of_position(p) : p) and its row's scale word.  Through LDS the wave turns
 // them so that 16 lanes store the 256 contiguous bytes of a row; straight from the lane each store instruction was 64
-// pieces of 16 bytes, 64 bytes apart (28672 x 4096 weights, 4 bits: 83 -> 50 us, 5.9 TB/s of codes and bf16).  Rows of 64 words are padded by 16: the four c of a read then use different banks.
+// pieces of 16 bytes, 64 bytes apart (28672 x 4096 weights, 4 bits: 83 -> 50 us, 5.9 TB/s of codes and bf16).  Rows of 64
+// words are padded by 16: the four c of a read then use different banks.
+// The stores go past the caches too: 24.5 -> 21.2 us on average over four layers, 5.8 -> 6.6 TB/s on the largest.
 // Every thread of the workgroup calls this (it synchronises); `live` is uniform over the wave.
 constexpr int kTurnWords = 3 * 80 + 64;
 template <bool SHUFFLED>
@@ -95,13 +106,15 @@ __device__ __forceinline__ void store_dequantized(uint32_t *turn, uint4 words, u
         uint32_t o[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const int n0 = SHUFFLED ? nibble_of_position(2 * i) : 2 * i, n1 = SHUFFLED ? nibble_of_position(2 * i + 1) : 2 * i + 1;
+            const int n0 = SHUFFLED ? nibble_of_position(2 * i) : 2 * i;
+            const int n1 = SHUFFLED ? nibble_of_position(2 * i + 1) : 2 * i + 1;
             // (q - z) * s: a 5-bit integer times an 8-bit significand, exact in fp32
             const float lo = ((float)((in >> (4 * n0)) & 0xFu) - z) * s;
             const float hi = ((float)((in >> (4 * n1)) & 0xFu) - z) * s;
             o[i] = pack_bf16x2(lo, hi);
         }
-        reinterpret_cast<uint4 *>(w_bf16 + (T * kTileRows + j) * K + G * kGroup)[u] = make_uint4(o[0], o[1], o[2], o[3]);
+        const u32x4_t ov = {o[0], o[1], o[2], o[3]};
+        __builtin_nontemporal_store(ov, reinterpret_cast<u32x4_t *>(w_bf16 + (T * kTileRows + j) * K + G * kGroup) + u);
     }
 }
 

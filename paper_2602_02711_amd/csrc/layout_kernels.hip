@@ -89,10 +89,7 @@ __global__ __launch_bounds__(256) void quantize_kernel(int64_t K, int64_t N,
     float v[8];
     float lo = 0.0f, hi = 0.0f;
     if (live) {
-        const float4 a = *reinterpret_cast<const float4 *>(w + word * 8);
-        const float4 b = *reinterpret_cast<const float4 *>(w + word * 8 + 4);
-        v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
-        v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+        load_weights(w + word * 8, v);
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             lo = fminf(lo, v[i]);

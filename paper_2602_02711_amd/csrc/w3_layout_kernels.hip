@@ -113,10 +113,7 @@ __global__ __launch_bounds__(256) void quantize3_kernel(int64_t K, int64_t N, co
     float v[8];
     float lo = 0.0f, hi = 0.0f;
     if (live) {
-        const float4 a = *reinterpret_cast<const float4 *>(w + oct * 8);
-        const float4 b = *reinterpret_cast<const float4 *>(w + oct * 8 + 4);
-        v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
-        v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+        load_weights(w + oct * 8, v);
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             lo = fminf(lo, v[i]);
