@@ -3,6 +3,7 @@
 #include <new>
 
 #include "glue.hpp"
+#include "mid_plan.hpp"
 #include "panel_plan.hpp"
 #include "wide_plan.hpp"
 
@@ -61,18 +62,36 @@ W3Path w3_path(int64_t M, int64_t K, int64_t N) {
 // The bf16 twin: GEMV, the direct-from-L2 skinny kernel for 2..8 rows (measured faster there than the
 // LDS-staged kernels), then the same size classes as INT4.
 enum class Bf16Path { Gemv, Stream, Skinny, Mid, GemmBig, Gemm };
+
+// M > 64, K >= 1024: whether the direct-to-LDS kernels beat the rollout-batch kernel.  While one round covers the layer they
+// take the same time whatever its width; the other kernel's time grows with its blocks (its own row blocks times 128 columns)
+// in the steps of its plan.  From 24 values of K, 56 .. 168 blocks and nine row counts in 90 .. 1000, weights from memory; us
+// at 200 rows, rollout-batch / tiled:
+//   up to 64 blocks (its workgroups fit one round)   K = 2048 24 / 29   K = 4096 38 / 50   K = 8192 58 / 88   K = 14336 93 / 160
+//   65 .. 95, K split four ways or more                                 4096, 72 48 / 50   8192, 72 76 / 85   14336, 72 126 / 161
+//   65 .. 128, fewer splits                   2048, 96 blocks 36 / 30   4096, 96 56 / 51   8192, 96 96 / 89   14336, 96 163 / 164
+//   above 128                                 2048, 132       49 / 31   4096, 132 77 / 53  8192, 132 136 / 95 14336, 132 237 / 174
+// The third class changes hands between K = 5120 (0.95 .. 1.09 of the tiled time over the row counts) and 6144 (0.91 .. 1.06)
+// and is the rollout-batch kernel's from there on, but for K = 8192 (0.96 .. 1.11; 7936 and 8704 0.91 .. 1.07) and for a K
+// whose groups do not split on its plan (8064, 96 blocks: 115 / 93).
+bool tiled_beats_rollout(int64_t M, int64_t K, int64_t N) {
+    const dmr::MidPlan m = dmr::plan_mid(M, K, N);
+    const int64_t blocks = m.mblocks * ((N + 127) / 128);
+    if (blocks <= 64 || blocks > 128) return blocks > 128;
+    return m.SK < 4 && (K < 5632 || K == 8192 || m.SK == 1);
+}
 Bf16Path bf16_path(int64_t M, int64_t K, int64_t N) {
     if (M == 1) return Bf16Path::Gemv;
     // the streaming kernel wins (by ~12 %) only for 9..16 rows of the widest layers; below that the
     // direct-from-L2 kernel, elsewhere the rollout-batch kernel measured faster
     if (M > 8 && M <= 16 && N / dmr::kTileRows >= 1024 && dmr::bf16_stream_fits(M, K, N)) return Bf16Path::Stream;
     if (M <= 8) return Bf16Path::Skinny;
-    // Measured crossover with the direct-to-LDS kernels (K >= 1024; nine layers, 65 .. 768 rows, us rollout-batch / tiled):
-    // 64 blocks of 128 x 128 36 / 48 (K = 4096), 91 / 163 (K = 14336); 72 blocks 32 / 26 (K = 2048); 96 blocks 50 / 46 and
-    // 55 / 48 (K = 4096), 142 / 152 (K = 14336); 192 blocks 81 / 50.  Exactly 128 blocks keep the rollout-batch kernel, the
-    // class that callers and tests know for them (512 x 4096 x 4096: 55 / 48).
-    const int64_t gemm_wgs = ((M + 127) / 128) * ((N + 127) / 128);
-    if (M <= 64 || gemm_wgs <= (K >= 1024 && K < 12288 ? 71 : 128) || gemm_wgs == 128) return Bf16Path::Mid;
+    if (M <= 64) return Bf16Path::Mid;
+    if (K < 1024) {                  // no direct-to-LDS kernel there
+        if (((M + 127) / 128) * ((N + 127) / 128) <= 128) return Bf16Path::Mid;
+    } else if (!tiled_beats_rollout(M, K, N)) {
+        return Bf16Path::Mid;
+    }
     return dmr::gemm_big_tile_rows(M, K, N) != 0 ? Bf16Path::GemmBig : Bf16Path::Gemm;
 }
 

@@ -10,6 +10,7 @@ namespace dmr {
 
 struct MidPlan {
     int MTW, WM, NW, R, SK, gps;
+    int64_t mblocks;      // row blocks of 16 MTW WM rows
 };
 
 // Pure host arithmetic (the workspace query must agree with the launch): 256 CUs assumed.
@@ -27,7 +28,7 @@ inline MidPlan plan_mid(int64_t M, int64_t K, int64_t N) {
         p.NW = 2;     // 8-wave workgroups (128 x 128 tiles) were measured too: no faster
     }
     const int BM = 16 * p.MTW * p.WM;
-    const int64_t mblocks = (M + BM - 1) / BM;
+    const int64_t mblocks = p.mblocks = (M + BM - 1) / BM;
     // Measured rules (gfx950, 256 CUs): split K while that keeps >= 8 groups per split and fewer than
     // 384 workgroups exist; two weight tiles per wave unless that leaves under 256 workgroups
     // even at the deepest split.

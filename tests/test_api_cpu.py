@@ -203,7 +203,7 @@ def test_w3_size_query_and_kernel_paths(lib):
     assert lib.dmr_qlinear_workspace_bytes(200, 256, 19200) > 0
     assert path(binding.DMR_FMT_W4_G128, 1, 32768, 528) == b"w4_skinny"
     assert path(binding.DMR_FMT_BF16, 1, 32768, 528) == b"bf16_skinny"
-    assert path(binding.DMR_FMT_BF16, 512, 4096, 4096) == b"bf16_mid"          # exactly 128 workgroups: not tiled yet
+    assert path(binding.DMR_FMT_BF16, 512, 4096, 4096) == b"bf16_gemm128_dma"  # 128 blocks: tiled (58 / 49 us)
     assert path(binding.DMR_FMT_BF16, 1024, 4096, 4096) == b"bf16_gemm128_dma"
     assert path(binding.DMR_FMT_BF16, 8192, 4096, 4096) == b"bf16_gemm256"
     assert path(binding.DMR_FMT_W4_G128, 4, 1000, 4096) == b"none"

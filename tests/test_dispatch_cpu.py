@@ -1,0 +1,36 @@
+"""Which kernel class serves a shape, on both sides of the measured crossovers (host arithmetic only)."""
+import pytest
+
+from paper_2602_02711_amd import binding
+
+
+@pytest.fixture(scope="module")
+def lib():
+    return binding.lib()
+
+
+def bf16_path(lib, M, K, N):
+    return lib.dmr_qlinear_kernel_path(binding.DMR_FMT_BF16, M, K, N)
+
+
+@pytest.mark.parametrize("M,K,N,tiled", [
+    (200, 2048, 4096, False), (200, 2048, 4224, True),          # 64 / 66 blocks of 128 x 128, K split twice
+    (200, 4096, 4608, False), (384, 4096, 3072, False),         # 72 blocks, K split four ways: 48 / 50 us
+    (200, 4096, 6144, True), (512, 4096, 4096, True),           # 96 and 128 blocks
+    (200, 8192, 4608, False), (384, 8192, 3072, False),         # 72 blocks: 76 / 85 us
+    (200, 8192, 6144, True),                                    # 96 blocks
+    (200, 6144, 6144, False), (200, 11264, 8192, False),        # 96 and 128 blocks of longer rows
+    (200, 6144, 8320, True), (200, 14336, 8320, True),          # 130 blocks
+    (450, 4096, 3328, True),                                    # five row blocks of 96 x 26 column blocks
+    (200, 8064, 6144, True),                                    # 63 groups: the rollout-batch kernel cannot split K
+    (200, 512, 8192, False), (200, 512, 8320, True),            # K < 1024: 128 / 130 blocks
+])
+def test_bf16_crossover(lib, M, K, N, tiled):
+    assert (bf16_path(lib, M, K, N) != b"bf16_mid") == tiled
+
+
+@pytest.mark.parametrize("K", [512, 1024, 2048, 4096, 5120, 8064, 8192, 11264, 14336])
+@pytest.mark.parametrize("M", [70, 128, 200, 450, 512, 1000])
+def test_bf16_crossover_has_no_holes(lib, M, K):
+    tiled = [bf16_path(lib, M, K, N) != b"bf16_mid" for N in range(128, 24576, 128)]
+    assert tiled == sorted(tiled)
