@@ -12,6 +12,7 @@
 // Data movement and LDS layout: `global_load_lds_dwordx4` (every lane names its own 16 global bytes, the wave's
 // 64 x 16 bytes land contiguously at a wave-uniform LDS address), four LDS stages of 32 k, rows of 64 bytes with the
 // 16-byte chunks XOR-swizzled on the global side, bare barriers, loads three to four steps ahead.
+#include <cstdint>
 #include <type_traits>
 
 #include "common.hpp"
@@ -277,9 +278,16 @@ hipError_t launch_one(const uint16_t *w, const uint16_t *x, int64_t M, int64_t K
 // preferred.  One workgroup of this kernel is resident per CU, so a launch runs in rounds of 256 tiles, and what a ragged
 // last round wastes decides: 3000 rows x 4096 outputs are 192 tiles of 256 rows (three quarters of a round), 256 tiles of
 // 192 rows (exactly one) or 768 blocks of 128 x 128 (one and a half rounds).  The time of a launch is taken as
-// (full rounds) * full + (a last round filled to f: base + slope * f), the numbers in us at K = 4096 from a sweep over six
-// layers and 300 .. 8192 rows (the choice was the fastest or within 7 % of it at every point):
-//     3000 rows, us with the former rule / now:  4096 -> 6144  221 / 163;  4096 -> 4096  127 / 92;  14336 -> 4096  433 / 312
+// (full rounds) * full + (a last round filled to f: base + slope * f), the numbers in us at K = 4096.  Against all four kernels
+// on five K of 1024 .. 14336, nine N of 1024 .. 28672 and 150 .. 8192 rows (774 points, weights from memory) the choice is
+// 0.1 % behind the fastest on average; at five rounds and more 192 and 256 rows lie within 6 % of each other with no order that
+// holds over K.
+//     3000 rows, us with 256 rows or 128 x 128 only / now:  4096 -> 6144  210 / 165;  4096 -> 4096  122 / 93;  14336 -> 4096  464 / 310
+// One and a half rounds of 128 x 128 blocks or less do better than that where the column blocks divide by the eight XCDs: each
+// XCD then keeps to its own columns and reads the weights once, which pays while they are the larger operand (us, 128 x 128 / 128
+// rows: 1400 x 4096 -> 3072 62 / 73, 700 x 4096 -> 6144 66 / 73, 600 x 8192 -> 8192 129 / 149; but 900 x 4096 -> 6000, 47 column
+// blocks, 6 % behind, 4300 x 4096 -> 1024 86 / 71, and with three or four row blocks 1 .. 18 % behind); a little less of a round
+// if the last row block is half empty, which the taller tiles feel less (1436 x 8192 -> 4096, 384 blocks: 7 % behind).
 // Below K = 1024 (not measured) the former rule stands: 256 rows from 1.5 tiles per CU on, or for one round that is at least
 // 80 % full.
 int gemm_big_tile_rows(int64_t M, int64_t K, int64_t N) {
@@ -292,10 +300,13 @@ int gemm_big_tile_rows(int64_t M, int64_t K, int64_t N) {
     struct Shape {
         int rows, full, base, slope;
     };
-    constexpr Shape shapes[3] = {{256, 114, 65, 49}, {192, 90, 50, 40}, {128, 69, 40, 29}};
+    const Shape shapes[3] = {{256, 114, 65, 49}, {192, K >= 8192 ? 93 : 90, 52, 40}, {128, 74, 40, 29}};
     // 128 x 128 blocks: 512 at a time, up to half of that one workgroup per CU
-    const int64_t blocks = ((M + 127) / 128) * ((N + 127) / 128), left = blocks % 512;
+    const int64_t nbm = (M + 127) / 128, nbn = (N + 127) / 128, blocks = nbm * nbn, left = blocks % 512;
+    const int64_t limit = (M - 1) % 128 < 64 ? 360 : 400;
+    if (blocks <= limit && nbn % 8 == 0 && nbm >= 5 && nbm <= nbn) return 0;
     int64_t best = 82 * (blocks / 512) * 256 + (left == 0 ? 0 : left <= 256 ? 36 * 256 + 12 * left : 62 * 256 + 20 * (left - 256));
+    if (nbn > 1 && ((M + 255) / 256) * ((N + 255) / 256) >= 384) best = INT64_MAX;      // 100000 x 4096 -> 384: 480, 256 rows 439
     int rows = 0;
     for (const Shape &s : shapes) {
         const int64_t tiles = ((M + s.rows - 1) / s.rows) * ((N + 255) / 256), last = tiles % 256;

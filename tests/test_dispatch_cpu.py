@@ -34,3 +34,20 @@ def test_bf16_crossover(lib, M, K, N, tiled):
 def test_bf16_crossover_has_no_holes(lib, M, K):
     tiled = [bf16_path(lib, M, K, N) != b"bf16_mid" for N in range(128, 24576, 128)]
     assert tiled == sorted(tiled)
+
+
+@pytest.mark.parametrize("M,K,N,name", [
+    (700, 4096, 6144, "bf16_gemm128_dma"), (1400, 4096, 3072, "bf16_gemm128_dma"),     # column blocks divide by the XCDs
+    (600, 8192, 8192, "bf16_gemm128_dma"), (1020, 4096, 5120, "bf16_gemm128_dma"),
+    (1240, 4096, 5120, "bf16_gemm128_dma"), (1200, 4096, 6144, "bf16_gemm128x256"),    # 400 and 480 blocks
+    (1436, 8192, 4096, "bf16_gemm128x256"), (1531, 8192, 4096, "bf16_gemm128_dma"),    # the last row block half empty / full
+    (900, 4096, 6000, "bf16_gemm128x256"), (4300, 4096, 1024, "bf16_gemm128x256"),     # 47 column blocks; a tall layer
+    (400, 4096, 16384, "bf16_gemm128x256"),                                            # four row blocks
+    (1300, 4096, 28672, "bf16_gemm256"), (1642, 8192, 14864, "bf16_gemm256"),
+    (4300, 8192, 16384, "bf16_gemm256"), (4300, 4096, 16384, "bf16_gemm192x256"),
+    (100000, 4096, 384, "bf16_gemm256"), (200000, 4096, 128, "bf16_gemm128_dma"),
+    (3000, 4096, 6144, "bf16_gemm192x256"), (2000, 4096, 4096, "bf16_gemm128x256"),
+    (1024, 4096, 4096, "bf16_gemm128_dma"), (8192, 4096, 4096, "bf16_gemm256"),
+])
+def test_bf16_tile(lib, M, K, N, name):
+    assert bf16_path(lib, M, K, N).decode() == name
