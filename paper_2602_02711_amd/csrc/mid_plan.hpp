@@ -11,6 +11,7 @@ namespace dmr {
 struct MidPlan {
     int MTW, WM, NW, R, SK, gps;
     int64_t mblocks;      // row blocks of 16 MTW WM rows
+    int64_t wgs;          // workgroups, splits of K included
 };
 
 // Pure host arithmetic (the workspace query must agree with the launch): 256 CUs assumed.
@@ -45,6 +46,7 @@ inline MidPlan plan_mid(int64_t M, int64_t K, int64_t N) {
     const int sk_env = env_int("DMR_MID_SK", 0);
     if (sk_env >= 1 && groups % sk_env == 0) p.SK = sk_env;
     p.gps = groups / p.SK;
+    p.wgs = wgs_for(p.R) * p.SK;
     return p;
 }
 

@@ -1,6 +1,7 @@
 // Launch planning of the chunked-panel kernel (w4_wide.hip): pure host arithmetic for 256 CUs.
 #pragma once
 #include "common.hpp"
+#include "mid_plan.hpp"
 
 namespace dmr {
 
@@ -20,11 +21,19 @@ inline size_t wide_lds_bytes(int MT, int R, int S, int CG) {
     return panels > red ? panels : red;
 }
 
-// 17 <= M <= 64.  K is split until every CU has a workgroup, while a split keeps two chunks or more: measured against the
-// rollout-batch kernel (us at 64 rows, that kernel / this one) 4096 -> 6144 17.5 / 16.5, 14336 -> 4096 26.2 / 24.4,
-// 2560 -> 13824 22.5 / 20.2, 8192 -> 8192 29.0 / 25.7; with one chunk per split 4096 -> 4096 13.4 / 15.1, 2048 -> 3072
-// 10.8 / 11.3.  (Splits x column blocks <= 256: the partials of 64 rows take at most 8 MiB.)
-inline WidePlan plan_wide(int64_t M, int64_t K, int64_t N) {
+// 17 <= M <= 64.  Layers of 1024 row tiles or more (half of the CUs without a split) are this kernel's; K is split in two
+// there if that fills the CUs and leaves each half three chunks (us unsplit / split at 17 and 64 rows: 3072 -> 16384 16.2 / 13.8
+// and 24.2 / 22.3, 4096 -> 16384 20.1 / 16.9 and 29.7 / 25.4; but 2048 -> 16384 17.8 / 18.7, 1536 -> 16384 14.7 / 18.2 at 64).
+// Narrower layers split K until every CU has a workgroup, while a split keeps two chunks, and go here where that beats the
+// rollout-batch kernel.  16 K x 12 N x 17, 32, 48, 64 rows, both formats; us at 17 / 64 rows, that kernel then this one:
+//   its two weight tiles per wave, or more workgroups than CUs:  4096 -> 6144 11.4 / 18.2, 11.2 / 17.0;  14336 -> 4096 18.9 / 27.0,
+//     17.1 / 25.1;  8192 -> 8192 18.7 / 28.8, 18.0 / 25.9;  4608 -> 8192 14.9 / 22.5, 13.1 / 19.9
+//   all its workgroups at once, one tile and at most 12 groups each:  1536 -> 12288 8.3 / 11.9, 10.4 / 16.4;  6144 -> 4096 11.4 /
+//     16.4, 11.9 / 17.3;  12288 -> 2048 12.2 / 17.4, 13.2 / 18.9: left to it (14 groups, 3584 -> 5120: 11.7 / 17.6, 10.7 / 16.2)
+//   two splits of more than seven chunks:  14336 -> 12288 31.7 / 49.1, 35.5 / 54.0: left to it while its partials, twice or four
+//     times as many, stay within the fixed scratch of dmr_qlinear_forward_static, which such a call otherwise would not fit
+// (Splits x column blocks <= 256: the partials of 64 rows take at most 8 MiB.)  `with_workspace` false: unsplit or not at all.
+inline WidePlan plan_wide(int64_t M, int64_t K, int64_t N, bool with_workspace = true) {
     WidePlan p{};
     p.ok = false;
     if (M < 17 || M > 64 || M * K >= (int64_t(1) << 31)) return p;
@@ -33,15 +42,18 @@ inline WidePlan plan_wide(int64_t M, int64_t K, int64_t N) {
     p.MT = (int)((M + 15) / 16);
     const int nch = (int)(groups / kWideChunk);
     const int64_t wgs = (tiles + kWideTilesPerWg - 1) / kWideTilesPerWg;
+    const bool wide = tiles >= 128 * kWideTilesPerWg;
     int sk = (int)(kCus / wgs);
-    sk = sk < 1 ? 1 : sk > nch ? nch : sk;
+    sk = sk < 1 || !with_workspace || (wide && nch < 6) ? 1 : sk > nch ? nch : sk;
     p.cps = (nch + sk - 1) / sk;
     p.SK = (nch + p.cps - 1) / p.cps;
-    p.ok = p.SK > 1 && p.cps >= 2;
-    if (!p.ok && tiles >= 128 * kWideTilesPerWg) {      // half of the CUs or more without a split
-        p.cps = nch;
-        p.SK = 1;
+    if (wide) {
         p.ok = true;
+    } else if (p.SK > 1 && p.cps >= 2) {
+        const MidPlan m = plan_mid(M, K, N);
+        const bool one_round = m.R == 1 && m.wgs <= kCus && m.gps <= 12;
+        const bool long_halves = p.SK == 2 && p.cps > 7;
+        p.ok = !one_round && (!long_halves || (size_t)m.SK * (size_t)(M * N) * sizeof(float) > DMR_STATIC_SCRATCH_BYTES);
     }
     return p;
 }
