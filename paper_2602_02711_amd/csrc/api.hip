@@ -122,6 +122,13 @@ dmr_status_t hip_status(hipError_t e) { return e == hipSuccess ? DMR_OK : DMR_ER
 
 namespace {
 
+// Whether the kernel that serves M rows of this layer also runs without the partials that the size query asks for: the
+// chunked-panel kernel does on layers that give half of the CUs a workgroup without a split of K (4096 -> 16384, 64 rows: 29.7 us
+// instead of 25.4).
+bool runs_unsplit(const dmr_qlinear_t *layer, int64_t M) {
+    return dmr::w4_wide_applies(M, layer->K, layer->N) && dmr::plan_wide(M, layer->K, layer->N, false).ok;
+}
+
 // The forwards with an optional bf16 residual added where the result is stored.
 dmr_status_t forward_quant(const dmr_qlinear_t *layer, const uint16_t *d_x, int64_t M, void *d_y, dmr_out_t out,
                            const uint16_t *res, void *d_ws, size_t ws_bytes, hipStream_t s) {
@@ -135,7 +142,10 @@ dmr_status_t forward_quant(const dmr_qlinear_t *layer, const uint16_t *d_x, int6
     if (layer->bits == 3) {
         const dmr::LayerView3 L3{layer->K, layer->N, layer->wt3, layer->sz};
         const size_t need3 = dmr_qlinear_w3_workspace_bytes(M, layer->K, layer->N);
-        if (need3 > 0 && (!d_ws || ws_bytes < need3)) return DMR_ERR_WORKSPACE;
+        if (need3 > 0 && (!d_ws || ws_bytes < need3)) {
+            if (!runs_unsplit(layer, M)) return DMR_ERR_WORKSPACE;
+            d_ws = nullptr;
+        }
         switch (w3_path(M, layer->K, layer->N)) {
             case W3Path::Gemv: return hip_status(dmr::launch_w3_gemv(L3, d_x, d_y, f32, res, s));
             case W3Path::Stream: return hip_status(dmr::launch_w3_stream(L3, d_x, M, d_y, f32, res, s));
@@ -148,7 +158,10 @@ dmr_status_t forward_quant(const dmr_qlinear_t *layer, const uint16_t *d_x, int6
         return DMR_ERR_UNSUPPORTED;
     }
     const size_t need = dmr_qlinear_workspace_bytes(M, layer->K, layer->N);
-    if (need > 0 && (!d_ws || ws_bytes < need)) return DMR_ERR_WORKSPACE;
+    if (need > 0 && (!d_ws || ws_bytes < need)) {
+        if (!runs_unsplit(layer, M)) return DMR_ERR_WORKSPACE;
+        d_ws = nullptr;
+    }
     const dmr::LayerView L{layer->K, layer->N, layer->wt, layer->sz, layer->szs};
     const W4Path path = w4_path(M, layer->K, layer->N);
     dmr::Fusion f;
@@ -501,7 +514,10 @@ dmr_status_t dmr_qlinear_forward_fused(const dmr_qlinear_t *layer, dmr_prologue_
     const dmr_status_t chk = check_fused(pro, d_in, d_gamma, eps, d_residual, M, d_y, out, d_ws);
     if (chk != DMR_OK || M == 0) return chk;
     const size_t need = dmr_qlinear_fused_workspace_bytes(layer, M, pro, d_residual != nullptr);
-    if (need > 0 && (!d_ws || ws_bytes < need)) return DMR_ERR_WORKSPACE;
+    if (need > 0 && (!d_ws || ws_bytes < need)) {
+        const size_t least = runs_unsplit(layer, M) ? fused_extra_bytes(M, layer->K, layer->N, pro, d_residual != nullptr) : need;
+        if (least > 0 && (!d_ws || ws_bytes < least)) return DMR_ERR_WORKSPACE;
+    }
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (M == 1 && layer->bits == 4) {
         const dmr::LayerView L{layer->K, layer->N, layer->wt, layer->sz, layer->szs};

@@ -263,10 +263,9 @@ hipError_t launch_cfg(const void *wt, const uint32_t *sz, int szs, int64_t K, in
 template <int BITS>
 hipError_t launch_wide(const void *wt, const uint32_t *sz, int szs, int64_t K, int64_t N, const uint16_t *x, int64_t M, void *y,
                        bool out_f32, const uint16_t *res, void *ws, hipStream_t stream) {
-    const WidePlan p = plan_wide(M, K, N);
+    const WidePlan p = plan_wide(M, K, N, ws != nullptr);
     if (!p.ok) return hipErrorInvalidValue;
     const bool split = p.SK > 1;
-    if (split && !ws) return hipErrorInvalidValue;
     void *dst = split ? ws : y;
     const int out_mode = split ? 2 : (out_f32 ? 0 : 1);
     const int iM = (int)M;
