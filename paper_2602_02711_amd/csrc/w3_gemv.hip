@@ -25,13 +25,18 @@ struct Item {
     uint32_t szw;
 };
 
+// shape = lgS | lgTW << 8 | out_f32 << 16, one word, and no use of the block size, so that everything read at the start (the grid
+// size follows the arguments) lies in the first 64 bytes: the first scalar loads of a wave wait for one cache line.  With the
+// residual's pointer added behind six ints they waited for two, 0.2 .. 0.35 us of a launch (us, weights from memory: 4096 -> 4096
+// 5.19 -> 4.91, 4096 -> 6144 6.31 -> 5.98, 2688 -> 3840 4.75 -> 4.50).
 template <int P, int XL>
 __global__ __launch_bounds__(1024) void w3_gemv_kernel(const uint32_t *__restrict__ wt,
                                                        const uint32_t *__restrict__ sz,
                                                        const uint16_t *__restrict__ x,
-                                                       void *__restrict__ y, int groups, int tiles,
-                                                       int lgS, int lgTW, int nT_max, int out_f32,
-                                                       const uint16_t *__restrict__ res) {
+                                                       void *__restrict__ y, const uint16_t *__restrict__ res,
+                                                       int groups, int tiles, int nT_max, int shape) {
+    const int lgS = shape & 0xFF, lgTW = (shape >> 8) & 0xFF, out_f32 = shape >> 16;
+    const int threads = 64 << (lgS + lgTW);
     extern __shared__ uint4 smem[];          // x (16 uint4 per group), X[groups], red[nT_max][TW][S][16]
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform (SGPR)
@@ -51,7 +56,7 @@ __global__ __launch_bounds__(1024) void w3_gemv_kernel(const uint32_t *__restric
     const int x16 = groups * 16;
 #pragma unroll
     for (int u = 0; u < XL; ++u) {
-        const int i = (int)threadIdx.x + u * (int)blockDim.x;
+        const int i = (int)threadIdx.x + u * threads;
         xreg[u] = reinterpret_cast<const uint4 *>(x)[i < x16 ? i : 0];
     }
 
@@ -85,7 +90,7 @@ __global__ __launch_bounds__(1024) void w3_gemv_kernel(const uint32_t *__restric
     float *red = xsum_lds + ((groups + 3) & ~3);
 #pragma unroll
     for (int u = 0; u < XL; ++u) {
-        const int i = (int)threadIdx.x + u * (int)blockDim.x;
+        const int i = (int)threadIdx.x + u * threads;
         // 16 consecutive threads hold one group's 128 activations: sum them (fp32, fixed order)
         float part = 0.f;
         const uint32_t xw[4] = {xreg[u].x, xreg[u].y, xreg[u].z, xreg[u].w};
@@ -160,7 +165,7 @@ __global__ __launch_bounds__(1024) void w3_gemv_kernel(const uint32_t *__restric
     // partials of one output sit in S adjacent lanes and fold by DPP adds in a fixed order.
     __syncthreads();
     const int total = (nT_max << (lgTW + lgS)) * 16;
-    for (int e = threadIdx.x; e < total; e += blockDim.x) {
+    for (int e = threadIdx.x; e < total; e += threads) {
         const int q = e & (S - 1), col = (e >> lgS) & 15, slot = e >> (lgS + 4);
         float v = red[((slot << lgS) + q) * 16 + col];
         if (S >= 2) v += dpp_move<0xB1>(v);       // quad_perm [1, 0, 3, 2]
@@ -248,10 +253,9 @@ hipError_t launch_w3_gemv(const LayerView3 &L, const uint16_t *x, void *y, bool 
     int P = items_max < 4 ? items_max : 4;
     P = env_int("DMR_GEMV3_P", P);
     const dim3 g(plan.grid), b(nw * 64);
-    const int of = out_f32 ? 1 : 0;
+    const int shape = lgS | lgTW << 8 | (out_f32 ? 1 : 0) << 16;
 #define DMR_GEMV3_LAUNCH(PP, XX)                                                                        \
-    hipLaunchKernelGGL((w3_gemv_kernel<PP, XX>), g, b, lds, stream, L.wt, L.sz, x, y, groups, tiles, lgS, \
-                       lgTW, nT_max, of, res)
+    hipLaunchKernelGGL((w3_gemv_kernel<PP, XX>), g, b, lds, stream, L.wt, L.sz, x, y, res, groups, tiles, nT_max, shape)
 #define DMR_GEMV3_CASE(PP)                                                                              \
     case PP:                                                                                           \
         if (xl_need <= 1) DMR_GEMV3_LAUNCH(PP, 1);                                                      \

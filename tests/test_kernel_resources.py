@@ -47,3 +47,21 @@ def test_no_kernel_uses_scratch_memory(listings):
 def test_no_inline_assembly_in_kernels(listings):
     for src, text in listings.items():
         assert "#ASMSTART" not in text, os.path.basename(src)
+
+
+def argument_bytes(text, kernel):
+    """name -> end of the last byte that each instance of `kernel` loads from its arguments."""
+    ends = {}
+    for m in re.finditer(r"^(\S*%s\S*):\s*;" % kernel, text, re.M):
+        body = text[m.end():text.index("s_endpgm", m.end())]
+        words = {"": 1, "x2": 2, "x3": 3, "x4": 4, "x8": 8, "x16": 16}
+        ends[m.group(1)] = max(int(off, 16) + 4 * words[n] for n, off in
+                               re.findall(r"s_load_dword(x\d+)?\s+\S+, s\[0:1\], (0x[0-9a-f]+)", body))
+    return ends
+
+
+def test_one_row_kernel_reads_one_line_of_arguments(listings):
+    # launches of a few microseconds: a second 64-byte line of arguments, fetched from memory, costs 0.2 .. 0.35 us of each
+    text = next(t for src, t in listings.items() if os.path.basename(src) == "w3_gemv.hip")
+    ends = argument_bytes(text, "w3_gemv_kernel")
+    assert ends and all(v <= 64 for v in ends.values()), ends
