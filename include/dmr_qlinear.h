@@ -165,12 +165,13 @@ dmr_status_t dmr_glue_swiglu(const uint16_t *d_in, int64_t M, int64_t I, uint16_
  *             DMR_PRO_SWIGLU:  the layer runs on swiglu(d_in), d_in = [M][2 K]
  *             DMR_PRO_NONE:    d_in = [M][K] as in the plain forward
  *   epilogue  d_residual (bf16 [M][N]) or NULL: y = acc + residual in fp32, rounded once to `out`.
- * M = 1 (both copies) fuses the prologue into the staging of the activation row and the residual
- * into the output store of the weight-streaming kernel; 2 <= M <= 16 fuses the residual only, where
- * the streaming kernel of that size class serves the shape (a prologue would be recomputed by every
- * workgroup, so it runs as a kernel of its own into d_ws); anything else runs the glue
- * kernels into d_ws and then the plain forward.  d_ws as the matching *_fused_workspace_bytes query says (never 0 with a
- * prologue or a residual).
+ * M = 1 (4 bits and bf16) fuses the prologue into the staging of the activation row; otherwise (every
+ * workgroup would recompute it) it runs as a kernel of its own into d_ws.  The residual is added, for
+ * any M, where the kernel that serves the shape, or the pass that adds the partial sums of a split K,
+ * stores its result; the few classes that cannot (and, at M > 1, an output that overlaps the activations
+ * the forward still reads, or the residual in part) leave an fp32 result in d_ws to which a further
+ * kernel adds the residual: the same sums.  A bf16 d_y may be d_residual itself.  d_ws as the matching
+ * *_fused_workspace_bytes query says (never 0 with a prologue or a residual).
  */
 typedef enum {
     DMR_PRO_NONE = 0,

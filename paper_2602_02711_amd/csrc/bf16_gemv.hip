@@ -34,10 +34,10 @@ constexpr int kWaves = 4;   // wavefronts per workgroup
 template <int XC, int PRO>
 __global__ __launch_bounds__(kWaves * 64) void bf16_gemv_kernel(const uint16_t *__restrict__ w,
                                                                 const uint16_t *__restrict__ x,
-                                                                void *__restrict__ y, int64_t K, int64_t N,
+                                                                void *y, int64_t K, int64_t N,
                                                                 int S, int rpw, int out_f32,
                                                                 const uint16_t *__restrict__ aux, float eps,
-                                                                const uint16_t *__restrict__ res) {
+                                                                const uint16_t *res) {
     extern __shared__ float red[];   // [kWaves][rpw]
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);

@@ -23,10 +23,10 @@ constexpr int ROW_BYTES = 272;   // one activation row of a k step in LDS: 128 b
 template <int MTW, int WM, int NW, int R>
 __global__ __launch_bounds__(64 * WM * NW, 2) void bf16_mid_kernel(const uint16_t *__restrict__ w,
                                                                    const uint16_t *__restrict__ x,
-                                                                   void *__restrict__ y, int M, int64_t K,
+                                                                   void *y, int M, int64_t K,
                                                                    int64_t N, int groups, int tiles, int gps,
                                                                    int out_mode,
-                                                                   const uint16_t *__restrict__ res) {
+                                                                   const uint16_t *res) {
     constexpr int THREADS = 64 * WM * NW;
     constexpr int BM = 16 * MTW * WM;
     constexpr int ROWS_PER_PASS = THREADS / 16;

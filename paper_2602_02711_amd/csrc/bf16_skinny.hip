@@ -41,8 +41,8 @@ __device__ __forceinline__ void load_step(StepRegs<MT> &r, const uint16_t *__res
 
 template <int MT, bool OUT_F32>
 __global__ __launch_bounds__(bf16_max_waves<MT>() * 64) void bf16_skinny_kernel(
-    const uint16_t *__restrict__ w, const uint16_t *__restrict__ x, void *__restrict__ y, int64_t M,
-    int64_t K, int64_t N, const uint16_t *__restrict__ res) {
+    const uint16_t *__restrict__ w, const uint16_t *__restrict__ x, void *y, int64_t M,
+    int64_t K, int64_t N, const uint16_t *res) {
     extern __shared__ float red[];   // [S][MT * 4][64]
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;

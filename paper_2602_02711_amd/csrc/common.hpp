@@ -55,9 +55,21 @@ __device__ __forceinline__ uint16_t f32_to_bf16(float f) {
     return (uint16_t)(pack_bf16x2(f, 0.0f) & 0xFFFFu);
 }
 
+// Output pointer of a forward kernel.  A residual may be the output's own buffer, so a kernel that reads one promises nothing
+// about y; without one y is the only way to its elements.  (The promise is worth 0.5 .. 1 % of a long prefill: the compiler then
+// loads the pointer at the start and not behind the main loop.)
+template <bool RES>
+struct OutPtr {
+    typedef void *__restrict__ type;
+};
+template <>
+struct OutPtr<true> {
+    typedef void *type;
+};
+
 // v plus element o of an optional bf16 residual (res == nullptr: v itself), the sum formed in fp32 before the output is
 // rounded, as the stand-alone residual kernel forms it.
-__device__ __forceinline__ float plus_residual(float v, const uint16_t *__restrict__ res, int64_t o) {
+__device__ __forceinline__ float plus_residual(float v, const uint16_t *res, int64_t o) {
     return res ? v + bf16_bits_to_f32(res[o]) : v;
 }
 
@@ -146,8 +158,10 @@ inline size_t sz_region_bytes(int64_t K, int64_t N) { return (size_t)N * (size_t
 inline size_t sz_region_bytes_per_channel(int64_t N) { return (size_t)N * 4; }
 
 // Kernel launchers (each returns hipGetLastError() after its launch).  `res`, where a forward has it: a bf16 residual
-// [M][N] that the store of the result adds in fp32 before rounding, or nullptr.  An element of it is read by the thread that
-// stores the same element of y, before it stores it, so y may be the residual's own buffer.
+// [M][N] that the store of the result adds in fp32 before rounding, or nullptr.  The value added to an element is read by the
+// thread that stores the same element of y, before it stores it, so y may be the residual's own buffer (and neither pointer is
+// __restrict__ in these kernels).  Epilogues that load a tile's residual at once clamp the addresses of rows and columns outside
+// the result to its last ones; what such a load returns, maybe while another thread stores there, goes nowhere.
 hipError_t launch_retile(int64_t K, int64_t N, const uint32_t *qweight, const uint16_t *scales,
                          const uint16_t *zeros, uint4 *wt, uint32_t *sz, bool per_channel,
                          hipStream_t stream);

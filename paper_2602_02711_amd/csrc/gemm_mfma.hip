@@ -125,9 +125,9 @@ template <int SRC, bool OUT_F32, bool RES>
 __global__ __launch_bounds__(256, 2) void gemm_kernel(const void *__restrict__ wsrc,
                                                    const uint32_t *__restrict__ sz,
                                                    const uint16_t *__restrict__ x,
-                                                   void *__restrict__ y, int64_t M, int64_t K,
+                                                   typename OutPtr<RES>::type y, int64_t M, int64_t K,
                                                    int64_t N, int szs, const uint32_t *__restrict__ only,
-                                                   int only_pairs, const uint16_t *__restrict__ res) {
+                                                   int only_pairs, const uint16_t *res) {
     // `only` (optional): one word per 32 columns; the block is computed here only when one of the words of its 128
     // columns is nonzero (with only_pairs: of the 256 columns of its aligned pair of blocks)
     if (only) {

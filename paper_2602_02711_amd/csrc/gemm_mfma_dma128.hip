@@ -90,8 +90,8 @@ __device__ __forceinline__ void mfma_16(const Frag (&a)[T], const Frag (&b)[T], 
 
 template <bool OUT_F32, bool RES, int T>
 __global__ __launch_bounds__(256) void gemm_dma_kernel(const uint16_t *__restrict__ w, const uint16_t *__restrict__ x,
-                                                       void *__restrict__ y, int64_t M, int64_t K, int64_t N, int nbn,
-                                                       const uint16_t *__restrict__ res) {
+                                                       typename OutPtr<RES>::type y, int64_t M, int64_t K, int64_t N, int nbn,
+                                                       const uint16_t *res) {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];   // NS stages of {A, B}
     const int tid = threadIdx.x;
     const int lane = tid & 63;

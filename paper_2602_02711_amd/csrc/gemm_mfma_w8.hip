@@ -87,8 +87,8 @@ __device__ __forceinline__ void mfma_all(const Frag (&a)[TM], const Frag (&b)[TN
 // step (both sub-steps, 48 registers) live in registers from its fetch phase to its multiply phase.
 template <int TM, bool OUT_F32, bool RES>
 __global__ __launch_bounds__(512) void gemm_w8_kernel(const uint16_t *__restrict__ w, const uint16_t *__restrict__ x,
-                                                         void *__restrict__ y, int64_t M, int64_t K, int64_t N, int nbm, int nbn, int lg_xm,
-                                                         const uint16_t *__restrict__ res) {
+                                                         typename OutPtr<RES>::type y, int64_t M, int64_t K, int64_t N, int nbm, int nbn, int lg_xm,
+                                                         const uint16_t *res) {
     using G = Geo<TM>;
     constexpr int BM = G::BM, A_BYTES = G::A_BYTES, STAGE_BYTES = G::STAGE_BYTES;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];

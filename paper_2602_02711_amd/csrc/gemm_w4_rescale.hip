@@ -223,8 +223,8 @@ __device__ __forceinline__ void read_wave_factors(const uint8_t *__restrict__ p,
 template <int WM, int WN, int TM, int TN, int BITS, bool OUT_F32, bool PC, bool RES>
 __global__ __launch_bounds__(64 * WM * WN, TM * TN <= 2 ? 2 : 1) void gemm_w4_rescale_kernel(
     const void *__restrict__ wt, const float *__restrict__ rfac, const uint16_t *__restrict__ x, const uint16_t *__restrict__ a2,
-    const uint16_t *__restrict__ b2, const uint32_t *__restrict__ flags, void *__restrict__ y, int64_t M, int64_t K, int64_t N,
-    int KP, int nbn, int lg_xm, const uint16_t *__restrict__ res) {
+    const uint16_t *__restrict__ b2, const uint32_t *__restrict__ flags, typename OutPtr<RES>::type y, int64_t M, int64_t K, int64_t N,
+    int KP, int nbn, int lg_xm, const uint16_t *res) {
     using G = Geo<WM, WN, TM, TN, BITS>;
     constexpr int BM = G::BM, BN = G::BN, STAGE_BYTES = G::STAGE_BYTES, A_BYTES = G::A_BYTES, A2S_BYTES = G::A2S_BYTES;
     constexpr int LA = G::LA, LB = G::LB, L2 = G::L2;

@@ -56,8 +56,8 @@ __global__ __launch_bounds__(256) void swiglu_kernel(const uint16_t *__restrict_
 }
 
 __global__ __launch_bounds__(256) void add_residual_kernel(const float *__restrict__ acc,
-                                                           const uint16_t *__restrict__ res, int64_t count,
-                                                           void *__restrict__ out, int out_f32) {
+                                                           const uint16_t *res, int64_t count,
+                                                           void *out, int out_f32) {
     const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
     if (i >= count) return;
     const f32x4 a = *reinterpret_cast<const f32x4 *>(acc + i);

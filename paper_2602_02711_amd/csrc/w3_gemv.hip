@@ -33,7 +33,7 @@ template <int P, int XL>
 __global__ __launch_bounds__(1024) void w3_gemv_kernel(const uint32_t *__restrict__ wt,
                                                        const uint32_t *__restrict__ sz,
                                                        const uint16_t *__restrict__ x,
-                                                       void *__restrict__ y, const uint16_t *__restrict__ res,
+                                                       void *y, const uint16_t *res,
                                                        int groups, int tiles, int nT_max, int shape) {
     const int lgS = shape & 0xFF, lgTW = (shape >> 8) & 0xFF, out_f32 = shape >> 16;
     const int threads = 64 << (lgS + lgTW);

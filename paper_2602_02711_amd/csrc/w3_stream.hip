@@ -44,10 +44,10 @@ template <int P>
 __global__ __launch_bounds__(1024) void w3_stream_kernel(const uint32_t *__restrict__ wt,
                                                          const uint32_t *__restrict__ sz,
                                                          const uint16_t *__restrict__ x,
-                                                         void *__restrict__ y, int M, int64_t N,
+                                                         void *y, int M, int64_t N,
                                                          int groups, int tiles, int lgS, int lgTW,
                                                          int nT_max, int gw_max, int out_f32, uint32_t x16_magic,
-                                                         const uint16_t *__restrict__ res) {
+                                                         const uint16_t *res) {
     extern __shared__ uint4 smem[];   // x rows [M][groups * 16 + 1] uint4, then red[TW][S][64] float4
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);

@@ -34,10 +34,10 @@ template <int P, int XL, int PRO>
 __global__ __launch_bounds__(1024) void w4_gemv_kernel(const uint4 *__restrict__ wt,
                                                        const uint32_t *__restrict__ sz,
                                                        const uint16_t *__restrict__ x,
-                                                       void *__restrict__ y, int groups, int tiles,
+                                                       void *y, int groups, int tiles,
                                                        int lgS, int lgTW, int nT_max, int out_f32,
                                                        const uint16_t *__restrict__ aux, float eps,
-                                                       const uint16_t *__restrict__ res, int szs) {
+                                                       const uint16_t *res, int szs) {
     extern __shared__ uint4 smem[];          // x (16 uint4 per group), X[groups], red[nT_max][TW][S][16], 16 floats
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform (SGPR)

@@ -34,8 +34,8 @@ constexpr int ROW_BYTES = 272;   // one activation row of a group in LDS: 128 bf
 template <int MTW, int WM, int NW, int R, int BITS>
 __global__ __launch_bounds__(64 * WM * NW, (WM * NW == 4) ? 2 : 1) void w4_mid_kernel(
     const void *__restrict__ wt, const uint32_t *__restrict__ sz, const uint16_t *__restrict__ x,
-    void *__restrict__ y, int M, int64_t K, int64_t N, int groups, int tiles, int gps, int out_mode, int szs,
-    const uint16_t *__restrict__ res) {
+    void *y, int M, int64_t K, int64_t N, int groups, int tiles, int gps, int out_mode, int szs,
+    const uint16_t *res) {
     constexpr int THREADS = 64 * WM * NW;
     constexpr int BM = 16 * MTW * WM;
     constexpr int ROWS_PER_PASS = THREADS / 16;
@@ -222,9 +222,9 @@ __global__ __launch_bounds__(64 * WM * NW, (WM * NW == 4) ? 2 : 1) void w4_mid_k
 
 // y = sum over splits of part[split], four outputs per thread, splits in ascending order; an optional residual is added
 // to the fp32 sum (a launch of its own for it cost 2-4 us and two more passes over M x N fp32).
-__global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *__restrict__ part, void *__restrict__ y,
+__global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *__restrict__ part, void *y,
                                                             int64_t total, int splits, int out_f32,
-                                                            const uint16_t *__restrict__ res) {
+                                                            const uint16_t *res) {
     const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 4;
     if (i >= total) return;
     f32x4 v = *reinterpret_cast<const f32x4 *>(part + i);

@@ -59,10 +59,10 @@ template <int MT, int R, int WAVES, int BITS>
 __global__ __launch_bounds__(64 * WAVES) void w4_panel_kernel(const void *__restrict__ wt,
                                                               const uint32_t *__restrict__ sz,
                                                               const uint16_t *__restrict__ x,
-                                                              void *__restrict__ y, int M, int64_t K, int64_t N,
+                                                              void *y, int M, int64_t K, int64_t N,
                                                               int groups, int tiles, int gq, int lgS,
                                                               int out_mode, uint32_t x16_magic, int szs,
-                                                              const uint16_t *__restrict__ res) {
+                                                              const uint16_t *res) {
     extern __shared__ uint4 smem[];   // panel [M][gq * 16 + 1] uint4, then xs [gq][MT][4] f32x4
     constexpr int P = 4;
     const int lane = threadIdx.x & 63;

@@ -52,10 +52,10 @@ template <int P, bool XS>
 __global__ __launch_bounds__(1024) void w4_stream_kernel(const uint4 *__restrict__ wt,
                                                          const uint32_t *__restrict__ sz,
                                                          const uint16_t *__restrict__ x,
-                                                         void *__restrict__ y, int M, int64_t N,
+                                                         void *y, int M, int64_t N,
                                                          int groups, int tiles, int lgS, int lgTW,
                                                          int nT_max, int gw_max, int out_f32,
-                                                         const uint16_t *__restrict__ res, uint32_t x16_magic, int szs) {
+                                                         const uint16_t *res, uint32_t x16_magic, int szs) {
     extern __shared__ uint4 smem[];   // x rows [M][groups * 16 + 1] uint4, xs[groups][4] float4, red[TW][S][64] float4
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);

@@ -37,9 +37,9 @@ constexpr int ilog2(int v) { return v <= 1 ? 0 : 1 + ilog2(v / 2); }
 // out_mode: 0 = fp32 y, 1 = bf16 y, 2 = fp32 partial [split][M][N] (no residual)
 template <int MT, int R, int S, int CG, int BITS>
 __global__ __launch_bounds__(512) void w4_wide_kernel(const void *__restrict__ wt, const uint32_t *__restrict__ sz,
-                                                      const uint16_t *__restrict__ x, void *__restrict__ y, int M,
+                                                      const uint16_t *__restrict__ x, void *y, int M,
                                                       int64_t K, int64_t N, int groups, int tiles, int cps, int out_mode, int szs,
-                                                      const uint16_t *__restrict__ res) {
+                                                      const uint16_t *res) {
     constexpr int WAVES = 8, THREADS = 512, TW = WAVES / S, GWc = CG / S, P = 2 * GWc;
     constexpr int ROW = CG * 16 + 1;                  // uint4 per panel row
     constexpr int ROWS = MT * 16;

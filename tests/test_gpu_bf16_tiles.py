@@ -30,3 +30,7 @@ def test_exact_integers(K, N, M, path):
     rd = res.to(torch.bfloat16).to(DEV)
     got = dmr.dmr_qlinear_bf16_forward_fused(wd, dmr.DMR_PRO_NONE, xd, residual=rd, out_dtype=torch.float32)
     assert torch.equal(got.cpu(), want + res)
+    y = dmr.dmr_qlinear_bf16_forward_fused(wd, dmr.DMR_PRO_NONE, xd, residual=rd)
+    assert torch.equal(y.cpu(), (want + res).to(torch.bfloat16))
+    dmr.dmr_qlinear_bf16_forward_fused(wd, dmr.DMR_PRO_NONE, xd, residual=rd, out=rd)     # over the residual
+    assert torch.equal(rd, y)

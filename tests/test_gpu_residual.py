@@ -75,7 +75,11 @@ def test_residual_on_flagged_columns(M):
     plain, fused = forwards("w4flag", weights(N, K, 81))
     x, res = acts((M, K), 82), acts((M, N), 83)
     want = plain(x, out_dtype=torch.float32) + res.float()
-    assert torch.equal(fused(dmr.DMR_PRO_NONE, x, residual=res), want.to(torch.bfloat16))
+    y = fused(dmr.DMR_PRO_NONE, x, residual=res)
+    assert torch.equal(y, want.to(torch.bfloat16))
+    over = res.clone()                                   # a tile stored twice would add the residual twice
+    fused(dmr.DMR_PRO_NONE, x, residual=over, out=over)
+    assert torch.equal(over, y)
 
 
 @pytest.mark.parametrize("fmt", ["w4", "w3", "bf16"])
