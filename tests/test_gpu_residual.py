@@ -44,8 +44,8 @@ def forwards(fmt, w):
 
 
 # M x (K, N): every size class of each format, with M, N off the tile sizes
-SHAPES = [(1, 384, 272), (2, 384, 272), (7, 2048, 400), (12, 512, 16400), (9, 14336, 272), (31, 1024, 272),
-          (33, 512, 16400), (40, 640, 16400), (70, 1024, 528), (129, 1024, 17936), (130, 1152, 144), (300, 512, 6160),
+SHAPES = [(1, 128, 272), (1, 384, 272), (1, 14336, 400), (1, 32768, 528), (2, 384, 272), (7, 2048, 400), (12, 512, 16400),
+          (9, 14336, 272), (31, 1024, 272), (33, 512, 16400), (40, 640, 16400), (70, 1024, 528), (129, 1024, 17936), (130, 1152, 144), (300, 512, 6160),
           (900, 512, 2576), (1100, 1024, 8208), (2000, 1280, 13328)]
 
 
@@ -55,12 +55,6 @@ def test_residual_is_added_to_the_fp32_result(fmt, M, K, N):
     plain, fused = forwards(fmt, weights(N, K, 71 + K + N))
     x, res = acts((M, K), 72 + M), acts((M, N), 73 + M)
     want = plain(x, out_dtype=torch.float32) + res.float()
-    if M == 1:
-        # the fused decode kernels add the slices of a row in an order of their own: fp32 sums of K <= 14336 products,
-        # 1e-5 rms apart at most (the bound of the fp32 outputs' parity tests), then one rounding to bf16
-        got = fused(dmr.DMR_PRO_NONE, x, residual=res, out_dtype=torch.float32)
-        assert float((got - want).abs().max()) <= 2e-5 * float(want.square().mean().sqrt())
-        return
     assert torch.equal(fused(dmr.DMR_PRO_NONE, x, residual=res, out_dtype=torch.float32), want)
     y = fused(dmr.DMR_PRO_NONE, x, residual=res)
     assert torch.equal(y, want.to(torch.bfloat16))
