@@ -30,14 +30,14 @@ __device__ __forceinline__ float wave_sum(float v) { return wave64_sum(v); }
 constexpr int kWaves = 4;   // wavefronts per workgroup
 
 // PRO: glue fused into the load of the activation slice (glue.hpp).  RMSNorm needs the whole row in
-// one wave (S == 1); `res`, if not null, is a bf16 residual added to the result.
-template <int XC, int PRO>
+// one wave (S == 1); `res`, if not null, is a bf16 residual added to the result (IN_PLACE: it is y).
+template <int XC, int PRO, bool IN_PLACE>
 __global__ __launch_bounds__(kWaves * 64) void bf16_gemv_kernel(const uint16_t *__restrict__ w,
                                                                 const uint16_t *__restrict__ x,
-                                                                void *y, int64_t K, int64_t N,
+                                                                typename OutPtr<IN_PLACE>::type y, int64_t K, int64_t N,
                                                                 int S, int rpw, int out_f32,
                                                                 const uint16_t *__restrict__ aux, float eps,
-                                                                const uint16_t *res) {
+                                                                typename OutPtr<IN_PLACE>::residual res) {
     extern __shared__ float red[];   // [kWaves][rpw]
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -156,9 +156,12 @@ hipError_t launch_bf16_gemv_fused(const uint16_t *w, const uint16_t *x, int64_t 
     const int of = out_f32 ? 1 : 0;
     const int irpw = (int)rpw;
     if (f.pro == kProRmsNorm && S != 1) return hipErrorInvalidValue;   // the row must sit in one wave
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(kWaves * 64), lds, stream, w, x, y, K, N, S, irpw, of, f.aux, f.eps, f.res);
+    };
+    const bool in_place = f.res && f.res == y;
 #define DMR_BF16_GEMV_LAUNCH(X, PRO)                                                                   \
-    hipLaunchKernelGGL((bf16_gemv_kernel<X, PRO>), dim3(grid), dim3(kWaves * 64), lds, stream, w, x, y, K, N, \
-                       S, irpw, of, f.aux, f.eps, f.res)
+    in_place ? go(&bf16_gemv_kernel<X, PRO, true>) : go(&bf16_gemv_kernel<X, PRO, false>)
 #define DMR_BF16_GEMV_CASE(X)                                                                          \
     case X:                                                                                            \
         if (f.pro == kProRmsNorm) DMR_BF16_GEMV_LAUNCH(X, kProRmsNorm);                                 \

@@ -55,17 +55,28 @@ __device__ __forceinline__ uint16_t f32_to_bf16(float f) {
     return (uint16_t)(pack_bf16x2(f, 0.0f) & 0xFFFFu);
 }
 
-// Output pointer of a forward kernel.  A residual may be the output's own buffer, so a kernel that reads one promises nothing
-// about y; without one y is the only way to its elements.  (The promise is worth 0.5 .. 1 % of a long prefill: the compiler then
-// loads the pointer at the start and not behind the main loop.)
-template <bool RES>
+// Output (and residual) pointer of a forward kernel.  A residual may be the output's own buffer; a kernel that can meet that
+// (SHARED) promises nothing about the two, the others are the only ones at y's elements.  (The promise is worth 0.5 .. 1 % of a
+// long prefill and 0.2 .. 0.4 us of a bf16 decode row, 4096 -> 6144 14.3 against 14.8 us: without it the compiler fetches the
+// pointer where it is first used and not at the start.)
+template <bool SHARED>
 struct OutPtr {
     typedef void *__restrict__ type;
+    typedef const uint16_t *__restrict__ residual;
 };
 template <>
 struct OutPtr<true> {
     typedef void *type;
+    typedef const uint16_t *residual;
 };
+
+// The rollout-batch kernels, which test for a residual at run time, have the promise too: a bit of their output argument says
+// that the residual is y's own buffer, which is then read through y.
+constexpr int kResidualInPlace = 4;
+__device__ __forceinline__ const uint16_t *residual_source(const void *y, const uint16_t *res, int out) {
+    return out & kResidualInPlace ? static_cast<const uint16_t *>(y) : res;
+}
+inline int residual_in_place(const void *y, const uint16_t *res) { return res && res == y ? kResidualInPlace : 0; }
 
 // v plus element o of an optional bf16 residual (res == nullptr: v itself), the sum formed in fp32 before the output is
 // rounded, as the stand-alone residual kernel forms it.
@@ -159,8 +170,8 @@ inline size_t sz_region_bytes_per_channel(int64_t N) { return (size_t)N * 4; }
 
 // Kernel launchers (each returns hipGetLastError() after its launch).  `res`, where a forward has it: a bf16 residual
 // [M][N] that the store of the result adds in fp32 before rounding, or nullptr.  The value added to an element is read by the
-// thread that stores the same element of y, before it stores it, so y may be the residual's own buffer (and neither pointer is
-// __restrict__ in these kernels).  Epilogues that load a tile's residual at once clamp the addresses of rows and columns outside
+// thread that stores the same element of y, before it stores it, so y may be the residual's own buffer (see
+// OutPtr and residual_source for what that asks of the kernels).  Epilogues that load a tile's residual at once clamp the addresses of rows and columns outside
 // the result to its last ones; what such a load returns, maybe while another thread stores there, goes nowhere.
 hipError_t launch_retile(int64_t K, int64_t N, const uint32_t *qweight, const uint16_t *scales,
                          const uint16_t *zeros, uint4 *wt, uint32_t *sz, bool per_channel,

@@ -30,12 +30,12 @@ namespace {
 constexpr int ROW_BYTES = 272;   // one activation row of a group in LDS: 128 bf16 + 16 bytes of padding
 
 
-// out_mode: 0 = fp32 y, 1 = bf16 y, 2 = fp32 partial [split][M][N]
+// out: 0 = fp32 y, 1 = bf16 y, 2 = fp32 partial [split][M][N]; kResidualInPlace
 template <int MTW, int WM, int NW, int R, int BITS>
 __global__ __launch_bounds__(64 * WM * NW, (WM * NW == 4) ? 2 : 1) void w4_mid_kernel(
     const void *__restrict__ wt, const uint32_t *__restrict__ sz, const uint16_t *__restrict__ x,
-    void *y, int M, int64_t K, int64_t N, int groups, int tiles, int gps, int out_mode, int szs,
-    const uint16_t *res) {
+    void *__restrict__ y, int M, int64_t K, int64_t N, int groups, int tiles, int gps, int out, int szs,
+    const uint16_t *__restrict__ res) {
     constexpr int THREADS = 64 * WM * NW;
     constexpr int BM = 16 * MTW * WM;
     constexpr int ROWS_PER_PASS = THREADS / 16;
@@ -189,7 +189,9 @@ __global__ __launch_bounds__(64 * WM * NW, (WM * NW == 4) ? 2 : 1) void w4_mid_k
         }
     }
 
-    if (res && out_mode != 2) {      // clamped, unconditional loads: all of them in flight at once
+    const int out_mode = out & 3;
+    const uint16_t *from = residual_source(y, res, out);
+    if (from && out_mode != 2) {      // clamped, unconditional loads: all of them in flight at once
 #pragma unroll
         for (int rt = 0; rt < R; ++rt)
 #pragma unroll
@@ -197,7 +199,7 @@ __global__ __launch_bounds__(64 * WM * NW, (WM * NW == 4) ? 2 : 1) void w4_mid_k
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const int m = min(m0 + (wm * MTW + mt) * 16 + c * 4 + q, M - 1);
-                    acc[rt][mt][q] += bf16_bits_to_f32(res[(int64_t)m * N + (int64_t)min(tile0 + rt, tiles - 1) * kTileRows + j]);
+                    acc[rt][mt][q] += bf16_bits_to_f32(from[(int64_t)m * N + (int64_t)min(tile0 + rt, tiles - 1) * kTileRows + j]);
                 }
     }
     const int64_t part = out_mode == 2 ? (int64_t)blockIdx.z * M * N : 0;
@@ -283,7 +285,7 @@ hipError_t launch_mid(const void *wt, const uint32_t *sz, int szs, int64_t K, in
     const bool split = p.SK > 1;
     if (split && !ws) return hipErrorInvalidValue;
     void *dst = split ? ws : y;
-    const int out_mode = split ? 2 : (out_f32 ? 0 : 1);
+    const int out_mode = split ? 2 : (out_f32 ? 0 : 1) | residual_in_place(y, res);
     const int iM = (int)M;
     hipError_t e;
     if (p.WM == 1) {
