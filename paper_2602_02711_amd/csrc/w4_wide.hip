@@ -8,8 +8,9 @@
 // sums of x that the zero-point term needs are formed once per workgroup and chunk (MFMAs against
 // all-ones, table [group][row tile][row quad] of fp32x4 behind a second barrier), so the main loop
 // spends its MFMAs on weights only.  The weights never touch LDS: wave (s, tw) streams the R blocks
-// of groups s * CG / S .. of every chunk straight into registers, two chunks ahead (one chunk ahead measured 4 %
-// slower at 20 and 33 rows, level at 64).  An activation fragment read from LDS feeds R weight
+// of groups s * CG / S .. of every chunk straight into registers, one chunk ahead (the requests cross chunk
+// boundaries freely; two chunks ahead, whose requests past the end of a split repeat its last block twice as often, measured
+// 0 .. 8 % slower: us, two / one, 64 rows 4096 -> 28672 33.9 / 33.3, 14336 -> 4096 26.4 / 25.9, 3 bits 34.8 / 33.0, 27.1 / 25.9).  An activation fragment read from LDS feeds R weight
 // tiles.  The S partial tiles of a workgroup meet in LDS at the end (the panels' memory) and are added
 // in ascending order.  Layers too narrow to give every CU a workgroup split K over blockIdx.y (fp32 partials
 // added by the shared reduction kernel).  What bounds it (64 rows, gate+up, 32 us): no single pipe; LDS reads 60 %, VALU
@@ -40,7 +41,7 @@ __global__ __launch_bounds__(512) void w4_wide_kernel(const void *__restrict__ w
                                                       const uint16_t *__restrict__ x, void *y, int M,
                                                       int64_t K, int64_t N, int groups, int tiles, int cps, int out_mode, int szs,
                                                       const uint16_t *res) {
-    constexpr int WAVES = 8, THREADS = 512, TW = WAVES / S, GWc = CG / S, P = 2 * GWc;
+    constexpr int WAVES = 8, THREADS = 512, TW = WAVES / S, GWc = CG / S, P = GWc;
     constexpr int ROW = CG * 16 + 1;                  // uint4 per panel row
     constexpr int ROWS = MT * 16;
     constexpr int PANEL = ROWS * ROW;                 // uint4 per buffer
@@ -166,15 +167,14 @@ __global__ __launch_bounds__(512) void w4_wide_kernel(const void *__restrict__ w
         }
     };
 
-    // One chunk: request the next panel, work through this wave's GWc items (the ring holds exactly one
-    // chunk's items, so each slot is refilled with the same item of the next chunk), publish the next
-    // panel and its sums.
+    // One chunk: request the next panel, work through this wave's GWc items (the ring holds exactly one chunk's items, so each
+    // slot is refilled with the same item of the next chunk), publish the next panel and its sums.
     auto chunk_step = [&](int ch, int buf, bool more) {      // buf = ch & 1, a constant where this is expanded
         fetch_x(min(ch + 1, nch - 1));                 // unconditional (the last chunk re-reads itself)
 #pragma unroll
         for (int i = 0; i < GWc; ++i) {
-            const WideItem<R> cur = ring[buf * GWc + i];
-            issue(ring[buf * GWc + i], (ch + 2) * GWc + i);
+            const WideItem<R> cur = ring[i];
+            issue(ring[i], (ch + 1) * GWc + i);
             consume(cur, buf, s * GWc + i);
         }
         if (more) {                                    // uniform over the workgroup
