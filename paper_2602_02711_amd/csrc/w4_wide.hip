@@ -198,18 +198,25 @@ __global__ __launch_bounds__(512) void w4_wide_kernel(const void *__restrict__ w
     }
 
     const int64_t part = out_mode == 2 ? (int64_t)blockIdx.y * M * N : 0;
-    auto store_tile = [&](int tile, int mt, const f32x4 &v) {
+    auto store_tile = [&](int tile, int mt, f32x4 v) {
         if (tile >= tiles) return;
+        if (res) {      // clamped, unconditional loads: the four in flight at once
+            float rv[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                rv[q] = bf16_bits_to_f32(res[(int64_t)min(mt * 16 + c * 4 + q, M - 1) * N + (int64_t)tile * kTileRows + j]);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) v[q] += rv[q];
+        }
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int row = mt * 16 + c * 4 + q;
             if (row < M) {
                 const int64_t o = (int64_t)row * N + (int64_t)tile * kTileRows + j;
-                const float r = plus_residual(v[q], res, o);
                 if (out_mode != 1)
-                    reinterpret_cast<float *>(y)[part + o] = r;
+                    reinterpret_cast<float *>(y)[part + o] = v[q];
                 else
-                    reinterpret_cast<uint16_t *>(y)[o] = f32_to_bf16(r);
+                    reinterpret_cast<uint16_t *>(y)[o] = f32_to_bf16(v[q]);
             }
         }
     };
