@@ -123,8 +123,8 @@ dmr_status_t hip_status(hipError_t e) { return e == hipSuccess ? DMR_OK : DMR_ER
 namespace {
 
 // Whether the kernel that serves M rows of this layer also runs without the partials that the size query asks for: the
-// chunked-panel kernel does on layers that give half of the CUs a workgroup without a split of K (4096 -> 16384, 64 rows: 29.7 us
-// instead of 25.4).
+// chunked-panel kernel does on layers that give half of the CUs a workgroup without a split of K (4096 -> 16384, 64 rows: 29.0 us
+// instead of 24.5).
 bool runs_unsplit(const dmr_qlinear_t *layer, int64_t M) {
     return dmr::w4_wide_applies(M, layer->K, layer->N) && dmr::plan_wide(M, layer->K, layer->N, false).ok;
 }

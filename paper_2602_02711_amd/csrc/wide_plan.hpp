@@ -22,15 +22,16 @@ inline size_t wide_lds_bytes(int MT, int R, int S, int CG) {
 }
 
 // 17 <= M <= 64.  Layers of 1024 row tiles or more (half of the CUs without a split) are this kernel's; K is split in two
-// there if that fills the CUs and leaves each half three chunks (us unsplit / split at 17 and 64 rows: 3072 -> 16384 16.2 / 13.8
-// and 24.2 / 22.3, 4096 -> 16384 20.1 / 16.9 and 29.7 / 25.4; but 2048 -> 16384 17.8 / 18.7, 1536 -> 16384 14.7 / 18.2 at 64).
+// there if that fills the CUs and leaves each half three chunks (us unsplit / split at 17 and 64 rows: 3072 -> 16384 16.4 / 13.9
+// and 23.4 / 21.1, 4096 -> 16384 20.1 / 16.6 and 29.0 / 24.5; but 2048 -> 16384 17.1 / 17.9, 1536 -> 16384 14.2 / 17.2 at 64).
 // Narrower layers split K until every CU has a workgroup, while a split keeps two chunks, and go here where that beats the
 // rollout-batch kernel.  16 K x 12 N x 17, 32, 48, 64 rows, both formats; us at 17 / 64 rows, that kernel then this one:
-//   its two weight tiles per wave, or more workgroups than CUs:  4096 -> 6144 11.4 / 18.2, 11.2 / 17.0;  14336 -> 4096 18.9 / 27.0,
-//     17.1 / 25.1;  8192 -> 8192 18.7 / 28.8, 18.0 / 25.9;  4608 -> 8192 14.9 / 22.5, 13.1 / 19.9
-//   all its workgroups at once, one tile and at most 12 groups each:  1536 -> 12288 8.3 / 11.9, 10.4 / 16.4;  6144 -> 4096 11.4 /
-//     16.4, 11.9 / 17.3;  12288 -> 2048 12.2 / 17.4, 13.2 / 18.9: left to it (14 groups, 3584 -> 5120: 11.7 / 17.6, 10.7 / 16.2)
-//   two splits of more than seven chunks:  14336 -> 12288 31.7 / 49.1, 35.5 / 54.0: left to it while its partials, twice or four
+//   its two weight tiles per wave, or more workgroups than CUs:  4096 -> 6144 11.4 / 18.3, 11.1 / 16.5;  14336 -> 4096 18.6 / 27.1,
+//     17.0 / 24.3;  8192 -> 8192 18.8 / 28.9, 17.5 / 25.3;  4608 -> 8192 14.9 / 22.8, 13.2 / 19.4
+//   all its workgroups at once with one tile each and whole steps of its four groups:  1536 -> 12288 8.2 / 11.9, 10.3 / 15.8;
+//     6144 -> 4096 11.4 / 16.5, 11.7 / 16.8;  12288 -> 2048 12.3 / 17.3, 13.0 / 18.2: left to it (9 groups, 4608 -> 4096: 11.3 /
+//     16.4, 11.0 / 15.8;  14 groups, 3584 -> 5120: 11.6 / 17.4, 10.6 / 15.7)
+//   two splits of more than seven chunks:  14336 -> 12288 31.5 / 48.6, 35.9 / 52.8: left to it while its partials, twice or four
 //     times as many, stay within the fixed scratch of dmr_qlinear_forward_static, which such a call otherwise would not fit
 // (Splits x column blocks <= 256: the partials of 64 rows take at most 8 MiB.)  `with_workspace` false: unsplit or not at all.
 inline WidePlan plan_wide(int64_t M, int64_t K, int64_t N, bool with_workspace = true) {
@@ -51,7 +52,7 @@ inline WidePlan plan_wide(int64_t M, int64_t K, int64_t N, bool with_workspace =
         p.ok = true;
     } else if (p.SK > 1 && p.cps >= 2) {
         const MidPlan m = plan_mid(M, K, N);
-        const bool one_round = m.R == 1 && m.wgs <= kCus && m.gps <= 12;
+        const bool one_round = m.R == 1 && m.wgs <= kCus && m.gps % 4 == 0;
         const bool long_halves = p.SK == 2 && p.cps > 7;
         p.ok = !one_round && (!long_halves || (size_t)m.SK * (size_t)(M * N) * sizeof(float) > DMR_STATIC_SCRATCH_BYTES);
     }

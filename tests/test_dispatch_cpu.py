@@ -56,7 +56,8 @@ def test_bf16_tile(lib, M, K, N, name):
 @pytest.mark.parametrize("K,N,rows,splits", [
     (1536, 12288, "mid", 1), (1536, 11008, "mid", 1),       # three chunks: one round of the rollout-batch kernel
     (3072, 8192, "mid", 2), (6144, 4096, "mid", 4), (12288, 2048, "mid", 8),
-    (3584, 5120, "wide", 4), (7168, 4096, "wide", 7),       # 14 groups to each of its workgroups
+    (3584, 5120, "wide", 4), (7168, 4096, "wide", 7),       # 14 groups to each of its workgroups, which take four at a time
+    (4608, 4096, "wide", 5), (5120, 4096, "wide", 5),       # 9 and 10
     (4096, 6144, "wide", 4), (14336, 4096, "wide", 7), (8192, 8192, "wide", 4), (4096, 11008, "wide", 2),
     (1536, 16384, "wide", 1), (2560, 16384, "wide", 1),     # 1024 row tiles: halves of fewer than three chunks
     (3072, 16384, "wide", 2), (4096, 16384, "wide", 2), (14336, 16384, "wide", 2), (4096, 28672, "wide", 1),
