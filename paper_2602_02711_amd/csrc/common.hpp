@@ -170,9 +170,10 @@ inline size_t sz_region_bytes_per_channel(int64_t N) { return (size_t)N * 4; }
 
 // Kernel launchers (each returns hipGetLastError() after its launch).  `res`, where a forward has it: a bf16 residual
 // [M][N] that the store of the result adds in fp32 before rounding, or nullptr.  The value added to an element is read by the
-// thread that stores the same element of y, before it stores it, so y may be the residual's own buffer (see
-// OutPtr and residual_source for what that asks of the kernels).  Epilogues that load a tile's residual at once clamp the addresses of rows and columns outside
-// the result to its last ones; what such a load returns, maybe while another thread stores there, goes nowhere.
+// thread that stores the same element of y, before it stores it, so y may be the residual's own buffer (see OutPtr and
+// residual_source for what that asks of the kernels).  Epilogues that load a tile's residual at once clamp the addresses of
+// rows and columns outside the result to its last ones; what such a load returns, maybe while another thread stores there, goes
+// nowhere.
 hipError_t launch_retile(int64_t K, int64_t N, const uint32_t *qweight, const uint16_t *scales,
                          const uint16_t *zeros, uint4 *wt, uint32_t *sz, bool per_channel,
                          hipStream_t stream);
@@ -247,8 +248,8 @@ hipError_t launch_w3_gemm_rescale(const LayerView3 &L, const uint16_t *x, int64_
                                   void *ws, hipStream_t stream);
 hipError_t launch_bf16_gemm(const uint16_t *w, const uint16_t *x, int64_t M, int64_t K, int64_t N,
                             void *y, bool out_f32, const uint16_t *res, hipStream_t stream);
-// 256 x 256 tiles on eight wavefronts (direct-to-LDS operand loads, four-stage pipeline, two waves per SIMD) for
-// problems large enough to fill the chip with them.
+// Tiles of 256, 192 or 128 rows by 256 columns on eight wavefronts (direct-to-LDS operand loads, four-stage pipeline, two
+// waves per SIMD) for problems large enough to fill the chip with them.
 int gemm_big_tile_rows(int64_t M, int64_t K, int64_t N);      // 256, 192, 128; 0: the 128 x 128 kernels
 hipError_t launch_bf16_gemm_w8(const uint16_t *w, const uint16_t *x, int64_t M, int64_t K, int64_t N, void *y, bool out_f32,
                                const uint16_t *res, hipStream_t stream);

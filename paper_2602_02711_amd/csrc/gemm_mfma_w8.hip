@@ -259,9 +259,10 @@ hipError_t launch_one(const uint16_t *w, const uint16_t *x, int64_t M, int64_t K
                                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)Geo<TM>::LDS_BYTES);
     if (attr_status != hipSuccess) return attr_status;
     // Workgroups go to the 8 XCDs round-robin by linear index and each XCD has its own L2.  When the
-    // grid of 256 x 256 tiles divides evenly, the index is decoded so that the 32 workgroups an XCD runs at
+    // grid of tiles divides evenly, the index is decoded so that the 32 workgroups an XCD runs at
     // a time form a compact 4 x 8 patch of tiles (12 operand panels instead of ~17) and the 8 patches of a
-    // round tile a compact region; otherwise plain order (a padded region would leave XCDs idle).
+    // round tile a compact region; otherwise each XCD walks a contiguous share of the tiles in bands of four
+    // tile rows (a padded region would leave XCDs idle).
     // Measured at (4096, 28672), M = 8192: L2 hit rate 53 % -> 79 %, time -7 %.  (Walking k in a different
     // order per tile was measured too and is slower: tiles in step share operand panels.)
     const int nbm = (int)((M + Geo<TM>::BM - 1) / Geo<TM>::BM), nbn = (int)((N + BN - 1) / BN);
