@@ -5,6 +5,7 @@
 #include "glue.hpp"
 #include "mid_plan.hpp"
 #include "panel_plan.hpp"
+#include "rows_plan.hpp"
 #include "wide_plan.hpp"
 
 struct dmr_qlinear {
@@ -23,8 +24,28 @@ constexpr int64_t kSkinnyMaxM = 64;
 
 // Which INT4 kernel serves M rows of a (K, N) layer (measured crossovers, 256 CUs).  The workspace
 // query and the forward call both go through this.
-enum class W4Path { Gemv, Stream, Panel, Wide, Skinny2, Mid, Gemm, GemmRescale };
+enum class W4Path { Gemv, Stream, Panel, Wide, Ragged, Mid, Gemm, GemmRescale };
 constexpr int kTiledMinBlocks = 140;
+int64_t blocks128(int64_t M, int64_t N) { return ((M + 127) / 128) * ((N + 127) / 128); }
+// Above 64 rows, both formats: whether the rows kernels serve the call, not the tiled MFMA GEMMs.  Those win from about 140 output
+// blocks of 128 x 128 on (measured: ahead at 144 and from there on, on 128-row tiles up to 256 blocks and on 256-row tiles
+// beyond; behind at 128), but not where one round of the tile kernel covers up to 512 rows (rows_fit_one_round).
+bool rows_beat_tiled(int64_t M, int64_t K, int64_t N) {
+    return M <= 128 || blocks128(M, N) < kTiledMinBlocks || dmr::rows_fit_one_round(M, K, N);
+}
+// Splits of K that the partials of a Mid call hold; one in the region that the tiled GEMMs had, whose calls need no workspace now.
+int mid_splits(int64_t M, int64_t K, int64_t N) {
+    return M <= 128 || blocks128(M, N) < kTiledMinBlocks ? dmr::plan_mid(M, K, N).SK : 1;
+}
+size_t mid_workspace_bytes(int64_t M, int64_t K, int64_t N) {
+    const int sk = mid_splits(M, K, N);
+    return sk > 1 ? (size_t)sk * (size_t)M * (size_t)N * sizeof(float) : 0;
+}
+// Layers of 1024 row tiles whose group count is not a multiple of four, 17..64 rows: the size that their calls have always asked for
+// (activations re-ordered by a kernel that is gone).
+size_t ragged_workspace_bytes(int64_t M, int64_t K) {
+    return (size_t)(K / dmr::kGroup) * (size_t)((M + 15) / 16) * (4096 + 64);
+}
 W4Path w4_path(int64_t M, int64_t K, int64_t N) {
     if (M == 1) return W4Path::Gemv;
     if (M <= 16) {
@@ -33,13 +54,8 @@ W4Path w4_path(int64_t M, int64_t K, int64_t N) {
         return dmr::w4_panel_applies(M, K, N) ? W4Path::Panel : W4Path::Mid;
     }
     if (M <= kSkinnyMaxM && dmr::w4_wide_applies(M, K, N)) return W4Path::Wide;
-    const int64_t tiles = N / dmr::kTileRows;
-    // wide layers already give the register-blocked streaming kernel 4 tiles per workgroup
-    if (M <= kSkinnyMaxM) return tiles >= 1024 ? W4Path::Skinny2 : W4Path::Mid;
-    // the tiled GEMM wins from about 140 output blocks of 128 x 128 on (measured: ahead at 144 and from there on, on
-    // 128-row tiles up to 256 blocks and on 256-row tiles beyond; behind at 128)
-    const int64_t gemm_wgs = ((M + 127) / 128) * ((N + 127) / 128);
-    if (M <= 128 || gemm_wgs < dmr::env_int("DMR_W4_GEMM_MIN_WGS", kTiledMinBlocks)) return W4Path::Mid;
+    if (M <= kSkinnyMaxM) return N / dmr::kTileRows >= 1024 ? W4Path::Ragged : W4Path::Mid;
+    if (rows_beat_tiled(M, K, N)) return W4Path::Mid;
     return dmr::w4_gemm_rescale_applies(M, N) ? W4Path::GemmRescale : W4Path::Gemm;
 }
 
@@ -54,8 +70,7 @@ W3Path w3_path(int64_t M, int64_t K, int64_t N) {
         return dmr::w4_panel_applies(M, K, N) ? W3Path::Panel : W3Path::Mid;
     }
     if (M <= kSkinnyMaxM && dmr::w4_wide_applies(M, K, N)) return W3Path::Wide;
-    const int64_t gemm_wgs = ((M + 127) / 128) * ((N + 127) / 128);
-    if (M <= 128 || gemm_wgs < kTiledMinBlocks) return W3Path::Mid;
+    if (rows_beat_tiled(M, K, N)) return W3Path::Mid;
     return dmr::w4_gemm_rescale_applies(M, N) ? W3Path::GemmRescale : W3Path::Gemm;
 }
 
@@ -122,11 +137,15 @@ dmr_status_t hip_status(hipError_t e) { return e == hipSuccess ? DMR_OK : DMR_ER
 
 namespace {
 
-// Whether the kernel that serves M rows of this layer also runs without the partials that the size query asks for: the
-// chunked-panel kernel does on layers that give half of the CUs a workgroup without a split of K (4096 -> 16384, 64 rows: 29.0 us
-// instead of 24.5).
+// Whether M rows of this layer also run without the partials that the size query asks for: layers that give half of the CUs a
+// workgroup without a split of K always did.
 bool runs_unsplit(const dmr_qlinear_t *layer, int64_t M) {
     return dmr::w4_wide_applies(M, layer->K, layer->N) && dmr::plan_wide(M, layer->K, layer->N, false).ok;
+}
+
+// Splits of K that a workspace of the size that the query gives holds partials for (Wide and Mid calls).
+int splits_held(int64_t M, int64_t K, int64_t N) {
+    return M <= kSkinnyMaxM && dmr::w4_wide_applies(M, K, N) ? dmr::plan_wide(M, K, N).SK : mid_splits(M, K, N);
 }
 
 // The forwards with an optional bf16 residual added where the result is stored.
@@ -150,8 +169,10 @@ dmr_status_t forward_quant(const dmr_qlinear_t *layer, const uint16_t *d_x, int6
             case W3Path::Gemv: return hip_status(dmr::launch_w3_gemv(L3, d_x, d_y, f32, res, s));
             case W3Path::Stream: return hip_status(dmr::launch_w3_stream(L3, d_x, M, d_y, f32, res, s));
             case W3Path::Panel: return hip_status(dmr::launch_w3_panel(L3, d_x, M, d_y, f32, res, d_ws, s));
-            case W3Path::Wide: return hip_status(dmr::launch_w3_wide(L3, d_x, M, d_y, f32, res, d_ws, s));
-            case W3Path::Mid: return hip_status(dmr::launch_w3_mid(L3, d_x, M, d_y, f32, res, d_ws, s));
+            case W3Path::Wide:
+            case W3Path::Mid:
+                if (dmr::rows_kernels_fit(M, L3.K)) return hip_status(dmr::launch_w3_rows(L3, d_x, M, d_y, f32, res, d_ws, splits_held(M, L3.K, L3.N), s));
+                return hip_status(dmr::launch_w3_mid(L3, d_x, M, d_y, f32, res, d_ws, s));
             case W3Path::Gemm: return hip_status(dmr::launch_w3_gemm(L3, d_x, M, d_y, f32, res, s));
             case W3Path::GemmRescale: return hip_status(dmr::launch_w3_gemm_rescale(L3, d_x, M, d_y, f32, res, d_ws, s));
         }
@@ -175,9 +196,11 @@ dmr_status_t forward_quant(const dmr_qlinear_t *layer, const uint16_t *d_x, int6
         if (e != hipErrorInvalidValue) return hip_status(e);   // else: activations do not fit LDS
     }
     if (path == W4Path::Panel) return hip_status(dmr::launch_w4_panel(L, d_x, M, d_y, f32, res, d_ws, s));
-    if (path == W4Path::Wide) return hip_status(dmr::launch_w4_wide(L, d_x, M, d_y, f32, res, d_ws, s));
-    if (path == W4Path::Mid) return hip_status(dmr::launch_w4_mid(L, d_x, M, d_y, f32, res, d_ws, s));
-    if (path == W4Path::Skinny2) return hip_status(dmr::launch_w4_skinny2(L, d_x, M, d_y, f32, d_ws, s));
+    if (path == W4Path::Wide || path == W4Path::Mid || path == W4Path::Ragged) {
+        if (dmr::rows_kernels_fit(M, L.K))
+            return hip_status(dmr::launch_w4_rows(L, d_x, M, d_y, f32, res, d_ws, path == W4Path::Ragged ? 1 : splits_held(M, L.K, L.N), s));
+        return hip_status(dmr::launch_w4_mid(L, d_x, M, d_y, f32, res, d_ws, s));
+    }
     if (M <= kSkinnyMaxM) return hip_status(dmr::launch_w4_skinny(L, d_x, M, d_y, f32, s));
     if (path == W4Path::GemmRescale) return hip_status(dmr::launch_w4_gemm_rescale(L, d_x, M, d_y, f32, res, d_ws, s));
     // Not reached with the present crossovers (the rescaling kernel takes every tiled shape and calls this kernel
@@ -236,10 +259,10 @@ size_t dmr_qlinear_storage_bytes(int64_t K, int64_t N, int32_t g) {
 size_t dmr_qlinear_workspace_bytes(int64_t M, int64_t K, int64_t N) {
     if (M <= 0 || K <= 0 || K % dmr::kGroup != 0 || N <= 0 || N % dmr::kTileRows != 0) return 0;
     switch (w4_path(M, K, N)) {
-        case W4Path::Mid: return dmr::w4_mid_workspace_bytes(M, K, N);    // fp32 partials when K is split
+        case W4Path::Mid: return mid_workspace_bytes(M, K, N);    // fp32 partials when K is split
         case W4Path::Panel: return dmr::w4_panel_workspace_bytes(M, K, N);    // likewise
         case W4Path::Wide: return dmr::w4_wide_workspace_bytes(M, K, N);      // likewise
-        case W4Path::Skinny2: return dmr::w4_skinny2_workspace_bytes(M, K);   // re-ordered activations
+        case W4Path::Ragged: return ragged_workspace_bytes(M, K);
         case W4Path::GemmRescale: return dmr::w4_gemm_rescale_workspace_bytes(M, K, N);   // zero-point operands, factors
         default: return 0;
     }
@@ -332,7 +355,7 @@ size_t dmr_qlinear_w3_workspace_bytes(int64_t M, int64_t K, int64_t N) {
     if (M <= 0 || K <= 0 || K % dmr::kGroup != 0 || N <= 0 || N % dmr::kTileRows != 0) return 0;
     switch (w3_path(M, K, N)) {
         case W3Path::Panel: return dmr::w4_panel_workspace_bytes(M, K, N);   // fp32 partials of the k slices
-        case W3Path::Mid: return dmr::w4_mid_workspace_bytes(M, K, N);       // fp32 partials when K is split
+        case W3Path::Mid: return mid_workspace_bytes(M, K, N);       // fp32 partials when K is split
         case W3Path::Wide: return dmr::w4_wide_workspace_bytes(M, K, N);     // likewise
         case W3Path::GemmRescale: return dmr::w4_gemm_rescale_workspace_bytes(M, K, N);   // zero-point operands, factors
         default: return 0;
@@ -458,12 +481,12 @@ dmr_status_t check_fused(dmr_prologue_t pro, const uint16_t *d_in, const uint16_
     return DMR_OK;
 }
 
-// Whether the kernel that serves M rows of this layer adds a residual where it stores the result (the two direct-from-L2
-// kernels do not).
+// Whether the kernel that serves M rows of this layer adds a residual where it stores the result (the direct-from-L2 kernel does
+// not).
 bool quant_adds_residual(const dmr_qlinear_t *layer, int64_t M) {
     if (layer->bits == 3) return true;
     const W4Path path = w4_path(M, layer->K, layer->N);
-    return path != W4Path::Skinny2 && !(path == W4Path::Gemv && !dmr::w4_gemv_fits(layer->K, layer->N, true));
+    return !(path == W4Path::Gemv && !dmr::w4_gemv_fits(layer->K, layer->N, true));
 }
 
 bool overlap(const void *a, size_t na, const void *b, size_t nb) {
@@ -619,7 +642,7 @@ const char *dmr_qlinear_kernel_path(dmr_format_t format, int64_t M, int64_t K, i
                 case W4Path::Stream: return "w4_stream";
                 case W4Path::Panel: return "w4_panel";
                 case W4Path::Wide: return "w4_wide";
-                case W4Path::Skinny2: return "w4_skinny2";
+                case W4Path::Ragged: return "w4_wide";
                 case W4Path::Mid: return "w4_mid";
                 case W4Path::GemmRescale:
                     if (dmr::w4_gemm_rescale_tile_rows(M, N) == 128) return "w4_gemm128_rescale";

@@ -190,13 +190,8 @@ bool w4_stream_fits(int64_t M, int64_t K, int64_t N);
 bool bf16_stream_fits(int64_t M, int64_t K, int64_t N);
 hipError_t launch_bf16_stream(const uint16_t *w, const uint16_t *x, int64_t M, int64_t K, int64_t N, void *y,
                               bool out_f32, const uint16_t *res, hipStream_t stream);
-// 16 < M <= 64: activation pre-pass into `ws` (w4_skinny2_workspace_bytes), then the streaming kernel.
-size_t w4_skinny2_workspace_bytes(int64_t M, int64_t K);
-hipError_t launch_w4_skinny2(const LayerView &L, const uint16_t *x, int64_t M, void *y, bool out_f32,
-                             void *ws, hipStream_t stream);
-// 16 < M up to a few hundred rows: weights straight into registers, activations through LDS, optional
-// split of K whose fp32 partials go to `ws` (w4_mid_workspace_bytes) and are added by a second kernel.
-size_t w4_mid_workspace_bytes(int64_t M, int64_t K, int64_t N);
+// Blocks of 16 rows: weights straight into registers, activations through LDS, optional split of K whose fp32 partials go to
+// `ws` and are added by a second kernel.
 hipError_t launch_w4_mid(const LayerView &L, const uint16_t *x, int64_t M, void *y, bool out_f32, const uint16_t *res,
                          void *ws, hipStream_t stream);
 // The same kernel on a 3-bit layer (same plan and workspace as launch_w4_mid).

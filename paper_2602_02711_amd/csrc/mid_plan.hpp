@@ -1,6 +1,6 @@
-// Launch planning shared by the rollout-batch kernels (INT4 and bf16): row tiles per wave, waves along
-// m and n, weight tiles per wave, and the split of K.  Pure host arithmetic for 256 CUs, so that the
-// workspace queries agree with the launches.
+// Launch planning of the bf16 rollout-batch kernel (and, up to 16 rows, of the INT4 / INT3 one): row tiles per wave, waves along
+// m and n, weight tiles per wave, and the split of K, which for INT4 / INT3 above 16 rows is what the workspace holds.  Pure host
+// arithmetic for 256 CUs, so that the workspace queries agree with the launches.
 #pragma once
 #include <cstdlib>
 

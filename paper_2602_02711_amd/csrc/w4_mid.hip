@@ -1,21 +1,17 @@
-// W4A16 for batches of 17 rows up to several hundred (a group of parallel rollouts decoding together,
-// or a short prefill): too many rows for the pure streaming kernels, too few for a tiled GEMM to fill
-// 256 CUs.  Also serves 2..16 rows when K is so long that the rows do not fit LDS whole.
+// W4A16 for up to 16 rows (per row block) where neither the rows nor a slice of them fit LDS: 2..16 rows of a K whose group
+// count does not slice, 3-bit decode rows beyond the GEMV's budget, and rows too long for 32-bit offsets inside a block.
 //
-// The streaming layout already is MFMA B-operand order, so the weights never touch LDS: a wave
-// loads its 1 KiB blocks straight into registers (nontemporal, requested four groups ahead),
-// unpacks them with the bf16 magic number and feeds v_mfma_f32_16x16x32_bf16.  Only the activations
-// go through LDS: the workgroup's BM x 128 slice of x for the current group, double buffered (and
-// requested three groups ahead into registers), rows padded to 272 bytes so that the 16-byte
-// A-operand reads of 8 consecutive lanes fall in distinct banks.  A wave owns MTW row tiles x R weight tiles; every A fragment it reads from LDS feeds R MFMAs
-// and every unpacked weight register MTW MFMAs.  The group sums of x come from one more MFMA against
-// an all-ones operand, already in accumulator layout, and a group contributes
+// The streaming layout already is MFMA B-operand order, so the weights never touch LDS: a wave loads its 1 KiB blocks
+// straight into registers (nontemporal, requested four groups ahead), unpacks them with the bf16 magic number and feeds
+// v_mfma_f32_16x16x32_bf16.  Only the activations go through LDS: the workgroup's 16 x 128 slice of x for the current group,
+// double buffered (and requested three groups ahead into registers), rows padded to 272 bytes so that the 16-byte A-operand
+// reads of 8 consecutive lanes fall in distinct banks.  A wave owns R weight tiles.  The group sums of x come from one more MFMA
+// against an all-ones operand, already in accumulator layout, and a group contributes
 //     acc += s (D - (128 + z) X)                                  (exact codes, fp32 scale)
 // as in the decode kernels, so this path has their accuracy.
 //
-// Small N x M leaves too few (row block, column block) pairs for the chip; then K is split over
-// blockIdx.z, each split writes an fp32 partial tile to the caller's workspace and a second kernel
-// adds the partials in ascending split order (deterministic, no atomics).
+// K is split over blockIdx.z where the columns leave CUs idle: each split writes an fp32 partial tile to the caller's workspace
+// and a second kernel adds the partials in ascending split order (deterministic, no atomics).
 //
 // BITS = 3 runs the same kernel on the 3-bit streaming layout (768-byte blocks, three words per lane).
 #include <algorithm>
@@ -28,16 +24,16 @@ namespace dmr {
 namespace {
 
 constexpr int ROW_BYTES = 272;   // one activation row of a group in LDS: 128 bf16 + 16 bytes of padding
+constexpr int NW = 4, BM = 16;    // waves (columns) and rows of a workgroup
 
 
 // out: 0 = fp32 y, 1 = bf16 y, 2 = fp32 partial [split][M][N]; kResidualInPlace
-template <int MTW, int WM, int NW, int R, int BITS>
-__global__ __launch_bounds__(64 * WM * NW, (WM * NW == 4) ? 2 : 1) void w4_mid_kernel(
+template <int R, int BITS>
+__global__ __launch_bounds__(64 * NW, 2) void w4_mid_kernel(
     const void *__restrict__ wt, const uint32_t *__restrict__ sz, const uint16_t *__restrict__ x,
     void *__restrict__ y, int M, int64_t K, int64_t N, int groups, int tiles, int gps, int out, int szs,
     const uint16_t *__restrict__ res) {
-    constexpr int THREADS = 64 * WM * NW;
-    constexpr int BM = 16 * MTW * WM;
+    constexpr int THREADS = 64 * NW;
     constexpr int ROWS_PER_PASS = THREADS / 16;
     constexpr int XL = BM / ROWS_PER_PASS;          // 16-byte pieces of x per thread and group
     static_assert(BM % ROWS_PER_PASS == 0, "activation rows must divide over the threads");
@@ -47,12 +43,11 @@ __global__ __launch_bounds__(64 * WM * NW, (WM * NW == 4) ? 2 : 1) void w4_mid_k
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c = lane >> 4, j = lane & 15;
-    const int wm = wave % WM, wn = wave / WM;
     const int m0 = (int)blockIdx.y * BM;
     const int gA = (int)blockIdx.z * gps;
     const int gB = min(groups, gA + gps);
 
-    const int tile0 = ((int)blockIdx.x * NW + wn) * R;
+    const int tile0 = ((int)blockIdx.x * NW + wave) * R;
     int64_t wbase[R];          // block index of (tile, group 0); ragged last column block re-reads the last tile
     int64_t sbase[R];          // its first scale / zero word (wave-uniform, like wbase)
 #pragma unroll
@@ -107,33 +102,23 @@ __global__ __launch_bounds__(64 * WM * NW, (WM * NW == 4) ? 2 : 1) void w4_mid_k
             *reinterpret_cast<u32x4_t *>(dst + (p * ROWS_PER_PASS + xrow) * ROW_BYTES + xpiece * 16) = xr[set][p];
     };
 
-    f32x4 acc[R][MTW];
+    f32x4 acc[R];
 #pragma unroll
-    for (int rt = 0; rt < R; ++rt)
-#pragma unroll
-        for (int mt = 0; mt < MTW; ++mt) acc[rt][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int rt = 0; rt < R; ++rt) acc[rt] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     Frag ones;
     ones.w[0] = ones.w[1] = ones.w[2] = ones.w[3] = 0x3F803F80u;
 
     auto compute = [&](const Slot &s, int buf, bool valid) {
-        const uint8_t *src = xl + buf * (BM * ROW_BYTES) + (wm * MTW * 16 + j) * ROW_BYTES + c * 64;
-        f32x4 d[R][MTW], xs[MTW];
+        const uint8_t *src = xl + buf * (BM * ROW_BYTES) + j * ROW_BYTES + c * 64;
+        f32x4 d[R], xs = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int mt = 0; mt < MTW; ++mt) {
-            xs[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int rt = 0; rt < R; ++rt) d[rt][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-        }
+        for (int rt = 0; rt < R; ++rt) d[rt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
-            Frag a[MTW];
-#pragma unroll
-            for (int mt = 0; mt < MTW; ++mt)
-                a[mt].u = *reinterpret_cast<const uint4 *>(src + mt * 16 * ROW_BYTES + t * 16);
-#pragma unroll
-            for (int mt = 0; mt < MTW; ++mt)
-                xs[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[mt].v, ones.v, xs[mt], 0, 0, 0);
+            Frag a;
+            a.u = *reinterpret_cast<const uint4 *>(src + t * 16);
+            xs = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, ones.v, xs, 0, 0, 0);
 #pragma unroll
             for (int rt = 0; rt < R; ++rt) {
                 Frag b;
@@ -146,9 +131,7 @@ __global__ __launch_bounds__(64 * WM * NW, (WM * NW == 4) ? 2 : 1) void w4_mid_k
                     if (t == 2) unpack3_step<2>(s.w[rt].x, s.w[rt].y, s.w[rt].z, b.w);
                     if (t == 3) unpack3_step<3>(s.w[rt].x, s.w[rt].y, s.w[rt].z, b.w);
                 }
-#pragma unroll
-                for (int mt = 0; mt < MTW; ++mt)
-                    d[rt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[mt].v, b.v, d[rt][mt], 0, 0, 0);
+                d[rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, b.v, d[rt], 0, 0, 0);
             }
         }
 #pragma unroll
@@ -157,10 +140,7 @@ __global__ __launch_bounds__(64 * WM * NW, (WM * NW == 4) ? 2 : 1) void w4_mid_k
             const float sc = valid ? __uint_as_float(s.s[rt] << 16) : 0.f;
             const float cz = __uint_as_float(s.s[rt] & 0xFFFF0000u);   // -(128 + z)
 #pragma unroll
-            for (int mt = 0; mt < MTW; ++mt)
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    acc[rt][mt][q] = fmaf(sc, fmaf(cz, xs[mt][q], d[rt][mt][q]), acc[rt][mt][q]);
+            for (int q = 0; q < 4; ++q) acc[rt][q] = fmaf(sc, fmaf(cz, xs[q], d[rt][q]), acc[rt][q]);
         }
     };
 
@@ -195,30 +175,26 @@ __global__ __launch_bounds__(64 * WM * NW, (WM * NW == 4) ? 2 : 1) void w4_mid_k
 #pragma unroll
         for (int rt = 0; rt < R; ++rt)
 #pragma unroll
-            for (int mt = 0; mt < MTW; ++mt)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int m = min(m0 + (wm * MTW + mt) * 16 + c * 4 + q, M - 1);
-                    acc[rt][mt][q] += bf16_bits_to_f32(from[(int64_t)m * N + (int64_t)min(tile0 + rt, tiles - 1) * kTileRows + j]);
-                }
+            for (int q = 0; q < 4; ++q) {
+                const int m = min(m0 + c * 4 + q, M - 1);
+                acc[rt][q] += bf16_bits_to_f32(from[(int64_t)m * N + (int64_t)min(tile0 + rt, tiles - 1) * kTileRows + j]);
+            }
     }
     const int64_t part = out_mode == 2 ? (int64_t)blockIdx.z * M * N : 0;
 #pragma unroll
     for (int rt = 0; rt < R; ++rt) {
         const int tile = tile0 + rt;
 #pragma unroll
-        for (int mt = 0; mt < MTW; ++mt)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int m = m0 + (wm * MTW + mt) * 16 + c * 4 + q;
-                if (m < M && tile < tiles) {
-                    const int64_t o = (int64_t)m * N + (int64_t)tile * kTileRows + j;
-                    if (out_mode == 1)
-                        reinterpret_cast<uint16_t *>(y)[o] = f32_to_bf16(acc[rt][mt][q]);
-                    else
-                        reinterpret_cast<float *>(y)[part + o] = acc[rt][mt][q];
-                }
+        for (int q = 0; q < 4; ++q) {
+            const int m = m0 + c * 4 + q;
+            if (m < M && tile < tiles) {
+                const int64_t o = (int64_t)m * N + (int64_t)tile * kTileRows + j;
+                if (out_mode == 1)
+                    reinterpret_cast<uint16_t *>(y)[o] = f32_to_bf16(acc[rt][q]);
+                else
+                    reinterpret_cast<float *>(y)[part + o] = acc[rt][q];
             }
+        }
     }
 }
 
@@ -252,30 +228,27 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *__restr
     }
 }
 
-template <int MTW, int WM, int NW, int R, int BITS>
+template <int R, int BITS>
 hipError_t launch_cfg(const void *wt, const uint32_t *sz, int szs, int64_t K, int64_t N, const uint16_t *x, int M, void *dst,
                       int out_mode, const uint16_t *res, const MidPlan &p, hipStream_t stream) {
-    constexpr int BM = 16 * MTW * WM;
     constexpr size_t lds = 2ull * BM * ROW_BYTES;
     // once per process and kernel instantiation (thread-safe static initialisation)
     static const hipError_t attr_status = hipFuncSetAttribute(
-        reinterpret_cast<const void *>(&w4_mid_kernel<MTW, WM, NW, R, BITS>), hipFuncAttributeMaxDynamicSharedMemorySize,
+        reinterpret_cast<const void *>(&w4_mid_kernel<R, BITS>), hipFuncAttributeMaxDynamicSharedMemorySize,
         (int)lds);
     if (attr_status != hipSuccess) return attr_status;
     const int groups = (int)(K / kGroup), tiles = (int)(N / kTileRows);
     const dim3 grid((unsigned)((tiles + NW * R - 1) / (NW * R)), (unsigned)((M + BM - 1) / BM), (unsigned)p.SK);
-    hipLaunchKernelGGL((w4_mid_kernel<MTW, WM, NW, R, BITS>), grid, dim3(64 * WM * NW), lds, stream, wt, sz, x, dst, M,
+    hipLaunchKernelGGL((w4_mid_kernel<R, BITS>), grid, dim3(64 * NW), lds, stream, wt, sz, x, dst, M,
                        K, N, groups, tiles, p.gps, out_mode, szs, res);
     return hipGetLastError();
 }
 
-template <int MTW, int WM, int NW, int BITS>
+template <int BITS>
 hipError_t launch_r(const void *wt, const uint32_t *sz, int szs, int64_t K, int64_t N, const uint16_t *x, int M, void *dst,
                     int out_mode, const uint16_t *res, const MidPlan &p, hipStream_t stream) {
-    // R = 4 was measured too: never faster, and with 4 row tiles per wave it needs more than the 256
-    // registers that two waves per SIMD leave
-    return p.R == 2 ? launch_cfg<MTW, WM, NW, 2, BITS>(wt, sz, szs, K, N, x, M, dst, out_mode, res, p, stream)
-                    : launch_cfg<MTW, WM, NW, 1, BITS>(wt, sz, szs, K, N, x, M, dst, out_mode, res, p, stream);
+    return p.R == 2 ? launch_cfg<2, BITS>(wt, sz, szs, K, N, x, M, dst, out_mode, res, p, stream)
+                    : launch_cfg<1, BITS>(wt, sz, szs, K, N, x, M, dst, out_mode, res, p, stream);
 }
 
 template <int BITS>
@@ -286,19 +259,7 @@ hipError_t launch_mid(const void *wt, const uint32_t *sz, int szs, int64_t K, in
     if (split && !ws) return hipErrorInvalidValue;
     void *dst = split ? ws : y;
     const int out_mode = split ? 2 : (out_f32 ? 0 : 1) | residual_in_place(y, res);
-    const int iM = (int)M;
-    hipError_t e;
-    if (p.WM == 1) {
-        switch (p.MTW) {
-            case 1: e = launch_r<1, 1, 4, BITS>(wt, sz, szs, K, N, x, iM, dst, out_mode, res, p, stream); break;
-            case 2: e = launch_r<2, 1, 4, BITS>(wt, sz, szs, K, N, x, iM, dst, out_mode, res, p, stream); break;
-            case 3: e = launch_r<3, 1, 4, BITS>(wt, sz, szs, K, N, x, iM, dst, out_mode, res, p, stream); break;
-            default: e = launch_r<4, 1, 4, BITS>(wt, sz, szs, K, N, x, iM, dst, out_mode, res, p, stream); break;
-        }
-    } else {
-        e = p.MTW == 3 ? launch_r<3, 2, 2, BITS>(wt, sz, szs, K, N, x, iM, dst, out_mode, res, p, stream)
-                       : launch_r<4, 2, 2, BITS>(wt, sz, szs, K, N, x, iM, dst, out_mode, res, p, stream);
-    }
+    const hipError_t e = launch_r<BITS>(wt, sz, szs, K, N, x, (int)M, dst, out_mode, res, p, stream);
     if (e != hipSuccess || !split) return e;
     return launch_splitk_reduce(static_cast<const float *>(ws), y, M * N, p.SK, out_f32, res, stream);
 }
@@ -310,11 +271,6 @@ hipError_t launch_splitk_reduce(const float *part, void *y, int64_t total, int s
     hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)((total / 4 + 255) / 256)), dim3(256), 0, stream, part, y,
                        total, splits, out_f32 ? 1 : 0, res);
     return hipGetLastError();
-}
-
-size_t w4_mid_workspace_bytes(int64_t M, int64_t K, int64_t N) {
-    const MidPlan p = plan_mid(M, K, N);
-    return p.SK > 1 ? (size_t)p.SK * (size_t)M * (size_t)N * sizeof(float) : 0;
 }
 
 hipError_t launch_w4_mid(const LayerView &L, const uint16_t *x, int64_t M, void *y, bool out_f32, const uint16_t *res,

@@ -1,0 +1,60 @@
+"""The two kernels for 17 rows up to several hundred (staged panels, slices of K), whole outputs against fp64 on the dequantised
+codes: edges of row and column tiles, group counts that do not divide over waves or splits, fewer groups than waves, every
+row-tile count, rows that share a workgroup's weights and rows in several blocks."""
+import pytest
+import torch
+
+import paper_2602_02711_amd as dmr
+from paper_2602_02711_amd import synth
+
+pytestmark = pytest.mark.gpu
+G = synth.GROUP
+DEV = "cuda:0"
+
+
+def make(fmt, w):
+    """(layer, exact weights in fp64)"""
+    N, K = w.shape
+    if fmt == "w3":
+        q, s, z = dmr.dmr_qlinear_quantize_w3(w, G)
+        layer = dmr.dmr_qlinear_w3_create(q, s, z, G)
+        bits = (q.view(N, K // 32, 3, 1) >> torch.arange(32, device=DEV, dtype=torch.int32)) & 1
+        bits = bits.view(N, K // 32, 32, 3)
+        codes = bits[..., 0] + 2 * bits[..., 1] + 4 * bits[..., 2]
+    else:
+        q, s, z = dmr.dmr_qlinear_quantize(w, G)
+        codes = (q.view(N, K // 8, 1) >> (4 * torch.arange(8, device=DEV, dtype=torch.int32))) & 15
+        if fmt == "w4pc":
+            s = (w.abs().amax(dim=1) / 7.5).to(torch.bfloat16)
+            return dmr.dmr_qlinear_create_per_channel(q, s), (codes.reshape(N, K).double() - 8.0) * s.double()[:, None]
+        layer = dmr.dmr_qlinear_create(q, s, z, G)
+    exact = (codes.reshape(N, K // G, G).double() - z.double()[..., None]) * s.double()[..., None]
+    return layer, exact.view(N, K)
+
+
+@pytest.mark.parametrize("M,K,N", [
+    # slices of K: one, two and four tiles; 1..4 row tiles' worth of rows, one group in all, five, eight and 29 over eight waves
+    (17, 128, 1024), (33, 640, 272), (48, 3712, 6144), (64, 384, 8208), (50, 14336, 4112), (65, 1152, 2064), (100, 128, 272),
+    (130, 2560, 4096), (250, 512, 1040),
+    # staged panels: chunks of four groups (32, 33 and 35 of them, split and whole), then of two in blocks of 96 and 128 rows
+    (20, 4224, 16400), (40, 4480, 16400), (64, 4096, 28688), (96, 512, 28688), (97, 384, 17936), (128, 1664, 16400),
+    (200, 1664, 12304), (200, 4096, 6160), (400, 640, 6160), (512, 384, 8192),
+])
+@pytest.mark.parametrize("fmt", ["w4", "w4pc", "w3"])
+def test_rows(fmt, M, K, N):
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(M + K + N)
+    layer, exact = make(fmt, 0.02 * torch.randn((N, K), generator=gen, device=DEV))
+    x = torch.randn((M, K), generator=gen, device=DEV).to(torch.bfloat16)
+    res = torch.randn((M, N), generator=gen, device=DEV).to(torch.bfloat16)
+    ref = x.double() @ exact.t()
+    need = (dmr.dmr_qlinear_w3_workspace_bytes if fmt == "w3" else dmr.dmr_qlinear_workspace_bytes)(M, K, N)
+    ws = torch.full((max(need, 16),), 0xFF, dtype=torch.uint8, device=DEV)        # NaN partials where nothing was written
+    y = dmr.dmr_qlinear_forward(layer, x, out_dtype=torch.float32, workspace=ws)
+    # fp32 sums of K products in units of (128 + q) ~ 20 times the result's own: the bound of this kernel class' parity tests
+    assert float((y.double() - ref).abs().max()) <= 1e-4 * float(ref.square().mean().sqrt())
+    # bf16 output, and a residual in the output's own buffer: the same fp32 sums, rounded once
+    assert torch.equal(dmr.dmr_qlinear_forward(layer, x), y.to(torch.bfloat16))
+    out = res.clone()
+    dmr.dmr_qlinear_forward_fused(layer, dmr.DMR_PRO_NONE, x, residual=out, out=out)
+    assert torch.equal(out, (y + res.float()).to(torch.bfloat16))
