@@ -2,6 +2,7 @@
 // the choice of kernel by M.  No device memory is allocated here or anywhere in the library.
 #include <new>
 
+#include "bf16_rows_plan.hpp"
 #include "glue.hpp"
 #include "mid_plan.hpp"
 #include "panel_plan.hpp"
@@ -74,9 +75,9 @@ W3Path w3_path(int64_t M, int64_t K, int64_t N) {
     return dmr::w4_gemm_rescale_applies(M, N) ? W3Path::GemmRescale : W3Path::Gemm;
 }
 
-// The bf16 twin: GEMV, the direct-from-L2 skinny kernel for 2..8 rows (measured faster there than the
-// LDS-staged kernels), then the same size classes as INT4.
-enum class Bf16Path { Gemv, Stream, Skinny, Mid, GemmBig, Gemm };
+// The bf16 twin: GEMV, up to 64 rows the kernel that keeps its activations in registers wherever its plan applies (bf16_rows_plan),
+// else the classes Skinny (no workspace: 2..8 rows, and 9..16 of short rows on wide layers) and Mid (fp32 partials).
+enum class Bf16Path { Gemv, Skinny, Mid, GemmBig, Gemm };
 
 // M > 64, K >= 1024: whether the direct-to-LDS kernels beat the rollout-batch kernel.  While one round covers the layer they
 // take the same time whatever its width; the other kernel's time grows with its blocks (its own row blocks times 128 columns)
@@ -97,10 +98,7 @@ bool tiled_beats_rollout(int64_t M, int64_t K, int64_t N) {
 }
 Bf16Path bf16_path(int64_t M, int64_t K, int64_t N) {
     if (M == 1) return Bf16Path::Gemv;
-    // the streaming kernel wins (by ~12 %) only for 9..16 rows of the widest layers; below that the
-    // direct-from-L2 kernel, elsewhere the rollout-batch kernel measured faster
-    if (M > 8 && M <= 16 && N / dmr::kTileRows >= 1024 && dmr::bf16_stream_fits(M, K, N)) return Bf16Path::Stream;
-    if (M <= 8) return Bf16Path::Skinny;
+    if (M <= 8 || (M <= 16 && N / dmr::kTileRows >= 1024 && M * (K / 8 + 1) <= 9216)) return Bf16Path::Skinny;
     if (M <= 64) return Bf16Path::Mid;
     if (K < 1024) {                  // no direct-to-LDS kernel there
         if (((M + 127) / 128) * ((N + 127) / 128) <= 128) return Bf16Path::Mid;
@@ -108,6 +106,10 @@ Bf16Path bf16_path(int64_t M, int64_t K, int64_t N) {
         return Bf16Path::Mid;
     }
     return dmr::gemm_big_tile_rows(M, K, N) != 0 ? Bf16Path::GemmBig : Bf16Path::Gemm;
+}
+
+dmr::Bf16RowsPlan bf16_rows_plan(int64_t M, int64_t K, int64_t N) {
+    return dmr::plan_bf16_rows(M, K, N, bf16_path(M, K, N) == Bf16Path::Mid ? dmr::plan_mid(M, K, N).SK : 1);
 }
 
 size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
@@ -232,8 +234,9 @@ dmr_status_t forward_bf16(const uint16_t *d_w, const uint16_t *d_x, int64_t M, i
         if (e != hipErrorInvalidValue) return hip_status(e);   // else: K outside its range
         return hip_status(dmr::launch_bf16_skinny(d_w, d_x, M, K, N, d_y, f32, res, s));
     }
+    const dmr::Bf16RowsPlan rows = bf16_rows_plan(M, K, N);
+    if (rows.ok) return hip_status(dmr::launch_bf16_rows(d_w, d_x, M, K, N, d_y, f32, res, d_ws, rows, s));
     switch (path) {
-        case Bf16Path::Stream: return hip_status(dmr::launch_bf16_stream(d_w, d_x, M, K, N, d_y, f32, res, s));
         case Bf16Path::Skinny: return hip_status(dmr::launch_bf16_skinny(d_w, d_x, M, K, N, d_y, f32, res, s));
         case Bf16Path::Mid: return hip_status(dmr::launch_bf16_mid(d_w, d_x, M, K, N, d_y, f32, res, d_ws, s));
         case Bf16Path::GemmBig: return hip_status(dmr::launch_bf16_gemm_w8(d_w, d_x, M, K, N, d_y, f32, res, s));
@@ -609,9 +612,9 @@ dmr_status_t dmr_probe_hbm_read(const void *d_buf, size_t bytes, uint32_t *d_sin
 const char *dmr_qlinear_kernel_path(dmr_format_t format, int64_t M, int64_t K, int64_t N) {
     if (M <= 0 || check_shape(K, N, dmr::kGroup) != DMR_OK) return "none";
     auto bf16_name = [&]() -> const char * {
+        if (M <= 64 && bf16_rows_plan(M, K, N).ok) return "bf16_rows";
         switch (bf16_path(M, K, N)) {
             case Bf16Path::Gemv: return dmr::bf16_gemv_fits(K) ? "bf16_gemv" : "bf16_skinny";
-            case Bf16Path::Stream: return "bf16_stream";
             case Bf16Path::Skinny: return "bf16_skinny";
             case Bf16Path::Mid: return "bf16_mid";
             case Bf16Path::GemmBig: {

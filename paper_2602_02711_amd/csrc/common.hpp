@@ -186,10 +186,6 @@ bool w4_gemv_fits(int64_t K, int64_t N, bool with_residual);
 bool bf16_gemv_fits(int64_t K);
 // 2 <= M <= 16 streaming kernel (launch_w4_stream_fused): whether the activations fit LDS.
 bool w4_stream_fits(int64_t M, int64_t K, int64_t N);
-// bf16 twin of the streaming kernel (optional residual added at the store).
-bool bf16_stream_fits(int64_t M, int64_t K, int64_t N);
-hipError_t launch_bf16_stream(const uint16_t *w, const uint16_t *x, int64_t M, int64_t K, int64_t N, void *y,
-                              bool out_f32, const uint16_t *res, hipStream_t stream);
 // Blocks of 16 rows: weights straight into registers, activations through LDS, optional split of K whose fp32 partials go to
 // `ws` and are added by a second kernel.
 hipError_t launch_w4_mid(const LayerView &L, const uint16_t *x, int64_t M, void *y, bool out_f32, const uint16_t *res,

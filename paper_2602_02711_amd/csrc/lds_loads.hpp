@@ -48,6 +48,11 @@ __device__ __forceinline__ uint32_t load_word(const void *base, uint32_t bytes, 
     return __builtin_amdgcn_raw_buffer_load_b32(__builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)bytes, 0x00020000),
                                                 (int)voff, (int)soff, 0);
 }
+__device__ __forceinline__ uint2 load_pair(const void *base, uint32_t bytes, uint32_t voff, uint32_t soff) {
+    const auto v = __builtin_amdgcn_raw_buffer_load_b64(__builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)bytes, 0x00020000),
+                                                        (int)voff, (int)soff, 0);
+    return make_uint2(v[0], v[1]);
+}
 
 // MFMA A operands of MT row tiles, STRIDE bytes apart in LDS.  Restrict pointers: their alias scopes keep the wait-count pass
 // from tying the reads to the loads into LDS in flight, whose completion the kernels wait for explicitly.  (A scope only
@@ -61,22 +66,41 @@ __device__ __forceinline__ void read_frags(const uint8_t *__restrict__ p, const 
         a[i].u = make_uint4(v[0], v[1], v[2], v[3]);
     }
 }
+__device__ __forceinline__ void read_frag(const uint8_t *__restrict__ p, const uint8_t *__restrict__ q, Frag &a) {
+    typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
+    const u32x2_t lo = *reinterpret_cast<const u32x2_t *>(p);
+    const u32x2_t hi = *reinterpret_cast<const u32x2_t *>(q + 8);
+    a.u = make_uint4(lo[0], lo[1], hi[0], hi[1]);
+}
 __device__ __forceinline__ uint32_t read_word(const uint8_t *__restrict__ p, const uint8_t *__restrict__ q) {
     const uint32_t lo = *reinterpret_cast<const uint16_t *>(p);
     const uint32_t hi = *reinterpret_cast<const uint16_t *>(q + 2);
     return lo | (hi << 16);
 }
 
+// 4 x 4 transpose within the quads of lanes: v[q] of lane jq = 0..3 holds element (q, jq); o[p] becomes element (jq, p).
+__device__ __forceinline__ void transpose_quad(const f32x4 &v, f32x4 &o, int jq) {
+    auto pick = [&](float e0, float e1, float e2, float e3) {
+        const float lo = jq & 1 ? e1 : e0, hi = jq & 1 ? e3 : e2;
+        return jq & 2 ? hi : lo;
+    };
+    o[0] = pick(dpp_move<0x00>(v[0]), dpp_move<0x00>(v[1]), dpp_move<0x00>(v[2]), dpp_move<0x00>(v[3]));
+    o[1] = pick(dpp_move<0x55>(v[0]), dpp_move<0x55>(v[1]), dpp_move<0x55>(v[2]), dpp_move<0x55>(v[3]));
+    o[2] = pick(dpp_move<0xAA>(v[0]), dpp_move<0xAA>(v[1]), dpp_move<0xAA>(v[2]), dpp_move<0xAA>(v[3]));
+    o[3] = pick(dpp_move<0xFF>(v[0]), dpp_move<0xFF>(v[1]), dpp_move<0xFF>(v[2]), dpp_move<0xFF>(v[3]));
+}
+
+__device__ __forceinline__ void add_quad(f32x4 &v, uint2 r) {
+    v[0] += __uint_as_float(r.x << 16);
+    v[1] += __uint_as_float(r.x & 0xFFFF0000u);
+    v[2] += __uint_as_float(r.y << 16);
+    v[3] += __uint_as_float(r.y & 0xFFFF0000u);
+}
+
 // Four consecutive results of a row, at element `at` of y, of a partial (fp32, from element `part` on), or of y with a bf16
 // residual added before rounding.  N is a multiple of 16, so four columns are whole and aligned.
 __device__ __forceinline__ void store_quad(f32x4 v, void *y, int64_t at, int64_t part, int out_mode, const uint16_t *res) {
-    if (res) {
-        const uint2 rv = *reinterpret_cast<const uint2 *>(res + at);
-        v[0] += __uint_as_float(rv.x << 16);
-        v[1] += __uint_as_float(rv.x & 0xFFFF0000u);
-        v[2] += __uint_as_float(rv.y << 16);
-        v[3] += __uint_as_float(rv.y & 0xFFFF0000u);
-    }
+    if (res) add_quad(v, *reinterpret_cast<const uint2 *>(res + at));
     if (out_mode == 1)
         *reinterpret_cast<uint2 *>(reinterpret_cast<uint16_t *>(y) + at) = make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
     else

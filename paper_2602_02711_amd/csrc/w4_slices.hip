@@ -197,17 +197,10 @@ __global__ __launch_bounds__(64 * kWaves, MT == 2 && R <= 2 ? 4 : 2) void w4_sli
 #pragma unroll
                 for (int e = 0; e < 4; ++e) v[e] += w2[e];
             }
-            // 4 x 4 transpose within the quads of lanes: rows 4 c + q of column j -> columns 4 (j / 4) + p of row 4 c + j % 4
+            // rows 4 c + q of column j -> columns 4 (j / 4) + p of row 4 c + j % 4
             f32x4 o;
             const int jq = j & 3;
-            auto pick = [&](float e0, float e1, float e2, float e3) {
-                const float lo = jq & 1 ? e1 : e0, hi = jq & 1 ? e3 : e2;
-                return jq & 2 ? hi : lo;
-            };
-            o[0] = pick(dpp_move<0x00>(v[0]), dpp_move<0x00>(v[1]), dpp_move<0x00>(v[2]), dpp_move<0x00>(v[3]));
-            o[1] = pick(dpp_move<0x55>(v[0]), dpp_move<0x55>(v[1]), dpp_move<0x55>(v[2]), dpp_move<0x55>(v[3]));
-            o[2] = pick(dpp_move<0xAA>(v[0]), dpp_move<0xAA>(v[1]), dpp_move<0xAA>(v[2]), dpp_move<0xAA>(v[3]));
-            o[3] = pick(dpp_move<0xFF>(v[0]), dpp_move<0xFF>(v[1]), dpp_move<0xFF>(v[2]), dpp_move<0xFF>(v[3]));
+            transpose_quad(v, o, jq);
             const int row = (u % MT) * 16 + c * 4 + jq, tile = tileb + r0 + u / MT;
             if (row < rows && tile < tiles)
                 store_quad(o, y, (int64_t)(m0 + row) * N + (int64_t)tile * kTileRows + (j & 12), part, out_mode, res);

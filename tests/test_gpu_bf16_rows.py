@@ -1,0 +1,42 @@
+"""The bf16 kernel for 2..64 rows that keeps its activations in registers, whole outputs against fp64: every row-tile count and
+number of groups per wave, group counts that leave waves short or idle, ragged rows and runs of tiles, K whole and split."""
+import pytest
+import torch
+
+import paper_2602_02711_amd as dmr
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.mark.parametrize("M,K,N", [
+    # groups per wave 1, 2, 3, 4, 6, 8; fewer groups than waves; one tile and several to a workgroup
+    (2, 640, 4112), (3, 1152, 4112), (8, 2688, 1040), (9, 128, 272), (16, 4096, 4128), (5, 5632, 528), (12, 8192, 528),
+    (17, 896, 1040), (32, 1920, 4112), (20, 2944, 8208), (31, 3584, 528), (32, 4096, 12304),
+    (33, 1024, 4112), (48, 1152, 272), (49, 896, 4112), (64, 2048, 8208),
+    # K split
+    (16, 11008, 1040), (32, 14336, 4112), (64, 4096, 6160), (40, 5120, 5136),
+])
+def test_bf16_rows(M, K, N):
+    assert dmr.dmr_qlinear_kernel_path(dmr.DMR_FMT_BF16, M, K, N) == "bf16_rows"
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(M + K + N)
+    w = (0.02 * torch.randn((N, K), generator=gen, device=DEV)).to(torch.bfloat16)
+    x = torch.randn((M, K), generator=gen, device=DEV).to(torch.bfloat16)
+    res = torch.randn((M, N), generator=gen, device=DEV).to(torch.bfloat16)
+    ref = x.double() @ w.double().t()
+    ws = torch.full((max(dmr.dmr_qlinear_bf16_workspace_bytes(M, K, N), 16),), 0xFF, dtype=torch.uint8, device=DEV)
+    y = dmr.dmr_qlinear_bf16_forward(w, x, out_dtype=torch.float32, workspace=ws)
+    # K products in fp32, at most K / 8 of them in one chain: sqrt(K) roundings of 2^-24 of a running sum of the result's size
+    assert float((y.double() - ref).abs().max()) <= 1e-5 * float(ref.square().mean().sqrt())
+    assert torch.equal(dmr.dmr_qlinear_bf16_forward(w, x), y.to(torch.bfloat16))
+    out = res.clone()
+    dmr.dmr_qlinear_bf16_forward_fused(w, dmr.DMR_PRO_NONE, x, residual=out, out=out)
+    assert torch.equal(out, (y + res.float()).to(torch.bfloat16))
+
+
+@pytest.mark.parametrize("M,K,N,path", [(8, 1024, 2560, "bf16_skinny"), (8, 1024, 2576, "bf16_rows"),     # 2.6 million weights
+                                        (8, 8192, 4096, "bf16_rows"), (8, 8320, 4096, "bf16_skinny"),     # 64 groups held
+                                        (64, 14336, 28672, "bf16_mid")])                                  # two splits, seven needed
+def test_bf16_rows_crossover(M, K, N, path):
+    assert dmr.dmr_qlinear_kernel_path(dmr.DMR_FMT_BF16, M, K, N) == path
