@@ -36,11 +36,6 @@ struct Ring {
     static_assert(LDS <= 160 * 1024, "");
 };
 
-__device__ __forceinline__ void load_item_piece(const void *base, uint32_t bytes, uint8_t *dst, uint32_t voff, uint32_t soff) {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)bytes, 0x00020000),
-                                             (lds_void *)dst, 16, (int)voff, (int)soff, 0, 2);      // nontemporal
-}
-
 // out_mode: 0 = fp32 y, 1 = bf16 y, 2 = fp32 partial [split][M][N]
 template <int MT, int GPW>
 __global__ __launch_bounds__(64 * kWaves) void bf16_rows_kernel(const uint16_t *w, const uint16_t *x, void *y, int M, int64_t K,
@@ -72,7 +67,7 @@ __global__ __launch_bounds__(64 * kWaves) void bf16_rows_kernel(const uint16_t *
         const uint32_t soff = (uint32_t)min(tile, nt - 1) * kTileRows * rowb + (uint32_t)(g0 + gi) * 256u;
         const uint32_t bytes = tile < nt && gi < n ? wbytes : 0u;
 #pragma unroll
-        for (int p = 0; p < 4; ++p) load_item_piece(wb, bytes, ring + slot * kItem + p * 1024, voff[p], soff);
+        for (int p = 0; p < 4; ++p) stream16_to_lds(wb, bytes, ring + slot * kItem + p * 1024, voff[p], soff);
     };
 
     // The ring's first items are the activations, an item to a row tile and group, in the same shape.

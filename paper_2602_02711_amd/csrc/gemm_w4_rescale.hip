@@ -22,6 +22,13 @@
 // of 32 rows and leaves a flag; a workgroup whose columns are flagged returns at once and the 128 x 128 exact
 // kernel, launched behind this one with the same flags, computes those columns instead.
 //
+// A per-channel layer has one scale s and one zero point z per row: nothing is rescaled, every scale qualifies, and the zero-point
+// term is -s (16 + z) X with X the sum of the whole activation row, added where the result is stored.  Its pre-pass is a sum over
+// the rows (fp64 sums of fp32 parts, kept in two floats: X adds nothing to the error of the product); no second loop, no flags, no
+// kernel behind.  Measured on K x N at 1000 rows, us, through the rescaling route / this one: 4096 x 4096 51.8 / 44.1, 4096 x 6144
+// 70.0 / 61.4, 4096 x 28672 208.7 / 191.2, 14336 x 4096 140.7 / 124.8; at 8192 rows 4096 x 28672 1463 / 1360.  (The sums taken
+// inside the kernel by v_dot2 on the fragments, without a pre-pass: 54, 67, 225, 163, 1627.)
+//
 // Shape of the work.  Eight wavefronts (2 x 4), two per SIMD, in three instantiations: a 256 x 256 tile with a 128 x 64
 // patch per wave (4 x 2 tiles of v_mfma_f32_32x32x16_bf16), for grids that one round of them covers a 256 x 128
 // tile with 128 x 32 per wave (4 x 1), and for outputs of at most 256 blocks of 128 x 128 a 128 x 128 tile with 64 x 32
@@ -215,6 +222,21 @@ __device__ __forceinline__ void read_wave_factors(const uint8_t *__restrict__ p,
         rf[0] = __uint_as_float(__float_as_uint(rf[0]) | (__float_as_uint(other) & 0u));
 }
 
+// What the pre-pass leaves for the kernel: rescale factors, the operands of the zero-point term and the flags; of a per-channel
+// layer the sum of every activation row (in two floats) alone, beside the layer's own scale / zero-point words.
+template <bool PC>
+struct Prepared {
+    const float *rfac;
+    const uint16_t *a2, *b2;
+    const uint32_t *flags;
+    int KP;
+};
+template <>
+struct Prepared<true> {
+    const uint32_t *sz;
+    const float2 *rowsum;
+};
+
 // wt: the layer's codes in the streaming layout (1 KiB, 3-bit 768 B, per row tile of 16 and group; the unit of lane
 // 16 c + j of a block is row j's 32 codes of k step c).  rfac: [row tile][groups + 1][16] fp32, factor of (row, group):
 // s[G - 1] / s[G] for G >= 1, the LAST scale for G = 0 (the accumulator is zero when group 0 starts, so that slot is
@@ -222,9 +244,8 @@ __device__ __forceinline__ void read_wave_factors(const uint8_t *__restrict__ p,
 // nonzero = those columns do not qualify; a tile with a flagged part is left to the other kernel as a whole.
 template <int WM, int WN, int TM, int TN, int BITS, bool OUT_F32, bool PC, bool RES>
 __global__ __launch_bounds__(64 * WM * WN, TM * TN <= 2 ? 2 : 1) void gemm_w4_rescale_kernel(
-    const void *__restrict__ wt, const float *__restrict__ rfac, const uint16_t *__restrict__ x, const uint16_t *__restrict__ a2,
-    const uint16_t *__restrict__ b2, const uint32_t *__restrict__ flags, typename OutPtr<RES>::type y, int64_t M, int64_t K, int64_t N,
-    int KP, int nbn, int lg_xm, const uint16_t *res) {
+    const void *__restrict__ wt, const uint16_t *__restrict__ x, typename OutPtr<RES>::type y, int64_t M, int64_t K, int64_t N, int nbn,
+    int lg_xm, const uint16_t *res, Prepared<PC> prep) {
     using G = Geo<WM, WN, TM, TN, BITS>;
     constexpr int BM = G::BM, BN = G::BN, STAGE_BYTES = G::STAGE_BYTES, A_BYTES = G::A_BYTES, A2S_BYTES = G::A2S_BYTES;
     constexpr int LA = G::LA, LB = G::LB, L2 = G::L2;
@@ -250,11 +271,11 @@ __global__ __launch_bounds__(64 * WM * WN, TM * TN <= 2 ? 2 : 1) void gemm_w4_re
     }
     const int64_t n0 = (int64_t)tn * BN;
     const int64_t m0 = (int64_t)tm * BM;
-    {
+    if constexpr (!PC) {
         const int f0 = (int)(n0 / 32), nf = (int)((N + 31) / 32);
         uint32_t fl = 0;
 #pragma unroll
-        for (int i = 0; i < BN / 32; ++i) fl |= f0 + i < nf ? flags[f0 + i] : 0u;
+        for (int i = 0; i < BN / 32; ++i) fl |= f0 + i < nf ? prep.flags[f0 + i] : 0u;
         if (fl != 0) return;
     }
     const int groups = (int)(K / kGroup);
@@ -300,11 +321,11 @@ __global__ __launch_bounds__(64 * WM * WN, TM * TN <= 2 ? 2 : 1) void gemm_w4_re
     };
     // ---- factors of the wave's 64 columns (lane = column), slot g + 1 of the table: s[g] / s[g + 1]
     constexpr bool RESCALE = !PC;
-    const float *fptr;
-    {
+    const float *fptr = nullptr;
+    if constexpr (RESCALE) {
         int64_t n = n0 + wn * 32 * TN + lane;
         if (n >= N) n = N - 1;
-        fptr = rfac + ((n / kTileRows) * (groups + 1)) * kTileRows + (n % kTileRows);
+        fptr = prep.rfac + ((n / kTileRows) * (groups + 1)) * kTileRows + (n % kTileRows);
     }
     auto issue_factors = [&](int slot) {
         __builtin_amdgcn_global_load_lds((global_void *)(fptr + (int64_t)slot * kTileRows), (lds_void *)(lds + G::FAC_OFF + wave * 256), 4,
@@ -524,13 +545,17 @@ __global__ __launch_bounds__(64 * WM * WN, TM * TN <= 2 ? 2 : 1) void gemm_w4_re
     bare_barrier();
 
     const int scol = wn * 32 * TN + (lane & 31);
-    {
+    const float2 *xr = reinterpret_cast<const float2 *>(lds);
+    if constexpr (PC) {
+        if (tid < BM) reinterpret_cast<float2 *>(lds)[tid] = prep.rowsum[min(m0 + tid, M - 1)];
+        __syncthreads();
+    } else {
         float sl[TN];
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
             int64_t n = n0 + scol + j * 32;
             if (n >= N) n = N - 1;
-            sl[j] = 2.f * rfac[((n / kTileRows) * (groups + 1)) * kTileRows + (n % kTileRows)];   // the operands were (16 + q) / 2
+            sl[j] = 2.f * prep.rfac[((n / kTileRows) * (groups + 1)) * kTileRows + (n % kTileRows)];   // the operands were (16 + q) / 2
         }
 #pragma unroll
         for (int i = 0; i < TM; ++i)
@@ -542,20 +567,20 @@ __global__ __launch_bounds__(64 * WM * WN, TM * TN <= 2 ? 2 : 1) void gemm_w4_re
 
     // ---- second loop: the zero-point term, bf16 operands A2[m][.] and B2[n][.] over KP columns, both direct-to-LDS in
     // stages of 32 k; wave v fills rows [16 LA v, ..) of A2's stage half and rows [16 LB v, ..) of B2's
-    {
-        const int steps2 = KP / BK;
+    if constexpr (!PC) {
+        const int KP = prep.KP, steps2 = KP / BK;
         const uint16_t *gp[L2];
 #pragma unroll
         for (int i = 0; i < LA; ++i) {
             const int row = wave * 16 * LA + i * 16 + (lane >> 2);
             const int64_t m = m0 + row < M ? m0 + row : M - 1;
-            gp[i] = a2 + m * KP + swz(row, lane & 3) * 8;
+            gp[i] = prep.a2 + m * KP + swz(row, lane & 3) * 8;
         }
 #pragma unroll
         for (int i = 0; i < LB; ++i) {
             const int row = wave * 16 * LB + i * 16 + (lane >> 2);
             const int64_t n = n0 + row < N ? n0 + row : N - 1;
-            gp[LA + i] = b2 + n * KP + swz(row, lane & 3) * 8;
+            gp[LA + i] = prep.b2 + n * KP + swz(row, lane & 3) * 8;
         }
         int at2 = 0;
         auto issue2 = [&](int step, int stage_idx) {
@@ -608,6 +633,19 @@ __global__ __launch_bounds__(64 * WM * WN, TM * TN <= 2 ? 2 : 1) void gemm_w4_re
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
             const int64_t n = n0 + wn * 32 * TN + j * 32 + (lane & 31);
+            if constexpr (PC) {
+                // one scale s and zero point z per row of weights: y = s (2 acc - (16 + z) X), X the sum of the activations
+                const uint32_t word = prep.sz[min(n, N - 1)];
+                const float sl = __uint_as_float(word << 16), cz = __uint_as_float(word & 0xFFFF0000u) + 112.f;       // -(16 + z)
+                __builtin_amdgcn_sched_barrier(0);    // (a tile's sums in registers at a time)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+#pragma clang fp contract(off)                        // (a residual is added to the rounded product, as elsewhere)
+                    const float2 X = xr[wm * 32 * TM + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)];
+                    acc[i][j][r] = sl * fmaf(cz, X.y, fmaf(cz, X.x, 2.f * acc[i][j][r]));
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
             float rv[16];
             if constexpr (RES) {      // unconditional loads, a tile's all in flight (with the branch at run time, no template
                 // flag, the calls without a residual ran 5-7 % slower)
@@ -692,7 +730,7 @@ __device__ __forceinline__ float scale_of(uint32_t szw) { return __uint_as_float
 // One launch does both parts; the blocks of this part come first in the grid (there are few of them and each runs
 // longer than a block of the activation part, which fills the rest of the chip meanwhile).
 __global__ __launch_bounds__(256) void gemm_w4_rescale_prepass_kernel(const uint16_t *__restrict__ x, const uint32_t *__restrict__ sz,
-                                                                      int szs, uint16_t *__restrict__ a2, uint16_t *__restrict__ b2,
+                                                                      uint16_t *__restrict__ a2, uint16_t *__restrict__ b2,
                                                                       float *__restrict__ rfac, uint32_t *__restrict__ flags, int64_t M,
                                                                       int64_t K, int64_t N, int KP, int nblocks) {
     if ((int)blockIdx.x >= nblocks) {
@@ -712,7 +750,7 @@ __global__ __launch_bounds__(256) void gemm_w4_rescale_prepass_kernel(const uint
             const int tile = idx >> 9, gl = (idx >> 4) & 31, j = idx & 15;
             const int64_t n = nbase + tile * 16 + j;
             const int g = g0 + gl;
-            w_sh[tile * 16 + j][gl] = (n < N && g < groups) ? sz[sz_index(n / kTileRows, g, groups, szs, j)] : 0x3F80u;
+            w_sh[tile * 16 + j][gl] = (n < N && g < groups) ? sz[sz_index(n / kTileRows, g, groups, 1, j)] : 0x3F80u;
         }
         __syncthreads();
         if (g0 == 0) {
@@ -773,6 +811,34 @@ __global__ __launch_bounds__(256) void gemm_w4_rescale_prepass_kernel(const uint
     if (tid == 0) flags[blockIdx.x] = (uint32_t)bad;
 }
 
+// ---- pre-pass of a per-channel layer ---------------------------------------------------------------------------------
+// A block per activation row: its sum, the parts of eight in fp32, added up in fp64 (so the zero-point term adds nothing to the
+// error of the product), in two floats.
+__global__ __launch_bounds__(256) void row_sum_kernel(const uint16_t *__restrict__ x, float2 *__restrict__ rowsum, int64_t K) {
+    const uint4 *xr = reinterpret_cast<const uint4 *>(x + (int64_t)blockIdx.x * K);
+    const int units = (int)(K / 8), tid = threadIdx.x;
+    double sum = 0.;
+#pragma unroll 4
+    for (int u = tid; u < units; u += 256) {
+        const uint4 v = xr[u];
+        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+        float part = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) part += __uint_as_float(w[i] << 16) + __uint_as_float(w[i] & 0xFFFF0000u);
+        sum += (double)part;
+    }
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) sum += __shfl_xor(sum, d);
+    __shared__ double wave_sum[4];
+    if ((tid & 63) == 0) wave_sum[tid >> 6] = sum;
+    __syncthreads();
+    if (tid == 0) {
+        sum = (wave_sum[0] + wave_sum[1]) + (wave_sum[2] + wave_sum[3]);
+        const float hi = (float)sum;
+        rowsum[blockIdx.x] = make_float2(hi, fabsf(hi) < __builtin_inff() ? (float)(sum - (double)hi) : 0.f);
+    }
+}
+
 struct RescalePlan {
     int KP;
     size_t off_a2, off_b2, off_r, off_flags, total;
@@ -792,15 +858,9 @@ RescalePlan plan_rescale(int64_t M, int64_t K, int64_t N) {
 }
 
 
-struct Operands {       // what the pre-pass leaves in the workspace
-    const uint16_t *a2, *b2;
-    const float *rfac;
-    const uint32_t *flags;
-};
-
-template <int WM, int WN, int TM, int TN, int BITS>
-hipError_t launch_tile(const void *wt, bool pc, const uint16_t *x, int64_t M, int64_t K, int64_t N, void *y, bool out_f32,
-                       const uint16_t *res, const RescalePlan &p, const Operands &o, hipStream_t stream) {
+template <int WM, int WN, int TM, int TN, int BITS, bool PC>
+hipError_t launch_tile(const void *wt, const uint16_t *x, int64_t M, int64_t K, int64_t N, void *y, bool out_f32, const uint16_t *res,
+                       const Prepared<PC> &prep, hipStream_t stream) {
     using G = Geo<WM, WN, TM, TN, BITS>;
     const int nbm = (int)((M + G::BM - 1) / G::BM), nbn = (int)((N + G::BN - 1) / G::BN);
     // XCD-aware tile order when the grid of tiles divides into regions of 8 patches of 4 x 8 tiles (see the kernel)
@@ -810,25 +870,30 @@ hipError_t launch_tile(const void *wt, bool pc, const uint16_t *x, int64_t M, in
         hipError_t st = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
                                             (int)G::LDS_BYTES);
         if (st != hipSuccess) return st;
-        hipLaunchKernelGGL(kernel, dim3((unsigned)(nbm * nbn)), dim3(G::THREADS), G::LDS_BYTES, stream, wt, o.rfac, x, o.a2, o.b2,
-                           o.flags, y, M, K, N, p.KP, nbn, lg_xm, res);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(nbm * nbn)), dim3(G::THREADS), G::LDS_BYTES, stream, wt, x, y, M, K, N, nbn, lg_xm,
+                           res, prep);
         return hipGetLastError();
     };
-    auto pick = [&](auto per_channel, auto with_res) {
-        constexpr bool PC = decltype(per_channel)::value, RES = decltype(with_res)::value;
-        return out_f32 ? go(&gemm_w4_rescale_kernel<WM, WN, TM, TN, BITS, true, PC, RES>)
-                       : go(&gemm_w4_rescale_kernel<WM, WN, TM, TN, BITS, false, PC, RES>);
-    };
-    if constexpr (BITS == 4) {
-        if (pc) return res ? pick(std::true_type{}, std::true_type{}) : pick(std::true_type{}, std::false_type{});
-    }
-    return res ? pick(std::false_type{}, std::true_type{}) : pick(std::false_type{}, std::false_type{});
+    if (res)
+        return out_f32 ? go(&gemm_w4_rescale_kernel<WM, WN, TM, TN, BITS, true, PC, true>)
+                       : go(&gemm_w4_rescale_kernel<WM, WN, TM, TN, BITS, false, PC, true>);
+    return out_f32 ? go(&gemm_w4_rescale_kernel<WM, WN, TM, TN, BITS, true, PC, false>)
+                   : go(&gemm_w4_rescale_kernel<WM, WN, TM, TN, BITS, false, PC, false>);
+}
+
+template <int BITS, bool PC>
+hipError_t launch_tiles(const void *wt, int64_t K, int64_t N, const uint16_t *x, int64_t M, void *y, bool out_f32, const uint16_t *res,
+                        const Prepared<PC> &prep, hipStream_t stream) {
+    if (w4_gemm_rescale_tile_rows(M, N) == 128) return launch_tile<2, 4, 2, 1, BITS>(wt, x, M, K, N, y, out_f32, res, prep, stream);
+    if (w4_gemm_rescale_wave_columns(M, N) == 4) return launch_tile<2, 4, 4, 2, BITS>(wt, x, M, K, N, y, out_f32, res, prep, stream);
+    // 256 x 128 tiles: eight waves of 128 x 32 (measured 0-8 % ahead of four waves of 128 x 64 and of eight of 64 x 64)
+    return launch_tile<2, 4, 4, 1, BITS>(wt, x, M, K, N, y, out_f32, res, prep, stream);
 }
 
 // Pre-pass, then the rescaling kernel; the caller launches the 128 x 128 exact kernel behind them for the column blocks
 // the pre-pass flagged (normally none: its workgroups then return at once).
 template <int BITS>
-hipError_t launch_rescale(const void *wt, const uint32_t *sz, int szs, int64_t K, int64_t N, const uint16_t *x, int64_t M, void *y,
+hipError_t launch_rescale(const void *wt, const uint32_t *sz, int64_t K, int64_t N, const uint16_t *x, int64_t M, void *y,
                           bool out_f32, const uint16_t *res, void *ws, const uint32_t **flags_out, bool *pairs_out, hipStream_t stream) {
     const RescalePlan p = plan_rescale(M, K, N);
     uint8_t *base = reinterpret_cast<uint8_t *>(ws);
@@ -837,18 +902,24 @@ hipError_t launch_rescale(const void *wt, const uint32_t *sz, int szs, int64_t K
     float *rfac = reinterpret_cast<float *>(base + p.off_r);
     uint32_t *flags = reinterpret_cast<uint32_t *>(base + p.off_flags);
     const int nblocks = (int)((N + PRE_ROWS - 1) / PRE_ROWS), mblocks = (int)((M + 3) / 4);
-    hipLaunchKernelGGL(gemm_w4_rescale_prepass_kernel, dim3((unsigned)(nblocks + mblocks)), dim3(256), 0, stream, x, sz, szs, a2, b2,
+    hipLaunchKernelGGL(gemm_w4_rescale_prepass_kernel, dim3((unsigned)(nblocks + mblocks)), dim3(256), 0, stream, x, sz, a2, b2,
                        rfac, flags, M, K, N, p.KP, nblocks);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const int wn = w4_gemm_rescale_tile_rows(M, N) == 128 ? 2 : w4_gemm_rescale_wave_columns(M, N);
-    const Operands o{a2, b2, rfac, flags};
     *flags_out = flags;
-    *pairs_out = wn == 4;
-    if (wn == 4) return launch_tile<2, 4, 4, 2, BITS>(wt, szs == 0, x, M, K, N, y, out_f32, res, p, o, stream);
-    if (w4_gemm_rescale_tile_rows(M, N) == 128) return launch_tile<2, 4, 2, 1, BITS>(wt, szs == 0, x, M, K, N, y, out_f32, res, p, o, stream);
-    // 256 x 128 tiles: eight waves of 128 x 32 (measured 0-8 % ahead of four waves of 128 x 64 and of eight of 64 x 64)
-    return launch_tile<2, 4, 4, 1, BITS>(wt, szs == 0, x, M, K, N, y, out_f32, res, p, o, stream);
+    *pairs_out = w4_gemm_rescale_tile_rows(M, N) != 128 && w4_gemm_rescale_wave_columns(M, N) == 4;
+    return launch_tiles<BITS, false>(wt, K, N, x, M, y, out_f32, res, Prepared<false>{rfac, a2, b2, flags, p.KP}, stream);
+}
+
+// Per-channel layers, with nothing to rescale: the row sums (at the front of the workspace, where a call of these sizes holds at
+// least 64 bytes per row), then the kernel.
+hipError_t launch_per_channel(const LayerView &Lv, const uint16_t *x, int64_t M, void *y, bool out_f32, const uint16_t *res, void *ws,
+                              hipStream_t stream) {
+    float2 *rowsum = reinterpret_cast<float2 *>(ws);
+    hipLaunchKernelGGL(row_sum_kernel, dim3((unsigned)M), dim3(256), 0, stream, x, rowsum, Lv.K);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    return launch_tiles<4, true>(Lv.wt, Lv.K, Lv.N, x, M, y, out_f32, res, Prepared<true>{Lv.sz, rowsum}, stream);
 }
 
 }  // namespace
@@ -888,9 +959,10 @@ size_t w4_gemm_rescale_workspace_bytes(int64_t M, int64_t K, int64_t N) { return
 
 hipError_t launch_w4_gemm_rescale(const LayerView &Lv, const uint16_t *x, int64_t M, void *y, bool out_f32, const uint16_t *res,
                                   void *ws, hipStream_t stream) {
+    if (Lv.szs == 0) return launch_per_channel(Lv, x, M, y, out_f32, res, ws, stream);
     const uint32_t *flags = nullptr;
     bool pairs = false;
-    const hipError_t e = launch_rescale<4>(Lv.wt, Lv.sz, Lv.szs, Lv.K, Lv.N, x, M, y, out_f32, res, ws, &flags, &pairs, stream);
+    const hipError_t e = launch_rescale<4>(Lv.wt, Lv.sz, Lv.K, Lv.N, x, M, y, out_f32, res, ws, &flags, &pairs, stream);
     if (e != hipSuccess) return e;
     return launch_w4_gemm_flagged(Lv, x, M, y, out_f32, res, flags, pairs, stream);
 }
@@ -899,7 +971,7 @@ hipError_t launch_w3_gemm_rescale(const LayerView3 &Lv, const uint16_t *x, int64
                                   void *ws, hipStream_t stream) {
     const uint32_t *flags = nullptr;
     bool pairs = false;
-    const hipError_t e = launch_rescale<3>(Lv.wt, Lv.sz, 1, Lv.K, Lv.N, x, M, y, out_f32, res, ws, &flags, &pairs, stream);
+    const hipError_t e = launch_rescale<3>(Lv.wt, Lv.sz, Lv.K, Lv.N, x, M, y, out_f32, res, ws, &flags, &pairs, stream);
     if (e != hipSuccess) return e;
     return launch_w3_gemm_flagged(Lv, x, M, y, out_f32, res, flags, pairs, stream);
 }

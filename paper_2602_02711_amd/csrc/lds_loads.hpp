@@ -28,6 +28,11 @@ __device__ __forceinline__ void load16_to_lds(const void *base, uint32_t bytes, 
     __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)bytes, 0x00020000),
                                              (lds_void *)dst, 16, (int)voff, (int)soff, 0, 0);
 }
+// The same past the caches, for weights that are read once.
+__device__ __forceinline__ void stream16_to_lds(const void *base, uint32_t bytes, uint8_t *dst, uint32_t voff, uint32_t soff) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)bytes, 0x00020000),
+                                             (lds_void *)dst, 16, (int)voff, (int)soff, 0, 2);
+}
 __device__ __forceinline__ void load4_to_lds(const void *base, uint32_t bytes, uint8_t *dst, uint32_t voff, uint32_t soff) {
     __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)bytes, 0x00020000),
                                              (lds_void *)dst, 4, (int)voff, (int)soff, 0, 0);
