@@ -29,11 +29,16 @@
 // 70.0 / 61.4, 4096 x 28672 208.7 / 191.2, 14336 x 4096 140.7 / 124.8; at 8192 rows 4096 x 28672 1463 / 1360.  (The sums taken
 // inside the kernel by v_dot2 on the fragments, without a pre-pass: 54, 67, 225, 163, 1627.)
 //
-// Shape of the work.  Eight wavefronts (2 x 4), two per SIMD, in three instantiations: a 256 x 256 tile with a 128 x 64
-// patch per wave (4 x 2 tiles of v_mfma_f32_32x32x16_bf16), for grids that one round of them covers a 256 x 128
-// tile with 128 x 32 per wave (4 x 1), and for outputs of at most 256 blocks of 128 x 128 a 128 x 128 tile with 64 x 32
-// per wave (2 x 1; 82 registers and 74 KiB of LDS, so two workgroups share a CU).  (The kernel is written for WM x WN waves of TM x TN tiles; 256 x 128 on four
-// waves of 128 x 64 and on eight of 64 x 64 were measured 0-8 % behind and are not instantiated.)
+// Shape of the work.  Eight wavefronts, two per SIMD, in three shapes: a 256 x 256 tile with a 128 x 64 patch per wave (4 x 2 tiles
+// of v_mfma_f32_32x32x16_bf16), for grids that one round of them covers a 256 x 128 tile with 128 x 32 per wave (4 x 1), and for
+// outputs of at most 256 blocks of 128 x 128 a 128 x 128 tile.  There a wave takes 64 x 64 (2 x 2) and two waves share a patch, each
+// with every other pair of MFMA rounds, and add up at the end: an activation fragment read from LDS feeds two MFMAs and the
+// codes come once per workgroup and group instead of once per wave, where 64 x 32 patches (2 x 1; what three bits keep) read as many
+// fragments as they multiply and fetch every code twice.  Measured at 1000 rows, us, 2 x 1 / 2 x 2: per channel 4096 x 4096 44.1 / 40.8,
+// 14336 x 4096 124.8 / 115.2; groups 54.8 / 53.6 and 156 / 146; at 200 rows 4096 x 4096 37.9 / 34.7 and 50.9 / 46.2.  (The kernel is
+// written for WM x WN x S waves of TM x TN tiles; 256 x 128 on four waves of 128 x 64 and on eight of 64 x 64 were measured 0-8 %
+// behind and are not instantiated.)  What the 128 x 128 loop takes per 64 k is 0.36 us with 64 workgroups and 0.46 with 256, the
+// MFMAs alone 0.21; without its loads 0.38, without its fragment reads 0.42, without the unpacking 0.44: no single one of them.
 //
 // The weight operand never sits in LDS unpacked.  The codes of a weight row are private to the waves that own its
 // column, so nothing has to be unpacked INTO a shared stage: the packed codes travel global -> LDS as they are (32 bytes
@@ -68,10 +73,10 @@ constexpr int BK2 = 64, ROW2 = BK2 * 2, NS2 = 3;
 constexpr int BK = 32, NS = 4;
 constexpr int ROW_BYTES = BK * 2;                          // 64
 
-// WM x WN wavefronts, each on TM x TN MFMA tiles of 32 x 32; code width BITS (4 or 3).
-template <int WM, int WN, int TM, int TN, int BITS>
+// WM x WN x S wavefronts, each on TM x TN MFMA tiles of 32 x 32 and every S-th part of K; code width BITS (4 or 3).
+template <int WM, int WN, int S, int TM, int TN, int BITS>
 struct Geo {
-    static constexpr int WAVES = WM * WN, THREADS = 64 * WAVES;
+    static constexpr int WAVES = WM * WN * S, THREADS = 64 * WAVES;
     static constexpr int BM = 32 * TM * WM;                                // 256 (or 128)
     static constexpr int BN = 32 * TN * WN;                                // 128 or 256
     // first loop
@@ -79,11 +84,15 @@ struct Geo {
     // the codes of a stage: 32 bytes per weight row, two row tiles of 16 per load instruction.  Where one instruction
     // per wave covers the tile's columns exactly once, every wave reads its columns from whichever wave fetched them;
     // otherwise every wave fetches the 2 TN row tiles of its own columns into a slot of its own.
-    static constexpr bool PRIVATE_CODES = BN / kTileRows != 2 * WAVES;
+    // With S = 2 every wave fetches the codes of one row tile for a whole group with every other stage, into one of two slots.
+    static constexpr bool GROUP_CODES = S == 2;
+    static constexpr bool PRIVATE_CODES = !GROUP_CODES && BN / kTileRows != 2 * WAVES;
+    static_assert(!GROUP_CODES || BN / kTileRows == WAVES, "one row tile per wave");
     static constexpr int RI = PRIVATE_CODES ? TN : 1;                      // code load instructions per wave and stage
     static constexpr int RAWB = WAVES * RI * 1024;
-    static constexpr int STAGE = A2S_BYTES + RAWB;                         // 40 or 36 KiB (48 with private codes)
-    static constexpr int FAC_OFF = NS2 * STAGE;                            // 256 bytes of factors per wave
+    static constexpr int STAGE = A2S_BYTES + (GROUP_CODES ? 0 : RAWB);     // 40 KiB (24 or 40 with private codes; 16 or 32)
+    static constexpr int CODE_OFF = NS2 * STAGE;                           // the codes of two groups
+    static constexpr int FAC_OFF = CODE_OFF + (GROUP_CODES ? 2 * RAWB : 0);          // 256 bytes of factors per wave
     static constexpr int MAIN_BYTES = FAC_OFF + WAVES * 256;
     static constexpr int RA = A2S_BYTES / 1024 / WAVES;                    // activation load instructions per wave and stage
     static constexpr int RL = RA + RI;                                     // ... plus the codes
@@ -96,7 +105,11 @@ struct Geo {
     static constexpr int LB = BN / 16 / WAVES;                             // B2 load instructions per wave and step
     static constexpr int L2 = LA + LB;
     static_assert(LA >= 1 && LB >= 1, "whole load instructions");
-    static constexpr size_t LDS_BYTES = MAIN_BYTES > PH2_BYTES ? MAIN_BYTES : PH2_BYTES;
+    // S = 2: half of every wave's tiles, exchanged; behind them the row sums of a per-channel call
+    static constexpr int EXCHANGE = S == 2 ? WAVES * (TM * TN / 2) * 4096 : 0;
+    static constexpr int END_BYTES = EXCHANGE + BM * 8;
+    static constexpr int LOOPS = MAIN_BYTES > PH2_BYTES ? MAIN_BYTES : PH2_BYTES;
+    static constexpr size_t LDS_BYTES = LOOPS > END_BYTES ? LOOPS : END_BYTES;
 };
 
 typedef __attribute__((address_space(3))) void lds_void;
@@ -212,6 +225,14 @@ __device__ __forceinline__ void read_code_units(const uint8_t *__restrict__ p, c
         rw[0] = u32x4_t{lo[0], lo[1], hi[0], hi[1]};
     }
 }
+// (S = 2: the wave's half of the units, 8 bytes, of the column tile and of the one 2 KiB further on.)
+typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ void read_code_halves(const uint8_t *__restrict__ p, const uint8_t *__restrict__ q, u32x4_t (&rw)[2]) {
+    const u32x2_t a = *reinterpret_cast<const u32x2_t *>(p);
+    const u32x2_t b = *reinterpret_cast<const u32x2_t *>(q);
+    rw[0] = u32x4_t{a[0], a[1], 0u, 0u};
+    rw[1] = u32x4_t{b[0], b[1], 0u, 0u};
+}
 template <int TN>
 __device__ __forceinline__ void read_wave_factors(const uint8_t *__restrict__ p, const uint8_t *__restrict__ q, float (&rf)[TN]) {
     rf[0] = *reinterpret_cast<const float *>(p);
@@ -242,11 +263,11 @@ struct Prepared<true> {
 // s[G - 1] / s[G] for G >= 1, the LAST scale for G = 0 (the accumulator is zero when group 0 starts, so that slot is
 // free), 1 in the slot behind the last group.  a2 / b2: bf16 [M][KP] / [N][KP].  flags: one word per 32 columns,
 // nonzero = those columns do not qualify; a tile with a flagged part is left to the other kernel as a whole.
-template <int WM, int WN, int TM, int TN, int BITS, bool OUT_F32, bool PC, bool RES>
-__global__ __launch_bounds__(64 * WM * WN, TM * TN <= 2 ? 2 : 1) void gemm_w4_rescale_kernel(
+template <int WM, int WN, int S, int TM, int TN, int BITS, bool OUT_F32, bool PC, bool RES>
+__global__ __launch_bounds__(64 * WM * WN * S, TM * TN <= 2 ? 2 : 1) void gemm_w4_rescale_kernel(
     const void *__restrict__ wt, const uint16_t *__restrict__ x, typename OutPtr<RES>::type y, int64_t M, int64_t K, int64_t N, int nbn,
     int lg_xm, const uint16_t *res, Prepared<PC> prep) {
-    using G = Geo<WM, WN, TM, TN, BITS>;
+    using G = Geo<WM, WN, S, TM, TN, BITS>;
     constexpr int BM = G::BM, BN = G::BN, STAGE_BYTES = G::STAGE_BYTES, A_BYTES = G::A_BYTES, A2S_BYTES = G::A2S_BYTES;
     constexpr int LA = G::LA, LB = G::LB, L2 = G::L2;
     constexpr int RA = G::RA, RI = G::RI, RL = G::RL, RSTAGE = G::STAGE;
@@ -254,7 +275,8 @@ __global__ __launch_bounds__(64 * WM * WN, TM * TN <= 2 ? 2 : 1) void gemm_w4_re
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave / WN, wn = wave % WN;
+    const int wm = wave / (WN * S), wn = wave / S % WN, ks = wave % S;
+    constexpr int ROUNDS = 4 / S;                // MFMA rounds of a wave per stage
     int tm, tn;
     if (lg_xm < 0) {
         tm = (int)blockIdx.x / nbn;
@@ -295,12 +317,12 @@ __global__ __launch_bounds__(64 * WM * WN, TM * TN <= 2 ? 2 : 1) void gemm_w4_re
     int64_t unit0[RI];
 #pragma unroll
     for (int i = 0; i < RI; ++i) {
-        int64_t wT = n0 / kTileRows + (G::PRIVATE_CODES ? wn * 2 * TN + 2 * i : 2 * wave) + (lane >> 5);
+        int64_t wT = n0 / kTileRows + (G::GROUP_CODES ? wave : (G::PRIVATE_CODES ? wn * 2 * TN + 2 * i : 2 * wave) + (lane >> 5));
         if (wT >= tiles_n) wT = tiles_n - 1;
-        unit0[i] = wT * groups * 64 + (lane & 31);
+        unit0[i] = wT * groups * 64 + (G::GROUP_CODES ? lane : lane & 31);
     }
     int at = 0;                  // the stage the activation pointers stand at
-    auto issue_stage = [&](int t, int off) {
+    auto issue_stage = [&](int t, int off, bool even) {     // even: of t, a constant where this is expanded
         const int target = t < stages ? t : stages - 1;        // past the end: the last stage again, never read
         const int adv = (target - at) * BK2;
         at = target;
@@ -311,8 +333,10 @@ __global__ __launch_bounds__(64 * WM * WN, TM * TN <= 2 ? 2 : 1) void gemm_w4_re
         }
 #pragma unroll
         for (int i = 0; i < RI; ++i) {
-            const int64_t unit = unit0[i] + (int64_t)(target >> 1) * 64 + (target & 1) * 32;
-            lds_void *dst = (lds_void *)(lds + off + A2S_BYTES + (wave * RI + i) * 1024);
+            if (G::GROUP_CODES && !even) break;
+            const int64_t unit = unit0[i] + (int64_t)(target >> 1) * 64 + (G::GROUP_CODES ? 0 : (target & 1) * 32);
+            lds_void *dst = (lds_void *)(G::GROUP_CODES ? lds + G::CODE_OFF + ((t >> 1) & 1) * G::RAWB + wave * 1024
+                                                        : lds + off + A2S_BYTES + (wave * RI + i) * 1024);
             if constexpr (BITS == 4)
                 __builtin_amdgcn_global_load_lds((global_void *)(reinterpret_cast<const uint4 *>(wt) + unit), dst, 16, 0, 0);
             else   // 12 bytes per unit, fetched as 16
@@ -334,11 +358,17 @@ __global__ __launch_bounds__(64 * WM * WN, TM * TN <= 2 ? 2 : 1) void gemm_w4_re
 
     // ---- what a lane reads back: its fragment addresses within a stage
     const int arow = wm * 32 * TM + (lane & 31);
-    const int abase = arow * ROW2 + (((4 * (lane >> 5)) ^ ((lane >> 1) & 7)) * 16);    // MFMA round w: abase ^ (16 w)
-    const int rbase = A2S_BYTES + ((G::PRIVATE_CODES ? wave : wn) * 2 * TN + ((lane & 31) >> 4)) * 512 + (lane >> 5) * 256 + (lane & 15) * 16;
+    const int abase = arow * ROW2 + (((4 * (lane >> 5)) ^ ((lane >> 1) & 7)) * 16) ^ (ks * ROUNDS * 16);    // MFMA round w: abase ^ (16 w)
+    // (S = 2: + 512 v for the group's half v, + 8 ks for the wave's two words of a unit)
+    const int rbase = G::GROUP_CODES ? G::CODE_OFF + (wn * 2 * TN + ((lane & 31) >> 4)) * 1024 + (lane >> 5) * 256 + (lane & 15) * 16 + ks * 8 :
+        A2S_BYTES + ((G::PRIVATE_CODES ? wave : wn) * 2 * TN + ((lane & 31) >> 4)) * 512 + (lane >> 5) * 256 + (lane & 15) * 16;
     auto read_a = [&](int off, int w, Frag (&a)[TM]) { const uint8_t *p = lds + off + (abase ^ (w << 4));
         read_a_frags<TM>(p, p + (TM / 2) * 32 * ROW2, a); };
-    auto read_raw = [&](int off, u32x4_t (&rw)[TN]) { read_code_units<TN>(lds + off + rbase, lds + off + rbase + (TN == 2 ? 1024 : 8), rw); };
+    auto read_raw = [&](int t, int v, int off, u32x4_t (&rw)[TN]) {        // v: t & 1, a constant where this is expanded
+        if constexpr (G::GROUP_CODES) {
+            const uint8_t *p = lds + rbase + ((t >> 1) & 1) * G::RAWB + v * 512;
+            read_code_halves(p, p + 2048, rw);
+        } else read_code_units<TN>(lds + off + rbase, lds + off + rbase + (TN == 2 ? 1024 : 8), rw); };
     auto unpack_b = [&](const u32x4_t (&rw)[TN], int w, Frag (&b)[TN]) {
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
@@ -381,14 +411,15 @@ __global__ __launch_bounds__(64 * WM * WN, TM * TN <= 2 ? 2 : 1) void gemm_w4_re
 
     // ---- prologue
     int off_c = 0, off_n = RSTAGE, off_nn = 2 * RSTAGE;
-    issue_stage(0, off_c);
-    issue_stage(1, off_n);
-    issue_stage(2, off_nn);
-    wait_vmcnt<2 * RL>();
+    issue_stage(0, off_c, true);
+    issue_stage(1, off_n, false);
+    issue_stage(2, off_nn, true);
+    constexpr int RL_ODD = G::GROUP_CODES ? RA : RL;       // loads of a stage with an odd number
+    wait_vmcnt<RL + RL_ODD>();
     bare_barrier();
     u32x4_t rw[TN];
     Frag fa[2][TM], fb[2][TN];
-    read_raw(off_c, rw);
+    read_raw(0, 0, off_c, rw);
     read_a(off_c, 0, fa[0]);
     unpack_b(rw, 0, fb[0]);
     float rf[TN];
@@ -400,7 +431,8 @@ __global__ __launch_bounds__(64 * WM * WN, TM * TN <= 2 ? 2 : 1) void gemm_w4_re
 #pragma unroll
         for (int v = 0; v < 2; ++v) {
             const int t = 2 * g + v;
-            // round 0
+            // the first round
+            if constexpr (ROUNDS > 1) {
             read_a(off_c, 1, fa[1]);
             unpack_b(rw, 1, fb[1]);
             if (v == 0 && RESCALE && TILES == 2) {
@@ -458,30 +490,32 @@ __global__ __launch_bounds__(64 * WM * WN, TM * TN <= 2 ? 2 : 1) void gemm_w4_re
                 round_plain(fa[0], fb[0]);
             }
             __builtin_amdgcn_sched_barrier(0);
-            // round 1
+            }
+            if constexpr (ROUNDS == 4) {
             read_a(off_c, 2, fa[0]);
             unpack_b(rw, 2, fb[0]);
             round_plain(fa[1], fb[1]);
             __builtin_amdgcn_sched_barrier(0);
-            // round 2
             read_a(off_c, 3, fa[1]);
             unpack_b(rw, 3, fb[1]);
             round_plain(fa[0], fb[0]);
             __builtin_amdgcn_sched_barrier(0);
+            }
             // stage t + 1 has landed (and, in the second half of a group, the factors to the next group); every wave
             // has read its last fragments of stage t
-            wait_vmcnt<RL>();
+            if (v == 0) wait_vmcnt<RL>();             // (stage t + 2 is in flight)
+            else wait_vmcnt<RL_ODD>();
             if (v == 1 && RESCALE) read_wave_factors<TN>(lds + fcol, lds + fcol + 128, rf);   // the wave's own slot: no barrier needed
             bare_barrier();
-            // round 3 starts at once; the requests for stage t + 3 and the first reads of stage t + 1 go between its MFMAs
+            // the last round starts at once; the requests for stage t + 3 and the first reads of stage t + 1 go between its MFMAs
             mfma_tile(0, fa[1], fb[1]);
             __builtin_amdgcn_sched_barrier(0);
             if (v == 0 && RESCALE) issue_factors(g + 1);
-            issue_stage(t + 3, off_c);
+            issue_stage(t + 3, off_c, v == 1);
             __builtin_amdgcn_sched_barrier(0);
             mfma_tile(1, fa[1], fb[1]);
             __builtin_amdgcn_sched_barrier(0);
-            read_raw(off_n, rw);
+            read_raw(t + 1, v ^ 1, off_n, rw);
             read_a(off_n, 0, fa[0]);
             __builtin_amdgcn_sched_barrier(0);
             if constexpr (TILES > 2) mfma_tile(2, fa[1], fb[1]);
@@ -545,11 +579,7 @@ __global__ __launch_bounds__(64 * WM * WN, TM * TN <= 2 ? 2 : 1) void gemm_w4_re
     bare_barrier();
 
     const int scol = wn * 32 * TN + (lane & 31);
-    const float2 *xr = reinterpret_cast<const float2 *>(lds);
-    if constexpr (PC) {
-        if (tid < BM) reinterpret_cast<float2 *>(lds)[tid] = prep.rowsum[min(m0 + tid, M - 1)];
-        __syncthreads();
-    } else {
+    if constexpr (!PC) {
         float sl[TN];
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
@@ -605,31 +635,73 @@ __global__ __launch_bounds__(64 * WM * WN, TM * TN <= 2 ? 2 : 1) void gemm_w4_re
         for (int j = 0; j < 4; ++j) issue2(j, j);
         wait_vmcnt<3 * L2>();
         bare_barrier();
-        load_frags(lds, lds + A_BYTES, 0, fa[0], fb[0], lane, wm, wn);
+        load_frags(lds, lds + A_BYTES, ks, fa[0], fb[0], lane, wm, wn);
         for (int kt = 0; kt < steps2; ++kt) {
             const uint8_t *cur = lds + (kt & 3) * STAGE_BYTES;
             const bool more = kt + 1 < steps2;
-            load_frags(cur, cur + A_BYTES, 1, fa[1], fb[1], lane, wm, wn);
-            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (S == 1) {
+                load_frags(cur, cur + A_BYTES, 1, fa[1], fb[1], lane, wm, wn);
+                __builtin_amdgcn_sched_barrier(0);
+            }
             mfma_all(fa[0], fb[0], acc);
             __builtin_amdgcn_sched_barrier(0);
             if (more) {
                 wait_vmcnt<2 * L2>();
                 bare_barrier();
                 const uint8_t *nxt = lds + ((kt + 1) & 3) * STAGE_BYTES;
-                load_frags(nxt, nxt + A_BYTES, 0, fa[0], fb[0], lane, wm, wn);
+                load_frags(nxt, nxt + A_BYTES, ks, fa[0], fb[0], lane, wm, wn);
                 __builtin_amdgcn_sched_barrier(0);
                 issue2(kt + 4, kt & 3);
             }
             __builtin_amdgcn_sched_barrier(0);
-            mfma_all(fa[1], fb[1], acc);
+            if constexpr (S == 1) mfma_all(fa[1], fb[1], acc);
             __builtin_amdgcn_sched_barrier(0);
         }
         wait_vmcnt<0>();
     }
 
+    // S = 2: of a pair of waves the first keeps the upper half of the row tiles, the second the lower
+    constexpr int KEEP = TM / S;
+    if constexpr (S == 2) {
+        bare_barrier();                               // every wave has read its last fragments
+        float *own = reinterpret_cast<float *>(lds) + wave * (KEEP * TN * 1024) + lane * 4;
+        const float *other = reinterpret_cast<const float *>(lds) + (wave ^ 1) * (KEEP * TN * 1024) + lane * 4;
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+        for (int i = 0; i < KEEP; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; r += 4) {
+                    f32x4 v;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float lo = acc[i][j][r + e], hi = acc[KEEP + i][j][r + e];
+                        v[e] = ks ? lo : hi;
+                        acc[i][j][r + e] = ks ? hi : lo;
+                    }
+                    *reinterpret_cast<f32x4 *>(own + ((i * TN + j) * 4 + r / 4) * 256) = v;
+                }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < KEEP; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; r += 4) {
+                    const f32x4 v = *reinterpret_cast<const f32x4 *>(other + ((i * TN + j) * 4 + r / 4) * 256);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[i][j][r + e] += v[e];
+                }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    const int row0 = (wm * TM + ks * KEEP) * 32;      // of the tiles that the wave stores
+    const float2 *xr = reinterpret_cast<const float2 *>(lds + G::EXCHANGE);
+    if constexpr (PC) {
+        if (tid < BM) reinterpret_cast<float2 *>(lds + G::EXCHANGE)[tid] = prep.rowsum[min(m0 + tid, M - 1)];
+        __syncthreads();
+    }
+#pragma unroll
+    for (int i = 0; i < KEEP; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
             const int64_t n = n0 + wn * 32 * TN + j * 32 + (lane & 31);
@@ -641,23 +713,24 @@ __global__ __launch_bounds__(64 * WM * WN, TM * TN <= 2 ? 2 : 1) void gemm_w4_re
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
 #pragma clang fp contract(off)                        // (a residual is added to the rounded product, as elsewhere)
-                    const float2 X = xr[wm * 32 * TM + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)];
+                    const float2 X = xr[row0 + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)];
                     acc[i][j][r] = sl * fmaf(cz, X.y, fmaf(cz, X.x, 2.f * acc[i][j][r]));
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
             float rv[16];
+            if constexpr (RES) __builtin_amdgcn_sched_barrier(0);
             if constexpr (RES) {      // unconditional loads, a tile's all in flight (with the branch at run time, no template
                 // flag, the calls without a residual ran 5-7 % slower)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
-                    const int64_t m = min(m0 + wm * 32 * TM + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3), M - 1);
+                    const int64_t m = min(m0 + row0 + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3), M - 1);
                     rv[r] = bf16_bits_to_f32(res[m * N + min(n, N - 1)]);
                 }
             }
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                const int64_t m = m0 + wm * 32 * TM + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+                const int64_t m = m0 + row0 + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
                 if (m < M && n < N) {
                     const float v = RES ? acc[i][j][r] + rv[r] : acc[i][j][r];
                     if (OUT_F32)
@@ -858,10 +931,10 @@ RescalePlan plan_rescale(int64_t M, int64_t K, int64_t N) {
 }
 
 
-template <int WM, int WN, int TM, int TN, int BITS, bool PC>
+template <int WM, int WN, int S, int TM, int TN, int BITS, bool PC>
 hipError_t launch_tile(const void *wt, const uint16_t *x, int64_t M, int64_t K, int64_t N, void *y, bool out_f32, const uint16_t *res,
                        const Prepared<PC> &prep, hipStream_t stream) {
-    using G = Geo<WM, WN, TM, TN, BITS>;
+    using G = Geo<WM, WN, S, TM, TN, BITS>;
     const int nbm = (int)((M + G::BM - 1) / G::BM), nbn = (int)((N + G::BN - 1) / G::BN);
     // XCD-aware tile order when the grid of tiles divides into regions of 8 patches of 4 x 8 tiles (see the kernel)
     int lg_xm = 2;
@@ -875,19 +948,24 @@ hipError_t launch_tile(const void *wt, const uint16_t *x, int64_t M, int64_t K, 
         return hipGetLastError();
     };
     if (res)
-        return out_f32 ? go(&gemm_w4_rescale_kernel<WM, WN, TM, TN, BITS, true, PC, true>)
-                       : go(&gemm_w4_rescale_kernel<WM, WN, TM, TN, BITS, false, PC, true>);
-    return out_f32 ? go(&gemm_w4_rescale_kernel<WM, WN, TM, TN, BITS, true, PC, false>)
-                   : go(&gemm_w4_rescale_kernel<WM, WN, TM, TN, BITS, false, PC, false>);
+        return out_f32 ? go(&gemm_w4_rescale_kernel<WM, WN, S, TM, TN, BITS, true, PC, true>)
+                       : go(&gemm_w4_rescale_kernel<WM, WN, S, TM, TN, BITS, false, PC, true>);
+    return out_f32 ? go(&gemm_w4_rescale_kernel<WM, WN, S, TM, TN, BITS, true, PC, false>)
+                   : go(&gemm_w4_rescale_kernel<WM, WN, S, TM, TN, BITS, false, PC, false>);
 }
 
 template <int BITS, bool PC>
 hipError_t launch_tiles(const void *wt, int64_t K, int64_t N, const uint16_t *x, int64_t M, void *y, bool out_f32, const uint16_t *res,
                         const Prepared<PC> &prep, hipStream_t stream) {
-    if (w4_gemm_rescale_tile_rows(M, N) == 128) return launch_tile<2, 4, 2, 1, BITS>(wt, x, M, K, N, y, out_f32, res, prep, stream);
-    if (w4_gemm_rescale_wave_columns(M, N) == 4) return launch_tile<2, 4, 4, 2, BITS>(wt, x, M, K, N, y, out_f32, res, prep, stream);
-    // 256 x 128 tiles: eight waves of 128 x 32 (measured 0-8 % ahead of four waves of 128 x 64 and of eight of 64 x 64)
-    return launch_tile<2, 4, 4, 1, BITS>(wt, x, M, K, N, y, out_f32, res, prep, stream);
+    if (w4_gemm_rescale_tile_rows(M, N) == 128) {
+        // pairs of waves that split K; not for three bits, whose unit does not fall into halves for the two
+        if constexpr (BITS == 4) return launch_tile<2, 2, 2, 2, 2, BITS>(wt, x, M, K, N, y, out_f32, res, prep, stream);
+        else return launch_tile<2, 4, 1, 2, 1, BITS>(wt, x, M, K, N, y, out_f32, res, prep, stream);
+    }
+    if (w4_gemm_rescale_wave_columns(M, N) == 4) return launch_tile<2, 4, 1, 4, 2, BITS>(wt, x, M, K, N, y, out_f32, res, prep, stream);
+    // 256 x 128 tiles: eight waves of 128 x 32 (measured 0-8 % ahead of four waves of 128 x 64 and of eight of 64 x 64; four waves of
+    // 128 x 64 with K split between pairs, as in the small tile: level per channel, 3 % behind with groups)
+    return launch_tile<2, 4, 1, 4, 1, BITS>(wt, x, M, K, N, y, out_f32, res, prep, stream);
 }
 
 // Pre-pass, then the rescaling kernel; the caller launches the 128 x 128 exact kernel behind them for the column blocks
