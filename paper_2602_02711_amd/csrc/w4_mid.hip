@@ -199,20 +199,42 @@ __global__ __launch_bounds__(64 * NW, 2) void w4_mid_kernel(
 }
 
 // y = sum over splits of part[split], four outputs per thread, splits in ascending order; an optional residual is added
-// to the fp32 sum (a launch of its own for it cost 2-4 us and two more passes over M x N fp32).
+// to the fp32 sum (a launch of its own for it cost 2-4 us and two more passes over M x N fp32).  A launch is short and waits for
+// memory: with the number of splits known (SK; 0: any) a thread has all its loads under way at once, where a loop waited for each
+// in turn.  us in a chain of launches, loop / this: 8 x 4096 of 4
+// splits 2.63 / 2.46, of 8 3.12 / 2.57, 64 x 4096 of 7 3.17 / 2.74, 200 x 4096 of 4 level; six layers of 64 rows 412 / 398.
+template <int SK>
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *__restrict__ part, void *y,
                                                             int64_t total, int splits, int out_f32,
                                                             const uint16_t *res) {
     const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 4;
     if (i >= total) return;
-    f32x4 v = *reinterpret_cast<const f32x4 *>(part + i);
-    for (int s = 1; s < splits; ++s) {
-        const f32x4 u = *reinterpret_cast<const f32x4 *>(part + (int64_t)s * total + i);
+    // (without a residual any address: behind a branch the load would be waited for at once)
+    const uint2 r = *reinterpret_cast<const uint2 *>((res ? res : reinterpret_cast<const uint16_t *>(part)) + i);
+    f32x4 v;
+    if constexpr (SK > 0) {
+        f32x4 u[SK];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) v[k] += u[k];
+        for (int s = 0; s < SK; ++s) u[s] = *reinterpret_cast<const f32x4 *>(part + (int64_t)s * total + i);
+        v = u[0];
+#pragma unroll
+        for (int s = 1; s < SK; ++s)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) v[k] += u[s][k];
+    } else {
+        v = *reinterpret_cast<const f32x4 *>(part + i);
+        for (int s0 = 1; s0 < splits; s0 += 4) {
+            f32x4 u[4];
+#pragma unroll
+            for (int s = 0; s < 4; ++s) u[s] = *reinterpret_cast<const f32x4 *>(part + (int64_t)min(s0 + s, splits - 1) * total + i);
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+                if (s0 + s < splits)
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) v[k] += u[s][k];
+        }
     }
     if (res) {
-        const uint2 r = *reinterpret_cast<const uint2 *>(res + i);
         v[0] += __uint_as_float(r.x << 16);
         v[1] += __uint_as_float(r.x & 0xFFFF0000u);
         v[2] += __uint_as_float(r.y << 16);
@@ -268,8 +290,20 @@ hipError_t launch_mid(const void *wt, const uint32_t *sz, int szs, int64_t K, in
 
 hipError_t launch_splitk_reduce(const float *part, void *y, int64_t total, int splits, bool out_f32, const uint16_t *res,
                                 hipStream_t stream) {
-    hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)((total / 4 + 255) / 256)), dim3(256), 0, stream, part, y,
-                       total, splits, out_f32 ? 1 : 0, res);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)((total / 4 + 255) / 256)), dim3(256), 0, stream, part, y, total, splits,
+                           out_f32 ? 1 : 0, res);
+    };
+    switch (splits) {
+        case 2: go(&splitk_reduce_kernel<2>); break;
+        case 3: go(&splitk_reduce_kernel<3>); break;
+        case 4: go(&splitk_reduce_kernel<4>); break;
+        case 5: go(&splitk_reduce_kernel<5>); break;
+        case 6: go(&splitk_reduce_kernel<6>); break;
+        case 7: go(&splitk_reduce_kernel<7>); break;
+        case 8: go(&splitk_reduce_kernel<8>); break;
+        default: go(&splitk_reduce_kernel<0>);
+    }
     return hipGetLastError();
 }
 
