@@ -1,8 +1,8 @@
-// bf16 twin of the rollout-batch kernel: y[M][N] = x[M][K] . W[N][K]^T for 17 rows up to a few hundred
-// (and whenever a tiled GEMM would leave most of the 256 CUs idle), fp32 accumulation.
+// bf16 twin of the rollout-batch kernel: y[M][N] = x[M][K] . W[N][K]^T for 65 rows up to a few hundred
+// (while a tiled GEMM would leave most of the 256 CUs idle) and for 9..64 rows where bf16_rows.hip would have to split K further
+// than the workspace allows; fp32 accumulation.
 //
-// Same skeleton as the INT4 kernel of this size class, so that the two copies of a routed step are
-// compared like for like: the workgroup's BM x 128 slice of x goes through double-buffered LDS (rows
+// Same skeleton as w4_mid.hip: the workgroup's BM x 128 slice of x goes through double-buffered LDS (rows
 // padded to 272 bytes), the weights go from global memory straight into MFMA B-operand registers.
 // A lane (c, j) of a wave supplies row 16 T + j of its weight tile and, for MFMA t of a 128-wide k
 // step, the 8 values k = 32 t + 8 c .. + 7: one 16-byte load, the four lanes c of a row covering 64
