@@ -13,13 +13,15 @@ struct Bf16RowsPlan {
 
 // MT GPW 16 <= 128 registers of activations, eight waves along K; K is split as little as that allows (a split costs its partials
 // and a launch: 32 rows 4096 -> 4096 whole 11.6 us, in two 14.7; 4096 -> 28672 42.1 / 47.8), at most into max_splits, what the
-// caller's workspace holds.  Layers of up to 2.6 million weights at 2..8 rows stay with the direct-from-L2 kernel, whose workgroups
-// are smaller (512 -> 1024 4.7 / 5.0 us, 1024 -> 2048 5.4 / 5.4, 1152 -> 2064 5.8 / 6.0; 1536 -> 2048 6.2 / 6.2, 2048 -> 2048 7.4 / 6.5).
+// caller's workspace holds.  At 2..8 rows the direct-from-L2 kernel, whose workgroups are smaller, keeps layers of up to 2.6 million
+// weights, rows of up to 512, and layers of up to 4096 outputs (one round of its workgroups) while K <= 1536, or 2048 up to four rows
+// (us, that kernel / this one, 2 rows: 1024 -> 4096 4.0 / 4.4, 2048 -> 4096 6.2 / 6.4; over K = 512 .. 8192 x N = 1024 .. 16384 at 2, 4
+// and 8 rows it is ahead by 1..18 % there, behind by up to 60 % elsewhere, but for 8192 outputs at K = 2048 and 4096, 0.91 .. 0.98).
 inline Bf16RowsPlan plan_bf16_rows(int64_t M, int64_t K, int64_t N, int max_splits) {
     Bf16RowsPlan p{};
     p.ok = false;
     if (M < 2 || M > 64 || K >= (int64_t(1) << 22) || N >= (int64_t(1) << 24)) return p;      // 32-bit byte offsets
-    if (M <= 8 && K * N <= (int64_t(5) << 19)) return p;
+    if (M <= 8 && (K * N <= (int64_t(5) << 19) || K <= 512 || (N <= 4096 && K <= (M <= 4 ? 2048 : 1536)))) return p;
     const int groups = (int)(K / kGroup), tiles = (int)(N / kTileRows);
     p.MT = (int)((M + 15) / 16);
     const int held = p.MT == 1 ? 8 : p.MT == 2 ? 4 : 2;

@@ -35,7 +35,11 @@ def test_bf16_rows(M, K, N):
     assert torch.equal(out, (y + res.float()).to(torch.bfloat16))
 
 
-@pytest.mark.parametrize("M,K,N,path", [(8, 1024, 2560, "bf16_skinny"), (8, 1024, 2576, "bf16_rows"),     # 2.6 million weights
+@pytest.mark.parametrize("M,K,N,path", [(8, 512, 4112, "bf16_skinny"), (8, 640, 4112, "bf16_rows"),        # rows of up to 512
+                                        (8, 1536, 4096, "bf16_skinny"), (8, 1536, 4112, "bf16_rows"),     # one round of its workgroups
+                                        (4, 2048, 4096, "bf16_skinny"), (5, 2048, 4096, "bf16_rows"),
+                                        (64, 4096, 4096, "bf16_mid"), (32, 4096, 4096, "bf16_rows"),      # one full round, K in four
+                                        (64, 4096, 4112, "bf16_rows"), (64, 4096, 3840, "bf16_rows"),
                                         (8, 8192, 4096, "bf16_rows"), (8, 8320, 4096, "bf16_skinny"),     # 64 groups held
                                         (64, 14336, 28672, "bf16_mid")])                                  # two splits, seven needed
 def test_bf16_rows_crossover(M, K, N, path):
