@@ -20,12 +20,13 @@
 #include "lds_loads.hpp"
 #include "mid_plan.hpp"
 #include "bf16_rows_plan.hpp"
+#include "wave_share.hpp"
 
 namespace dmr {
 
 namespace {
 
-constexpr int kWaves = 8;
+constexpr int kWaves = kSharingWaves;
 constexpr int kItem = 4096;          // bytes of an item: 16 rows x 128 bf16
 
 template <int MT>
@@ -48,11 +49,9 @@ __global__ __launch_bounds__(64 * kWaves) void bf16_rows_kernel(const uint16_t *
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c = lane >> 4, j = lane & 15;
-    // this wave's groups [g0, g0 + n) and this workgroup's tiles [t0, t0 + nt)
-    const int gA = (int)blockIdx.y * gps, ng = min(groups - gA, gps);
-    const int per = ng / kWaves, rest = ng % kWaves;
-    const int n = per + (wave < rest ? 1 : 0);
-    const int g0 = gA + wave * per + min(wave, rest);
+    const WaveShare mine = wave_share(groups, gps, (int)blockIdx.y, wave);
+    const int n = mine.n;
+    // this workgroup's tiles: [t0, t0 + nt)
     const int t0 = (int)blockIdx.x * tpw, nt = min(tpw, tiles - t0);
 
     const uint32_t rowb = (uint32_t)K * 2u;
@@ -64,7 +63,7 @@ __global__ __launch_bounds__(64 * kWaves) void bf16_rows_kernel(const uint16_t *
     uint8_t *ring = smem + wave * NS * kItem;
     // item i of the wave: group i % GPW of tile i / GPW
     auto request = [&](int slot, int tile, int gi) {
-        const uint32_t soff = (uint32_t)min(tile, nt - 1) * kTileRows * rowb + (uint32_t)(g0 + gi) * 256u;
+        const uint32_t soff = (uint32_t)min(tile, nt - 1) * kTileRows * rowb + (uint32_t)requested_group(mine, gi, groups) * 256u;
         const uint32_t bytes = tile < nt && gi < n ? wbytes : 0u;
 #pragma unroll
         for (int p = 0; p < 4; ++p) stream16_to_lds(wb, bytes, ring + slot * kItem + p * 1024, voff[p], soff);
@@ -84,7 +83,7 @@ __global__ __launch_bounds__(64 * kWaves) void bf16_rows_kernel(const uint16_t *
             return;
         }
         const int gi = i / MT, mt = i % MT;
-        const uint32_t soff = (uint32_t)mt * kTileRows * rowb + (uint32_t)(g0 + gi) * 256u, bytes = gi < n ? xbytes : 0u;
+        const uint32_t soff = (uint32_t)mt * kTileRows * rowb + (uint32_t)requested_group(mine, gi, groups) * 256u, bytes = gi < n ? xbytes : 0u;
 #pragma unroll
         for (int p = 0; p < 4; ++p) load16_to_lds(x, bytes, ring + slot * kItem + p * 1024, mt == MT - 1 ? vlast[p] : voff[p], soff);
     };
@@ -112,7 +111,9 @@ __global__ __launch_bounds__(64 * kWaves) void bf16_rows_kernel(const uint16_t *
     // a lane's four results of a tile (waves 0..MT-1) and their residual, requested when the tile begins: behind the stream's
     // requests it would wait for all of them
     const int orow = wave * 16 + c * 4 + (j & 3);
-    const uint32_t rvoff = ((uint32_t)min(orow, M - 1) * (uint32_t)N + (uint32_t)(j & 12)) * 2u, rbytes = res ? (uint32_t)M * (uint32_t)N * 2u : 0u;
+    // (without a residual: no bytes, and no offset either)
+    const uint32_t rvoff = res ? ((uint32_t)min(orow, M - 1) * (uint32_t)N + (uint32_t)(j & 12)) * 2u : 0u;
+    const uint32_t rstep = res ? kTileRows * 2u : 0u, rbytes = res ? (uint32_t)M * (uint32_t)N * 2u : 0u;
     uint2 rv;
     auto reduce = [&](int tile, int buf) {            // waves 0..MT-1
         const f32x4 *src = reinterpret_cast<const f32x4 *>(smem + kWaves * NS * kItem + buf * L::RED) + wave * 64 + lane;
@@ -135,7 +136,7 @@ __global__ __launch_bounds__(64 * kWaves) void bf16_rows_kernel(const uint16_t *
         f32x4 acc[MT];
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-        rv = load_pair(res, rbytes, rvoff, (uint32_t)(t0 + tile) * kTileRows * 2u);
+        rv = load_pair(res, rbytes, rvoff, (uint32_t)(t0 + tile) * rstep);
 #pragma unroll
         for (int gi = 0; gi < GPW; ++gi) {
             const int slot = (P + gi) % NS;

@@ -20,13 +20,14 @@
 #include "mid_plan.hpp"
 #include "rows_plan.hpp"
 #include "w3_unpack.hpp"
+#include "wave_share.hpp"
 
 namespace dmr {
 
 namespace {
 
 constexpr uint32_t kOnes = 0x3F803F80u;    // bf16 pair (1.0, 1.0)
-constexpr int kWaves = 8;                  // all along k
+constexpr int kWaves = kSharingWaves;      // all along k
 
 template <int MT, int R>
 struct Geo {
@@ -50,11 +51,8 @@ __global__ __launch_bounds__(64 * kWaves, MT == 2 && R <= 2 ? 4 : 2) void w4_sli
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c = lane >> 4, j = lane & 15;
-    // this wave's groups: [g0, g0 + n)
-    const int gA = (int)blockIdx.y * gps, ng = min(groups - gA, gps);
-    const int per = ng / kWaves, rest = ng % kWaves;
-    const int n = per + (wave < rest ? 1 : 0);
-    const int g0 = gA + wave * per + min(wave, rest);
+    const WaveShare mine = wave_share(groups, gps, (int)blockIdx.y, wave);
+    const int g0 = mine.g0, n = mine.n;
     const int tileb = (int)blockIdx.x * R;            // the last workgroup may have fewer than R tiles of its own
     uint8_t *slot = smem + wave * G::SLOT;
 
@@ -111,7 +109,7 @@ __global__ __launch_bounds__(64 * kWaves, MT == 2 && R <= 2 ? 4 : 2) void w4_sli
         const uint8_t *sw = slot + G::XB + sbuf_i * G::SB;
         const int in_block = min(4, n - b);
         for (int i = 0; i < in_block; ++i) {
-            const int g = g0 + b + i;
+            const int next = requested_group(mine, b + i + 1, groups);
             const bool more = b + i + 1 < n;
             __builtin_amdgcn_sched_barrier(0);
             if (i == 0)
@@ -127,7 +125,7 @@ __global__ __launch_bounds__(64 * kWaves, MT == 2 && R <= 2 ? 4 : 2) void w4_sli
             wait_lds();                               // the slot is free
             __builtin_amdgcn_sched_barrier(0);
             f32x4 xs[MT];
-            const uint32_t xb = more ? xbytes : 0u, goff = (uint32_t)(g + 1) * 256u;
+            const uint32_t xb = more ? xbytes : 0u, goff = (uint32_t)next * 256u;
 #pragma unroll
             for (int t = 0; t < 4; ++t)
 #pragma unroll
@@ -169,7 +167,7 @@ __global__ __launch_bounds__(64 * kWaves, MT == 2 && R <= 2 ? 4 : 2) void w4_sli
                 }
                 if (r > 0) fold(r - 1);
                 __builtin_amdgcn_sched_barrier(0);    // the codes' last use lies above: the load goes to the same registers
-                fetch_codes(r, g + 1, wb);
+                fetch_codes(r, next, wb);
             }
             fold(R - 1);
         }

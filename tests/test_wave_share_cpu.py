@@ -1,0 +1,63 @@
+"""Requests of the row kernels, on the host: how the waves of a workgroup share the groups of K, and that every request, those past a
+wave's last group included, names bytes of the layer."""
+import os
+import subprocess
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+PROGRAM = r"""
+#include <cstdio>
+#include "bf16_rows_plan.hpp"
+#include "rows_plan.hpp"
+#include "wave_share.hpp"
+using namespace dmr;
+
+// The waves of all splits cover the groups once and in order; each asks for `ahead` items beyond its own.
+static int check(int groups, int gps, int splits, int held, int ahead) {
+    int next = 0;
+    for (int split = 0; split < splits; ++split)
+        for (int wave = 0; wave < kSharingWaves; ++wave) {
+            const WaveShare s = wave_share(groups, gps, split, wave);
+            if (s.g0 != next || s.n < 0 || s.n > held) return 1;
+            next += s.n;
+            for (int i = 0; i < s.n + ahead; ++i) {
+                const int g = requested_group(s, i, groups);
+                if (g < 0 || g >= groups || (i < s.n && g != s.g0 + i)) return 2;
+            }
+        }
+    return next == groups ? 0 : 3;
+}
+
+int main() {
+    for (int K = 128; K <= 20480; K += 128)
+        for (int N : {16, 272, 1024, 4096, 6160, 8208, 28672})
+            for (int M : {2, 8, 9, 16, 17, 32, 33, 48, 49, 64, 100, 250}) {
+                const int groups = K / kGroup;
+                for (int max_splits : {1, 2, 4, 8}) {
+                    int bad = 0;
+                    const Bf16RowsPlan b = plan_bf16_rows(M, K, N, max_splits);
+                    if (b.ok) bad = check(groups, b.gps, b.SK, b.GPW, b.GPW - 1);        // items of a tile: GPW, whatever the wave holds
+                    if (!bad && M >= 17) {
+                        const RowsPlan r = plan_rows(M, K, N, max_splits);
+                        if (r.slices) bad = check(groups, r.gps, r.SK, groups, 1);
+                    }
+                    if (bad) {
+                        std::printf("K=%d N=%d M=%d splits<=%d: %d\n", K, N, M, max_splits, bad);
+                        return 1;
+                    }
+                }
+            }
+    return 0;
+}
+"""
+
+
+def test_every_request_names_a_group_of_the_layer(tmp_path):
+    src, exe = tmp_path / "share.hip", tmp_path / "share"
+    src.write_text(PROGRAM)
+    inc = os.path.join(ROOT, "paper_2602_02711_amd", "csrc")
+    built = subprocess.run(["hipcc", "--offload-arch=gfx950", "--offload-host-only", "-std=c++17", "-I", inc, str(src), "-o", str(exe)],
+                           capture_output=True, text=True)
+    assert built.returncode == 0, built.stderr[-2000:]
+    ran = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert ran.returncode == 0, ran.stdout
