@@ -243,30 +243,22 @@ __device__ __forceinline__ void read_wave_factors(const uint8_t *__restrict__ p,
         rf[0] = __uint_as_float(__float_as_uint(rf[0]) | (__float_as_uint(other) & 0u));
 }
 
-// What the pre-pass leaves for the kernel: rescale factors, the operands of the zero-point term and the flags; of a per-channel
-// layer the sum of every activation row (in two floats) alone, beside the layer's own scale / zero-point words.
-template <bool PC>
-struct Prepared {
-    const float *rfac;
-    const uint16_t *a2, *b2;
-    const uint32_t *flags;
-    int KP;
-};
-template <>
-struct Prepared<true> {
-    const uint32_t *sz;
-    const float2 *rowsum;
-};
-
 // wt: the layer's codes in the streaming layout (1 KiB, 3-bit 768 B, per row tile of 16 and group; the unit of lane
 // 16 c + j of a block is row j's 32 codes of k step c).  rfac: [row tile][groups + 1][16] fp32, factor of (row, group):
 // s[G - 1] / s[G] for G >= 1, the LAST scale for G = 0 (the accumulator is zero when group 0 starts, so that slot is
 // free), 1 in the slot behind the last group.  a2 / b2: bf16 [M][KP] / [N][KP].  flags: one word per 32 columns,
-// nonzero = those columns do not qualify; a tile with a flagged part is left to the other kernel as a whole.
+// nonzero = those columns do not qualify; a tile with a flagged part is left to the other kernel as a whole.  Of a per-channel layer
+// (PC) the pre-pass leaves the sums of the activation rows alone: rfac points to them (two floats a row), flags to the layer's own
+// scale / zero-point words.
+// The arguments stay in this order and apart: as members of one struct they shortened the prologue by four words, and the 256 x 256
+// group kernel's main loop, instruction for instruction the same, began 12 bytes into a 64-byte line instead of 20 and ran 1 .. 2 %
+// slower (loop moved by padding words, 14336 -> 20480 at 450 / 8192 rows, us: 12 bytes 331.7 / 4017, 20 328 / 3973, 28 326 / 3962,
+// 32 333 / 4022, 40 326 / 3960, 48 330 / 3988, 0 332 / 4023; tests/test_kernel_resources.py holds it to the good places).
 template <int WM, int WN, int S, int TM, int TN, int BITS, bool OUT_F32, bool PC, bool RES>
 __global__ __launch_bounds__(64 * WM * WN * S, TM * TN <= 2 ? 2 : 1) void gemm_w4_rescale_kernel(
-    const void *__restrict__ wt, const uint16_t *__restrict__ x, typename OutPtr<RES>::type y, int64_t M, int64_t K, int64_t N, int nbn,
-    int lg_xm, const uint16_t *res, Prepared<PC> prep) {
+    const void *__restrict__ wt, const float *__restrict__ rfac, const uint16_t *__restrict__ x, const uint16_t *__restrict__ a2,
+    const uint16_t *__restrict__ b2, const uint32_t *__restrict__ flags, typename OutPtr<RES>::type y, int64_t M, int64_t K, int64_t N,
+    int KP, int nbn, int lg_xm, const uint16_t *res) {
     using G = Geo<WM, WN, S, TM, TN, BITS>;
     constexpr int BM = G::BM, BN = G::BN, STAGE_BYTES = G::STAGE_BYTES, A_BYTES = G::A_BYTES, A2S_BYTES = G::A2S_BYTES;
     constexpr int LA = G::LA, LB = G::LB, L2 = G::L2;
@@ -297,7 +289,7 @@ __global__ __launch_bounds__(64 * WM * WN * S, TM * TN <= 2 ? 2 : 1) void gemm_w
         const int f0 = (int)(n0 / 32), nf = (int)((N + 31) / 32);
         uint32_t fl = 0;
 #pragma unroll
-        for (int i = 0; i < BN / 32; ++i) fl |= f0 + i < nf ? prep.flags[f0 + i] : 0u;
+        for (int i = 0; i < BN / 32; ++i) fl |= f0 + i < nf ? flags[f0 + i] : 0u;
         if (fl != 0) return;
     }
     const int groups = (int)(K / kGroup);
@@ -349,7 +341,7 @@ __global__ __launch_bounds__(64 * WM * WN * S, TM * TN <= 2 ? 2 : 1) void gemm_w
     if constexpr (RESCALE) {
         int64_t n = n0 + wn * 32 * TN + lane;
         if (n >= N) n = N - 1;
-        fptr = prep.rfac + ((n / kTileRows) * (groups + 1)) * kTileRows + (n % kTileRows);
+        fptr = rfac + ((n / kTileRows) * (groups + 1)) * kTileRows + (n % kTileRows);
     }
     auto issue_factors = [&](int slot) {
         __builtin_amdgcn_global_load_lds((global_void *)(fptr + (int64_t)slot * kTileRows), (lds_void *)(lds + G::FAC_OFF + wave * 256), 4,
@@ -585,7 +577,7 @@ __global__ __launch_bounds__(64 * WM * WN * S, TM * TN <= 2 ? 2 : 1) void gemm_w
         for (int j = 0; j < TN; ++j) {
             int64_t n = n0 + scol + j * 32;
             if (n >= N) n = N - 1;
-            sl[j] = 2.f * prep.rfac[((n / kTileRows) * (groups + 1)) * kTileRows + (n % kTileRows)];   // the operands were (16 + q) / 2
+            sl[j] = 2.f * rfac[((n / kTileRows) * (groups + 1)) * kTileRows + (n % kTileRows)];   // the operands were (16 + q) / 2
         }
 #pragma unroll
         for (int i = 0; i < TM; ++i)
@@ -598,19 +590,19 @@ __global__ __launch_bounds__(64 * WM * WN * S, TM * TN <= 2 ? 2 : 1) void gemm_w
     // ---- second loop: the zero-point term, bf16 operands A2[m][.] and B2[n][.] over KP columns, both direct-to-LDS in
     // stages of 32 k; wave v fills rows [16 LA v, ..) of A2's stage half and rows [16 LB v, ..) of B2's
     if constexpr (!PC) {
-        const int KP = prep.KP, steps2 = KP / BK;
+        const int steps2 = KP / BK;
         const uint16_t *gp[L2];
 #pragma unroll
         for (int i = 0; i < LA; ++i) {
             const int row = wave * 16 * LA + i * 16 + (lane >> 2);
             const int64_t m = m0 + row < M ? m0 + row : M - 1;
-            gp[i] = prep.a2 + m * KP + swz(row, lane & 3) * 8;
+            gp[i] = a2 + m * KP + swz(row, lane & 3) * 8;
         }
 #pragma unroll
         for (int i = 0; i < LB; ++i) {
             const int row = wave * 16 * LB + i * 16 + (lane >> 2);
             const int64_t n = n0 + row < N ? n0 + row : N - 1;
-            gp[LA + i] = prep.b2 + n * KP + swz(row, lane & 3) * 8;
+            gp[LA + i] = b2 + n * KP + swz(row, lane & 3) * 8;
         }
         int at2 = 0;
         auto issue2 = [&](int step, int stage_idx) {
@@ -697,7 +689,7 @@ __global__ __launch_bounds__(64 * WM * WN * S, TM * TN <= 2 ? 2 : 1) void gemm_w
     const int row0 = (wm * TM + ks * KEEP) * 32;      // of the tiles that the wave stores
     const float2 *xr = reinterpret_cast<const float2 *>(lds + G::EXCHANGE);
     if constexpr (PC) {
-        if (tid < BM) reinterpret_cast<float2 *>(lds + G::EXCHANGE)[tid] = prep.rowsum[min(m0 + tid, M - 1)];
+        if (tid < BM) reinterpret_cast<float2 *>(lds + G::EXCHANGE)[tid] = reinterpret_cast<const float2 *>(rfac)[min(m0 + tid, M - 1)];
         __syncthreads();
     }
 #pragma unroll
@@ -707,7 +699,7 @@ __global__ __launch_bounds__(64 * WM * WN * S, TM * TN <= 2 ? 2 : 1) void gemm_w
             const int64_t n = n0 + wn * 32 * TN + j * 32 + (lane & 31);
             if constexpr (PC) {
                 // one scale s and zero point z per row of weights: y = s (2 acc - (16 + z) X), X the sum of the activations
-                const uint32_t word = prep.sz[min(n, N - 1)];
+                const uint32_t word = flags[min(n, N - 1)];
                 const float sl = __uint_as_float(word << 16), cz = __uint_as_float(word & 0xFFFF0000u) + 112.f;       // -(16 + z)
                 __builtin_amdgcn_sched_barrier(0);    // (a tile's sums in registers at a time)
 #pragma unroll
@@ -931,9 +923,16 @@ RescalePlan plan_rescale(int64_t M, int64_t K, int64_t N) {
 }
 
 
+struct Operands {       // what the pre-pass leaves for the kernel (see there)
+    const float *rfac;
+    const uint16_t *a2, *b2;
+    const uint32_t *flags;
+    int KP;
+};
+
 template <int WM, int WN, int S, int TM, int TN, int BITS, bool PC>
 hipError_t launch_tile(const void *wt, const uint16_t *x, int64_t M, int64_t K, int64_t N, void *y, bool out_f32, const uint16_t *res,
-                       const Prepared<PC> &prep, hipStream_t stream) {
+                       const Operands &o, hipStream_t stream) {
     using G = Geo<WM, WN, S, TM, TN, BITS>;
     const int nbm = (int)((M + G::BM - 1) / G::BM), nbn = (int)((N + G::BN - 1) / G::BN);
     // XCD-aware tile order when the grid of tiles divides into regions of 8 patches of 4 x 8 tiles (see the kernel)
@@ -943,8 +942,8 @@ hipError_t launch_tile(const void *wt, const uint16_t *x, int64_t M, int64_t K, 
         hipError_t st = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
                                             (int)G::LDS_BYTES);
         if (st != hipSuccess) return st;
-        hipLaunchKernelGGL(kernel, dim3((unsigned)(nbm * nbn)), dim3(G::THREADS), G::LDS_BYTES, stream, wt, x, y, M, K, N, nbn, lg_xm,
-                           res, prep);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(nbm * nbn)), dim3(G::THREADS), G::LDS_BYTES, stream, wt, o.rfac, x, o.a2, o.b2,
+                           o.flags, y, M, K, N, o.KP, nbn, lg_xm, res);
         return hipGetLastError();
     };
     if (res)
@@ -956,16 +955,16 @@ hipError_t launch_tile(const void *wt, const uint16_t *x, int64_t M, int64_t K, 
 
 template <int BITS, bool PC>
 hipError_t launch_tiles(const void *wt, int64_t K, int64_t N, const uint16_t *x, int64_t M, void *y, bool out_f32, const uint16_t *res,
-                        const Prepared<PC> &prep, hipStream_t stream) {
+                        const Operands &o, hipStream_t stream) {
     if (w4_gemm_rescale_tile_rows(M, N) == 128) {
         // pairs of waves that split K; not for three bits, whose unit does not fall into halves for the two
-        if constexpr (BITS == 4) return launch_tile<2, 2, 2, 2, 2, BITS>(wt, x, M, K, N, y, out_f32, res, prep, stream);
-        else return launch_tile<2, 4, 1, 2, 1, BITS>(wt, x, M, K, N, y, out_f32, res, prep, stream);
+        if constexpr (BITS == 4) return launch_tile<2, 2, 2, 2, 2, BITS, PC>(wt, x, M, K, N, y, out_f32, res, o, stream);
+        else return launch_tile<2, 4, 1, 2, 1, BITS, PC>(wt, x, M, K, N, y, out_f32, res, o, stream);
     }
-    if (w4_gemm_rescale_wave_columns(M, N) == 4) return launch_tile<2, 4, 1, 4, 2, BITS>(wt, x, M, K, N, y, out_f32, res, prep, stream);
+    if (w4_gemm_rescale_wave_columns(M, N) == 4) return launch_tile<2, 4, 1, 4, 2, BITS, PC>(wt, x, M, K, N, y, out_f32, res, o, stream);
     // 256 x 128 tiles: eight waves of 128 x 32 (measured 0-8 % ahead of four waves of 128 x 64 and of eight of 64 x 64; four waves of
     // 128 x 64 with K split between pairs, as in the small tile: level per channel, 3 % behind with groups)
-    return launch_tile<2, 4, 1, 4, 1, BITS>(wt, x, M, K, N, y, out_f32, res, prep, stream);
+    return launch_tile<2, 4, 1, 4, 1, BITS, PC>(wt, x, M, K, N, y, out_f32, res, o, stream);
 }
 
 // Pre-pass, then the rescaling kernel; the caller launches the 128 x 128 exact kernel behind them for the column blocks
@@ -986,7 +985,7 @@ hipError_t launch_rescale(const void *wt, const uint32_t *sz, int64_t K, int64_t
     if (e != hipSuccess) return e;
     *flags_out = flags;
     *pairs_out = w4_gemm_rescale_tile_rows(M, N) != 128 && w4_gemm_rescale_wave_columns(M, N) == 4;
-    return launch_tiles<BITS, false>(wt, K, N, x, M, y, out_f32, res, Prepared<false>{rfac, a2, b2, flags, p.KP}, stream);
+    return launch_tiles<BITS, false>(wt, K, N, x, M, y, out_f32, res, Operands{rfac, a2, b2, flags, p.KP}, stream);
 }
 
 // Per-channel layers, with nothing to rescale: the row sums (at the front of the workspace, where a call of these sizes holds at
@@ -997,7 +996,7 @@ hipError_t launch_per_channel(const LayerView &Lv, const uint16_t *x, int64_t M,
     hipLaunchKernelGGL(row_sum_kernel, dim3((unsigned)M), dim3(256), 0, stream, x, rowsum, Lv.K);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return launch_tiles<4, true>(Lv.wt, Lv.K, Lv.N, x, M, y, out_f32, res, Prepared<true>{Lv.sz, rowsum}, stream);
+    return launch_tiles<4, true>(Lv.wt, Lv.K, Lv.N, x, M, y, out_f32, res, Operands{reinterpret_cast<const float *>(rowsum), nullptr, nullptr, Lv.sz, 0}, stream);
 }
 
 }  // namespace

@@ -65,3 +65,23 @@ def test_one_row_kernel_reads_one_line_of_arguments(listings):
     text = next(t for src, t in listings.items() if os.path.basename(src) == "w3_gemv.hip")
     ends = argument_bytes(text, "w3_gemv_kernel")
     assert ends and all(v <= 64 for v in ends.values()), ends
+
+
+def test_place_of_the_long_prefill_loop(tmp_path):
+    # the main loop of the 256 x 256 INT4 group kernel without a residual, 2708 bytes: 1 .. 2 % slower where it begins 0, 4, 12 or 32 bytes
+    # into a 64-byte line, 0.5 % at 48 and 56, than at 20, 28 or 40
+    src = next(s for s in SOURCES if os.path.basename(s) == "gemm_w4_rescale.hip")
+    obj, co = str(tmp_path / "k.o"), str(tmp_path / "k.co")
+    llvm = "/opt/rocm/llvm/bin/"
+    run = lambda *cmd: subprocess.run(cmd, check=True, capture_output=True, text=True).stdout
+    run("hipcc", *[f for f in FLAGS if f != "-S"], "-c", src, "-o", obj)
+    run(llvm + "clang-offload-bundler", "--unbundle", "--type=o", "--targets=hipv4-amdgcn-amd-amdhsa--gfx950", "--input=" + obj,
+        "--output=" + co)
+    text = run(llvm + "llvm-objdump", "-d", "--no-show-raw-insn", co)
+    kernels = re.findall(r"<(\S*gemm_w4_rescale_kernelILi2ELi4ELi1ELi4ELi2ELi4ELb[01]ELb0ELb0E\S*)>:\n(.*?)\n\n", text, re.S)
+    assert len(kernels) == 2                          # bf16 and fp32 output
+    for name, body in kernels:
+        back = [(int(a, 16) + 4 + (int(off) - 65536) * 4, int(a, 16)) for off, a in
+                re.findall(r"s_cbranch_\S+ (\d+)\s*//\s*([0-9A-F]+):", body) if int(off) > 32767]
+        first, end = back[0]
+        assert 2000 < end - first < 4000 and first % 64 in (20, 28, 40), (name, first % 64, end - first)
