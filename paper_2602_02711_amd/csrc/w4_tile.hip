@@ -56,6 +56,10 @@ __global__ __launch_bounds__(64 * kWaves) void w4_tile_kernel(const void *wt, co
                                                               int64_t K, int64_t N, int groups, int tiles, int gps, int out_mode,
                                                               int szs, const uint16_t *res) {
     using G = Geo<MT, WM, S>;
+    // Whether requests past the end of a split read its last group again.  Up to 64 rows they ask for no bytes: 17 / 32 / 64 rows 1024 ->
+    // 28672 8.17 / 8.49 / 11.2 us reading, 7.70 / 8.04 / 10.9 not (two chunks to a workgroup, as many again behind them).  Above, the
+    // selects cost what the reads do at short K and up to 1 % at K = 14336.
+    constexpr bool TAIL = WM > 1;
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -84,9 +88,9 @@ __global__ __launch_bounds__(64 * kWaves) void w4_tile_kernel(const void *wt, co
         vrow[u] = RPP == 1 ? 0u : (uint32_t)(min(row0 + row_lane, rows - 1) - min(row0, rows - 1)) * rowb;
     }
     auto panel_offset = [&](int ch) { return (uint32_t)min(gA + ch * S + gl_lane, last) * 256u + lane16; };
-    auto fetch_piece = [&](int u, uint32_t koff, int buf) {
+    auto fetch_piece = [&](int u, uint32_t koff, uint32_t bytes, int buf) {
         const uint32_t swizzled = koff ^ (uint32_t)(((wave * G::XL + u) * RPP & 15) * 16);
-        load16_to_lds(xm, xbytes, smem + buf * G::PANEL + (wave * G::XL + u) * 1024, vrow[u] + swizzled, xrow[u]);
+        load16_to_lds(xm, bytes, smem + buf * G::PANEL + (wave * G::XL + u) * 1024, vrow[u] + swizzled, xrow[u]);
     };
 
     // codes and scale words of the wave's tiles (those past the layer's last tile: copies of it)
@@ -99,8 +103,8 @@ __global__ __launch_bounds__(64 * kWaves) void w4_tile_kernel(const void *wt, co
     const uint32_t wbytes = mytiles * (uint32_t)groups * BLOCK, sbytes = mytiles * (uint32_t)sz_row * 64u;
     const uint32_t wvoff = (uint32_t)lane * (BLOCK / 64), svoff = (uint32_t)j * 4u;
     Item ring[2];
-    auto fetch_codes = [&](Item &dst, int r, int g) {
-        dst.w[r] = load_codes<BITS>(wbuf, wbytes, wvoff, ((uint32_t)min(r, spare) * (uint32_t)groups + (uint32_t)g) * BLOCK);
+    auto fetch_codes = [&](Item &dst, int r, int g, uint32_t bytes) {
+        dst.w[r] = load_codes<BITS>(wbuf, bytes, wvoff, ((uint32_t)min(r, spare) * (uint32_t)groups + (uint32_t)g) * BLOCK);
     };
     auto fetch_scale = [&](Item &dst, int r, int g) {
         dst.s[r] = load_word(sbuf, sbytes, svoff, ((uint32_t)min(r, spare) * (uint32_t)sz_row + (uint32_t)(g * szs)) * 64u);
@@ -121,7 +125,9 @@ __global__ __launch_bounds__(64 * kWaves) void w4_tile_kernel(const void *wt, co
     auto chunk_step = [&](int ch, int buf) {
         Item &it = ring[buf];
         const int g = gA + ch * S + s, next = min(g + 2 * S, last);
-        const uint32_t koff = panel_offset(ch + 1);   // past the end: the last group again
+        const uint32_t koff = panel_offset(ch + 1);
+        // past the end of the split: its last group's addresses, and no bytes up to 64 rows
+        const uint32_t xb = TAIL || ch + 1 < nch ? xbytes : 0u, wb = TAIL || g + 2 * S < gE ? wbytes : 0u;
         float sc[R], cz[R];
 #pragma unroll
         for (int r = 0; r < R; ++r) {
@@ -172,10 +178,10 @@ __global__ __launch_bounds__(64 * kWaves) void w4_tile_kernel(const void *wt, co
             __builtin_amdgcn_sched_barrier(0);
             if (r < R / 2) {
 #pragma unroll
-                for (; u < (r + 1) * G::XL / (R / 2); ++u) fetch_piece(u, koff, buf ^ 1);
+                for (; u < (r + 1) * G::XL / (R / 2); ++u) fetch_piece(u, koff, xb, buf ^ 1);
             } else {
-                fetch_codes(it, 2 * r - R, next);
-                fetch_codes(it, 2 * r - R + 1, next);
+                fetch_codes(it, 2 * r - R, next, wb);
+                fetch_codes(it, 2 * r - R + 1, next, wb);
             }
         }
         fold(R - 1);
@@ -191,14 +197,14 @@ __global__ __launch_bounds__(64 * kWaves) void w4_tile_kernel(const void *wt, co
     {
         const uint32_t koff = panel_offset(0);
 #pragma unroll
-        for (int u = 0; u < G::XL; ++u) fetch_piece(u, koff, 0);
+        for (int u = 0; u < G::XL; ++u) fetch_piece(u, koff, xbytes, 0);
     }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int p = 0; p < 2; ++p) {
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            fetch_codes(ring[p], r, min(gA + p * S + s, last));
+            fetch_codes(ring[p], r, min(gA + p * S + s, last), TAIL || gA + p * S + s < gE ? wbytes : 0u);
             fetch_scale(ring[p], r, min(gA + p * S + s, last));
         }
         __builtin_amdgcn_sched_barrier(0);
