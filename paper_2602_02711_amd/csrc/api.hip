@@ -618,6 +618,7 @@ dmr_status_t dmr_probe_hbm_read(const void *d_buf, size_t bytes, uint32_t *d_sin
 
 const char *dmr_qlinear_kernel_path(dmr_format_t format, int64_t M, int64_t K, int64_t N) {
     if (M <= 0 || check_shape(K, N, dmr::kGroup) != DMR_OK) return "none";
+    auto tile = [&](int max_splits) { return !dmr::plan_rows(M, K, N, max_splits).slices; };
     auto bf16_name = [&]() -> const char * {
         if (M <= 64 && bf16_rows_plan(M, K, N).ok) return "bf16_rows";
         switch (bf16_path(M, K, N)) {
@@ -638,8 +639,10 @@ const char *dmr_qlinear_kernel_path(dmr_format_t format, int64_t M, int64_t K, i
                 case W3Path::Gemv: return "w3_gemv";
                 case W3Path::Stream: return "w3_stream";
                 case W3Path::Panel: return "w3_panel";
-                case W3Path::Wide: return "w3_wide";
-                case W3Path::Mid: return "w3_mid";
+                case W3Path::Wide:
+                case W3Path::Mid:
+                    if (!dmr::rows_kernels_fit(M, K)) return "w3_mid";
+                    return tile(splits_held(M, K, N)) ? "w3_tile" : "w3_slices";
                 case W3Path::GemmRescale:
                     if (dmr::w4_gemm_rescale_tile_rows(M, N) == 128) return "w3_gemm128_rescale";
                     return dmr::w4_gemm_rescale_wave_columns(M, N) == 4 ? "w3_gemm256_rescale" : "w3_gemm256x128_rescale";
@@ -651,9 +654,11 @@ const char *dmr_qlinear_kernel_path(dmr_format_t format, int64_t M, int64_t K, i
                 case W4Path::Gemv: return dmr::w4_gemv_fits(K, N, false) ? "w4_gemv" : "w4_skinny";
                 case W4Path::Stream: return "w4_stream";
                 case W4Path::Panel: return "w4_panel";
-                case W4Path::Wide: return "w4_wide";
-                case W4Path::Ragged: return "w4_wide";
-                case W4Path::Mid: return "w4_mid";
+                case W4Path::Wide:
+                case W4Path::Ragged:
+                case W4Path::Mid:
+                    if (!dmr::rows_kernels_fit(M, K)) return "w4_mid";
+                    return tile(w4_path(M, K, N) == W4Path::Ragged ? 1 : splits_held(M, K, N)) ? "w4_tile" : "w4_slices";
                 case W4Path::GemmRescale:
                     if (dmr::w4_gemm_rescale_tile_rows(M, N) == 128) return "w4_gemm128_rescale";
                     return dmr::w4_gemm_rescale_wave_columns(M, N) == 4 ? "w4_gemm256_rescale" : "w4_gemm256x128_rescale";

@@ -54,16 +54,18 @@ def test_bf16_tile(lib, M, K, N, name):
 
 
 @pytest.mark.parametrize("K,N,rows,splits", [
-    (1536, 12288, "mid", 1), (1536, 11008, "mid", 1),       # three chunks: one round of the rollout-batch kernel
-    (3072, 8192, "mid", 2), (6144, 4096, "mid", 4), (12288, 2048, "mid", 8),
-    (3584, 5120, "wide", 4), (7168, 4096, "wide", 7),       # 14 groups to each of its workgroups, which take four at a time
-    (4608, 4096, "wide", 5), (5120, 4096, "wide", 5),       # 9 and 10
-    (4096, 6144, "wide", 4), (14336, 4096, "wide", 7), (8192, 8192, "wide", 4), (4096, 11008, "wide", 2),
-    (1536, 16384, "wide", 1), (2560, 16384, "wide", 1),     # 1024 row tiles: halves of fewer than three chunks
-    (3072, 16384, "wide", 2), (4096, 16384, "wide", 2), (14336, 16384, "wide", 2), (4096, 28672, "wide", 1),
+    (1536, 12288, "slices", 1), (1536, 11008, "slices", 1),       # three chunks
+    (3072, 8192, "slices", 2), (6144, 4096, "slices", 4), (12288, 2048, "slices", 8),
+    (3584, 5120, "slices", 4), (7168, 4096, "slices", 7),
+    (4608, 4096, "slices", 5), (5120, 4096, "slices", 5),
+    (4096, 6144, "slices", 4), (14336, 4096, "slices", 7), (8192, 8192, "slices", 4), (4096, 11008, "slices", 2),
+    (1536, 16384, "slices", 1), (2560, 16384, "slices", 1),       # 1024 row tiles: halves of fewer than three chunks
+    (3072, 16384, "slices", 2), (4096, 16384, "slices", 2), (14336, 16384, {17: "tile", 33: "slices", 64: "slices"}, 2),
+    (4096, 28672, "tile", 1),
 ])
 @pytest.mark.parametrize("M", [17, 33, 64])
 def test_rollout_kernel_and_splits(lib, M, K, N, rows, splits):
+    rows = rows if isinstance(rows, str) else rows[M]
     need = 4 * splits * M * N if splits > 1 else 0
     for fmt, name in ((binding.DMR_FMT_W4_G128, "w4_"), (binding.DMR_FMT_W3_G128, "w3_")):
         assert lib.dmr_qlinear_kernel_path(fmt, M, K, N).decode() == name + rows
@@ -75,7 +77,7 @@ def test_long_halves_give_way_within_the_fixed_scratch(lib):
     # K = 14336 -> 12288 in two splits of 14 chunks is 11 % behind four splits of the rollout-batch kernel, whose partials
     # exceed the library's own scratch from 43 rows on
     path = lib.dmr_qlinear_kernel_path
-    assert path(binding.DMR_FMT_W4_G128, 42, 14336, 12288) == b"w4_mid"
-    assert path(binding.DMR_FMT_W4_G128, 43, 14336, 12288) == b"w4_wide"
+    for M in (42, 43):
+        assert path(binding.DMR_FMT_W4_G128, M, 14336, 12288) == b"w4_slices"
     for M in (17, 42, 43, 64):
         assert 0 < lib.dmr_qlinear_workspace_bytes(M, 14336, 12288) <= binding.DMR_STATIC_SCRATCH_BYTES

@@ -7,7 +7,7 @@ W4, PC, W3, BF16 = (binding.DMR_FMT_W4_G128, binding.DMR_FMT_W4_PER_CHANNEL, bin
 
 
 @pytest.mark.parametrize("M,K,N,path,asks", [
-    (400, 4096, 6144, "mid", False), (512, 4096, 8192, "mid", False),                    # 192 and 256 blocks of 128 x 128: one round
+    (400, 4096, 6144, "tile", False), (512, 4096, 8192, "tile", False),                    # 192 and 256 blocks of 128 x 128: one round
     (513, 4096, 6144, "gemm128_rescale", True), (400, 4096, 16384, "gemm256x128_rescale", True),
 ])
 def test_quantised_rows(M, K, N, path, asks):

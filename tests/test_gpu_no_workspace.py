@@ -56,7 +56,7 @@ def test_other_split_layers_still_refuse(K, N):
     layer = dmr.dmr_qlinear_create(*dmr.dmr_qlinear_quantize(torch.zeros((N, K), device=DEV), G), G)
     x = torch.zeros((33, K), dtype=torch.bfloat16, device=DEV)
     y = torch.empty((33, N), dtype=torch.bfloat16, device=DEV)
-    assert dmr.dmr_qlinear_kernel_path(dmr.DMR_FMT_W4_G128, 33, K, N) == "w4_wide"
+    assert dmr.dmr_qlinear_kernel_path(dmr.DMR_FMT_W4_G128, 33, K, N) == "w4_slices"
     lib = binding.lib()
     assert lib.dmr_qlinear_forward(layer.handle, x.data_ptr(), 33, y.data_ptr(), 0, None, 0, None) == binding.DMR_ERR_WORKSPACE
     assert lib.dmr_qlinear_forward_fused(layer.handle, 0, x.data_ptr(), None, 0.0, None, 33, y.data_ptr(), 0, None, 0,

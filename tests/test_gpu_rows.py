@@ -32,16 +32,23 @@ def make(fmt, w):
     return layer, exact.view(N, K)
 
 
-@pytest.mark.parametrize("M,K,N", [
-    # slices of K: one, two and four tiles; 1..4 row tiles' worth of rows, one group in all, five, eight and 29 over eight waves
-    (17, 128, 1024), (33, 640, 272), (48, 3712, 6144), (64, 384, 8208), (50, 14336, 4112), (65, 1152, 2064), (100, 128, 272),
+SLICES = [
+    # one, two and four tiles; 1..4 row tiles' worth of rows, one group in all, five, eight and 29 over eight waves
+    (17, 128, 1024), (33, 640, 272), (48, 3712, 6144), (64, 384, 8208), (65, 1152, 2064), (100, 128, 272),
     (130, 2560, 4096), (250, 512, 1040),
-    # staged panels: chunks of four groups (32, 33 and 35 of them, split and whole), then of two in blocks of 96 and 128 rows
-    (20, 4224, 16400), (40, 4480, 16400), (64, 4096, 28688), (96, 512, 28688), (97, 384, 17936), (128, 1664, 16400),
+]
+TILE = [
+    # chunks of four groups (32, 33 and 35 of them; seven splits of 16), then of two in blocks of 96 and 128 rows
+    (20, 4224, 16400), (40, 4480, 16400), (64, 4096, 28688), (50, 14336, 4112), (96, 512, 28688), (97, 384, 17936), (128, 1664, 16400),
     (200, 1664, 12304), (200, 4096, 6160), (400, 640, 6160), (512, 384, 8192),
-])
+]
+CODE = {"w4": dmr.DMR_FMT_W4_G128, "w4pc": dmr.DMR_FMT_W4_PER_CHANNEL, "w3": dmr.DMR_FMT_W3_G128}
+
+
+@pytest.mark.parametrize("M,K,N,path", [(*c, "slices") for c in SLICES] + [(*c, "tile") for c in TILE])
 @pytest.mark.parametrize("fmt", ["w4", "w4pc", "w3"])
-def test_rows(fmt, M, K, N):
+def test_rows(fmt, M, K, N, path):
+    assert dmr.dmr_qlinear_kernel_path(CODE[fmt], M, K, N) == fmt[:2] + "_" + path
     gen = torch.Generator(device=DEV)
     gen.manual_seed(M + K + N)
     layer, exact = make(fmt, 0.02 * torch.randn((N, K), generator=gen, device=DEV))

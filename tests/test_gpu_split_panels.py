@@ -12,10 +12,11 @@ DEV = "cuda:0"
 
 
 @pytest.mark.parametrize("fmt", ["w4", "w3"])
-@pytest.mark.parametrize("M,K,N", [(17, 14336, 4096), (33, 14336, 4112), (64, 11264, 2704), (48, 4096, 6144), (32, 2560, 8208)])
-def test_split_panels(fmt, M, K, N):
+@pytest.mark.parametrize("M,K,N,path", [(17, 14336, 4096, "slices"), (33, 14336, 4112, "tile"), (64, 11264, 2704, "slices"),
+                                        (48, 4096, 6144, "slices"), (32, 2560, 8208, "slices")])
+def test_split_panels(fmt, M, K, N, path):
     code = dmr.DMR_FMT_W4_G128 if fmt == "w4" else dmr.DMR_FMT_W3_G128
-    assert dmr.dmr_qlinear_kernel_path(code, M, K, N) == fmt + "_wide"
+    assert dmr.dmr_qlinear_kernel_path(code, M, K, N) == fmt + "_" + path
     gen = torch.Generator(device=DEV)
     gen.manual_seed(M + K + N)
     w = 0.02 * torch.randn((N, K), generator=gen, device=DEV)
