@@ -61,12 +61,11 @@ size_t dmr_qlinear_storage_bytes(int64_t K, int64_t N, int32_t g);
 
 /* Bytes of scratch dmr_qlinear_forward (resp. dmr_qlinear_bf16_forward) needs for this shape
  * (d_ws); may be 0, and then d_ws may be NULL.  Non-zero for batches of rollouts (a few to a few
- * hundred rows): either the activations re-ordered once per call, or fp32 partial sums when K is
- * split over workgroups because M x N alone would leave most of the chip idle.  Non-zero also for the
- * 4-bit and 3-bit tiled path (prefill, and more than 128 rows on very wide layers): per call it keeps there the operands of the zero-point
+ * hundred rows) whose K is split over workgroups because M x N alone would leave most of the chip idle:
+ * fp32 partial sums.  Non-zero also for the 4-bit and 3-bit tiled path (prefill, and more than 128 rows on very wide layers): per call it keeps there the operands of the zero-point
  * term (bf16, 12 (M + N) K / 128 bytes), one fp32 factor per (row, group) and a few flags.  A 4-bit or
- * 3-bit layer of 16384 outputs at 17 .. 64 rows also takes a smaller workspace or none, and then runs
- * without a split of K (about 15 % slower).  The workspace may arrive uninitialised; its contents are undefined after the call. */
+ * 3-bit layer of 16384 outputs or more at 17 .. 64 rows also takes a smaller workspace or none, and then runs
+ * without a split of K (few split: 17 rows from K = 9728 on, or more than 32768 outputs).  The workspace may arrive uninitialised; its contents are undefined after the call. */
 size_t dmr_qlinear_workspace_bytes(int64_t M, int64_t K, int64_t N);
 size_t dmr_qlinear_bf16_workspace_bytes(int64_t M, int64_t K, int64_t N);
 

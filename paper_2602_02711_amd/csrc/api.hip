@@ -6,8 +6,7 @@
 #include "glue.hpp"
 #include "mid_plan.hpp"
 #include "panel_plan.hpp"
-#include "rows_plan.hpp"
-#include "wide_plan.hpp"
+#include "row_splits.hpp"
 
 struct dmr_qlinear {
     int64_t K, N;
@@ -24,28 +23,12 @@ namespace {
 constexpr int64_t kSkinnyMaxM = 64;
 
 // Which INT4 kernel serves M rows of a (K, N) layer (measured crossovers, 256 CUs).  The workspace
-// query and the forward call both go through this.
-enum class W4Path { Gemv, Stream, Panel, Wide, Ragged, Mid, Gemm, GemmRescale };
-constexpr int kTiledMinBlocks = 140;
-int64_t blocks128(int64_t M, int64_t N) { return ((M + 127) / 128) * ((N + 127) / 128); }
-// Above 64 rows, both formats: whether the rows kernels serve the call, not the tiled MFMA GEMMs.  Those win from about 140 output
-// blocks of 128 x 128 on (measured: ahead at 144 and from there on, on 128-row tiles up to 256 blocks and on 256-row tiles
-// beyond; behind at 128), but not where one round of the tile kernel covers up to 512 rows (rows_fit_one_round).
-bool rows_beat_tiled(int64_t M, int64_t K, int64_t N) {
-    return M <= 128 || blocks128(M, N) < kTiledMinBlocks || dmr::rows_fit_one_round(M, K, N);
-}
-// Splits of K that the partials of a Mid call hold; one in the region that the tiled GEMMs had, whose calls need no workspace now.
-int mid_splits(int64_t M, int64_t K, int64_t N) {
-    return M <= 128 || blocks128(M, N) < kTiledMinBlocks ? dmr::plan_mid(M, K, N).SK : 1;
-}
+// query and the forward call both go through this.  Rows: the tile or the slices kernel, as rows_call says.  Mid: what neither of
+// these nor the streaming kernels take, up to 16 rows and rows of 2^24 and more.
+enum class W4Path { Gemv, Stream, Panel, Rows, Mid, Gemm, GemmRescale };
 size_t mid_workspace_bytes(int64_t M, int64_t K, int64_t N) {
-    const int sk = mid_splits(M, K, N);
+    const int sk = dmr::plan_mid(M, K, N).SK;
     return sk > 1 ? (size_t)sk * (size_t)M * (size_t)N * sizeof(float) : 0;
-}
-// Layers of 1024 row tiles whose group count is not a multiple of four, 17..64 rows: the size that their calls have always asked for
-// (activations re-ordered by a kernel that is gone).
-size_t ragged_workspace_bytes(int64_t M, int64_t K) {
-    return (size_t)(K / dmr::kGroup) * (size_t)((M + 15) / 16) * (4096 + 64);
 }
 W4Path w4_path(int64_t M, int64_t K, int64_t N) {
     if (M == 1) return W4Path::Gemv;
@@ -54,24 +37,21 @@ W4Path w4_path(int64_t M, int64_t K, int64_t N) {
         // long rows: k-sliced panels of x in LDS (measured 10-15 % ahead of the rollout-batch kernel)
         return dmr::w4_panel_applies(M, K, N) ? W4Path::Panel : W4Path::Mid;
     }
-    if (M <= kSkinnyMaxM && dmr::w4_wide_applies(M, K, N)) return W4Path::Wide;
-    if (M <= kSkinnyMaxM) return N / dmr::kTileRows >= 1024 ? W4Path::Ragged : W4Path::Mid;
-    if (rows_beat_tiled(M, K, N)) return W4Path::Mid;
+    if (M <= kSkinnyMaxM || dmr::rows_beat_tiled(M, K, N)) return dmr::rows_kernels_fit(M, K) ? W4Path::Rows : W4Path::Mid;
     return dmr::w4_gemm_rescale_applies(M, N) ? W4Path::GemmRescale : W4Path::Gemm;
 }
 
 // 3-bit layers: the 4-bit size classes on the native 3-bit kernels; a decode row too long for the GEMV's LDS
 // budget takes the rollout-batch kernel (which slices K).  The workspace query and the forward call both go
 // through this.
-enum class W3Path { Gemv, Stream, Panel, Wide, Mid, Gemm, GemmRescale };
+enum class W3Path { Gemv, Stream, Panel, Rows, Mid, Gemm, GemmRescale };
 W3Path w3_path(int64_t M, int64_t K, int64_t N) {
     if (M == 1) return dmr::w3_gemv_fits(K, N) ? W3Path::Gemv : W3Path::Mid;
     if (M <= 16) {
         if (dmr::w4_stream_fits(M, K, N)) return W3Path::Stream;
         return dmr::w4_panel_applies(M, K, N) ? W3Path::Panel : W3Path::Mid;
     }
-    if (M <= kSkinnyMaxM && dmr::w4_wide_applies(M, K, N)) return W3Path::Wide;
-    if (rows_beat_tiled(M, K, N)) return W3Path::Mid;
+    if (M <= kSkinnyMaxM || dmr::rows_beat_tiled(M, K, N)) return dmr::rows_kernels_fit(M, K) ? W3Path::Rows : W3Path::Mid;
     return dmr::w4_gemm_rescale_applies(M, N) ? W3Path::GemmRescale : W3Path::Gemm;
 }
 
@@ -146,17 +126,6 @@ dmr_status_t hip_status(hipError_t e) { return e == hipSuccess ? DMR_OK : DMR_ER
 
 namespace {
 
-// Whether M rows of this layer also run without the partials that the size query asks for: layers that give half of the CUs a
-// workgroup without a split of K always did.
-bool runs_unsplit(const dmr_qlinear_t *layer, int64_t M) {
-    return dmr::w4_wide_applies(M, layer->K, layer->N) && dmr::plan_wide(M, layer->K, layer->N, false).ok;
-}
-
-// Splits of K that a workspace of the size that the query gives holds partials for (Wide and Mid calls).
-int splits_held(int64_t M, int64_t K, int64_t N) {
-    return M <= kSkinnyMaxM && dmr::w4_wide_applies(M, K, N) ? dmr::plan_wide(M, K, N).SK : mid_splits(M, K, N);
-}
-
 // The forwards with an optional bf16 residual added where the result is stored.
 dmr_status_t forward_quant(const dmr_qlinear_t *layer, const uint16_t *d_x, int64_t M, void *d_y, dmr_out_t out,
                            const uint16_t *res, void *d_ws, size_t ws_bytes, hipStream_t s) {
@@ -171,17 +140,16 @@ dmr_status_t forward_quant(const dmr_qlinear_t *layer, const uint16_t *d_x, int6
         const dmr::LayerView3 L3{layer->K, layer->N, layer->wt3, layer->sz};
         const size_t need3 = dmr_qlinear_w3_workspace_bytes(M, layer->K, layer->N);
         if (need3 > 0 && (!d_ws || ws_bytes < need3)) {
-            if (!runs_unsplit(layer, M)) return DMR_ERR_WORKSPACE;
+            if (!dmr::runs_unsplit(M, layer->K, layer->N)) return DMR_ERR_WORKSPACE;
             d_ws = nullptr;
         }
         switch (w3_path(M, layer->K, layer->N)) {
             case W3Path::Gemv: return hip_status(dmr::launch_w3_gemv(L3, d_x, d_y, f32, res, s));
             case W3Path::Stream: return hip_status(dmr::launch_w3_stream(L3, d_x, M, d_y, f32, res, s));
             case W3Path::Panel: return hip_status(dmr::launch_w3_panel(L3, d_x, M, d_y, f32, res, d_ws, s));
-            case W3Path::Wide:
-            case W3Path::Mid:
-                if (dmr::rows_kernels_fit(M, L3.K)) return hip_status(dmr::launch_w3_rows(L3, d_x, M, d_y, f32, res, d_ws, splits_held(M, L3.K, L3.N), s));
-                return hip_status(dmr::launch_w3_mid(L3, d_x, M, d_y, f32, res, d_ws, s));
+            case W3Path::Rows:
+                return hip_status(dmr::launch_w3_rows(L3, d_x, M, d_y, f32, res, d_ws, dmr::rows_call(M, L3.K, L3.N, d_ws), s));
+            case W3Path::Mid: return hip_status(dmr::launch_w3_mid(L3, d_x, M, d_y, f32, res, d_ws, s));
             case W3Path::Gemm: return hip_status(dmr::launch_w3_gemm(L3, d_x, M, d_y, f32, res, s));
             case W3Path::GemmRescale: return hip_status(dmr::launch_w3_gemm_rescale(L3, d_x, M, d_y, f32, res, d_ws, s));
         }
@@ -189,7 +157,7 @@ dmr_status_t forward_quant(const dmr_qlinear_t *layer, const uint16_t *d_x, int6
     }
     const size_t need = dmr_qlinear_workspace_bytes(M, layer->K, layer->N);
     if (need > 0 && (!d_ws || ws_bytes < need)) {
-        if (!runs_unsplit(layer, M)) return DMR_ERR_WORKSPACE;
+        if (!dmr::runs_unsplit(M, layer->K, layer->N)) return DMR_ERR_WORKSPACE;
         d_ws = nullptr;
     }
     const dmr::LayerView L{layer->K, layer->N, layer->wt, layer->sz, layer->szs};
@@ -205,11 +173,9 @@ dmr_status_t forward_quant(const dmr_qlinear_t *layer, const uint16_t *d_x, int6
         if (e != hipErrorInvalidValue) return hip_status(e);   // else: activations do not fit LDS
     }
     if (path == W4Path::Panel) return hip_status(dmr::launch_w4_panel(L, d_x, M, d_y, f32, res, d_ws, s));
-    if (path == W4Path::Wide || path == W4Path::Mid || path == W4Path::Ragged) {
-        if (dmr::rows_kernels_fit(M, L.K))
-            return hip_status(dmr::launch_w4_rows(L, d_x, M, d_y, f32, res, d_ws, path == W4Path::Ragged ? 1 : splits_held(M, L.K, L.N), s));
-        return hip_status(dmr::launch_w4_mid(L, d_x, M, d_y, f32, res, d_ws, s));
-    }
+    if (path == W4Path::Rows)
+        return hip_status(dmr::launch_w4_rows(L, d_x, M, d_y, f32, res, d_ws, dmr::rows_call(M, L.K, L.N, d_ws), s));
+    if (path == W4Path::Mid) return hip_status(dmr::launch_w4_mid(L, d_x, M, d_y, f32, res, d_ws, s));
     if (M <= kSkinnyMaxM) return hip_status(dmr::launch_w4_skinny(L, d_x, M, d_y, f32, s));
     if (path == W4Path::GemmRescale) return hip_status(dmr::launch_w4_gemm_rescale(L, d_x, M, d_y, f32, res, d_ws, s));
     // Not reached with the present crossovers (the rescaling kernel takes every tiled shape and calls this kernel
@@ -271,8 +237,7 @@ size_t dmr_qlinear_workspace_bytes(int64_t M, int64_t K, int64_t N) {
     switch (w4_path(M, K, N)) {
         case W4Path::Mid: return mid_workspace_bytes(M, K, N);    // fp32 partials when K is split
         case W4Path::Panel: return dmr::w4_panel_workspace_bytes(M, K, N);    // likewise
-        case W4Path::Wide: return dmr::w4_wide_workspace_bytes(M, K, N);      // likewise
-        case W4Path::Ragged: return ragged_workspace_bytes(M, K);
+        case W4Path::Rows: return dmr::rows_workspace_bytes(M, K, N);         // likewise
         case W4Path::GemmRescale: return dmr::w4_gemm_rescale_workspace_bytes(M, K, N);   // zero-point operands, factors
         default: return 0;
     }
@@ -280,6 +245,8 @@ size_t dmr_qlinear_workspace_bytes(int64_t M, int64_t K, int64_t N) {
 
 size_t dmr_qlinear_bf16_workspace_bytes(int64_t M, int64_t K, int64_t N) {
     if (M <= 0 || K <= 0 || K % dmr::kGroup != 0 || N <= 0 || N % dmr::kTileRows != 0) return 0;
+    const dmr::Bf16RowsPlan rows = bf16_rows_plan(M, K, N);
+    if (rows.ok) return rows.SK > 1 ? (size_t)rows.SK * (size_t)M * (size_t)N * sizeof(float) : 0;
     return bf16_path(M, K, N) == Bf16Path::Mid ? dmr::bf16_mid_workspace_bytes(M, K, N) : 0;
 }
 
@@ -366,7 +333,7 @@ size_t dmr_qlinear_w3_workspace_bytes(int64_t M, int64_t K, int64_t N) {
     switch (w3_path(M, K, N)) {
         case W3Path::Panel: return dmr::w4_panel_workspace_bytes(M, K, N);   // fp32 partials of the k slices
         case W3Path::Mid: return mid_workspace_bytes(M, K, N);       // fp32 partials when K is split
-        case W3Path::Wide: return dmr::w4_wide_workspace_bytes(M, K, N);     // likewise
+        case W3Path::Rows: return dmr::rows_workspace_bytes(M, K, N);        // likewise
         case W3Path::GemmRescale: return dmr::w4_gemm_rescale_workspace_bytes(M, K, N);   // zero-point operands, factors
         default: return 0;
     }
@@ -548,7 +515,7 @@ dmr_status_t dmr_qlinear_forward_fused(const dmr_qlinear_t *layer, dmr_prologue_
     if (chk != DMR_OK || M == 0) return chk;
     const size_t need = dmr_qlinear_fused_workspace_bytes(layer, M, pro, d_residual != nullptr);
     if (need > 0 && (!d_ws || ws_bytes < need)) {
-        const size_t least = runs_unsplit(layer, M) ? fused_extra_bytes(M, layer->K, layer->N, pro, d_residual != nullptr) : need;
+        const size_t least = dmr::runs_unsplit(M, layer->K, layer->N) ? fused_extra_bytes(M, layer->K, layer->N, pro, d_residual != nullptr) : need;
         if (least > 0 && (!d_ws || ws_bytes < least)) return DMR_ERR_WORKSPACE;
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
@@ -618,7 +585,6 @@ dmr_status_t dmr_probe_hbm_read(const void *d_buf, size_t bytes, uint32_t *d_sin
 
 const char *dmr_qlinear_kernel_path(dmr_format_t format, int64_t M, int64_t K, int64_t N) {
     if (M <= 0 || check_shape(K, N, dmr::kGroup) != DMR_OK) return "none";
-    auto tile = [&](int max_splits) { return !dmr::plan_rows(M, K, N, max_splits).slices; };
     auto bf16_name = [&]() -> const char * {
         if (M <= 64 && bf16_rows_plan(M, K, N).ok) return "bf16_rows";
         switch (bf16_path(M, K, N)) {
@@ -639,10 +605,8 @@ const char *dmr_qlinear_kernel_path(dmr_format_t format, int64_t M, int64_t K, i
                 case W3Path::Gemv: return "w3_gemv";
                 case W3Path::Stream: return "w3_stream";
                 case W3Path::Panel: return "w3_panel";
-                case W3Path::Wide:
-                case W3Path::Mid:
-                    if (!dmr::rows_kernels_fit(M, K)) return "w3_mid";
-                    return tile(splits_held(M, K, N)) ? "w3_tile" : "w3_slices";
+                case W3Path::Rows: return dmr::rows_call(M, K, N).slices ? "w3_slices" : "w3_tile";
+                case W3Path::Mid: return "w3_mid";
                 case W3Path::GemmRescale:
                     if (dmr::w4_gemm_rescale_tile_rows(M, N) == 128) return "w3_gemm128_rescale";
                     return dmr::w4_gemm_rescale_wave_columns(M, N) == 4 ? "w3_gemm256_rescale" : "w3_gemm256x128_rescale";
@@ -654,11 +618,8 @@ const char *dmr_qlinear_kernel_path(dmr_format_t format, int64_t M, int64_t K, i
                 case W4Path::Gemv: return dmr::w4_gemv_fits(K, N, false) ? "w4_gemv" : "w4_skinny";
                 case W4Path::Stream: return "w4_stream";
                 case W4Path::Panel: return "w4_panel";
-                case W4Path::Wide:
-                case W4Path::Ragged:
-                case W4Path::Mid:
-                    if (!dmr::rows_kernels_fit(M, K)) return "w4_mid";
-                    return tile(w4_path(M, K, N) == W4Path::Ragged ? 1 : splits_held(M, K, N)) ? "w4_tile" : "w4_slices";
+                case W4Path::Rows: return dmr::rows_call(M, K, N).slices ? "w4_slices" : "w4_tile";
+                case W4Path::Mid: return "w4_mid";
                 case W4Path::GemmRescale:
                     if (dmr::w4_gemm_rescale_tile_rows(M, N) == 128) return "w4_gemm128_rescale";
                     return dmr::w4_gemm_rescale_wave_columns(M, N) == 4 ? "w4_gemm256_rescale" : "w4_gemm256x128_rescale";

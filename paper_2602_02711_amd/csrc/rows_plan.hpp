@@ -14,6 +14,12 @@ struct RowsPlan {
 
 constexpr int kTileCols = 128;      // columns of a workgroup of the tile kernel
 
+// Above 64 rows, both formats: the tiled MFMA GEMMs win from about 140 output blocks of 128 x 128 on (measured: ahead at 144 and from
+// there on, on 128-row tiles up to 256 blocks and on 256-row tiles beyond; behind at 128), but not where one round of the tile
+// kernel covers up to 512 rows (rows_fit_one_round).
+constexpr int kTiledMinBlocks = 140;
+inline int64_t blocks128(int64_t M, int64_t N) { return ((M + 127) / 128) * ((N + 127) / 128); }
+
 // Rows of activations and of a layer's tiles are addressed with 32-bit byte offsets inside a block of at most 128 rows.
 inline bool rows_kernels_fit(int64_t M, int64_t K) { return M >= 17 && K < (int64_t(1) << 24); }
 
@@ -78,6 +84,10 @@ inline bool rows_fit_one_round(int64_t M, int64_t K, int64_t N) {
     return cols * ((M + 127) / 128) <= kCus;
 }
 
+inline bool rows_beat_tiled(int64_t M, int64_t K, int64_t N) {
+    return M <= 128 || blocks128(M, N) < kTiledMinBlocks || rows_fit_one_round(M, K, N);
+}
+
 hipError_t launch_w4_tile(const LayerView &L, const uint16_t *x, int64_t M, void *y, bool out_f32, const uint16_t *res, void *ws,
                           const RowsPlan &p, hipStream_t stream);
 hipError_t launch_w3_tile(const LayerView3 &L, const uint16_t *x, int64_t M, void *y, bool out_f32, const uint16_t *res, void *ws,
@@ -87,15 +97,13 @@ hipError_t launch_w4_slices(const LayerView &L, const uint16_t *x, int64_t M, vo
 hipError_t launch_w3_slices(const LayerView3 &L, const uint16_t *x, int64_t M, void *y, bool out_f32, const uint16_t *res, void *ws,
                             const RowsPlan &p, hipStream_t stream);
 
-// `ws` holds fp32 partials for max_splits splits (nullptr: K stays whole).
+// `ws`: fp32 partials for the plan's splits.
 inline hipError_t launch_w4_rows(const LayerView &L, const uint16_t *x, int64_t M, void *y, bool out_f32, const uint16_t *res, void *ws,
-                                 int max_splits, hipStream_t stream) {
-    const RowsPlan p = plan_rows(M, L.K, L.N, ws ? max_splits : 1);
+                                 const RowsPlan &p, hipStream_t stream) {
     return (p.slices ? launch_w4_slices : launch_w4_tile)(L, x, M, y, out_f32, res, ws, p, stream);
 }
 inline hipError_t launch_w3_rows(const LayerView3 &L, const uint16_t *x, int64_t M, void *y, bool out_f32, const uint16_t *res, void *ws,
-                                 int max_splits, hipStream_t stream) {
-    const RowsPlan p = plan_rows(M, L.K, L.N, ws ? max_splits : 1);
+                                 const RowsPlan &p, hipStream_t stream) {
     return (p.slices ? launch_w3_slices : launch_w3_tile)(L, x, M, y, out_f32, res, ws, p, stream);
 }
 

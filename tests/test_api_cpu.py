@@ -35,25 +35,23 @@ def test_size_queries(lib):
     assert lib.dmr_qlinear_storage_bytes(1024, 1024, 64) == 0
     assert lib.dmr_qlinear_workspace_bytes(1, 4096, 4096) == 0
     assert lib.dmr_qlinear_workspace_bytes(16, 4096, 4096) == 0
-    # 16 < M <= 64 on a wide layer: activation panels in LDS, no workspace; when the group count is not a
-    # multiple of four: activations in MFMA operand order (4 KiB per group and row tile) plus their group sums
+    # 16 < M <= 64: nothing where K stays whole, fp32 partials of a 4-way split on long rows
     assert lib.dmr_qlinear_workspace_bytes(64, 4096, 28672) == 0
-    assert lib.dmr_qlinear_workspace_bytes(17, 4096, 28672) == 0
-    assert lib.dmr_qlinear_workspace_bytes(64, 4224, 28672) == 33 * 4 * (4096 + 64)
-    # rollout batches on layers too small to fill the chip: fp32 partials of a 4-way (8-way) split of K
-    assert lib.dmr_qlinear_workspace_bytes(64, 4096, 4096) == 4 * 64 * 4096 * 4
-    assert lib.dmr_qlinear_workspace_bytes(17, 4096, 4096) == 4 * 17 * 4096 * 4
-    assert lib.dmr_qlinear_workspace_bytes(65, 4096, 4096) == 4 * 65 * 4096 * 4
+    assert lib.dmr_qlinear_workspace_bytes(64, 4224, 28672) == 0
+    assert lib.dmr_qlinear_workspace_bytes(64, 4096, 4096) == 0
+    assert lib.dmr_qlinear_workspace_bytes(17, 14336, 4096) == 4 * 17 * 4096 * 4
+    assert lib.dmr_qlinear_workspace_bytes(64, 14336, 4096) == 4 * 64 * 4096 * 4
     assert lib.dmr_qlinear_workspace_bytes(8, 14336, 4096) == 4 * 8 * 4096 * 4    # rows exceed LDS: four k slices
     # enough column blocks: no split
     assert lib.dmr_qlinear_workspace_bytes(128, 4096, 28672) == 0
     # the tiled GEMM (more than 128 rows here): zero-point operands, rescale factors and flags
     assert lib.dmr_qlinear_workspace_bytes(200, 4096, 28672) > 200 * 192 * 2 + 28672 * 192 * 2
     assert lib.dmr_qlinear_workspace_bytes(600, 4096, 28672) > 600 * 192 * 2 + 28672 * 192 * 2
-    # the bf16 twin splits K under the same rule
+    # the bf16 twin
     assert lib.dmr_qlinear_bf16_workspace_bytes(1, 4096, 4096) == 0
     assert lib.dmr_qlinear_bf16_workspace_bytes(8, 4096, 4096) == 0
-    assert lib.dmr_qlinear_bf16_workspace_bytes(16, 4096, 4096) == 4 * 16 * 4096 * 4
+    assert lib.dmr_qlinear_bf16_workspace_bytes(16, 4096, 4096) == 0
+    assert lib.dmr_qlinear_bf16_workspace_bytes(16, 14336, 4096) == 2 * 16 * 4096 * 4
     assert lib.dmr_qlinear_bf16_workspace_bytes(64, 4096, 4096) == 4 * 64 * 4096 * 4
     assert lib.dmr_qlinear_bf16_workspace_bytes(128, 4096, 28672) == 0
     assert lib.dmr_qlinear_bf16_workspace_bytes(128, 4096, 4096) == 4 * 128 * 4096 * 4

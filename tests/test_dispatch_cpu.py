@@ -53,19 +53,15 @@ def test_bf16_tile(lib, M, K, N, name):
     assert bf16_path(lib, M, K, N).decode() == name
 
 
-@pytest.mark.parametrize("K,N,rows,splits", [
-    (1536, 12288, "slices", 1), (1536, 11008, "slices", 1),       # three chunks
-    (3072, 8192, "slices", 2), (6144, 4096, "slices", 4), (12288, 2048, "slices", 8),
-    (3584, 5120, "slices", 4), (7168, 4096, "slices", 7),
-    (4608, 4096, "slices", 5), (5120, 4096, "slices", 5),
-    (4096, 6144, "slices", 4), (14336, 4096, "slices", 7), (8192, 8192, "slices", 4), (4096, 11008, "slices", 2),
-    (1536, 16384, "slices", 1), (2560, 16384, "slices", 1),       # 1024 row tiles: halves of fewer than three chunks
-    (3072, 16384, "slices", 2), (4096, 16384, "slices", 2), (14336, 16384, {17: "tile", 33: "slices", 64: "slices"}, 2),
-    (4096, 28672, "tile", 1),
+@pytest.mark.parametrize("M,K,N,rows,splits", [
+    (33, 1536, 12288, "slices", 1), (64, 4096, 6144, "slices", 1), (64, 8192, 8192, "slices", 1), (17, 4096, 11008, "slices", 1),
+    (17, 12288, 2048, "slices", 4), (64, 12288, 2048, "slices", 4), (33, 7168, 4096, "slices", 4), (64, 14336, 4096, "slices", 4),
+    (50, 14336, 4112, "tile", 7), (64, 4096, 28672, "tile", 1), (400, 4096, 6144, "tile", 1),
+    # 1024 row tiles and more: these also run without the partials
+    (17, 11264, 16384, "tile", 2), (33, 4096, 16384, "slices", 1), (64, 14336, 16384, "slices", 1), (33, 6912, 33216, "tile", 2),
 ])
-@pytest.mark.parametrize("M", [17, 33, 64])
-def test_rollout_kernel_and_splits(lib, M, K, N, rows, splits):
-    rows = rows if isinstance(rows, str) else rows[M]
+def test_rows_kernel_and_splits(lib, M, K, N, rows, splits):
+    # the workspace is the partials of the splits that the launch makes, nothing where K stays whole
     need = 4 * splits * M * N if splits > 1 else 0
     for fmt, name in ((binding.DMR_FMT_W4_G128, "w4_"), (binding.DMR_FMT_W3_G128, "w3_")):
         assert lib.dmr_qlinear_kernel_path(fmt, M, K, N).decode() == name + rows
@@ -73,11 +69,16 @@ def test_rollout_kernel_and_splits(lib, M, K, N, rows, splits):
     assert lib.dmr_qlinear_w3_workspace_bytes(M, K, N) == need
 
 
-def test_long_halves_give_way_within_the_fixed_scratch(lib):
-    # K = 14336 -> 12288 in two splits of 14 chunks is 11 % behind four splits of the rollout-batch kernel, whose partials
-    # exceed the library's own scratch from 43 rows on
-    path = lib.dmr_qlinear_kernel_path
-    for M in (42, 43):
-        assert path(binding.DMR_FMT_W4_G128, M, 14336, 12288) == b"w4_slices"
-    for M in (17, 42, 43, 64):
-        assert 0 < lib.dmr_qlinear_workspace_bytes(M, 14336, 12288) <= binding.DMR_STATIC_SCRATCH_BYTES
+@pytest.mark.parametrize("M,K,N,splits", [
+    (32, 4096, 4096, 1), (17, 4096, 28672, 1), (32, 14336, 4096, 4), (64, 4096, 28672, 2), (64, 14336, 4096, 7), (64, 2048, 4096, 1),
+])
+def test_bf16_rows_splits(lib, M, K, N, splits):
+    assert bf16_path(lib, M, K, N) == b"bf16_rows"
+    assert lib.dmr_qlinear_bf16_workspace_bytes(M, K, N) == (4 * splits * M * N if splits > 1 else 0)
+
+
+def test_partials_of_64_rows_fit_the_fixed_scratch(lib):
+    for M in (17, 33, 42, 43, 48, 64):
+        for K in range(128, 28672, 128):
+            for N in (272, 1024, 2704, 4096, 4112, 6144, 8208, 11008, 12288, 16368):
+                assert lib.dmr_qlinear_workspace_bytes(M, K, N) <= binding.DMR_STATIC_SCRATCH_BYTES, (M, K, N)
