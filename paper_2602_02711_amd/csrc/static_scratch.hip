@@ -45,8 +45,8 @@ dmr_status_t dmr_qlinear_forward_static(const dmr_qlinear_t *layer, const uint16
     if (dmr_qlinear_shape(layer, &K, &N, nullptr) != DMR_OK) return DMR_ERR_NULL;
     const size_t need = dmr_qlinear_bits(layer) == 3 ? dmr_qlinear_w3_workspace_bytes(M, K, N)
                                                      : dmr_qlinear_workspace_bytes(M, K, N);
-    if (need > kScratchBytes) return DMR_ERR_WORKSPACE;      // beyond the fixed scratch: use dmr_qlinear_forward
-    if (need == 0) return dmr_qlinear_forward(layer, d_x, M, d_y, out, nullptr, 0, stream);
+    // beyond the fixed scratch: refused (use dmr_qlinear_forward with a workspace), or unsplit where the layer also runs so
+    if (need == 0 || need > kScratchBytes) return dmr_qlinear_forward(layer, d_x, M, d_y, out, nullptr, 0, stream);
     void *ws = nullptr;
     const dmr_status_t st = scratch_on_current_device(&ws);
     if (st != DMR_OK) return st;

@@ -78,3 +78,19 @@ def test_forward_static_refuses_what_exceeds_its_scratch():
     lib = binding.lib()
     assert lib.dmr_qlinear_forward_static(None, x.data_ptr(), M, y.data_ptr(), 1, None) == binding.DMR_ERR_NULL
     assert lib.dmr_qlinear_forward_static(layer.handle, x.data_ptr(), 0, y.data_ptr(), 1, None) == binding.DMR_OK
+
+
+@pytest.mark.parametrize("bits", [4, 3])
+def test_forward_static_runs_wide_layers_unsplit(bits):
+    # partials of two splits exceed the scratch; such layers also run without
+    M, K, N = 33, 6912, 33216
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(9730)
+    w = 0.02 * torch.randn((N, K), generator=gen, device=DEV)
+    x = torch.randn((M, K), generator=gen, device=DEV).to(torch.bfloat16)
+    layer = dmr.dmr_qlinear_create(*dmr.dmr_qlinear_quantize(w, G), G) if bits == 4 else \
+        dmr.dmr_qlinear_w3_create(*dmr.dmr_qlinear_quantize_w3(w, G), G)
+    need = (dmr.dmr_qlinear_workspace_bytes if bits == 4 else dmr.dmr_qlinear_w3_workspace_bytes)(M, K, N)
+    assert need > binding.DMR_STATIC_SCRATCH_BYTES
+    want = dmr.dmr_qlinear_forward(layer, x, out_dtype=torch.float32, workspace=torch.empty(16, dtype=torch.uint8, device=DEV))
+    assert torch.equal(dmr.dmr_qlinear_forward_static(layer, x, out_dtype=torch.float32), want)
