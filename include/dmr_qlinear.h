@@ -62,10 +62,12 @@ size_t dmr_qlinear_storage_bytes(int64_t K, int64_t N, int32_t g);
 /* Bytes of scratch dmr_qlinear_forward (resp. dmr_qlinear_bf16_forward) needs for this shape
  * (d_ws); may be 0, and then d_ws may be NULL.  Non-zero for batches of rollouts (a few to a few
  * hundred rows) whose K is split over workgroups because M x N alone would leave most of the chip idle:
- * fp32 partial sums.  Non-zero also for the 4-bit and 3-bit tiled path (prefill, and more than 128 rows on very wide layers): per call it keeps there the operands of the zero-point
- * term (bf16, 12 (M + N) K / 128 bytes), one fp32 factor per (row, group) and a few flags.  A 4-bit or
+ * fp32 partial sums.  Non-zero also for the 4-bit and 3-bit tiled path (prefill, and more than 128 rows on
+ * very wide layers): per call it keeps there the operands of the zero-point term (bf16, 12 (M + N) K / 128 bytes), one fp32 factor per (row, group) and a few flags (a
+ * per-channel layer 8 bytes per row of x, and then takes a workspace of that size).  A 4-bit or
  * 3-bit layer of 16384 outputs or more at 17 .. 64 rows also takes a smaller workspace or none, and then runs
- * without a split of K (few split: 17 rows from K = 9728 on, or more than 32768 outputs).  The workspace may arrive uninitialised; its contents are undefined after the call. */
+ * without a split of K (few split: 17 rows from K = 9728 on, or more than 32768 outputs).  The workspace may
+ * arrive uninitialised; its contents are undefined after the call. */
 size_t dmr_qlinear_workspace_bytes(int64_t M, int64_t K, int64_t N);
 size_t dmr_qlinear_bf16_workspace_bytes(int64_t M, int64_t K, int64_t N);
 
@@ -118,12 +120,12 @@ dmr_status_t dmr_qlinear_forward(const dmr_qlinear_t *layer, const uint16_t *d_x
  * dmr_qlinear_forward for callers that cannot allocate device memory and therefore cannot bring the
  * workspace: code running under HIP-graph capture, tight serving loops, harnesses that forbid hipMalloc.
  * Same arguments, results (bit for bit) and errors as dmr_qlinear_forward, minus d_ws / ws_bytes: the
- * scratch (fp32 partial sums of the kernels that split K, re-ordered activations, the tiled path's
- * zero-point operands) is a fixed array of
+ * scratch (fp32 partial sums of the kernels that split K, the tiled path's zero-point operands) is a fixed array of
  * DMR_STATIC_SCRATCH_BYTES in device memory that belongs to the library itself; each GPU the library runs
  * on holds one copy until the process ends.  The call allocates and frees nothing.  A shape whose
  * dmr_qlinear_workspace_bytes (dmr_qlinear_w3_workspace_bytes for a 3-bit layer) exceeds that size is
- * refused with DMR_ERR_WORKSPACE before anything is launched; such calls go through dmr_qlinear_forward.
+ * refused with DMR_ERR_WORKSPACE before anything is launched, but for layers that dmr_qlinear_forward also runs without
+ * it; such calls go through dmr_qlinear_forward.
  * All calls on one GPU share the one array: two calls whose work overlaps in time on the same GPU (different
  * streams, or threads) race on it; calls on one stream are ordered and safe.  Nothing needs clearing
  * between calls.  The first call on a device looks up the array's address (one runtime query).

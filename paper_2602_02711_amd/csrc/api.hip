@@ -126,6 +126,14 @@ dmr_status_t hip_status(hipError_t e) { return e == hipSuccess ? DMR_OK : DMR_ER
 
 namespace {
 
+// What M rows of this layer take: what the query says for the shape, less for the tiled kernels of a per-channel layer, which keep the
+// sums of the activation rows alone there.
+size_t layer_workspace_bytes(const dmr_qlinear_t *layer, int64_t M) {
+    if (layer->bits == 3) return dmr_qlinear_w3_workspace_bytes(M, layer->K, layer->N);
+    if (layer->szs == 0 && w4_path(M, layer->K, layer->N) == W4Path::GemmRescale) return (size_t)M * sizeof(float2);
+    return dmr_qlinear_workspace_bytes(M, layer->K, layer->N);
+}
+
 // The forwards with an optional bf16 residual added where the result is stored.
 dmr_status_t forward_quant(const dmr_qlinear_t *layer, const uint16_t *d_x, int64_t M, void *d_y, dmr_out_t out,
                            const uint16_t *res, void *d_ws, size_t ws_bytes, hipStream_t s) {
@@ -138,7 +146,7 @@ dmr_status_t forward_quant(const dmr_qlinear_t *layer, const uint16_t *d_x, int6
     const bool f32 = out == DMR_OUT_FP32;
     if (layer->bits == 3) {
         const dmr::LayerView3 L3{layer->K, layer->N, layer->wt3, layer->sz};
-        const size_t need3 = dmr_qlinear_w3_workspace_bytes(M, layer->K, layer->N);
+        const size_t need3 = layer_workspace_bytes(layer, M);
         if (need3 > 0 && (!d_ws || ws_bytes < need3)) {
             if (!dmr::runs_unsplit(M, layer->K, layer->N)) return DMR_ERR_WORKSPACE;
             d_ws = nullptr;
@@ -155,7 +163,7 @@ dmr_status_t forward_quant(const dmr_qlinear_t *layer, const uint16_t *d_x, int6
         }
         return DMR_ERR_UNSUPPORTED;
     }
-    const size_t need = dmr_qlinear_workspace_bytes(M, layer->K, layer->N);
+    const size_t need = layer_workspace_bytes(layer, M);
     if (need > 0 && (!d_ws || ws_bytes < need)) {
         if (!dmr::runs_unsplit(M, layer->K, layer->N)) return DMR_ERR_WORKSPACE;
         d_ws = nullptr;
@@ -428,9 +436,7 @@ dmr_status_t dmr_glue_swiglu(const uint16_t *d_in, int64_t M, int64_t I, uint16_
 size_t dmr_qlinear_fused_workspace_bytes(const dmr_qlinear_t *layer, int64_t M, dmr_prologue_t pro,
                                          int32_t has_residual) {
     if (!layer || M <= 0) return 0;
-    const size_t inner = layer->bits == 3 ? dmr_qlinear_w3_workspace_bytes(M, layer->K, layer->N)
-                                          : dmr_qlinear_workspace_bytes(M, layer->K, layer->N);
-    return fused_extra_bytes(M, layer->K, layer->N, pro, has_residual != 0) + inner;
+    return fused_extra_bytes(M, layer->K, layer->N, pro, has_residual != 0) + layer_workspace_bytes(layer, M);
 }
 
 size_t dmr_qlinear_bf16_fused_workspace_bytes(int64_t M, int64_t K, int64_t N, dmr_prologue_t pro,

@@ -988,8 +988,7 @@ hipError_t launch_rescale(const void *wt, const uint32_t *sz, int64_t K, int64_t
     return launch_tiles<BITS, false>(wt, K, N, x, M, y, out_f32, res, Operands{rfac, a2, b2, flags, p.KP}, stream);
 }
 
-// Per-channel layers, with nothing to rescale: the row sums (at the front of the workspace, where a call of these sizes holds at
-// least 64 bytes per row), then the kernel.
+// Per-channel layers, with nothing to rescale: the row sums (all that the workspace holds then), then the kernel.
 hipError_t launch_per_channel(const LayerView &Lv, const uint16_t *x, int64_t M, void *y, bool out_f32, const uint16_t *res, void *ws,
                               hipStream_t stream) {
     float2 *rowsum = reinterpret_cast<float2 *>(ws);

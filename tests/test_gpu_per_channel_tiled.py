@@ -37,6 +37,12 @@ def test_per_channel_tiled(M, K, N, path):
     subnormal = 2.0 ** -149 / 2.0 ** -130 / float(ref.square().mean().sqrt())    # half a step of the column of tiny outputs
     assert err <= 1e-4 + subnormal
     assert torch.equal(dmr.dmr_qlinear_forward(layer, x), y.to(torch.bfloat16))
+    # two floats a row are all that such a call writes there
+    ws = torch.full((8 * M + 4096,), 0xA5, dtype=torch.uint8, device=DEV)
+    assert torch.equal(dmr.dmr_qlinear_forward(layer, x, out_dtype=torch.float32, workspace=ws[:8 * M]), y)
+    assert bool((ws[8 * M:] == 0xA5).all())
+    with pytest.raises(dmr.DmrError):
+        dmr.dmr_qlinear_forward(layer, x, workspace=ws[:8 * M - 1])
     out = res.clone()
     dmr.dmr_qlinear_forward_fused(layer, dmr.DMR_PRO_NONE, x, residual=out, out=out)
     assert torch.equal(out, (y + res.float()).to(torch.bfloat16))
