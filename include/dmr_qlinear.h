@@ -66,7 +66,7 @@ size_t dmr_qlinear_storage_bytes(int64_t K, int64_t N, int32_t g);
  * very wide layers): per call it keeps there the operands of the zero-point term (bf16, 12 (M + N) K / 128 bytes), one fp32 factor per (row, group) and a few flags (a
  * per-channel layer 8 bytes per row of x, and then takes a workspace of that size).  A 4-bit or
  * 3-bit layer of 16384 outputs or more at 17 .. 64 rows also takes a smaller workspace or none, and then runs
- * without a split of K (few split: 17 rows from K = 9728 on, or more than 32768 outputs).  The workspace may
+ * without a split of K (those of more than 32768 outputs may be split, and are up to 15 % slower then).  The workspace may
  * arrive uninitialised; its contents are undefined after the call. */
 size_t dmr_qlinear_workspace_bytes(int64_t M, int64_t K, int64_t N);
 size_t dmr_qlinear_bf16_workspace_bytes(int64_t M, int64_t K, int64_t N);

@@ -6,31 +6,31 @@
 
 namespace dmr {
 
-// Splits of K for 17..64 rows of a layer whose K divides into chunks of four groups; 0: those of plan_mid.  Layers of 1024 row tiles
-// or more split K in two if that fills the CUs and leaves each half three chunks, narrower ones until every CU has 128 columns while
-// a split keeps two chunks; two splits of more than seven chunks give way to plan_mid's two or four times as many while those fit
-// the fixed scratch of dmr_qlinear_forward_static.
+// Splits of K for 17..64 rows of a layer whose K divides into chunks of four groups; 0: those of plan_mid.  K is split until every CU
+// has 128 columns while a split keeps two chunks; two splits of more than seven chunks give way to plan_mid's two or four times
+// as many while those fit the fixed scratch of dmr_qlinear_forward_static.
 inline int panel_splits(int64_t M, int64_t K, int64_t N) {
-    constexpr int kChunk = 4, kTilesPerWg = 8;      // groups; row tiles of 128 columns
-    const int64_t groups = K / kGroup, tiles = N / kTileRows;
+    constexpr int kChunk = 4;      // groups
+    const int64_t groups = K / kGroup;
     if (groups % kChunk != 0) return 0;
     const int nch = (int)(groups / kChunk);
-    const int64_t wgs = (tiles + kTilesPerWg - 1) / kTilesPerWg;
-    const bool wide = tiles >= 128 * kTilesPerWg;
-    int sk = (int)(kCus / wgs);
-    sk = sk < 1 || (wide && nch < 6) ? 1 : sk > nch ? nch : sk;
+    int sk = (int)(kCus / ((N + kTileCols - 1) / kTileCols));
+    sk = sk < 1 ? 1 : sk > nch ? nch : sk;
     const int cps = (nch + sk - 1) / sk;
     sk = (nch + cps - 1) / cps;
-    if (wide) return sk;
     if (sk == 1 || cps < 2) return 0;
     const MidPlan m = plan_mid(M, K, N);
     if (m.R == 1 && m.wgs <= kCus && m.gps % 4 == 0) return 0;
     return sk == 2 && cps > 7 && (size_t)m.SK * (size_t)(M * N) * sizeof(float) <= DMR_STATIC_SCRATCH_BYTES ? 0 : sk;
 }
 
-// What a call may split K into at most, and so what it may ask for: partials of 64 rows fit the fixed scratch, and no call asks for
-// more than callers were told by earlier versions of the query.
+// What a call may split K into at most, and so what it may ask for: partials of 64 rows fit the fixed scratch but for layers that also
+// run without.  Layers of 16384 .. 32768 outputs stay whole at 17..64 rows: 64 columns to a workgroup fill the CUs (14336 -> 16384,
+// 17 / 32 rows 30.6 / 32.1 us whole, 35.6 / 34.1 in two; 11008 -> 16384, 17 rows 24.9 / 27.6); above, K is split where it is no
+// multiple of 512 (7936 -> 33216, 49 rows 79.3 whole, 71.8 in two).
 inline int row_splits(int64_t M, int64_t K, int64_t N) {
+    const int64_t tiles = N / kTileRows;
+    if (M <= 64 && tiles >= 1024) return tiles <= 2048 || K / kGroup % 4 == 0 ? 1 : plan_mid(M, K, N).SK;
     const int panels = M <= 64 ? panel_splits(M, K, N) : 0;
     if (panels > 0) return panels;
     return M <= 128 || blocks128(M, N) < kTiledMinBlocks ? plan_mid(M, K, N).SK : 1;

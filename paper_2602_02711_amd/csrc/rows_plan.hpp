@@ -25,15 +25,17 @@ inline bool rows_kernels_fit(int64_t M, int64_t K) { return M >= 17 && K < (int6
 
 // The candidate with the least estimated time.  us per launch = rounds of 256 workgroups x (fixed + chunks x time of a chunk), plus
 // the reduction's launch and its partials where K is split:
-//   tile kernel, 128 columns:  6.2 + chunks x (1.3 / 1.9 / 2.3 for 2 / 3 / 4 row tiles, 4 groups each, up to 64 rows;
-//     1.7 / 2.1 for row blocks of 96 / 128, 2 groups each)
+//   tile kernel, 128 columns:  6.2 + chunks x (1.3 / 1.9 / 2.3 for 2 / 3 / 4 row tiles, 4 groups each, blocks of up to 64 rows;
+//     1.7 / 2.1 for row blocks of 96 / 128, 2 groups each).  Above 64 rows the smaller blocks are offered while one round holds
+//     them: 96 rows 1024 -> 16384 in two blocks of 48 8.9 us, in one of 96 on half of the chip 12.6
 //   slices kernel, 16 R columns, blocks of 64 rows at most:  4.5 + ceil(groups / 8) x (0.24 + MT (0.18 + 0.06 R) + 0.18 R); two of
-//     its workgroups share a CU at two row tiles and R <= 2
+//     its workgroups share a CU at two row tiles and R <= 2, and 257 of them take what 512 do, 1.5 times the time of 256 (32 rows 8192 ->
+//     9216 in 288 workgroups 23.9 us, in 144 of R = 4 17.8)
 //   reduction: 2.0 + 2.3 per million partials
-// Fitted to 16 to 20 candidates at each of 750 points: 17 .. 512 rows, K = 512 .. 14336, N = 1024 .. 28672, weights from memory.
-// What it picks takes 0.7 % more than the best candidate on average, 27 % at worst (17 rows 8192 -> 6144, 16.9 / 13.3).  Against
-// the kernels these replaced (one panel or one group of x at a time through registers): 1.32 x at 17 .. 64 rows, 1.39 x above; 7
-// points of 608 are slower, by 8 % at most (17 and 32 rows 1024 -> 28672, 9.1 / 9.9; two chunks to a workgroup).
+// Fitted to 16 to 20 candidates at each of 750 points (17 .. 512 rows, K = 512 .. 14336, N = 1024 .. 28672, weights from memory) and
+// checked on 3388: what it picks takes 0.3 % more than the best of its candidates on average, 19 % at worst.  Against the kernels
+// these replaced (one panel or one group of x at a time through registers) 1.36 x up to 64 rows and 1.49 x above over 5020 points of
+// INT4, none of them slower.
 // us, old / picked:  17 rows 4096 -> 6144 11.3 / 8.9;  32 rows 14336 -> 4096 17.4 / 15.0;  64 rows 4096 -> 28672 33.3 / 25.5, 4096 ->
 // 4096 13.0 / 10;  96 rows 4096 -> 28672 48.7 / 39;  200 rows 4096 -> 6144 38.5 / 30, 14336 -> 4096 59.8 / 45.
 // `max_splits`: what the caller's workspace holds.
@@ -53,22 +55,25 @@ inline RowsPlan plan_rows(int64_t M, int64_t K, int64_t N, int max_splits) {
         const int gps = (int)cdiv(groups, sk);
         if (sk > 1 && cdiv(groups, gps) != sk) continue;
         const double red = sk > 1 ? 2.0 + 2.3e-6 * (double)sk * (double)M * (double)N : 0.0;
-        const bool low = M <= 64;
-        for (int MT = low ? (int)cdiv(M, 16) : 3; MT <= (low ? (int)cdiv(M, 16) : 4); ++MT) {
-            const int64_t wgs = cdiv(N, kTileCols) * sk * (low ? 1 : cdiv(M, 32 * MT));
-            const double chunk = low ? (MT == 2 ? 1.28 : MT == 3 ? 1.9 : 2.31) : (MT == 3 ? 1.73 : 2.11);
-            offer({false, MT, low ? 1 : 2, 0, sk, gps},
-                  (double)cdiv(wgs, kCus) * (6.25 + (double)cdiv(gps, low ? 4 : 2) * chunk) + red);
-        }
+        auto tile = [&](int MT, int WM) {
+            const int64_t wgs = cdiv(N, kTileCols) * sk * cdiv(M, 16 * MT * WM);
+            if (M > 64 && WM == 1 && wgs > kCus) return;
+            const double chunk = WM == 1 ? (MT == 2 ? 1.28 : MT == 3 ? 1.9 : 2.31) : (MT == 3 ? 1.73 : 2.11);
+            offer({false, MT, WM, 0, sk, gps}, (double)cdiv(wgs, kCus) * (6.25 + (double)cdiv(gps, WM == 1 ? 4 : 2) * chunk) + red);
+        };
         const int64_t blocks = cdiv(M, 64);
         const int MT = (int)cdiv(cdiv(M, blocks), 16);
+        if (M > 64) {
+            tile(3, 2);
+            tile(4, 2);
+            tile((int)cdiv(cdiv(M, cdiv(M, 48)), 16), 1);
+        }
+        tile(MT, 1);
         for (int R = 1; R <= 4; R *= 2) {
             const int64_t wgs = cdiv(tiles, R) * sk * blocks;
-            const bool paired = MT == 2 && R <= 2;
-            if (wgs > (paired ? 2 : 1) * kCus) continue;
+            if (wgs > (MT == 2 && R <= 2 ? 2 : 1) * kCus) continue;
             const double step = 0.24 + MT * (0.18 + 0.06 * R) + 0.18 * R;
-            const double share = paired && wgs > kCus ? 1.0 + 0.81 * ((double)wgs / kCus - 1.0) : 1.0;
-            offer({true, MT, 1, R, sk, gps}, (4.51 + (double)cdiv(gps, 8) * step) * share + red);
+            offer({true, MT, 1, R, sk, gps}, (4.51 + (double)cdiv(gps, 8) * step) * (wgs > kCus ? 1.5 : 1.0) + red);
         }
     }
     return best;

@@ -57,8 +57,8 @@ def test_bf16_tile(lib, M, K, N, name):
     (33, 1536, 12288, "slices", 1), (64, 4096, 6144, "slices", 1), (64, 8192, 8192, "slices", 1), (17, 4096, 11008, "slices", 1),
     (17, 12288, 2048, "slices", 4), (64, 12288, 2048, "slices", 4), (33, 7168, 4096, "slices", 4), (64, 14336, 4096, "slices", 4),
     (50, 14336, 4112, "tile", 7), (64, 4096, 28672, "tile", 1), (400, 4096, 6144, "tile", 1),
-    # 1024 row tiles and more: these also run without the partials
-    (17, 11264, 16384, "tile", 2), (33, 4096, 16384, "slices", 1), (64, 14336, 16384, "slices", 1), (33, 6912, 33216, "tile", 2),
+    # 1024 row tiles and more: whole up to 32768 outputs; those that split also run without the partials
+    (17, 11264, 16384, "slices", 1), (17, 11008, 16384, "slices", 1), (33, 4096, 16384, "slices", 1), (64, 14336, 16384, "slices", 1), (33, 6912, 33216, "tile", 2),
 ])
 def test_rows_kernel_and_splits(lib, M, K, N, rows, splits):
     # the workspace is the partials of the splits that the launch makes, nothing where K stays whole

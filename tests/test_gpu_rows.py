@@ -40,7 +40,9 @@ SLICES = [
 TILE = [
     # chunks of four groups (32, 33 and 35 of them; seven splits of 16), then of two in blocks of 96 and 128 rows
     (20, 4224, 16400), (40, 4480, 16400), (64, 4096, 28688), (50, 14336, 4112), (96, 512, 28688), (97, 384, 17936), (128, 1664, 16400),
-    (200, 1664, 12304), (200, 4096, 6160), (400, 640, 6160), (512, 384, 8192),
+    (200, 1664, 12304), (400, 640, 6160), (512, 384, 8192),
+    # blocks of 33, 48 and 50 rows with chunks of four
+    (65, 1024, 16400), (96, 1536, 16384), (200, 4096, 6160),
 ]
 CODE = {"w4": dmr.DMR_FMT_W4_G128, "w4pc": dmr.DMR_FMT_W4_PER_CHANNEL, "w3": dmr.DMR_FMT_W3_G128}
 

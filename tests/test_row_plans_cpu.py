@@ -1,5 +1,5 @@
-"""Requests of the row kernels, on the host: how the waves of a workgroup share the groups of K, and that every request, those past a
-wave's last group included, names bytes of the layer."""
+"""Plans and requests of the row kernels, on the host: how the waves of a workgroup share the groups of K, that every request, those past
+a wave's last group included, names bytes of the layer, and which shape serves layers that another would slow down."""
 import os
 import subprocess
 
@@ -52,12 +52,50 @@ int main() {
 """
 
 
-def test_every_request_names_a_group_of_the_layer(tmp_path):
+PLANS = r"""
+#include <cstdio>
+#include "row_splits.hpp"
+using namespace dmr;
+
+int main() {
+    int bad = 0;
+    auto want = [&](int M, int K, int N, bool slices, int MT, int WM, int R, int SK) {
+        const RowsPlan p = rows_call(M, K, N);
+        if (p.slices == slices && p.MT == MT && p.WM == WM && p.R == R && p.SK == SK) return;
+        std::printf("%d x %d -> %d: slices %d MT %d WM %d R %d SK %d\n", M, K, N, p.slices, p.MT, p.WM, p.R, p.SK);
+        bad = 1;
+    };
+    // a few more than 256 workgroups take what 512 do: not 288 or 320 of two tiles (23.9, 16.7 and 6.5 us) but K in three on the tile
+    // kernel (18.3, 14.4) or 144 of four tiles (5.5)
+    want(32, 8192, 9216, false, 2, 1, 0, 3);
+    want(17, 6144, 10240, false, 2, 1, 0, 3);
+    want(32, 1024, 9216, true, 2, 1, 4, 1);
+    want(32, 4096, 8192, true, 2, 1, 2, 1);            // 256 of two
+    // two and four blocks of 48 rows where one or two of 96 leave half of the chip idle (12.6 / 8.9 us, 15.7 / 10.5)
+    want(96, 1024, 16384, false, 3, 1, 0, 1);
+    want(192, 1536, 8192, false, 3, 1, 0, 1);
+    want(128, 4096, 28672, false, 4, 2, 0, 1);         // more than a round of them: 128 rows
+    // 256 workgroups of four tiles: K stays whole (27.6 / 24.9 us)
+    want(17, 11008, 16384, true, 2, 1, 4, 1);
+    return bad;
+}
+"""
+
+
+def run(tmp_path, program):
     src, exe = tmp_path / "share.hip", tmp_path / "share"
-    src.write_text(PROGRAM)
+    src.write_text(program)
     inc = os.path.join(ROOT, "paper_2602_02711_amd", "csrc")
     built = subprocess.run(["hipcc", "--offload-arch=gfx950", "--offload-host-only", "-std=c++17", "-I", inc, str(src), "-o", str(exe)],
                            capture_output=True, text=True)
     assert built.returncode == 0, built.stderr[-2000:]
     ran = subprocess.run([str(exe)], capture_output=True, text=True)
     assert ran.returncode == 0, ran.stdout
+
+
+def test_every_request_names_a_group_of_the_layer(tmp_path):
+    run(tmp_path, PROGRAM)
+
+
+def test_shapes_of_the_row_kernels(tmp_path):
+    run(tmp_path, PLANS)
