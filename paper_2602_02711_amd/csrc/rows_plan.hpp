@@ -10,6 +10,7 @@ struct RowsPlan {
     int MT, WM;     // row tiles of 16 per wave, waves along the rows (tile kernel)
     int R;          // weight tiles per workgroup (slices kernel)
     int SK, gps;    // splits of K over blockIdx.y, groups per split (the last one may have fewer)
+    bool half;      // tile kernel: codes in units that keep the sums small
 };
 
 constexpr int kTileCols = 128;      // columns of a workgroup of the tile kernel
@@ -51,6 +52,8 @@ inline RowsPlan plan_rows(int64_t M, int64_t K, int64_t N, int max_splits) {
             best = p;
         }
     };
+    // calls of a size that the tiled GEMM would have, while it is the more exact one on 128 + q (see w4_tile.hip)
+    const bool half = M > 128 && blocks128(M, N) >= kTiledMinBlocks && K < 8192;
     for (int sk = 1; sk <= max_splits; ++sk) {
         const int gps = (int)cdiv(groups, sk);
         if (sk > 1 && cdiv(groups, gps) != sk) continue;
@@ -59,7 +62,7 @@ inline RowsPlan plan_rows(int64_t M, int64_t K, int64_t N, int max_splits) {
             const int64_t wgs = cdiv(N, kTileCols) * sk * cdiv(M, 16 * MT * WM);
             if (M > 64 && WM == 1 && wgs > kCus) return;
             const double chunk = WM == 1 ? (MT == 2 ? 1.28 : MT == 3 ? 1.9 : 2.31) : (MT == 3 ? 1.73 : 2.11);
-            offer({false, MT, WM, 0, sk, gps}, (double)cdiv(wgs, kCus) * (6.25 + (double)cdiv(gps, WM == 1 ? 4 : 2) * chunk) + red);
+            offer({false, MT, WM, 0, sk, gps, half}, (double)cdiv(wgs, kCus) * (6.25 + (double)cdiv(gps, WM == 1 ? 4 : 2) * chunk) + red);
         };
         const int64_t blocks = cdiv(M, 64);
         const int MT = (int)cdiv(cdiv(M, blocks), 16);
@@ -73,7 +76,7 @@ inline RowsPlan plan_rows(int64_t M, int64_t K, int64_t N, int max_splits) {
             const int64_t wgs = cdiv(tiles, R) * sk * blocks;
             if (wgs > (MT == 2 && R <= 2 ? 2 : 1) * kCus) continue;
             const double step = 0.24 + MT * (0.18 + 0.06 * R) + 0.18 * R;
-            offer({true, MT, 1, R, sk, gps}, (4.51 + (double)cdiv(gps, 8) * step) * (wgs > kCus ? 1.5 : 1.0) + red);
+            offer({true, MT, 1, R, sk, gps, false}, (4.51 + (double)cdiv(gps, 8) * step) * (wgs > kCus ? 1.5 : 1.0) + red);
         }
     }
     return best;

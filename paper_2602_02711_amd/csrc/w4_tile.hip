@@ -19,6 +19,13 @@
 // same way, x through registers, two barriers per chunk, LDS reads shared by two tiles), us: 4096 -> 28672 64 rows 33.3 / 25.5,
 // 128 rows 58.8 / 45;  128 rows 4096 -> 6144 29.0 / 24.5, 14336 -> 4096 42.3 / 32.8 (200 rows 59.8 / 44.9).
 // BITS = 3 runs the same kernel on the 3-bit streaming layout (768-byte blocks, three words per lane).
+// HALF multiplies (16 + q) / 2 instead of 128 + q and doubles the sums at the end: the error against fp64 falls from 1.8e-6 to 1.7e-7 of
+// the result's rms (3 bits: 3.7e-6 to 2.7e-7), for a shift more per eight codes, 1 .. 4 % of the time above 64 rows (256 rows 4096 ->
+// 12288 39.7 / 41.3 us).  It serves the calls that the rescaling GEMM had, whose error grows with K and reaches that of 128 + q at 4096
+// (groups, 1.8e-6), 5600 (3 bits) and 7200 (per channel).
+#include <type_traits>
+
+#include "half_codes.hpp"
 #include "lds_loads.hpp"
 #include "mid_plan.hpp"
 #include "rows_plan.hpp"
@@ -51,7 +58,7 @@ struct Item {
 
 // out_mode: 0 = fp32 y, 1 = bf16 y, 2 = fp32 partial [split][M][N].  No __restrict__ on what the ring loads from: the loads must
 // stay between the barriers they are written between, which the waits count on.
-template <int MT, int WM, int S, int BITS>
+template <int MT, int WM, int S, int BITS, bool HALF>
 __global__ __launch_bounds__(64 * kWaves) void w4_tile_kernel(const void *wt, const uint32_t *sz, const uint16_t *x, void *y, int M,
                                                               int64_t K, int64_t N, int groups, int tiles, int gps, int out_mode,
                                                               int szs, const uint16_t *res) {
@@ -133,6 +140,7 @@ __global__ __launch_bounds__(64 * kWaves) void w4_tile_kernel(const void *wt, co
         for (int r = 0; r < R; ++r) {
             sc[r] = g < gE ? __uint_as_float(it.s[r] << 16) : 0.f;
             cz[r] = __uint_as_float(it.s[r] & 0xFFFF0000u);   // -(128 + z)
+            if constexpr (HALF) cz[r] = fmaf(cz[r], 0.5f, 56.f);                    // -(16 + z) / 2, exact
         }
         __builtin_amdgcn_sched_barrier(0);
         Frag a[4][MT];
@@ -160,7 +168,11 @@ __global__ __launch_bounds__(64 * kWaves) void w4_tile_kernel(const void *wt, co
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
                 Frag b;
-                if constexpr (BITS == 4) {
+                if constexpr (HALF && BITS == 4) {
+                    unpack4_word(it.w[r][t], b);
+                } else if constexpr (HALF) {
+                    unpack3_chunk(it.w[r], t, b);
+                } else if constexpr (BITS == 4) {
                     unpack_word(it.w[r][t], b.w);
                 } else {
                     if (t == 0) unpack3_step<0>(it.w[r].x, it.w[r].y, it.w[r].z, b.w);
@@ -246,21 +258,24 @@ __global__ __launch_bounds__(64 * kWaves) void w4_tile_kernel(const void *wt, co
 #pragma unroll
             for (int e = 0; e < 4; ++e) v[e] += u[e];
         }
+        if constexpr (HALF)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] *= 2.f;
         store_quad(v, y, (int64_t)(m0 + row) * N + n, part, out_mode, res);
     }
 }
 
-template <int MT, int WM, int S, int BITS>
+template <int MT, int WM, int S, int BITS, bool HALF>
 hipError_t launch_cfg(const void *wt, const uint32_t *sz, int szs, int64_t K, int64_t N, const uint16_t *x, int M, void *y,
                       int out_mode, const uint16_t *res, const RowsPlan &p, hipStream_t stream) {
     using G = Geo<MT, WM, S>;
     // once per process and kernel instantiation (thread-safe static initialisation)
-    static const hipError_t attr_status = hipFuncSetAttribute(reinterpret_cast<const void *>(&w4_tile_kernel<MT, WM, S, BITS>),
+    static const hipError_t attr_status = hipFuncSetAttribute(reinterpret_cast<const void *>(&w4_tile_kernel<MT, WM, S, BITS, HALF>),
                                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)G::LDS);
     if (attr_status != hipSuccess) return attr_status;
     const int groups = (int)(K / kGroup), tiles = (int)(N / kTileRows);
     const dim3 grid((unsigned)((N + G::COLS - 1) / G::COLS), (unsigned)p.SK, (unsigned)((M + G::BM - 1) / G::BM));
-    hipLaunchKernelGGL((w4_tile_kernel<MT, WM, S, BITS>), grid, dim3(64 * kWaves), G::LDS, stream, wt, sz, x, y, M, K, N, groups,
+    hipLaunchKernelGGL((w4_tile_kernel<MT, WM, S, BITS, HALF>), grid, dim3(64 * kWaves), G::LDS, stream, wt, sz, x, y, M, K, N, groups,
                        tiles, p.gps, out_mode, szs, out_mode == 2 ? nullptr : res);
     return hipGetLastError();
 }
@@ -274,14 +289,20 @@ hipError_t launch_tile(const void *wt, const uint32_t *sz, int szs, int64_t K, i
     const int out_mode = split ? 2 : (out_f32 ? 0 : 1);
     const int iM = (int)M;
     hipError_t e = hipErrorInvalidValue;
-    if (p.WM == 1) {
-        if (p.MT == 2) e = launch_cfg<2, 1, 4, BITS>(wt, sz, szs, K, N, x, iM, dst, out_mode, res, p, stream);
-        if (p.MT == 3) e = launch_cfg<3, 1, 4, BITS>(wt, sz, szs, K, N, x, iM, dst, out_mode, res, p, stream);
-        if (p.MT == 4) e = launch_cfg<4, 1, 4, BITS>(wt, sz, szs, K, N, x, iM, dst, out_mode, res, p, stream);
-    } else {
-        if (p.MT == 3) e = launch_cfg<3, 2, 2, BITS>(wt, sz, szs, K, N, x, iM, dst, out_mode, res, p, stream);
-        if (p.MT == 4) e = launch_cfg<4, 2, 2, BITS>(wt, sz, szs, K, N, x, iM, dst, out_mode, res, p, stream);
-    }
+    auto go = [&](auto half) {
+        constexpr bool HALF = decltype(half)::value;
+        if (p.WM == 2) {
+            if (p.MT == 3) e = launch_cfg<3, 2, 2, BITS, HALF>(wt, sz, szs, K, N, x, iM, dst, out_mode, res, p, stream);
+            if (p.MT == 4) e = launch_cfg<4, 2, 2, BITS, HALF>(wt, sz, szs, K, N, x, iM, dst, out_mode, res, p, stream);
+            return;
+        }
+        if constexpr (!HALF)
+            if (p.MT == 2) e = launch_cfg<2, 1, 4, BITS, HALF>(wt, sz, szs, K, N, x, iM, dst, out_mode, res, p, stream);
+        if (p.MT == 3) e = launch_cfg<3, 1, 4, BITS, HALF>(wt, sz, szs, K, N, x, iM, dst, out_mode, res, p, stream);
+        if (p.MT == 4) e = launch_cfg<4, 1, 4, BITS, HALF>(wt, sz, szs, K, N, x, iM, dst, out_mode, res, p, stream);
+    };
+    if (p.half) go(std::true_type{});
+    else go(std::false_type{});
     if (e != hipSuccess || !split) return e;
     return launch_splitk_reduce(static_cast<const float *>(ws), y, M * N, p.SK, out_f32, res, stream);
 }

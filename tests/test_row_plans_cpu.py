@@ -31,7 +31,7 @@ static int check(int groups, int gps, int splits, int held, int ahead) {
 int main() {
     for (int K = 128; K <= 20480; K += 128)
         for (int N : {16, 272, 1024, 4096, 6160, 8208, 28672})
-            for (int M : {2, 8, 9, 16, 17, 32, 33, 48, 49, 64, 100, 250}) {
+            for (int M : {2, 8, 9, 16, 17, 32, 33, 48, 49, 64, 100, 129, 145, 193, 250, 289, 385, 512}) {
                 const int groups = K / kGroup;
                 for (int max_splits : {1, 2, 4, 8}) {
                     int bad = 0;
@@ -40,6 +40,7 @@ int main() {
                     if (!bad && M >= 17) {
                         const RowsPlan r = plan_rows(M, K, N, max_splits);
                         if (r.slices) bad = check(groups, r.gps, r.SK, groups, 1);
+                        if (r.half && (r.slices || r.MT < 3)) bad = 4;              // not instantiated
                     }
                     if (bad) {
                         std::printf("K=%d N=%d M=%d splits<=%d: %d\n", K, N, M, max_splits, bad);
