@@ -78,7 +78,7 @@ bool tiled_beats_rollout(int64_t M, int64_t K, int64_t N) {
 }
 Bf16Path bf16_path(int64_t M, int64_t K, int64_t N) {
     if (M == 1) return Bf16Path::Gemv;
-    if (M <= 8 || (M <= 16 && N / dmr::kTileRows >= 1024 && M * (K / 8 + 1) <= 9216)) return Bf16Path::Skinny;
+    if (M <= 8 || (M <= 16 && N / dmr::kTileRows > 1024 && M * (K / 8 + 1) <= 9216)) return Bf16Path::Skinny;
     if (M <= 64) return Bf16Path::Mid;
     if (K < 1024) {                  // no direct-to-LDS kernel there
         if (((M + 127) / 128) * ((N + 127) / 128) <= 128) return Bf16Path::Mid;
@@ -88,14 +88,15 @@ Bf16Path bf16_path(int64_t M, int64_t K, int64_t N) {
     return dmr::gemm_big_tile_rows(M, K, N) != 0 ? Bf16Path::GemmBig : Bf16Path::Gemm;
 }
 
-// The rollout-batch kernel keeps 33..64 rows where its plan is one full round of one-tile workgroups with four splits of K: 48 rows
-// 4096 -> 4096 13.0 / 13.6 us (this kernel with K in two); at 3 / 4 of a round 12.8 / 11.9 (3072 outputs), with two splits of a full
-// round 12.7 / 11.8 (2048 -> 8192), with eight level (8192 -> 2048 14.2 / 14.3).
+// The rollout-batch kernel keeps 33..64 rows where its plan is one full round of one-tile workgroups with four splits of K and this one's
+// has two, whose last round of tiles is ragged: K = 4096 and 3700 .. 4096 outputs (us, that kernel / this one: 48 rows 4096 -> 4096 13.0 /
+// 14.2, -> 3968 0.81 of its time, -> 3712 0.87, -> 3840 0.99; level at 3072 and 3584, 1.4 x behind from 4112 on).  With three splits and
+// more here it is 8 .. 25 % behind over K = 4608 .. 8192 and the same widths.
 dmr::Bf16RowsPlan bf16_rows_plan(int64_t M, int64_t K, int64_t N) {
     const bool mid = bf16_path(M, K, N) == Bf16Path::Mid;
     const dmr::MidPlan m = dmr::plan_mid(M, K, N);
     dmr::Bf16RowsPlan p = dmr::plan_bf16_rows(M, K, N, mid ? m.SK : 1);
-    if (mid && M > 32 && m.R == 1 && m.SK == 4 && m.wgs > dmr::kCus * 15 / 16 && m.wgs <= dmr::kCus) p.ok = false;
+    if (mid && M > 32 && p.SK == 2 && m.R == 1 && m.SK == 4 && m.wgs > dmr::kCus * 7 / 8 && m.wgs <= dmr::kCus) p.ok = false;
     return p;
 }
 

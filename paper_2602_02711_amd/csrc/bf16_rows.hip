@@ -210,7 +210,9 @@ hipError_t launch_bf16_rows(const uint16_t *w, const uint16_t *x, int64_t M, int
     DMR_BF16_ROWS(1, 2);
     DMR_BF16_ROWS(1, 3);
     DMR_BF16_ROWS(1, 4);
+    DMR_BF16_ROWS(1, 5);
     DMR_BF16_ROWS(1, 6);
+    DMR_BF16_ROWS(1, 7);
     DMR_BF16_ROWS(1, 8);
     DMR_BF16_ROWS(2, 1);
     DMR_BF16_ROWS(2, 2);

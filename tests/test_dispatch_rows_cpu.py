@@ -24,3 +24,23 @@ def test_quantised_rows(M, K, N, path, asks):
 ])
 def test_bf16_rows(M, K, N, rows):
     assert (binding.lib().dmr_qlinear_kernel_path(BF16, M, K, N) == b"bf16_rows") == rows
+
+
+@pytest.mark.parametrize("M,K,N,path", [
+    # 2..8 rows: short rows on any width, up to 4096 outputs, up to 8192, and 8192 itself at K = 2048 and 4096
+    (2, 896, 8208, "skinny"), (2, 1024, 8208, "rows"), (5, 896, 12288, "skinny"), (5, 1024, 12288, "rows"), (7, 768, 9216, "skinny"),
+    (7, 896, 9216, "rows"), (8, 640, 8208, "skinny"), (8, 768, 8208, "rows"), (3, 1024, 16384, "skinny"), (3, 1024, 16368, "rows"),
+    (4, 2560, 4096, "skinny"), (4, 2688, 4096, "rows"), (6, 1792, 4096, "skinny"), (6, 1920, 4096, "rows"), (8, 1536, 4096, "skinny"),
+    (8, 1664, 4096, "rows"), (4, 1536, 8192, "skinny"), (4, 1664, 8192, "rows"), (7, 1280, 4112, "skinny"), (7, 1408, 4112, "rows"),
+    (8, 768, 8192, "skinny"), (8, 896, 8192, "rows"), (2, 4096, 8192, "skinny"), (2, 4096, 8128, "rows"), (4, 2048, 8144, "skinny"),
+    (4, 2560, 8192, "rows"), (8, 8192, 4096, "rows"), (8, 8320, 4096, "skinny"),          # 64 groups held
+    # 9..64 rows up to K = 512
+    (16, 512, 4096, "rows"), (16, 512, 4112, "mid"), (16, 512, 16384, "mid"), (16, 512, 16400, "rows"), (16, 640, 8192, "rows"),
+    (16, 256, 4096, "rows"), (16, 256, 16400, "skinny"), (32, 256, 4096, "mid"), (33, 256, 4096, "rows"), (64, 256, 20480, "mid"),
+    (32, 384, 4096, "rows"), (32, 512, 9216, "mid"), (64, 512, 16400, "rows"), (64, 640, 9216, "rows"),
+    # 33..64 rows: one full round of the other kernel with K in four, in two here
+    (64, 4096, 4096, "mid"), (33, 4096, 3600, "mid"), (64, 4096, 3584, "rows"), (64, 4096, 4112, "rows"), (64, 4608, 4096, "rows"),
+    (32, 4096, 4096, "rows"), (64, 8192, 4096, "rows"), (64, 14336, 28672, "mid"),        # two splits held, seven needed
+])
+def test_bf16_rows_crossover(M, K, N, path):
+    assert binding.lib().dmr_qlinear_kernel_path(BF16, M, K, N).decode() == "bf16_" + path

@@ -10,8 +10,8 @@ DEV = "cuda:0"
 
 
 @pytest.mark.parametrize("M,K,N", [
-    # groups per wave 1, 2, 3, 4, 6, 8; fewer groups than waves; one tile and several to a workgroup
-    (2, 640, 4112), (3, 1152, 4112), (8, 2688, 1040), (9, 128, 272), (16, 4096, 4128), (5, 5632, 528), (12, 8192, 528),
+    # groups per wave 1 to 8; fewer groups than waves; one tile and several to a workgroup
+    (8, 896, 8208), (3, 1152, 8208), (8, 2688, 1040), (9, 128, 272), (16, 4096, 4128), (5, 5632, 528), (12, 8192, 528), (16, 4608, 528), (7, 6656, 1040),
     (17, 896, 1040), (32, 1920, 4112), (20, 2944, 8208), (31, 3584, 528), (32, 4096, 12304),
     (33, 1024, 4112), (48, 1152, 272), (49, 896, 4112), (64, 2048, 8208),
     # K split
@@ -33,14 +33,3 @@ def test_bf16_rows(M, K, N):
     out = res.clone()
     dmr.dmr_qlinear_bf16_forward_fused(w, dmr.DMR_PRO_NONE, x, residual=out, out=out)
     assert torch.equal(out, (y + res.float()).to(torch.bfloat16))
-
-
-@pytest.mark.parametrize("M,K,N,path", [(8, 512, 4112, "bf16_skinny"), (8, 640, 4112, "bf16_rows"),        # rows of up to 512
-                                        (8, 1536, 4096, "bf16_skinny"), (8, 1536, 4112, "bf16_rows"),     # one round of its workgroups
-                                        (4, 2048, 4096, "bf16_skinny"), (5, 2048, 4096, "bf16_rows"),
-                                        (64, 4096, 4096, "bf16_mid"), (32, 4096, 4096, "bf16_rows"),      # one full round, K in four
-                                        (64, 4096, 4112, "bf16_rows"), (64, 4096, 3840, "bf16_rows"),
-                                        (8, 8192, 4096, "bf16_rows"), (8, 8320, 4096, "bf16_skinny"),     # 64 groups held
-                                        (64, 14336, 28672, "bf16_mid")])                                  # two splits, seven needed
-def test_bf16_rows_crossover(M, K, N, path):
-    assert dmr.dmr_qlinear_kernel_path(dmr.DMR_FMT_BF16, M, K, N) == path
