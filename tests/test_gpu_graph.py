@@ -1,6 +1,6 @@
 """HIP-graph capture of the forwards (how bench.py launches them): every replay must reproduce the
 eager result bit for bit, also with eager work of the same library between the replays and with the
-kernels that use a workspace (split of K and its reduction pass, the activation pre-pass)."""
+kernels that use a workspace (split of K and its reduction pass, the tiled path's pre-pass)."""
 import pytest
 import torch
 

@@ -217,8 +217,7 @@ def test_prefill_ragged_shapes(K, N, M):
 @pytest.mark.parametrize("K,N,M", [(1024, 1024, 65), (4096, 4096, 100), (512, 272, 130), (1792, 512, 96),
                                    (1024, 4096, 200), (2048, 1040, 257), (4096, 6144, 384)])
 def test_forward_rollout_batch_sizes(K, N, M):
-    # 64 < M <= 512: row blocks of 96 / 128, ragged column blocks, K split over workgroups (also with an
-    # odd number of groups per split) and the partial-sum pass
+    # 64 < M <= 512: several blocks of rows, ragged column blocks
     _, words, s, z = quantized(7000 + K + N + M, N, K)
     x = synth.activations_bf16(7001 + K + N + M, M, K)
     y32, y16 = forward_both(make_layer(words, s, z), x)
@@ -229,9 +228,9 @@ def test_forward_rollout_batch_sizes(K, N, M):
 @pytest.mark.parametrize("K,N,M", [(512, 16400, 17), (1536, 16400, 33), (1024, 16512, 48), (1536, 16528, 64),
                                    (2560, 16384, 20), (640, 16400, 40)])
 def test_forward_wide_layers_small_batches(K, N, M):
-    # 17 <= M <= 64 on layers of >= 1024 weight tiles: chunked activation panels in LDS (one chunk, an odd
+    # 17 <= M <= 64 on layers of >= 1024 weight tiles: staged activation panels in LDS (one chunk, an odd
     # and an even number of chunks), 2..4 row tiles with a ragged last one, a ragged last column block; five
-    # groups (not a multiple of the chunk): the pre-pass kernel that re-orders the activations in memory
+    # groups (not a multiple of the chunk)
     _, words, s, z = quantized(7500 + K + N + M, N, K)
     x = synth.activations_bf16(7501 + K + N + M, M, K)
     y32, y16 = forward_both(make_layer(words, s, z), x)

@@ -1,6 +1,7 @@
 """The two kernels for 17 rows up to several hundred (staged panels, slices of K), whole outputs against fp64 on the dequantised
-codes: edges of row and column tiles, group counts that do not divide over waves or splits, fewer groups than waves, every
-row-tile count, rows that share a workgroup's weights and rows in several blocks."""
+codes: every shape that the plan can choose with K whole and split (tests/test_row_plans_cpu.py holds the lists to that), edges of
+row and column tiles, group counts that do not divide over waves or splits, fewer groups than waves, rows that share a workgroup's
+weights and rows in several blocks."""
 import pytest
 import torch
 
@@ -35,7 +36,10 @@ def make(fmt, w):
 SLICES = [
     # one, two and four tiles; 1..4 row tiles' worth of rows, one group in all, five, eight and 29 over eight waves
     (17, 128, 1024), (33, 640, 272), (48, 3712, 6144), (64, 384, 8208), (65, 1152, 2064), (100, 128, 272),
-    (130, 2560, 4096), (250, 512, 1040),
+    (130, 2560, 4096), (250, 512, 1040), (17, 128, 4320), (32, 2560, 8208),
+    # K split, two to sixteen ways
+    (17, 4096, 272), (17, 16384, 272), (30, 16384, 640), (33, 3328, 272), (65, 8192, 272), (65, 16384, 272), (49, 3328, 272), (196, 4096, 272),
+    (196, 8192, 272),
 ]
 TILE = [
     # chunks of four groups (32, 33 and 35 of them; seven splits of 16), then of two in blocks of 96 and 128 rows
@@ -43,6 +47,8 @@ TILE = [
     (200, 1664, 12304), (400, 640, 6160), (512, 384, 8192),
     # blocks of 33, 48 and 50 rows with chunks of four
     (65, 1024, 16400), (96, 1536, 16384), (200, 4096, 6160),
+    # K split on two and three row tiles and on blocks of 96 and 128 rows; codes in smaller units in blocks of 48 and 64
+    (17, 6656, 4320), (322, 4608, 1376), (455, 6144, 2112), (343, 14336, 1376), (129, 384, 9392), (259, 384, 6160),
 ]
 CODE = {"w4": dmr.DMR_FMT_W4_G128, "w4pc": dmr.DMR_FMT_W4_PER_CHANNEL, "w3": dmr.DMR_FMT_W3_G128}
 

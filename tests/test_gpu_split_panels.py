@@ -1,5 +1,5 @@
-"""The chunked-panel kernel with K split over workgroups (layers of 17..64 rows too narrow to give every CU a workgroup),
-whole outputs against fp64 on the dequantised codes: uneven last split, ragged rows and columns, every row-tile count."""
+"""17..64 rows of layers too narrow to give every CU 128 columns, K split over workgroups or whole as the plan has it: whole outputs
+against fp64 on the dequantised codes, uneven last split, ragged rows and columns, every row-tile count."""
 import pytest
 import torch
 

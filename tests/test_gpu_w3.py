@@ -55,11 +55,11 @@ def test_w3_device_quantiser_matches_oracle_bit_for_bit(K, N):
                                    (14336, 4096, 1), (4096, 6144, 1), (1024, 1024, 5), (384, 48, 64),
                                    (1024, 400, 300), (384, 48, 2), (1920, 272, 7), (4096, 4112, 16), (4096, 28672, 8),
                                    (256, 4112, 3), (14336, 528, 4), (14336, 528, 12),
-                                   # rollout batches beyond 16 rows: the register-unpack kernel with and without a split of K,
-                                   # one and two weight tiles per wave, 1..4 row tiles, 8-wave workgroups above 64 rows
+                                   # rollout batches beyond 16 rows: the slices and tile kernels with and without a split of K,
+                                   # 2..4 row tiles, several blocks of rows
                                    (4096, 4096, 64), (14336, 4096, 40), (4096, 28672, 20), (2048, 1040, 128),
                                    (512, 4096, 200), (1024, 2064, 130), (640, 80, 17), (4096, 6144, 33),
-                                   # wide layers at 17..64 rows: the wide-layer kernel (2, 3 and 4 row tiles, ragged last workgroup)
+                                   # wide layers at 17..64 rows: 2, 3 and 4 row tiles, ragged last workgroup
                                    (512, 16400, 24), (512, 16448, 40), (1024, 16384, 64)])
 def test_w3_forward(K, N, M):
     _, words, s, z = quantized3(7200 + K + N, N, K)
@@ -109,8 +109,8 @@ def test_w3_one_hot_and_exact_cases():
 @pytest.mark.parametrize("K,N,M", [(1024, 1024, 1), (384, 48, 7), (4096, 4096, 1), (1920, 272, 33), (512, 256, 200),
                                    (512, 1024, 6400),      # large enough for the tiled GEMM
                                    # one case per kernel class that reads the row's single scale word: streaming (2..16),
-                                   # k-sliced panels, wide-layer, its variant for odd group counts, rollout batch with K
-                                   # split, and the direct-from-L2 kernel that very long decode rows fall back to
+                                   # k-sliced panels, tile (an even and an odd group count), slices, and the direct-from-L2
+                                   # kernel that very long decode rows fall back to
                                    (4096, 4096, 16), (14336, 528, 8), (512, 16400, 24), (640, 16400, 40), (2048, 1024, 64),
                                    (32768, 64, 1), (4096, 28672, 1)])
 def test_per_channel_symmetric_layer(K, N, M):

@@ -3,6 +3,8 @@ a wave's last group included, names bytes of the layer, and which shape serves l
 import os
 import subprocess
 
+from test_gpu_rows import SLICES, TILE
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 PROGRAM = r"""
@@ -92,6 +94,7 @@ def run(tmp_path, program):
     assert built.returncode == 0, built.stderr[-2000:]
     ran = subprocess.run([str(exe)], capture_output=True, text=True)
     assert ran.returncode == 0, ran.stdout
+    return ran.stdout
 
 
 def test_every_request_names_a_group_of_the_layer(tmp_path):
@@ -100,3 +103,27 @@ def test_every_request_names_a_group_of_the_layer(tmp_path):
 
 def test_shapes_of_the_row_kernels(tmp_path):
     run(tmp_path, PLANS)
+
+
+def test_the_gpu_cases_cover_every_shape(tmp_path):
+    cases = ", ".join("{%d, %d, %d}" % c for c in SLICES + TILE)
+    out = run(tmp_path, r"""
+#include <cstdio>
+#include "row_splits.hpp"
+struct Case {
+    int M, K, N;
+};
+int main() {
+    for (const auto &c : {%s}) {
+        const dmr::RowsPlan p = dmr::rows_call(c.M, c.K, c.N);
+        std::printf("%%d %%d %%d %%d %%d %%d\n", p.slices, p.MT, p.WM, p.R, p.half, p.SK > 1);
+    }
+    return 0;
+}
+""" % cases.replace("{", "Case{"))
+    got = [tuple(map(int, line.split())) for line in out.splitlines()]
+    assert all(p[0] == 1 for p in got[:len(SLICES)]) and all(p[0] == 0 for p in got[len(SLICES):])
+    want = {(1, mt, 1, r, 0, split) for mt in (2, 3, 4) for r in (1, 2, 4) for split in (0, 1)}
+    want |= {(0, mt, wm, 0, 0, split) for mt, wm in ((2, 1), (3, 1), (4, 1), (3, 2), (4, 2)) for split in (0, 1)}
+    want |= {(0, mt, wm, 0, 1, 0) for mt, wm in ((3, 1), (4, 1), (3, 2), (4, 2))}
+    assert want == set(got), (want - set(got), set(got) - want)
