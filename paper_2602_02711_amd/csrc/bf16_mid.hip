@@ -1,6 +1,6 @@
 // bf16 twin of the rollout-batch kernel: y[M][N] = x[M][K] . W[N][K]^T for 65 rows up to a few hundred
 // (while a tiled GEMM would leave most of the 256 CUs idle) and for 9..64 rows where bf16_rows.hip would have to split K further
-// than the workspace allows; fp32 accumulation.
+// than the workspace allows or its rule calls the rows too short; fp32 accumulation.
 //
 // Same skeleton as w4_mid.hip: the workgroup's BM x 128 slice of x goes through double-buffered LDS (rows
 // padded to 272 bytes), the weights go from global memory straight into MFMA B-operand registers.

@@ -34,8 +34,7 @@ struct Geo {
     static constexpr int XB = MT * 16 * 256;                 // a wave's slot: one group of x, rows of 256 bytes
     static constexpr int SB = R * 256;                       // scale words of four groups
     static constexpr int SLOT = XB + 2 * SB;
-    static constexpr int RP = R < 4 ? R : 4;                 // tiles per pass of the final sum
-    static constexpr size_t RED = (size_t)RP * MT * kWaves * 1024;
+    static constexpr size_t RED = (size_t)R * MT * kWaves * 1024;
     static constexpr size_t LDS = (size_t)kWaves * SLOT > RED ? (size_t)kWaves * SLOT : RED;
     static_assert(LDS <= 160 * 1024, "");
 };
@@ -173,39 +172,34 @@ __global__ __launch_bounds__(64 * kWaves, MT == 2 && R <= 2 ? 4 : 2) void w4_sli
         }
     }
 
-    // the waves' partial tiles meet in LDS, RP tiles at a time: red[unit][wave][lane]
+    // the waves' partial tiles meet in LDS: red[unit][wave][lane]
     wait_loads<0>();
     const int64_t part = out_mode == 2 ? (int64_t)blockIdx.y * M * N : 0;
     f32x4 *red = reinterpret_cast<f32x4 *>(smem);
+    __syncthreads();
 #pragma unroll
-    for (int r0 = 0; r0 < R; r0 += G::RP) {
-        __syncthreads();
+    for (int r = 0; r < R; ++r)
 #pragma unroll
-        for (int r = r0; r < (r0 + G::RP < R ? r0 + G::RP : R); ++r)
+        for (int mt = 0; mt < MT; ++mt) red[((r * MT + mt) * kWaves + wave) * 64 + lane] = acc[r][mt];
+    __syncthreads();
+    for (int u = wave; u < R * MT; u += kWaves) {
+        const f32x4 *src = red + u * kWaves * 64 + lane;
+        f32x4 v = src[0];
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt) red[(((r - r0) * MT + mt) * kWaves + wave) * 64 + lane] = acc[r][mt];
-        __syncthreads();
-        const int units = (r0 + G::RP < R ? G::RP : R - r0) * MT;
-        for (int u = wave; u < units; u += kWaves) {
-            const f32x4 *src = red + u * kWaves * 64 + lane;
-            f32x4 v = src[0];
+        for (int k = 1; k < kWaves; ++k) {
+            const f32x4 w2 = src[k * 64];
 #pragma unroll
-            for (int k = 1; k < kWaves; ++k) {
-                const f32x4 w2 = src[k * 64];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] += w2[e];
-            }
-            // rows 4 c + q of column j -> columns 4 (j / 4) + p of row 4 c + j % 4
-            f32x4 o;
-            const int jq = j & 3;
-            transpose_quad(v, o, jq);
-            const int row = (u % MT) * 16 + c * 4 + jq, tile = tileb + r0 + u / MT;
-            if (row < rows && tile < tiles)
-                store_quad(o, y, (int64_t)(m0 + row) * N + (int64_t)tile * kTileRows + (j & 12), part, out_mode, res);
+            for (int e = 0; e < 4; ++e) v[e] += w2[e];
         }
+        // rows 4 c + q of column j -> columns 4 (j / 4) + p of row 4 c + j % 4
+        f32x4 o;
+        const int jq = j & 3;
+        transpose_quad(v, o, jq);
+        const int row = (u % MT) * 16 + c * 4 + jq, tile = tileb + u / MT;
+        if (row < rows && tile < tiles)
+            store_quad(o, y, (int64_t)(m0 + row) * N + (int64_t)tile * kTileRows + (j & 12), part, out_mode, res);
     }
 }
-
 
 template <int MT, int R, int BITS>
 hipError_t launch_cfg(const void *wt, const uint32_t *sz, int szs, int64_t K, int64_t N, const uint16_t *x, int M, void *y,
