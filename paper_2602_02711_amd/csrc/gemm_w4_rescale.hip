@@ -983,10 +983,10 @@ int w4_gemm_rescale_wave_columns(int64_t M, int64_t N) {
     return narrow > compute_units() ? 4 : 2;
 }
 
-// Rows of the tile: 128 while one round of 128 x 128 tiles (pairs of waves on 64 x 64 patches, up to two workgroups per
-// CU) covers the output; measured with one wave per 64 x 32 against w4_mid.hip and the 256-row tiles: attn-out at 768 / 1024 rows 48 / 52
-// against 55 / 64 us, qkv at 384 / 512 rows 49 / 50 against 55 / 55, down at 768 / 1024 rows 146 / 152 against 173 / 191;
-// behind both from 288 blocks on.
+// Rows of the tile: 128 while one round of 128 x 128 tiles (pairs of waves on 64 x 64 patches, one workgroup per CU: but for the
+// group kernel without a residual and three bits they take more than 128 registers) covers the output; measured with one wave per
+// 64 x 32 against a rollout-batch kernel that is gone and the 256-row tiles: attn-out at 768 / 1024 rows 48 / 52 against 55 / 64 us,
+// qkv at 384 / 512 rows 49 / 50 against 55 / 55, down at 768 / 1024 rows 146 / 152 against 173 / 191; behind both from 288 blocks on.
 int w4_gemm_rescale_tile_rows(int64_t M, int64_t N) {
     const int forced = env_int("DMR_W4_RESCALE_BM", 0);
     if (forced == 128 || forced == 256) return forced;

@@ -3,8 +3,9 @@
 //
 // Eight wavefronts: WM along the rows, 2 lanes of four weight tiles (64 columns), S along k, each on its own group of the
 // chunk.  The chunk's panel of x (16 MT WM rows x 256 S bytes, 64 KiB at most) sits in one of two LDS buffers; it goes there by
-// buffer loads into LDS, one barrier per chunk, 16-byte pieces XOR-swizzled with the row so that the A-operand reads are free
-// of conflicts.  A wave takes its group's 16 A fragments once and feeds each to four weight tiles; every unpacked word feeds
+// buffer loads into LDS, one barrier per chunk, 16-byte pieces XOR-swizzled with the row.  (That spreads 16 consecutive lanes over
+// all banks, but a 16-byte read is not served so: four conflict cycles each were counted, 9.2e5 of 2.2e6 LDS cycles at 64 rows 4096
+// -> 28672; w4_slices.hip the same, bf16_rows.hip none.)  A wave takes its group's 16 A fragments once and feeds each to four weight tiles; every unpacked word feeds
 // MT MFMAs.  Weights and scales are requested one chunk ahead into the registers they are used from; loads return in order, so
 // they are requested behind the next panel's pieces, and the wait for the panel leaves them in flight.  The group sums of x come
 // from MFMAs against all-ones, and a group contributes  acc += s (D - (128 + z) X)  (exact codes, fp32 scale).  The S partial
