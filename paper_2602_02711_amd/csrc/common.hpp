@@ -110,6 +110,14 @@ __device__ __forceinline__ float row16_sum(float v) {
     return row_ror_add<1>(v);
 }
 
+// Workgroup barrier without the fences of __syncthreads(), which would wait for every load in flight (those into LDS are LDS writes).
+// What must have landed is waited for explicitly before it; the signal fences keep the compiler from moving memory accesses across.
+__device__ __forceinline__ void bare_barrier() {
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    __builtin_amdgcn_s_barrier();
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+}
+
 // One streaming-layout word (8 nibbles) -> four MFMA B-operand registers, register i = the bf16 pair
 // (128 + nibble i, 128 + nibble i + 4), i.e. ((w >> 4 i) & 0x000F000F) | 0x43004300, in 7 VALU
 // instructions: two masks split the nibbles into bytes and v_perm_b32 interleaves them with the

@@ -43,16 +43,6 @@ __device__ __forceinline__ void wait_vmcnt() {
     __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (0 << 8));
 }
 
-// Workgroup barrier without the release / acquire fences of __syncthreads(): those would make the
-// compiler wait for every direct-to-LDS load in flight (they are LDS writes), i.e. for the whole
-// prefetch.  What must have landed is waited for explicitly (wait_vmcnt) before this is called; the
-// signal fences keep the compiler from moving memory accesses across the barrier.
-__device__ __forceinline__ void bare_barrier() {
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-    __builtin_amdgcn_s_barrier();
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-}
-
 __device__ __forceinline__ int swz(int row, int chunk) { return chunk ^ ((row >> 2) & 3); }
 
 // Operand fragments of one 16-wide k sub-step (ks = 0, 1) of an LDS stage.  The stage pointer is

@@ -123,14 +123,6 @@ __device__ __forceinline__ void wait_vmcnt() {
     __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (0 << 8));
 }
 
-// Workgroup barrier without the fences of __syncthreads() (which would wait for every direct-to-LDS load in
-// flight); what must have landed is waited for explicitly before this is called.
-__device__ __forceinline__ void bare_barrier() {
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-    __builtin_amdgcn_s_barrier();
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-}
-
 __device__ __forceinline__ int swz(int row, int chunk) { return chunk ^ ((row >> 2) & 3); }
 
 // Fragments of the second loop's stages.  (Restrict pointers: see read_a_frags.)

@@ -16,13 +16,6 @@ __device__ __forceinline__ void wait_loads() {      // until at most N vector lo
 }
 __device__ __forceinline__ void wait_lds() { __builtin_amdgcn_s_waitcnt(15 | (3 << 14) | (7 << 4)); }
 
-// Workgroup barrier without the fences of __syncthreads(), which would wait for every load in flight.
-__device__ __forceinline__ void bare_barrier() {
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-    __builtin_amdgcn_s_barrier();
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-}
-
 // 16 or 4 bytes per lane from base + voff + soff, lane after lane to `dst`.
 __device__ __forceinline__ void load16_to_lds(const void *base, uint32_t bytes, uint8_t *dst, uint32_t voff, uint32_t soff) {
     __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)bytes, 0x00020000),
